@@ -3,7 +3,7 @@
 //
 //     Wd[o][j] = ( sum_i S_i[o][j] * (U_i V_i^T)[o][j] ) / s[j]        (Eq. 8, Eq. 4 folded into the columns)
 //
-// in caller-owned memory (k_tile<true> in panel.hip), and the batch then meets it in one dense
+// in caller-owned memory (restore.hip), and the batch then meets it in one dense
 // product Y = X Wd^T on the matrix cores (k_gemm below).  Restoring costs the same per weight
 // element whatever the batch, so for prefill-sized batches this beats rebuilding weight tiles per
 // token tile; the price is out x in x 2 bytes of scratch, shared by all stacks of a model.

@@ -344,7 +344,7 @@ static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t work
         double t_mat = 0.0;
         for (int r0 = 0; r0 < g.out; r0 += slab) {
             const int rows = slab < g.out - r0 ? slab : g.out - r0;
-            t_mat += 8.0 + restore_time_us(rows, g.in, n_loaded, nullptr) + dense_time_us(rows, g.in, batch);
+            t_mat += 8.0 + restore_time_us(rows, g.in, n_loaded) + dense_time_us(rows, g.in, batch);
         }
         if (t_mat < t_best) kernel = BITSTACK_KERNEL_MATERIALISE;
     }

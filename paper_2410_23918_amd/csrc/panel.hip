@@ -676,11 +676,6 @@ constexpr int kTileFixedLds = 8 * 2 * kVPriv + 2 * kPanelRows * kPanelLd * 2;
 constexpr int kTileMaxBlocks = (160 * 1024 - kTileFixedLds) / 2048 - 1;
 constexpr int kTileTokens = 512;   // tokens per workgroup
 
-// kRestore: the same construction of the weight tile, but the parked tiles are copied to a dense
-// fp16 matrix W' diag(1/s) [out][in] in memory instead of being multiplied with activations (the
-// restoring step of the appendix on inference throughput, "level 2"); blockIdx.y then selects a
-// range of chunk pairs instead of a token tile.
-template <bool kRestore>
 __global__ __launch_bounds__(512) void k_tile(KParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -693,14 +688,10 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
     const int nch = p.in / kChunkCols;
     const int iters = (nch + 1) / 2;
     const int n = p.n_loaded;
-    const int its_per_wg = kRestore ? (iters + int(gridDim.y) - 1) / int(gridDim.y) : iters;
-    const int it_first = kRestore ? int(blockIdx.y) * its_per_wg : 0;
-    const int it_end = min(iters, it_first + its_per_wg);
-    if (it_first >= it_end) return;
-    const int total = (it_end - it_first) * n;
-    const int rt0 = blockIdx.x * 2 + (kRestore ? p.row_begin / kTileRows : 0), nrt = p.out / kTileRows;
+    const int total = iters * n;
+    const int rt0 = blockIdx.x * 2, nrt = p.out / kTileRows;
     const int rtc[2] = {min(rt0, nrt - 1), min(rt0 + 1, nrt - 1)};   // clamped for loads
-    const int tok_w = kRestore ? 0 : blockIdx.y * kTileTokens + wave * 64;   // my first token in the product stage
+    const int tok_w = blockIdx.y * kTileTokens + wave * 64;   // my first token in the product stage
 
     for (int idx = tid; idx < n * 128; idx += 512) {   // U rows of my 64 output rows, all blocks -> LDS
         const int i = idx >> 7, piece = idx & 127;
@@ -807,15 +798,8 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) yacc[a][b][v] = 0.0f;
 
-    // shifts that bring the sign bits of a register pair (word bits 8*mf + k + 4*hl and that + 16) to
-    // bits 15 and 31: per lane (eight registers) where registers are to spare, else the word is moved
-    // down by 4*hl first and the shifts are immediates
-    constexpr bool kLaneShift = kRestore;
-    unsigned sh[2][4];
-#pragma unroll
-    for (int mf = 0; mf < 2; ++mf)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sh[mf][k] = unsigned(15 - 8 * mf - k) - (kLaneShift ? unsigned(4 * hl) : 0u);
+    // the sign bits of a register pair (word bits 8*mf + k + 4*hl and that + 16) go to bits 15 and 31: the word is
+    // moved down by 4*hl, the shifts from there are immediates
 
     // first = the chunk's first block: the accumulator starts from zero instead of being cleared
     // beforehand, so that its 64 registers are free during the product stage
@@ -827,7 +811,7 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
     };
     auto sign_and_add = [&](auto first, int tb, const v16f& m, const SIn& sg) {
         const int tile = tb >> 1, rg = tb & 1;
-        const unsigned wrd = unsigned(tile ? sg.w[rg].y : sg.w[rg].x) >> (kLaneShift ? 0 : 4 * hl);
+        const unsigned wrd = unsigned(tile ? sg.w[rg].y : sg.w[rg].x) >> (4 * hl);
 #pragma unroll
         for (int mf = 0; mf < 2; ++mf) {
             unsigned r4[4];
@@ -837,7 +821,7 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
                 h2 c;
                 c[0] = _Float16(m[4 * mf + k]);
                 c[1] = _Float16(m[4 * mf + k + 8]);
-                const unsigned flip = ~(wrd << sh[mf][k]) & 0x80008000u;   // a cleared bit marks a negative sign
+                const unsigned flip = ~(wrd << (15 - 8 * mf - k)) & 0x80008000u;   // a cleared bit marks a negative sign
                 r4[k] = __builtin_bit_cast(unsigned, c) ^ flip;
             }
             if (decltype(first)::value && mf == 0) {
@@ -853,21 +837,8 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
     };
     // tile-blocks tb = 2 * tile + row group
     auto rebuild = [&](auto first, const SIn& sg, v8h uf0, v8h uf1, v8h vf0, v8h vf1) {
-        if (kRestore) {
-            // registers to spare: the magnitude product of the next tile-block is issued before the
-            // vector work on the current one, which then covers its latency
-            v16f m0 = magnitude(0, uf0, uf1, vf0, vf1);
-            v16f m1 = magnitude(1, uf0, uf1, vf0, vf1);
-            sign_and_add(first, 0, m0, sg);
-            m0 = magnitude(2, uf0, uf1, vf0, vf1);
-            sign_and_add(first, 1, m1, sg);
-            m1 = magnitude(3, uf0, uf1, vf0, vf1);
-            sign_and_add(first, 2, m0, sg);
-            sign_and_add(first, 3, m1, sg);
-        } else {
 #pragma unroll
-            for (int tb = 0; tb < 4; ++tb) sign_and_add(first, tb, magnitude(tb, uf0, uf1, vf0, vf1), sg);
-        }
+        for (int tb = 0; tb < 4; ++tb) sign_and_add(first, tb, magnitude(tb, uf0, uf1, vf0, vf1), sg);
     };
 
     // end of a chunk: park my piece of W' diag(1/s) in LDS, then the product stage for both teams' chunks
@@ -891,16 +862,7 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
                 }
             }
         lds_barrier();   // both tiles parked
-        if (kRestore) {
-            __half* const wd = static_cast<__half*>(p.wdense);
-            for (int idx = tid; idx < 2 * kPanelRows * 32; idx += 512) {   // 16-byte pieces, a row's 32 in a row
-                const int tm = idx >> 11, r = (idx >> 5) & 63, piece = idx & 31;
-                const int chc = 2 * it + tm, row = (rt0 + (r >> 5)) * kTileRows + (r & 31);
-                if (chc < nch && row < p.out)
-                    *reinterpret_cast<uint4*>(wd + size_t(row - p.row_begin) * p.in + chc * kChunkCols + piece * 8) =
-                        *reinterpret_cast<const uint4*>(wt + (tm * kPanelRows + r) * kPanelLd + piece * 8);
-            }
-        } else if (tok_w < p.batch) {
+        if (tok_w < p.batch) {
             // fragments of my two token groups: [group][in / 16][64 lanes][8]
             const __half* xrow[2];
 #pragma unroll
@@ -944,7 +906,7 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
         lds_barrier();   // tiles free for the next pair of chunks
     };
 
-    Pos q = pos_at(it_first, 0);
+    Pos q = pos_at(0, 0);
     VIn vA = fetch_v(q);
     SIn sA = fetch_s(q);
     q = advance(q);
@@ -952,40 +914,33 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
     SIn sB = fetch_s(q);
     q = advance(q);
     VIn vC = fetch_v(q);
-    // Signs of step s + 3 are requested once step s has used its own (into the same registers) where
-    // registers are to spare; else signs run one step behind V (step s + 2 at the start of step s, into
-    // the third set) and need a position of their own.
-    constexpr bool kSignsLate = kRestore;
+    // signs run one step behind V (step s + 2 at the start of step s, into the third set) and have a position of their own
     Pos qs = q;       // position of step s + 2
     SIn sC;
-    if (kSignsLate) sC = fetch_s(q);
     q = advance(q);   // position of step s + 3
     stage_v(vA, 0);
     v8h vf0 = read_vf(0, 0), vf1 = read_vf(0, 1);
     __syncthreads();   // U cache complete
 
-    int ci = 0, it = it_first;
+    int ci = 0, it = 0;
 #define BS_TILE_STEP(S, CUR, NXT, FAR)                                                     \
     {                                                                                      \
         const v8h uf0 = read_u(ci, 0), uf1 = read_u(ci, 1);                                \
         stage_v(v##NXT, ((S) + 1) & 1);                                                    \
         const v8h vn0 = read_vf(((S) + 1) & 1, 0), vn1 = read_vf(((S) + 1) & 1, 1);        \
-        if (!kSignsLate) {                                                                 \
-            s##FAR = fetch_s(qs);                                                          \
-            qs = advance(qs);                                                              \
-        }                                                                                  \
+        s##FAR = fetch_s(qs);                                                              \
+        qs = advance(qs);                                                                  \
         v##CUR = fetch_v(q);                                                               \
         if (ci == 0)                                                                       \
             rebuild(std::true_type{}, s##CUR, uf0, uf1, vf0, vf1);                         \
         else                                                                               \
             rebuild(std::false_type{}, s##CUR, uf0, uf1, vf0, vf1);                        \
-        if (kSignsLate) s##CUR = fetch_s(q);                                               \
         q = advance(q);                                                                    \
         vf0 = vn0;                                                                         \
         vf1 = vn1;                                                                         \
         if (++ci == n) {                                                                   \
             ci = 0;                                                                        \
-            if (it < it_end) flush_and_multiply(it);                                       \
+            if (it < iters) flush_and_multiply(it);                                        \
             ++it;                                                                          \
         }                                                                                  \
     }
@@ -997,7 +952,6 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
     }
 #undef BS_TILE_STEP
 
-    if (kRestore) return;
     // C[i = token][n = row]: lane (row ln), register v holds token 8*(v/4) + 4*hl + v%4 of the group
 #pragma unroll
     for (int rg = 0; rg < 2; ++rg)
@@ -1019,7 +973,7 @@ static hipError_t launch_tile(const KParams& p, hipStream_t st) {
     const size_t smem = size_t(kTileFixedLds) + size_t(p.n_loaded) * 2048;
     static std::atomic<bool> attr_set{false};   // setting the attribute twice is harmless
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile<false>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile),
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            kTileFixedLds + kTileMaxBlocks * 2048);
         if (e != hipSuccess) return e;
@@ -1027,60 +981,8 @@ static hipError_t launch_tile(const KParams& p, hipStream_t st) {
     }
     launch_xpack(p, st);
     dim3 grid((p.out + 2 * kTileRows - 1) / (2 * kTileRows), (p.batch + kTileTokens - 1) / kTileTokens);
-    hipLaunchKernelGGL(k_tile<false>, grid, dim3(512), smem, st, p);
+    hipLaunchKernelGGL(k_tile, grid, dim3(512), smem, st, p);
     return hipGetLastError();
-}
-
-// W' diag(1/s) of the loaded prefix as a dense fp16 matrix [out][in] (row-major) at a.wdense.
-// Estimated duration of restoring `rows` rows (microseconds) and the number of column slices per row
-// tile pair it assumes: rounds of 256 workgroups x (chunk pairs per workgroup x (~0.93 us per block +
-// ~2.5 us for the flush) + ~3 us fixed) (a slab of 2048 rows of 28672x8192: ~40 us inside a run of
-// slabs, the whole matrix 520-600).
-double restore_time_us(int rows, int in, int n_loaded, int* slices_out) {
-    const int iters = (in / kChunkCols + 1) / 2;
-    const int row_wgs = (rows + 2 * kTileRows - 1) / (2 * kTileRows);
-    int slices = 1;
-    double best = 0.0;
-    for (int sl = 1; sl <= iters; sl *= 2) {
-        const int per = (iters + sl - 1) / sl;
-        const double t = double((row_wgs * sl + 255) / 256) * (per * (0.93 * n_loaded + 2.5) + 3.0);
-        if (sl == 1 || t < best) {
-            best = t;
-            slices = sl;
-        }
-    }
-    if (slices_out) *slices_out = slices;
-    return best;
-}
-
-hipError_t launch_restore(const LaunchArgs& a, hipStream_t st) {
-    KParams p = make_params(a);
-    if (a.n_loaded < 1 || !restore_fits(p.block_stride, a.n_loaded) || p.wdense == nullptr) return hipErrorInvalidValue;
-    const size_t smem = size_t(kTileFixedLds) + size_t(p.n_loaded) * 2048;
-    static std::atomic<bool> attr_set{false};   // setting the attribute twice is harmless
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile<true>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           kTileFixedLds + kTileMaxBlocks * 2048);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    // Column slices per row tile pair: few, long workgroups pay the fixed costs (copy of the U
-    // rows, first loads, ~3 us) less often, many short ones fill the last round of the 256
-    // compute units better (restore_time_us).
-    const int slab_rows = a.rows ? a.rows : p.out;
-    if (a.row_begin % 256 || a.row_begin < 0 || a.row_begin >= p.out || slab_rows < 1) return hipErrorInvalidValue;
-    const int rows = min(slab_rows, p.out - a.row_begin);
-    const int row_wgs = (rows + 2 * kTileRows - 1) / (2 * kTileRows);
-    int slices = 1;
-    restore_time_us(rows, p.in, p.n_loaded, &slices);
-    hipLaunchKernelGGL(k_tile<true>, dim3(row_wgs, slices), dim3(512), smem, st, p);
-    return hipGetLastError();
-}
-int restore_max_blocks() { return kTileMaxBlocks; }
-// U cache in LDS; the kernel reaches the loaded blocks through one buffer descriptor with 32-bit offsets
-bool restore_fits(size_t block_stride, int n_loaded) {
-    return n_loaded <= kTileMaxBlocks && size_t(n_loaded) * block_stride < (size_t(1) << 32);
 }
 
 // Estimated durations (microseconds, constants fitted to measurements).  k_fused: per round of

@@ -1,0 +1,202 @@
+// Restoring the dense weight of the loaded prefix (the restoring step of the appendix on inference throughput, "level 2"):
+//
+//     Wd[o][j] = ( sum_i S_i[o][j] * (U_i V_i^T)[o][j] ) / s[j]        (Eq. 8, Eq. 4 folded into the columns)
+//
+// as fp16, row-major, in caller-owned memory (dense.hip multiplies it).  One wavefront rebuilds units of 32 rows x 256
+// columns (rebuild.h); a workgroup is four of them, 128 rows x one column chunk, and two workgroups share a compute
+// unit, so that one's barrier or turn through LDS is covered by the other's arithmetic.
+//
+// 14336 x 4096, 16 blocks: 78 us (before, with the weight-tile kernel's rebuild stage: 145); 28672 x 8192, 16 blocks: 346 us
+// (490-530); 2048 x 8192, 16 blocks: 27 us (40).  What bounds it: issue of vector and matrix instructions (64 of these us at
+// 14336 x 4096 with every input from cache and nothing stored) and the traffic of signs, U, V and dense rows, which overlap
+// in part.
+#include <hip/hip_fp16.h>
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "kernels.h"
+#include "kparams.h"
+#include "layout.h"
+#include "rebuild.h"
+
+namespace bitstack {
+
+constexpr int kRestoreMaxBlocks = 29;
+constexpr int kRestoreRows = kRebuildWaves * kTileRows;   // a row group: 32 rows per wavefront
+constexpr unsigned kStepBytes = kRebuildWaves * kWaveStepBytes, kRing = 4;
+constexpr unsigned kRsLds = kRing * kStepBytes, kTurnLds = kRsLds + kChunkCols * 4;
+constexpr unsigned kTurnBytes = 32 * 64;
+
+// A workgroup restores one column chunk of `groups_per_wg` row groups.  Chunks are the fastest index of the grid: ids are
+// dealt round-robin to the XCDs, so an XCD sees few chunks of a wide matrix (an eighth, where the number of chunks is a
+// multiple of eight) and keeps their V panels in its L2 while all row groups pass.
+__global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, int row_groups, int groups_per_wg) {
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kTurnLds + kRebuildWaves * kTurnBytes];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hl = lane >> 5, ln = lane & 31;
+    const int nch = p.in / kChunkCols, n = p.n_loaded;
+    const int ch = blockIdx.x;
+    const int rg0 = int(blockIdx.y) * groups_per_wg, rg1 = min(row_groups, rg0 + groups_per_wg);
+    if (rg0 >= rg1) return;
+    const int nrt = p.out / kTileRows, rt_first = p.row_begin / kTileRows + wave;
+
+    const unsigned stride = unsigned(p.block_stride);
+    __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(p.blocks), 0, unsigned(n) * stride, 0x00020000);
+    __amdgpu_buffer_rsrc_t rs_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.rs), 0, unsigned(p.in) * 4u, 0x00020000);
+    // (a load's constant offset counts in memory and in LDS: taken off here)
+    const unsigned s_lane = unsigned(ch) * kUnitBytes + unsigned(lane) * 16u;
+    const unsigned v_lane = unsigned(p.off_v) + unsigned(ch) * kVChunkBytes + unsigned(wave) * 2048u + v_piece_offset(unsigned(lane)) - kVOffset;
+    const unsigned u_lane = unsigned(p.off_u) + unsigned(ln) * 32u + unsigned(hl) * 16u - kUOffset;
+    const unsigned lds0 = unsigned(reinterpret_cast<uintptr_t>((lds_void*)smem));
+    const unsigned v_rd = lds0 + v_read_offset(unsigned(lane));
+    const unsigned s_rd = lds0 + unsigned(wave) * kWaveStepBytes + unsigned(lane) * 16u;
+    const v4h ident = accumulate_matrix(unsigned(lane));
+
+    // a step = (row group, block), row groups outermost; its inputs are requested three steps ahead, into a ring of
+    // four buffers in LDS.  Rows past the end of the matrix repeat its last tile: computed, never stored.
+    auto row_tile = [&](int rg) { return min(rt_first + rg * kRebuildWaves, nrt - 1); };
+    int qi = 0, qrg = rg0;
+    unsigned qv = 0, qs = unsigned(row_tile(rg0)) * unsigned(nch) * kUnitBytes, qu = unsigned(row_tile(rg0)) * 1024u;
+    unsigned qbuf = 0;
+    auto request = [&]() {
+        unsigned char* const mine = smem + qbuf + wave * kWaveStepBytes;
+        load_to_lds<0>(rsrc, mine, s_lane, qs);
+        load_to_lds<kVOffset>(rsrc, mine, v_lane, qv);
+        load_to_lds<kVOffset + kVClassBytes>(rsrc, mine, v_lane, qv);
+        load_to_lds<kUOffset>(rsrc, mine, u_lane, qu);
+        qv += stride;
+        qs += stride;
+        qu += stride;
+        if (++qi == n) {
+            qi = 0;
+            qv = 0;
+            qrg = min(qrg + 1, rg1 - 1);   // past the last step the last row group is read again, harmlessly
+            qs = unsigned(row_tile(qrg)) * unsigned(nch) * kUnitBytes;
+            qu = unsigned(row_tile(qrg)) * 1024u;
+        }
+        qbuf = (qbuf + kStepBytes) & (kRing * kStepBytes - 1);
+    };
+    constexpr int kInFlight = 4;   // loads of one step and wavefront
+
+    UnitAcc acc;
+    StepInputs in;
+    unsigned buf = 0;
+    load4_to_lds(rs_rsrc, smem + kRsLds + wave * 256, unsigned(lane) * 4u, unsigned(ch) * (kChunkCols * 4) + unsigned(wave) * 256u);
+    request();
+    request();
+    loads_barrier<kInFlight>();
+    request();
+    begin_steps(in, v_rd, s_rd);
+    auto step = [&](auto first) __attribute__((always_inline)) {
+        // the next step's inputs have landed (this wavefront's loads, then everybody's), and nobody reads the previous
+        // step's any more
+        loads_barrier<kInFlight>();
+        request();
+        const unsigned nb = (buf + kStepBytes) & (kRing * kStepBytes - 1);
+        add_block<decltype(first)::value>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
+        buf = nb;
+    };
+    // The unit times 1/s (Eq. 4 folded into the columns), as fp16 to the dense matrix.  A lane holds 256
+    // consecutive bytes of one row; it is turned through LDS (private to the wavefront, no barrier), 64 bytes per row
+    // of a half at a time, so that four lanes store 64 consecutive bytes.  Stored as the lanes hold them, 16 bytes each
+    // at 64 places, the stores took as long as everything else together.
+    const unsigned rs_rd = lds0 + kRsLds + unsigned(hl) * 512u;
+    const unsigned turn = lds0 + kTurnLds + unsigned(wave) * kTurnBytes;
+    const unsigned wr = turn + unsigned(ln) * 64u, swz = (unsigned(ln) >> 2) & 3u;
+    const unsigned rd = turn + (unsigned(lane) >> 2) * 64u + (((unsigned(lane) & 3u) ^ (unsigned(lane) >> 4)) * 16u);
+    auto flush = [&](int rt) {
+        unsigned char* const dst = static_cast<unsigned char*>(p.wdense) +
+                                   (size_t(rt * kTileRows + (lane >> 2) - p.row_begin) * p.in + ch * kChunkCols) * 2 + (lane & 3) * 16;
+        unsigned char* const dst16 = dst + size_t(p.in) * 32;   // 16 rows further down
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            v4f r[4][2];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
+                             : "=&v"(r[b][0]), "=&v"(r[b][1])
+                             : "v"(rs_rd), "n"((w * 4 + b) * 32), "n"((w * 4 + b) * 32 + 16));
+            asm volatile("s_waitcnt lgkmcnt(0)"
+                         : "+v"(r[0][0]), "+v"(r[0][1]), "+v"(r[1][0]), "+v"(r[1][1]), "+v"(r[2][0]), "+v"(r[2][1]), "+v"(r[3][0]),
+                           "+v"(r[3][1]));
+            v4i o[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int t = 0; t < 8; t += 2) {   // (product and conversion in one instruction)
+                    int d;
+                    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(d) : "v"(acc[t][w][b]), "v"(r[b][t >> 2][t & 3]));
+                    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(d) : "v"(acc[t + 1][w][b]), "v"(r[b][t >> 2][(t & 3) + 1]));
+                    o[b][t >> 1] = d;
+                }
+            v4i q[4];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                if (hl == half) {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) asm volatile("ds_write_b128 %0, %1" ::"v"(wr + ((unsigned(b) ^ swz) * 16u)), "v"(o[b]));
+                }
+                asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:1024"
+                             : "=&v"(q[2 * half]), "=&v"(q[2 * half + 1])
+                             : "v"(rd));
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]));
+            *reinterpret_cast<v4i*>(dst + w * 64) = q[0];
+            *reinterpret_cast<v4i*>(dst16 + w * 64) = q[1];
+            *reinterpret_cast<v4i*>(dst + 256 + w * 64) = q[2];
+            *reinterpret_cast<v4i*>(dst16 + 256 + w * 64) = q[3];
+        }
+    };
+    for (int rg = rg0; rg < rg1; ++rg) {
+        step(std::true_type{});
+        for (int i = 1; i < n; ++i) step(std::false_type{});
+        const int rt = rt_first + rg * kRebuildWaves;
+        if (rt < nrt) flush(rt);
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // no load may land in LDS after the workgroup has given it back
+}
+
+// Row groups per workgroup: one, until the workgroups are many more than the 512 that run at a time; then a few, whose
+// first loads are paid once (28672 x 8192: 7168 workgroups of one group 386 us, 1792 of four 346 us; 14336 x 4096: 1792 of
+// one 78 us, 448 of four, whose last round is three quarters empty, 96 us).
+static int restore_groups_per_wg(int groups, int chunks) {
+    const int per = groups * chunks / 1536;
+    return per < 1 ? 1 : per > 4 ? 4 : per;
+}
+
+// The restoring part of the materialising path in the choice of kernel (microseconds): rounds of 256 workgroups of 64 rows x
+// a power of two of column slices, as the former kernel had them.  k_restore is 1.4-1.9 times faster; the choice stays
+// where both sides of it were measured.
+double restore_time_us(int rows, int in, int n_loaded) {
+    const int iters = (in / kChunkCols + 1) / 2, row_wgs = (rows + 63) / 64;
+    double best = 0.0;
+    for (int sl = 1; sl <= iters; sl *= 2) {
+        const double t = double((row_wgs * sl + 255) / 256) * (((iters + sl - 1) / sl) * (0.93 * n_loaded + 2.5) + 3.0);
+        if (sl == 1 || t < best) best = t;
+    }
+    return best;
+}
+
+// restored blocks are limited by what the weight-tile kernel holds, whose place this path takes; the kernel reaches the
+// loaded blocks through one buffer descriptor with 32-bit offsets
+int restore_max_blocks() { return kRestoreMaxBlocks; }
+bool restore_fits(size_t block_stride, int n_loaded) {
+    return n_loaded <= kRestoreMaxBlocks && size_t(n_loaded) * block_stride < (size_t(1) << 32);
+}
+
+hipError_t launch_restore(const LaunchArgs& a, hipStream_t st) {
+    KParams p = make_params(a);
+    if (a.n_loaded < 1 || !restore_fits(p.block_stride, a.n_loaded) || p.wdense == nullptr) return hipErrorInvalidValue;
+    const int slab_rows = a.rows ? a.rows : p.out;
+    if (a.row_begin % 256 || a.row_begin < 0 || a.row_begin >= p.out || slab_rows < 1) return hipErrorInvalidValue;
+    const int rows = min(slab_rows, p.out - a.row_begin);
+    const int groups = (rows + kRestoreRows - 1) / kRestoreRows;
+    const int chunks = p.in / kChunkCols, per = restore_groups_per_wg(groups, chunks);
+    hipLaunchKernelGGL(k_restore, dim3(chunks, (groups + per - 1) / per), dim3(kRebuildWaves * 64), 0, st, p, groups, per);
+    return hipGetLastError();
+}
+
+}  // namespace bitstack
