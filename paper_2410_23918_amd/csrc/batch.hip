@@ -1,0 +1,310 @@
+// Batch kernel for 2 to 64 tokens on rebuilt weight units (rebuild.h): Y += X (W' diag(1/s))^T, W' of a unit summed over its
+// blocks in registers, multiplied with the activations from there and never stored.
+//
+// One workgroup = 64 output rows x all tokens; 8 wavefronts = 4 teams (column chunks) x 2 row tiles.  A wavefront rebuilds
+// its unit of 32 rows x 256 columns block by block; a lane then holds 128 columns of one row, which, scaled by 1/s and
+// rounded to fp16, are the B operands of 16 products over 16 columns each, and the activations as they lie in memory (8
+// columns of a token: 16 bytes) the A operands.  So the weight costs the same for one token as for 64, and a block costs
+// three matrix-core products' worth less than where every block's signed tile meets the activations itself (k_fused in
+// panel.hip).  The activations of a chunk come through the same ring of LDS buffers as the blocks' inputs, as one to four
+// further steps after the last block.
+//
+// 8 wavefronts and not two workgroups of 4: the teams' partial tiles meet in LDS, so a quarter of the workspace serves, and
+// the workspace is what limits the column split of small stacks (14336 x 4096, 3 blocks, 16 tokens: 28 us against 33).
+// 14336 x 4096, 16 blocks: 86 us for 2-32 tokens (k_fused 104), 98 us for 64 (k_fused 214, weight-tile kernel 152);
+// 28672 x 8192: 354 us for 16 tokens (462).  Bound by the issue of vector and matrix instructions: a step (8 tiles per wavefront,
+// two wavefronts per SIMD) takes 1.05-1.25 us, the same instructions without loads and barriers 0.92.
+#include <hip/hip_fp16.h>
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "kernels.h"
+#include "kparams.h"
+#include "layout.h"
+#include "rebuild.h"
+
+namespace bitstack {
+
+namespace {
+
+// TOK tokens (16 or 32) per group of activations, GROUPS of them
+template <int TOK, int GROUPS>
+__global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
+    constexpr int RT = 2, TEAMS = 4, kRows = RT * kTileRows, kRing = 3;
+    typedef StepLayout<RT> L;
+    constexpr unsigned kStep = TEAMS * L::kBytes;
+    // an activation step brings TOK tokens x kPieces columns of eight per half, 8 KiB per team
+    constexpr int kPieces = 256 / TOK, kPerGroup = 16 / kPieces, kXSteps = GROUPS * kPerGroup, kXRowBytes = kPieces * 32;
+    constexpr unsigned kRsLds = kRing * kStep;   // [2][TEAMS][256] floats
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int team = wave / RT, tile = wave % RT;
+    const int hl = lane >> 5, ln = lane & 31;
+    const int nch = p.in / kChunkCols, n = p.n_loaded, nrt = p.out / kTileRows;
+    const int ksplit = p.n_ks;
+    const int c_lo = int(blockIdx.y) * nch / ksplit, c_hi = (int(blockIdx.y) + 1) * nch / ksplit;
+    const int iters = (c_hi - c_lo + TEAMS - 1) / TEAMS;
+    const int rt = int(blockIdx.x) * RT + tile, rtc = min(rt, nrt - 1);
+
+    const unsigned stride = unsigned(p.block_stride);
+    __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(p.blocks), 0, unsigned(n) * stride, 0x00020000);
+    __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(p.x), 0,
+                                                                      unsigned(p.batch) * unsigned(p.in) * 2u, 0x00020000);
+    __amdgpu_buffer_rsrc_t rs_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.rs), 0, unsigned(p.in) * 4u, 0x00020000);
+    const unsigned s_lane = unsigned(size_t(rtc) * nch * kUnitBytes) + unsigned(lane) * 16u;
+    const unsigned v_lane = v_lane_offset<RT>(unsigned(p.off_v), unsigned(tile), unsigned(lane));
+    const unsigned u_lane = u_lane_offset<RT>(unsigned(p.off_u), unsigned(rtc), unsigned(lane));
+    const unsigned lds0 = unsigned(reinterpret_cast<uintptr_t>((lds_void*)smem));
+    const unsigned v_rd = lds0 + unsigned(team) * L::kBytes + v_read_offset(unsigned(lane));
+    const unsigned s_rd = lds0 + unsigned(wave) * L::kWaveBytes + unsigned(lane) * 16u;
+    // x in LDS: a token's 2 kPieces 16-byte pieces in a row, piece j of token t at position j ^ (t & 15)
+    const unsigned x_rd = lds0 + unsigned(team) * L::kBytes + unsigned(ln % TOK) * unsigned(kXRowBytes);
+    const v4h ident = accumulate_matrix(unsigned(lane));
+
+    // steps of a chunk: its n blocks, then kXSteps steps of activations
+    int qi = 0, qit = 0;
+    unsigned qbuf = 0, qoff = 0;
+    auto next_buf = [](unsigned q) { return q == (kRing - 1) * kStep ? 0u : q + kStep; };
+    auto request = [&]() {
+        const int ch = min(c_lo + qit * TEAMS + team, c_hi - 1);
+        if (qi < n) {
+            load_step<RT>(rsrc, smem + qbuf + wave * L::kWaveBytes, s_lane, v_lane, u_lane, qoff + unsigned(ch) * kUnitBytes,
+                          qoff + unsigned(ch) * kVChunkBytes, qoff);
+            qoff += stride;
+        } else {
+            // four loads of 1 KiB per wavefront (and, to keep the number of loads the same in every step, the last one again)
+            const int xs = qi - n, g = xs / kPerGroup, e0 = xs % kPerGroup * kPieces;
+            unsigned char* const mine = smem + qbuf + team * L::kBytes + tile * 4096;
+#pragma unroll
+            for (int k = 0; k < kStepLoads<RT>; ++k) {
+                const int kk = k < 4 ? k : 3;
+                const int lin = kk * 64 + lane, t = tile * (4096 / kXRowBytes) + lin / (2 * kPieces);   // token of the group
+                const int j = (lin % (2 * kPieces)) ^ (t & 15);   // piece: [half][kPieces]
+                const int tok = min(g * TOK + t, p.batch - 1);
+                const unsigned off = unsigned(tok) * unsigned(p.in) * 2u + unsigned(j / kPieces) * 256u + unsigned(j % kPieces + e0) * 16u;
+                load_to_lds<0>(x_rsrc, mine + kk * 1024, off, unsigned(ch) * 512u);
+            }
+        }
+        if (++qi == n + kXSteps) {
+            qi = 0;
+            qoff = 0;
+            qit = min(qit + 1, iters - 1);   // past the last step the last chunks are read again, harmlessly
+        }
+        qbuf = next_buf(qbuf);
+    };
+    
+    auto request_rs = [&](int it) {   // 1/s of the team's chunk of iteration it, 1 KiB by the team's wavefronts
+        const int ch = min(c_lo + it * TEAMS + team, c_hi - 1);
+#pragma unroll
+        for (int k = 0; k < 4 / RT; ++k) {
+            const unsigned part = unsigned(tile * (4 / RT) + k) * 256u;
+            load4_to_lds(rs_rsrc, smem + kRsLds + (it & 1) * (TEAMS * 1024) + team * 1024 + part, unsigned(lane) * 4u,
+                         unsigned(ch) * (kChunkCols * 4) + part);
+        }
+    };
+
+    v16f yacc[GROUPS];
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) yacc[g] = zero16();
+
+    UnitAcc acc;
+    StepInputs in;
+    unsigned buf = 0;
+    request_rs(0);
+    // step s's inputs are requested two steps ahead
+    request();
+    loads_barrier<0>();
+    request();
+    {
+        FirstReads first;
+        begin_reads<RT>(in, first, v_rd, s_rd);
+        wait_inputs(in, first.f7, first.signs);
+    }
+    for (int it = 0; it < iters; ++it) {
+        auto step = [&](auto first) __attribute__((always_inline)) {
+            loads_barrier<0>();
+            request();
+            const unsigned nb = next_buf(buf);
+            add_block<decltype(first)::value, RT>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
+            buf = nb;
+        };
+        step(std::true_type{});
+        for (int i = 1; i < n; ++i) step(std::false_type{});
+        // (what the last step read ahead was activations: read again below)
+        const bool valid = c_lo + it * TEAMS + team < c_hi;   // uniform over the wavefront
+        const unsigned rs_rd = lds0 + kRsLds + unsigned(it & 1) * (TEAMS * 1024) + unsigned(team) * 1024u + unsigned(hl) * 512u;
+        v4i b[16];   // W' diag(1/s) of the unit as B operands: step e = columns 8 e .. 8 e + 7 of both halves
+        v4f r[2][2];
+        auto scale = [&](auto e) __attribute__((always_inline)) {
+            constexpr int E = decltype(e)::value;
+            v4f(&q)[2] = r[E & 1];
+            if constexpr (E < 15) {
+                read_scales<(E < 15 ? E + 1 : 15)>(r[(E + 1) & 1], rs_rd);
+                wait_scales<2>(q);
+            } else {
+                wait_scales<0>(q);
+            }
+#pragma unroll
+            for (int t = 0; t < 8; t += 2)
+                b[E][t >> 1] = scaled_pair(acc[t][E >> 2][E & 3], acc[t + 1][E >> 2][E & 3], q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        read_scales<0>(r[0], rs_rd);
+#define BS_SCALE(E) scale(std::integral_constant<int, E>{});
+        BS_SCALE(0) BS_SCALE(1) BS_SCALE(2) BS_SCALE(3) BS_SCALE(4) BS_SCALE(5) BS_SCALE(6) BS_SCALE(7)
+        BS_SCALE(8) BS_SCALE(9) BS_SCALE(10) BS_SCALE(11) BS_SCALE(12) BS_SCALE(13) BS_SCALE(14) BS_SCALE(15)
+#undef BS_SCALE
+        FirstReads first;
+#pragma unroll
+        for (int xs = 0; xs < kXSteps; ++xs) {
+            const int g = xs / kPerGroup, e0 = xs % kPerGroup * kPieces;
+            loads_barrier<0>();
+            if (xs == 0) request_rs(it + 1);
+            request();
+            const unsigned nb = next_buf(buf);
+            if (xs == kXSteps - 1) begin_reads<RT>(in, first, v_rd + nb, s_rd + nb);   // the next chunk's first step
+#pragma unroll
+            for (int eq = 0; eq < kPieces / 4; ++eq) {
+                v4i a[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const unsigned pos = unsigned(hl * kPieces + eq * 4 + k) ^ unsigned(ln & 15);
+                    read16<0>(a[k], x_rd + buf + pos * 16u);
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
+                if (valid) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        yacc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a[k]),
+                                                                         __builtin_bit_cast(v8h, b[e0 + eq * 4 + k]), yacc[g], 0, 0, 0);
+                }
+            }
+            buf = nb;
+        }
+        wait_inputs(in, first.f7, first.signs);
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    // the teams' partial tiles meet in LDS; D[i = token][n = row]: lane (row ln), register v holds token
+    // 8 (v / 4) + 4 hl + v % 4 of the group
+    float* const red = reinterpret_cast<float*>(smem);   // [wave][16][64]
+    float* const mine = p.part + size_t(blockIdx.y) * p.batch * p.out;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+        if (g) __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = yacc[g][v];
+        __syncthreads();
+        // thread = (row, token): consecutive lanes take consecutive rows
+        for (int o = tid; o < kRows * TOK; o += 512) {
+            const int row = o & (kRows - 1), t = o / kRows;   // token of the group
+            const int v = (t >> 3) * 4 + (t & 3), l = ((t >> 2) & 1) * 32 + (row & 31);
+            float sum = 0.0f;
+#pragma unroll
+            for (int w = 0; w < TEAMS; ++w) sum += red[((w * RT + (row >> 5)) * 16 + v) * 64 + l];
+            const int tok = g * TOK + t, r = int(blockIdx.x) * kRows + row;
+            if (tok < p.batch && r < p.out) {
+                if (ksplit == 1)
+                    store_y(p, size_t(tok) * p.out + r, sum);
+                else   // write-through: the reader may sit on another XCD
+                    __hip_atomic_store(mine + size_t(tok) * p.out + r, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    if (ksplit == 1) return;
+
+    // column split: the last workgroup of this row group adds the ksplit partial tiles in a fixed order and stores y (same
+    // protocol as the decode kernel: write-through stores, one relaxed agent-scope counter after a barrier, agent-scope
+    // loads by the last one)
+    unsigned* const flag = reinterpret_cast<unsigned*>(smem + 8 * 4096);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // each wavefront's stores are acknowledged before it reaches the barrier
+    __syncthreads();
+    unsigned* const ctr = p.ctr + blockIdx.x;
+    if (tid == 0) {
+        const unsigned old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = (old + 1u == unsigned(ksplit)) ? 1u : 0u;
+    }
+    __syncthreads();
+    if (*flag) {
+        const unsigned span = unsigned(size_t(ksplit) * p.batch * p.out * 4);
+        __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(p.part, 0, span, 0x00020000);
+        constexpr int kAgentScope = 16;   // sc1
+        // thread = (token, 4 consecutive rows)
+        for (int o = tid; o < p.batch * (kRows / 4); o += 512) {
+            const int tok = o / (kRows / 4), row = int(blockIdx.x) * kRows + 4 * (o & (kRows / 4 - 1));
+            if (row >= p.out) continue;   // out is a multiple of 32: a quad is inside or outside as a whole
+            v4i v[8];
+#pragma unroll
+            for (int z = 0; z < 8; ++z)
+                v[z] = __builtin_amdgcn_raw_buffer_load_b128(
+                    prs, z < ksplit ? unsigned(((size_t(z) * p.batch + tok) * p.out + row) * 4) : span, 0, kAgentScope);
+            float o4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int z = 0; z < 8; ++z)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) o4[k] += __int_as_float(v[z][k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) store_y(p, size_t(tok) * p.out + row + k, o4[k]);
+        }
+        if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+}  // namespace
+
+constexpr int kBatchMaxSplit = 8;
+
+// Column split: too few row groups to fill the chip share their column chunks among several workgroups (the workspace must
+// hold a partial row per split and token).  The split with the fewest rounds x chunk iterations is taken, the smallest of
+// equals.
+static int batch_split(int out, int in, int batch, int part_slots) {
+    const int groups = (out + 63) / 64, nch = in / kChunkCols;
+    int best = 1;
+    long best_cost = 0;
+    for (int k = 1; k <= kBatchMaxSplit && k <= nch && (k == 1 || k * batch <= part_slots); ++k) {
+        const long cost = long((groups * k + 255) / 256) * (((nch + k - 1) / k + 3) / 4);
+        if (k == 1 || cost < best_cost) {
+            best = k;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+template <int TOK, int GROUPS>
+static hipError_t launch_batch_t(KParams p, hipStream_t st) {
+    const size_t smem = size_t(3) * 4 * StepLayout<2>::kBytes + 2 * 4 * kChunkCols * 4;
+    static std::atomic<bool> attr_set{false};   // setting the attribute twice is harmless
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch<TOK, GROUPS>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(smem));
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    p.n_ks = batch_split(p.out, p.in, p.batch, p.part_slots);
+    hipLaunchKernelGGL((k_batch<TOK, GROUPS>), dim3((p.out + 63) / 64, p.n_ks), dim3(512), smem, st, p);
+    return hipGetLastError();
+}
+
+// Estimated duration (microseconds; fitted to 553 cases from 512 x 512 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens: 3.7 %
+// root mean square): per round and chunk iteration of a workgroup 1.05-1.25 us per block and ~2-4 us for scaling and product
+double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
+    const int groups = (out + 63) / 64, nch = in / kChunkCols, split = batch_split(out, in, batch, part_slots);
+    const int wgs = groups * split, xsteps = batch > 32 ? 4 : batch > 16 ? 2 : 1;
+    const double its = double((wgs + 255) / 256) * (((nch + split - 1) / split + 3) / 4), fill = wgs < 256 ? wgs / 256.0 : 1.0;
+    return 4.3 + its * (n_loaded * (1.05 + 0.2 * fill) + 1.2 + 0.63 * xsteps) + (split > 1 ? 1.9 + 0.018 * batch * split : 0.0);
+}
+
+bool batch_fits(const KParams& p) {   // one 32-bit buffer descriptor over the loaded blocks, one counter per row group
+    return size_t(p.n_loaded) * p.block_stride < (size_t(1) << 32) && (p.out + 63) / 64 <= kCounterSlots;
+}
+
+hipError_t launch_batch(const KParams& p, hipStream_t st) {
+    return p.batch > 32 ? launch_batch_t<32, 2>(p, st) : p.batch > 16 ? launch_batch_t<32, 1>(p, st) : launch_batch_t<16, 1>(p, st);
+}
+
+}  // namespace bitstack

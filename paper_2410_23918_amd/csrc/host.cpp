@@ -327,7 +327,9 @@ static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t work
     double t_panel;
     if (batch <= kSmallBatch) {
         t_panel = fused_time_us(g.out, g.in, batch, n_loaded, g.part_slots);
-        if (batch > 32 && g.xpack_bytes) {   // launch_panel takes the cheaper of the two here
+        const double t_batch = batch_time_us(g.out, g.in, batch, n_loaded, g.part_slots);   // launch_panel takes the cheapest
+        t_panel = t_batch < t_panel ? t_batch : t_panel;
+        if (batch > 32 && g.xpack_bytes) {
             const double t_tile = tile_time_us(g.out, g.in, batch, n_loaded);
             t_panel = t_tile < t_panel ? t_tile : t_panel;
         }

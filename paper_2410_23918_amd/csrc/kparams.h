@@ -78,6 +78,10 @@ inline KParams make_params(const LaunchArgs& a) {
     return p;
 }
 
+// batch kernel for up to 64 tokens (batch.hip)
+bool batch_fits(const KParams& p);
+hipError_t launch_batch(const KParams& p, hipStream_t st);
+
 // p.x [batch][in] -> p.xpack in matrix-core fragment order (tokens padded with zeros to a multiple of 32)
 void launch_xpack(const KParams& p, hipStream_t st);
 

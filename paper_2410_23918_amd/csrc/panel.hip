@@ -985,15 +985,16 @@ static hipError_t launch_tile(const KParams& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Estimated durations (microseconds, constants fitted to measurements).  k_fused: per round of
-// 256 workgroups ~8 us fixed + ~0.80 us per block and pair of column chunks of a workgroup; later
-// workgroups start as earlier ones end, so rounds beyond the first count fractionally.
+// Estimated durations (microseconds).  k_fused (fitted to the same 553 cases as batch_time_us): per round of 256 workgroups ~8 us
+// and 0.65-0.82 us per block and pair of column chunks of a workgroup; later workgroups start as earlier ones end, so rounds
+// beyond the first count fractionally.
 double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
     const int row_tiles = (out + 2 * kTileRows - 1) / (2 * kTileRows), chunk_pairs = (in / kChunkCols + 1) / 2;
     const int split = small_batch_split(out, in, batch, part_slots);
     const int wgs = row_tiles * ((batch + 31) / 32) * split;
-    const double rounds = wgs <= 256 ? 1.0 : wgs / 256.0;
-    return rounds * (8.0 + 0.80 * n_loaded * ((chunk_pairs + split - 1) / split)) + (split > 1 ? 4.0 : 0.0);
+    const double rounds = wgs <= 256 ? 1.0 : wgs / 256.0, fill = wgs < 256 ? wgs / 256.0 : 1.0;
+    return rounds * (20.1 + n_loaded * ((chunk_pairs + split - 1) / split) * (0.65 + 0.17 * fill)) - 12.2 +
+           (split > 1 ? 1.5 - 0.013 * batch * split : 0.0);
 }
 // k_tile: per pair of column chunks ~0.9 us per block for the rebuild + 12-14 us for the product
 // (14 when several token tiles of a row tile run at once, 6.5 up to 256 tokens, where only one
@@ -1008,12 +1009,19 @@ double tile_time_us(int out, int in, int batch, int n_loaded) {
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     KParams p = make_params(a);
     if (a.n_loaded < 1 || a.batch < 1) return hipErrorInvalidValue;
-    // 33..64 tokens: k_fused rebuilds the signed tiles twice; with many row tiles the weight-tile
-    // kernel, which rebuilds once, is the cheaper one
-    if (a.batch > 32 && a.batch <= kFusedMaxBatch && fused_fits(p) && tile_fits(p) &&
-        tile_time_us(p.out, p.in, p.batch, p.n_loaded) < fused_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots))
-        return launch_tile(p, st);
-    if (a.batch <= kFusedMaxBatch && fused_fits(p)) return launch_fused(p, st);
+    if (a.batch <= kFusedMaxBatch) {
+        // the cheapest of three estimates: k_batch sums the weight over the blocks before it multiplies (many blocks, many
+        // tokens); k_fused multiplies every block's tile and has less to do per chunk (few blocks), but rebuilds the tiles per 32
+        // tokens; the weight-tile kernel is a candidate from 33 tokens on
+        const bool batch_ok = batch_fits(p);
+        const double tb = batch_ok ? batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 0.0;
+        const double tf = fused_fits(p) ? fused_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 0.0;
+        const bool take_batch = batch_ok && (tf == 0.0 || tb < tf);
+        if (a.batch > 32 && tile_fits(p) && tile_time_us(p.out, p.in, p.batch, p.n_loaded) < (take_batch ? tb : tf))
+            return launch_tile(p, st);
+        if (take_batch) return launch_batch(p, st);
+        if (tf != 0.0) return launch_fused(p, st);
+    }
     if (a.batch > kFusedMaxBatch && tile_fits(p)) return launch_tile(p, st);
     if (a.batch > 256) return launch_panel_t<4>(p, st);
     if (a.batch > 128) return launch_panel_t<2>(p, st);

@@ -45,11 +45,15 @@ constexpr int kClasses = 8;                 // column classes of a unit (bit pos
 constexpr int kVClassBytes = 1024;          // V of one class: 2 halves x 16 ranks x 16 columns fp16
 constexpr int kVChunkBytes = kClasses * kVClassBytes;
 
-// A workgroup has four wavefronts; each loads its own signs and U and two classes of the V panel that they share.  One
-// step's inputs in LDS, per wavefront: [signs 1 KiB][V of classes 2 wave, 2 wave + 1][U 1 KiB].
-constexpr int kRebuildWaves = 4;
-constexpr int kWaveStepBytes = 4096, kVOffset = 1024, kUOffset = 3072;
-constexpr int frag_offset(int t) { return (t >> 1) * kWaveStepBytes + kVOffset + (t & 1) * kVClassBytes; }
+// The RT wavefronts (4 or 2 row tiles) that work on the same column chunk share its V panel; each loads its own signs and U
+// and 8 / RT classes of V.  One step's inputs in LDS, per wavefront: [signs 1 KiB][V of its classes][U 1 KiB].
+template <int RT>
+struct StepLayout {
+    static constexpr int kClassesPerWave = kClasses / RT;
+    static constexpr int kVOffset = 1024, kUOffset = kVOffset + kClassesPerWave * kVClassBytes, kWaveBytes = kUOffset + 1024;
+    static constexpr int kBytes = RT * kWaveBytes;
+    static constexpr int frag(int t) { return t / kClassesPerWave * kWaveBytes + kVOffset + t % kClassesPerWave * kVClassBytes; }
+};
 
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -90,11 +94,11 @@ struct VFrag {
     v2u q0, q1;
 };
 // A operand of the magnitude product of class T: two reads
-template <int T>
+template <int T, int RT>
 __device__ __forceinline__ void read_frag(VFrag& f, unsigned addr) {
     asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
                  : "=&v"(f.q0), "=&v"(f.q1)
-                 : "v"(addr), "n"(frag_offset(T)), "n"(frag_offset(T) + 512));
+                 : "v"(addr), "n"(StepLayout<RT>::frag(T)), "n"(StepLayout<RT>::frag(T) + 512));
 }
 template <int OFF>
 __device__ __forceinline__ void read16(v4i& d, unsigned addr) {
@@ -107,6 +111,35 @@ __device__ __forceinline__ void wait_lds(VFrag& f) {
 template <int N>
 __device__ __forceinline__ void wait_lds(v4i& d) {
     asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(d) : "n"(N));
+}
+
+// One wavefront's part of a step's inputs: signs at s_off, V of its classes at v_off (class 0 of the chunk + the wavefront's
+// share), U at u_off.  (A load's constant offset counts in memory and in LDS: v_lane and u_lane have it taken off.)
+template <int RT>
+__device__ __forceinline__ void load_step(__amdgpu_buffer_rsrc_t rsrc, unsigned char* mine, unsigned s_lane, unsigned v_lane,
+                                          unsigned u_lane, unsigned s_off, unsigned v_off, unsigned u_off) {
+    typedef StepLayout<RT> L;
+    load_to_lds<0>(rsrc, mine, s_lane, s_off);
+    load_to_lds<L::kVOffset>(rsrc, mine, v_lane, v_off);
+    load_to_lds<L::kVOffset + kVClassBytes>(rsrc, mine, v_lane, v_off);
+    if constexpr (RT == 4) {
+        load_to_lds<L::kUOffset>(rsrc, mine, u_lane, u_off);
+    } else {   // (constant offsets reach 4095)
+        static_assert(RT == 4 || RT == 2, "");
+        load_to_lds<L::kVOffset + 2 * kVClassBytes>(rsrc, mine, v_lane, v_off);
+        load_to_lds<0>(rsrc, mine + 4096, v_lane, v_off + 4096u);
+        load_to_lds<L::kUOffset - 4096>(rsrc, mine + 4096, u_lane, u_off);
+    }
+}
+template <int RT>
+constexpr int kStepLoads = kClasses / RT + 2;
+template <int RT>
+__device__ __forceinline__ unsigned v_lane_offset(unsigned off_v, unsigned wave_of_team, unsigned lane) {
+    return off_v + wave_of_team * unsigned(kClasses / RT * kVClassBytes) + v_piece_offset(lane) - unsigned(StepLayout<RT>::kVOffset);
+}
+template <int RT>
+__device__ __forceinline__ unsigned u_lane_offset(unsigned off_u, unsigned row_tile, unsigned lane) {
+    return off_u + (row_tile * kTileRows + (lane & 31)) * 32u + (lane >> 5) * 16u - unsigned(StepLayout<RT>::kUOffset % 4096);
 }
 
 // A operand of the accumulating product: output row i of a lane's group takes slot 0, 2, 1, 3 (the pairs hold
@@ -131,6 +164,25 @@ __device__ __forceinline__ v16f zero16() {
 #pragma unroll
     for (int v = 0; v < 16; ++v) z[v] = 0.0f;
     return z;
+}
+
+// 1/s of the eight columns of byte E: addr = LDS byte address of the lane's half of a chunk's 256 scales
+template <int E>
+__device__ __forceinline__ void read_scales(v4f (&d)[2], unsigned addr) {
+    asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
+                 : "=&v"(d[0]), "=&v"(d[1])
+                 : "v"(addr), "n"(E * 32), "n"(E * 32 + 16));
+}
+template <int N>
+__device__ __forceinline__ void wait_scales(v4f (&d)[2]) {
+    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(d[0]), "+v"(d[1]) : "n"(N));
+}
+// fp16 pair (a ra, b rb), product and conversion in one instruction each
+__device__ __forceinline__ int scaled_pair(float a, float b, float ra, float rb) {
+    int d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(d) : "v"(a), "v"(ra));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(d) : "v"(b), "v"(rb));
+    return d;
 }
 
 // acc[t][w][b]: column 128 g + 32 w + 8 b + t of row lane % 32, g = lane / 32
@@ -164,22 +216,24 @@ __device__ __forceinline__ void wait_inputs(StepInputs& in, VFrag& f7, v4i& sign
     asm("v_mov_b64 %0, %1" : "=v"(in.s[1]) : "v"(hi));
 }
 
-// the first reads of the first step.  vaddr: LDS byte address of its V panel + v_read_offset; saddr: of the lane's 16
-// bytes of signs (its 16 bytes of U are kUOffset further on)
-__device__ __forceinline__ void begin_steps(StepInputs& in, unsigned vaddr, unsigned saddr) {
-    VFrag f;
+// The first reads of a step that no step precedes: requested by begin_reads, taken over by wait_inputs.  vaddr: LDS byte
+// address of its V panel + v_read_offset; saddr: of the lane's 16 bytes of signs (its 16 bytes of U are kUOffset further on)
+struct FirstReads {
+    VFrag f7;
     v4i signs;
-    read_frag<7>(f, vaddr);
-    read16<kUOffset>(in.u, saddr);
-    read16<0>(signs, saddr);
-    read_frag<6>(in.f, vaddr);
-    wait_inputs(in, f, signs);
+};
+template <int RT>
+__device__ __forceinline__ void begin_reads(StepInputs& in, FirstReads& r, unsigned vaddr, unsigned saddr) {
+    read_frag<7, RT>(r.f7, vaddr);
+    read16<StepLayout<RT>::kUOffset>(in.u, saddr);
+    read16<0>(r.signs, saddr);
+    read_frag<6, RT>(in.f, vaddr);
 }
 
 // One block onto the wavefront's unit.  vnext, snext: addresses of the next step.  FIRST: the accumulators start
 // from zero.  A SIMD issues one vector or matrix instruction per four cycles, and with two wavefronts to it a
 // wavefront issues one instruction of any kind per eight: what counts is the number of instructions.
-template <bool FIRST>
+template <bool FIRST, int RT>
 __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned vaddr, unsigned vnext, unsigned snext, v4h ident) {
     typedef unsigned long long u64;
     // per pair of words, for the class at hand: bytes 1, 3 (hi) and 0, 2 (lo) of each word at its bits 15, 31
@@ -221,13 +275,13 @@ __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned
     v16f n;
 #define BS_CLASS(T, CUR, NXT, F0, F1)                     \
     {                                                     \
-        read_frag<T - 2>(F0, vaddr);                      \
+        read_frag<T - 2, RT>(F0, vaddr);                  \
         wait_lds<2>(F1);                                  \
         NXT = magnitude(F1, in.u);                        \
         __builtin_amdgcn_sched_barrier(0);                \
         apply(acc[T], CUR, true);                         \
     }
-    read_frag<5>(f, vaddr);
+    read_frag<5, RT>(f, vaddr);
     n = magnitude(in.f, in.u);
     __builtin_amdgcn_sched_barrier(0);
     apply(acc[7], in.m, true);
@@ -242,10 +296,10 @@ __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned
     __builtin_amdgcn_sched_barrier(0);
     apply(acc[1], in.m, true);
     v4i signs;
-    read_frag<7>(f, vnext);
-    read16<kUOffset>(in.u, snext);
+    read_frag<7, RT>(f, vnext);
+    read16<StepLayout<RT>::kUOffset>(in.u, snext);
     read16<0>(signs, snext);
-    read_frag<6>(in.f, vnext);
+    read_frag<6, RT>(in.f, vnext);
     apply(acc[0], n, false);
     wait_inputs(in, f, signs);
     __builtin_amdgcn_sched_barrier(0);

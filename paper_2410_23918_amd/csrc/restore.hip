@@ -23,8 +23,10 @@
 namespace bitstack {
 
 constexpr int kRestoreMaxBlocks = 29;
+constexpr int kRebuildWaves = 4;                          // wavefronts of a workgroup
 constexpr int kRestoreRows = kRebuildWaves * kTileRows;   // a row group: 32 rows per wavefront
-constexpr unsigned kStepBytes = kRebuildWaves * kWaveStepBytes, kRing = 4;
+typedef StepLayout<kRebuildWaves> Step;
+constexpr unsigned kStepBytes = Step::kBytes, kRing = 4;
 constexpr unsigned kRsLds = kRing * kStepBytes, kTurnLds = kRsLds + kChunkCols * 4;
 constexpr unsigned kTurnBytes = 32 * 64;
 
@@ -46,13 +48,12 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(p.blocks), 0, unsigned(n) * stride, 0x00020000);
     __amdgpu_buffer_rsrc_t rs_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.rs), 0, unsigned(p.in) * 4u, 0x00020000);
-    // (a load's constant offset counts in memory and in LDS: taken off here)
     const unsigned s_lane = unsigned(ch) * kUnitBytes + unsigned(lane) * 16u;
-    const unsigned v_lane = unsigned(p.off_v) + unsigned(ch) * kVChunkBytes + unsigned(wave) * 2048u + v_piece_offset(unsigned(lane)) - kVOffset;
-    const unsigned u_lane = unsigned(p.off_u) + unsigned(ln) * 32u + unsigned(hl) * 16u - kUOffset;
+    const unsigned v_lane = v_lane_offset<kRebuildWaves>(unsigned(p.off_v), unsigned(wave), unsigned(lane)) + unsigned(ch) * kVChunkBytes;
+    const unsigned u_lane = u_lane_offset<kRebuildWaves>(unsigned(p.off_u), 0u, unsigned(lane));
     const unsigned lds0 = unsigned(reinterpret_cast<uintptr_t>((lds_void*)smem));
     const unsigned v_rd = lds0 + v_read_offset(unsigned(lane));
-    const unsigned s_rd = lds0 + unsigned(wave) * kWaveStepBytes + unsigned(lane) * 16u;
+    const unsigned s_rd = lds0 + unsigned(wave) * Step::kWaveBytes + unsigned(lane) * 16u;
     const v4h ident = accumulate_matrix(unsigned(lane));
 
     // a step = (row group, block), row groups outermost; its inputs are requested three steps ahead, into a ring of
@@ -62,11 +63,7 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     unsigned qv = 0, qs = unsigned(row_tile(rg0)) * unsigned(nch) * kUnitBytes, qu = unsigned(row_tile(rg0)) * 1024u;
     unsigned qbuf = 0;
     auto request = [&]() {
-        unsigned char* const mine = smem + qbuf + wave * kWaveStepBytes;
-        load_to_lds<0>(rsrc, mine, s_lane, qs);
-        load_to_lds<kVOffset>(rsrc, mine, v_lane, qv);
-        load_to_lds<kVOffset + kVClassBytes>(rsrc, mine, v_lane, qv);
-        load_to_lds<kUOffset>(rsrc, mine, u_lane, qu);
+        load_step<kRebuildWaves>(rsrc, smem + qbuf + wave * Step::kWaveBytes, s_lane, v_lane, u_lane, qs, qv, qu);
         qv += stride;
         qs += stride;
         qu += stride;
@@ -79,7 +76,7 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
         }
         qbuf = (qbuf + kStepBytes) & (kRing * kStepBytes - 1);
     };
-    constexpr int kInFlight = 4;   // loads of one step and wavefront
+    constexpr int kInFlight = kStepLoads<kRebuildWaves>;   // loads of one step and wavefront
 
     UnitAcc acc;
     StepInputs in;
@@ -89,14 +86,18 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     request();
     loads_barrier<kInFlight>();
     request();
-    begin_steps(in, v_rd, s_rd);
+    {
+        FirstReads first;
+        begin_reads<kRebuildWaves>(in, first, v_rd, s_rd);
+        wait_inputs(in, first.f7, first.signs);
+    }
     auto step = [&](auto first) __attribute__((always_inline)) {
         // the next step's inputs have landed (this wavefront's loads, then everybody's), and nobody reads the previous
         // step's any more
         loads_barrier<kInFlight>();
         request();
         const unsigned nb = (buf + kStepBytes) & (kRing * kStepBytes - 1);
-        add_block<decltype(first)::value>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
+        add_block<decltype(first)::value, kRebuildWaves>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
         buf = nb;
     };
     // The unit times 1/s (Eq. 4 folded into the columns), as fp16 to the dense matrix.  A lane holds 256

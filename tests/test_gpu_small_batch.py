@@ -1,0 +1,51 @@
+"""The batch kernel for up to 64 tokens at the edges of its tiling: row counts that end inside a workgroup, chunk counts that
+leave teams without a chunk, both sides of its 16- and 32-token groups, with and without a column split (whose partial
+tiles meet in the workspace).  45 blocks: more than the other small-batch kernel holds, so this one runs.  Every
+element of y in fp32."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("out,inn", [
+    (32, 256),       # one row tile, one chunk: three of four teams idle
+    (96, 1280),      # 5 chunks: split over workgroups
+    (160, 2816),     # 11 chunks, a ragged second row group
+])
+@pytest.mark.parametrize("batch", [2, 16, 17, 32, 33, 64])
+def test_every_output_of_the_small_batch_kernel(out, inn, batch):
+    import torch
+    import paper_2410_23918_amd as B
+    n = 45
+    g = torch.Generator(device="cuda:0").manual_seed(out + inn + batch)
+    s = np.exp(0.5 * np.random.default_rng(batch).standard_normal(inn)).astype(np.float32)
+    ps = B.PackedStack.empty(out, inn, n, s, max_batch=64)
+    w = torch.zeros((out, inn), device="cuda:0")
+    mag = torch.zeros_like(w)   # sum over blocks of |U V^T|
+    bits = torch.arange(32, device="cuda:0", dtype=torch.int32)
+    for _ in range(n):
+        words = torch.randint(-2**31, 2**31, (out, inn // 32), generator=g, device="cuda:0", dtype=torch.int64).to(torch.int32)
+        u = (0.1 * torch.randn((out, 16), generator=g, device="cuda:0")).half()
+        v = (0.1 * torch.randn((inn, 16), generator=g, device="cuda:0")).half()
+        ps.push_block_device(words, u, v)
+        m = u.float() @ v.float().t().contiguous()
+        w += torch.where(((words[:, :, None] >> bits) & 1).reshape(out, inn).bool(), m, -m)
+        mag += m.abs()
+    rs = torch.from_numpy(1.0 / s).to("cuda:0")
+    w *= rs
+    mag *= rs
+    x = torch.randn((batch, inn), generator=g, device="cuda:0").half()
+    y = torch.full((batch, out), float("nan"), device="cuda:0")
+    for _ in range(2):   # the second call finds the counters as the first left them
+        ps.linear_batched(x, n, y=y, kernel=B.KERNEL_PANEL)
+        torch.cuda.synchronize()
+        xa = x.float().abs().double()
+        want = x.double() @ w.double().t().contiguous()
+        # magnitudes rounded to fp16 (2^-11 of each), their sum times 1/s rounded once more; then fp32 sums of 16-column
+        # products: at most in / 16 + 16 roundings of 2^-24 of the sum of absolute values
+        werr = 2.0**-11 * (mag + w.abs()) * 1.01 + 2.0**-20 * rs + 2.0**-24
+        bound = xa @ werr.double().t().contiguous() + (inn / 16 + 16) * 2.0**-24 * (xa @ w.abs().double().t().contiguous())
+        worst = ((y.double() - want).abs() / bound).max().item()
+        print(f"{out}x{inn} batch {batch}: largest error {worst:.3f} of its bound", flush=True)
+        assert worst <= 1.0   # also false for an element that was not written (NaN)
