@@ -8,13 +8,15 @@
 // "SVD" is a block power (subspace) iteration with k + 16 columns followed by a Rayleigh-Ritz
 // step; any method that returns the leading triplets is a valid reading.  The two tall products
 // per round, |R| X and |R|^T Y, run on the bf16 matrix cores from bf16 copies of |R| (written once
-// per block, row-major and transposed); the product of the Rayleigh-Ritz step, which fixes U and V,
+// per block, as it lies and transposed); the product of the Rayleigh-Ritz step, which fixes U and V,
 // reads the fp32 residual (|.| applied as it is loaded); sums are fp32, the 32 x 32 Gram /
 // Cholesky / eigenvalue problems fp64.  The sign matrix is never materialised.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "kernels.h"
 #include "layout.h"
@@ -23,65 +25,160 @@ namespace bitstack {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-constexpr int kL = 32;        // subspace width: rank 16 + 16 columns of oversampling
-constexpr int kDcTile = 128;  // output indices per workgroup of the tall products
-constexpr int kDcChunk = 32;  // reduction indices per LDS stage
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) volatile double lds_double;
 
-__global__ __launch_bounds__(256) void k_dc_scale(const float* W, const float* s, float* R, size_t total, int in) {
-    const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i < total) R[i] = W[i] * s[i % size_t(in)];
+constexpr int kL = 32;        // subspace width: rank 16 + 16 columns of oversampling
+constexpr int kDcTile = 128;  // output indices per workgroup of the fp32 product
+constexpr int kDcChunk = 32;  // its reduction indices per LDS stage
+
+// Fragment order: a bf16 matrix A (M x K) as the matrix cores take it, [M / 32][K / 16][half][row % 32][8 values of K], so that
+// a wavefront's operand for 32 rows and 16 reduction indices is 1 KiB in the order of its lanes.  M is a multiple of 32, K of 16.
+__device__ __forceinline__ size_t frag_piece(int row, int k8, int K) {   // index of the 16-byte piece with A[row][8 k8 ..]
+    return (size_t(row >> 5) * (K >> 4) + (k8 >> 1)) * 64 + (k8 & 1) * 32 + (row & 31);
 }
 
-// start vectors: any full-rank matrix will do; a counter-based hash keeps it reproducible
-__global__ __launch_bounds__(256) void k_dc_random(float* X, size_t total, unsigned seed) {
-    const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= total) return;
-    unsigned h = unsigned(i) * 2654435761u ^ seed;
+// start vectors: any full-rank matrix will do; a counter-based hash keeps it reproducible.  X (in x kL) in fragment order
+// of its transpose: thread = 8 rows of one column.
+__device__ __forceinline__ float start_value(unsigned i, unsigned seed) {
+    unsigned h = i * 2654435761u ^ seed;
     h ^= h >> 16; h *= 0x85ebca6bu; h ^= h >> 13; h *= 0xc2b2ae35u; h ^= h >> 16;
-    X[i] = float(int(h >> 8) - (1 << 23)) * (1.0f / float(1 << 23));
+    return float(int(h >> 8) - (1 << 23)) * (1.0f / float(1 << 23));
 }
 
 // fp32 -> bf16, round to nearest even (the residual is finite)
-__device__ __forceinline__ unsigned short bf16_of(float x) {
+__device__ __forceinline__ unsigned bf16_of(float x) {
     const unsigned u = __float_as_uint(x);
-    return (unsigned short)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// canonical sign words of the residual: bit b of word w of a row = (R[row][32 w + b] >= 0),
-// -0.0 and 0.0 both count as +1.  One wavefront per 64 consecutive columns of a row.
-__global__ __launch_bounds__(256) void k_dc_signs(const float* R, uint32_t* words, int out, int in) {
-    const size_t wid = size_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int groups = in / 64;
-    if (wid >= size_t(out) * groups) return;   // whole wavefront
-    const size_t row = wid / groups, cg = wid % groups;
-    const float x = R[row * in + cg * 64 + lane];
-    const unsigned long long m = __ballot(!(x < 0.0f));
-    if (lane == 0) {
-        words[row * (in / 32) + cg * 2] = uint32_t(m);
-        words[row * (in / 32) + cg * 2 + 1] = uint32_t(m >> 32);
+__global__ __launch_bounds__(256) void k_dc_random(uint4* Xf, int in, unsigned seed) {
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= in / 8 * kL) return;
+    const int c = idx % kL, k8 = idx / kL;
+    unsigned w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        w[e] = bf16_of(start_value(unsigned((8 * k8 + 2 * e) * kL + c), seed)) |
+               bf16_of(start_value(unsigned((8 * k8 + 2 * e + 1) * kL + c), seed)) << 16;
+    Xf[frag_piece(c, k8, in)] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// One pass over the residual per block: the first block's residual R = W diag(s), every later one's R <- R - sign(R) (.) (U V^T)
+// with the previous block's factors as stored (fp16); from it the canonical sign words of the block (bit b of word w of a row =
+// (R[row][32 w + b] >= 0), -0.0 and 0.0 both count as +1) and |R| as bf16, as it lies (Rh) and transposed (RhT), both in fragment
+// order.  128 rows x 64 columns per workgroup; a thread owns 8 consecutive columns of 4 rows.  Bound by memory: 12 bytes per
+// element.  4096 x 4096: 37 us for the first block and 47 us for a later one, where scaling, packing of the signs, conversion
+// and update as kernels of their own took about 90 and 120.
+constexpr int kResRows = 128, kResCols = 64, kResLd = kResCols + 8;
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_dc_residual(const float* W, const float* s, float* R, const __half* U, const __half* V,
+                                                     uint32_t* words, uint4* Rh, uint4* RhT, int out, int in) {
+    __shared__ float Us[FIRST ? 1 : kResRows][kRank + 4];
+    __shared__ float Vs[FIRST ? 1 : kResCols][kRank + 4];
+    __shared__ __attribute__((aligned(16))) unsigned short Ts[kResRows][kResLd];
+    const int tid = threadIdx.x;
+    const int o0 = blockIdx.y * kResRows, j0 = blockIdx.x * kResCols;   // in is a multiple of 64, out of 32
+    const int oct = tid & 7, r0 = tid >> 3;   // rows r0 + 32 i
+    const float* const src = FIRST ? W : R;
+    float x[4][8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const size_t at = size_t(min(o0 + r0 + 32 * i, out - 1)) * in + j0 + 8 * oct;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float4 v = *reinterpret_cast<const float4*>(src + at + 4 * q);
+            x[i][4 * q] = v.x; x[i][4 * q + 1] = v.y; x[i][4 * q + 2] = v.z; x[i][4 * q + 3] = v.w;
+        }
+    }
+    if constexpr (FIRST) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float sc = s[j0 + 8 * oct + e];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i][e] *= sc;
+        }
+    } else {
+        for (int idx = tid; idx < kResRows * kRank; idx += 256) {
+            const int r = idx / kRank, c = idx % kRank;
+            Us[r][c] = __half2float(U[size_t(min(o0 + r, out - 1)) * kRank + c]);
+        }
+        for (int idx = tid; idx < kResCols * kRank; idx += 256) {   // column 8 o + e in row 8 e + o: a wavefront's reads are spread over the banks
+            const int j = idx / kRank, c = idx % kRank;
+            Vs[(j & 7) * 8 + (j >> 3)][c] = __half2float(V[size_t(j0 + j) * kRank + c]);
+        }
+        __syncthreads();
+        float m[4][8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) m[i][e] = 0.f;
+#pragma unroll
+        for (int c = 0; c < kRank; c += 4) {
+            float4 u[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) u[i] = *reinterpret_cast<const float4*>(&Us[r0 + 32 * i][c]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float4 v = *reinterpret_cast<const float4*>(&Vs[e * 8 + oct][c]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    m[i][e] = fmaf(u[i].w, v.w, fmaf(u[i].z, v.z, fmaf(u[i].y, v.y, fmaf(u[i].x, v.x, m[i][e]))));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[i][e] = (x[i][e] < 0.0f) ? x[i][e] + m[i][e] : x[i][e] - m[i][e];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int o = o0 + r0 + 32 * i;
+        unsigned h[4], bits = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bits |= (x[i][e] < 0.0f) ? 0u : 1u << e;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = bf16_of(fabsf(x[i][2 * e])) | bf16_of(fabsf(x[i][2 * e + 1])) << 16;
+        *reinterpret_cast<uint4*>(&Ts[r0 + 32 * i][8 * oct]) = make_uint4(h[0], h[1], h[2], h[3]);
+        bits <<= 8 * (oct & 3);   // the four lanes of a word are neighbours
+        bits |= __shfl_xor(bits, 1);
+        bits |= __shfl_xor(bits, 2);
+        if (o < out) {
+            float* const dst = R + size_t(o) * in + j0 + 8 * oct;
+            *reinterpret_cast<float4*>(dst) = make_float4(x[i][0], x[i][1], x[i][2], x[i][3]);
+            *reinterpret_cast<float4*>(dst + 4) = make_float4(x[i][4], x[i][5], x[i][6], x[i][7]);
+            if ((oct & 3) == 0) words[size_t(o) * (in / 32) + j0 / 32 + oct / 4] = bits;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {   // pieces of Rh: consecutive lanes take consecutive rows
+        const int idx = tid + 256 * i, r = idx % kResRows, k8 = idx / kResRows;
+        if (o0 + r < out) Rh[frag_piece(o0 + r, j0 / 8 + k8, in)] = *reinterpret_cast<const uint4*>(&Ts[r][8 * k8]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {   // pieces of RhT: consecutive lanes take consecutive columns
+        const int idx = tid + 256 * i, c = idx % kResCols, k8 = idx / kResCols;
+        unsigned w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = unsigned(Ts[8 * k8 + 2 * e][c]) | unsigned(Ts[8 * k8 + 2 * e + 1][c]) << 16;
+        if (o0 + 8 * k8 < out) RhT[frag_piece(j0 + c, o0 / 8 + k8, out)] = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
 
-// Tall products with A = |R| (out x in, row-major), kL columns on the other side, on the fp32
-// matrix cores (v_mfma_f32_32x32x2_f32: 32 output indices x 32 columns, two reduction indices
-// per instruction).
-//   TRANS = false:  P[slice][o][c] = sum_{j in slice} |R[o][j]| X[j][c]     (M = out, K = in)
-//   TRANS = true :  P[slice][j][c] = sum_{o in slice} |R[o][j]| X[o][c]     (M = in,  K = out)
-// A workgroup (4 wavefronts) owns 128 output indices and one slice of the reduction range; the
-// residual chunk goes to LDS as As[reduction index][output index] (|.| applied on the way), so
-// that an operand is 32 consecutive floats for either orientation.  The slices are added up by
-// the kernel that reads the product.
-template <bool TRANS>
-__global__ __launch_bounds__(256) void k_dc_mul(const float* R, const float* X, float* P, int out, int in,
-                                                int chunks_per_slice) {
+// The product of the Rayleigh-Ritz step, from the fp32 residual on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: 32 output
+// indices x 32 columns, two reduction indices per instruction):
+//   P[slice][j][c] = sum_{o in slice} |R[o][j]| X[o][c]     (M = in, K = out)
+// A workgroup (4 wavefronts) owns 128 output indices and one slice of the reduction range; the residual chunk goes to LDS
+// as As[reduction index][output index] (|.| applied on the way).  The slices are added up by the kernel that reads the product.
+__global__ __launch_bounds__(256) void k_dc_mul(const float* R, const float* X, float* P, int out, int in, int chunks_per_slice) {
     __shared__ float As[kDcChunk][kDcTile + 4];
     __shared__ float Xs[kDcChunk][kL];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int hl = lane >> 5, ln = lane & 31;
-    const int M = TRANS ? in : out, K = TRANS ? out : in;
     const int m0 = blockIdx.x * kDcTile;
-    const int chunks = K / kDcChunk;
+    const int chunks = out / kDcChunk;
     const int c_begin = blockIdx.y * chunks_per_slice;
     const int c_end = min(chunks, c_begin + chunks_per_slice);
     v16f acc;
@@ -91,20 +188,10 @@ __global__ __launch_bounds__(256) void k_dc_mul(const float* R, const float* X, 
         const int k0 = ch * kDcChunk;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int idx = tid + 256 * i;
+            const int idx = tid + 256 * i, kk = idx >> 5, q = idx & 31;   // row k0 + kk, columns m0 + 4 q ..
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (!TRANS) {
-                const int m = idx >> 3, q = idx & 7;   // row m0 + m, columns k0 + 4 q ..
-                if (m0 + m < M) v = *reinterpret_cast<const float4*>(R + size_t(m0 + m) * in + k0 + 4 * q);
-                As[4 * q + 0][m] = fabsf(v.x);
-                As[4 * q + 1][m] = fabsf(v.y);
-                As[4 * q + 2][m] = fabsf(v.z);
-                As[4 * q + 3][m] = fabsf(v.w);
-            } else {
-                const int kk = idx >> 5, q = idx & 31;   // row k0 + kk, columns m0 + 4 q ..
-                if (m0 + 4 * q < M) v = *reinterpret_cast<const float4*>(R + size_t(k0 + kk) * in + m0 + 4 * q);
-                *reinterpret_cast<float4*>(&As[kk][4 * q]) = make_float4(fabsf(v.x), fabsf(v.y), fabsf(v.z), fabsf(v.w));
-            }
+            if (m0 + 4 * q < in) v = *reinterpret_cast<const float4*>(R + size_t(k0 + kk) * in + m0 + 4 * q);
+            *reinterpret_cast<float4*>(&As[kk][4 * q]) = make_float4(fabsf(v.x), fabsf(v.y), fabsf(v.z), fabsf(v.w));
         }
         {
             const int kk = tid >> 3, q = tid & 7;
@@ -117,238 +204,266 @@ __global__ __launch_bounds__(256) void k_dc_mul(const float* R, const float* X, 
         __syncthreads();
     }
     // D[i = output index][n = column]: lane (column ln), register v holds index 8*(v/4) + 4*hl + v%4
-    float* Ps = P + size_t(blockIdx.y) * M * kL;
+    float* Ps = P + size_t(blockIdx.y) * in * kL;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int m = m0 + wave * 32 + 8 * (v >> 2) + 4 * hl + (v & 3);
-        if (m < M) Ps[size_t(m) * kL + ln] = acc[v];
+        if (m < in) Ps[size_t(m) * kL + ln] = acc[v];
     }
 }
 
-// |R| as bf16, twice: Rh[o][j] and its transpose RhT[j][o], for the power rounds' tall products
-// (half the bytes of the fp32 residual, and a reduction index that is contiguous in memory for
-// either orientation).  64 x 64 tiles through LDS.
-__global__ __launch_bounds__(256) void k_dc_half(const float* R, unsigned short* Rh, unsigned short* RhT, int out, int in) {
-    __shared__ unsigned short Ts[64][64 + 2];
-    const int tid = threadIdx.x;
-    const int o0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+// The power rounds' tall products on the bf16 matrix cores: P[slice][m][c] = sum_{k in slice} A[m][k] X[k][c] with A = Rh (M =
+// out, K = in) or RhT (M = in, K = out) and the transpose of X (K x kL, rounded to bf16 by the kernel that made it), both in
+// fragment order: an operand is one coalesced load of 1 KiB, and nothing goes through LDS or waits at a barrier.  A
+// perturbation of |R| and of the iterate of 2^-9 relative per element turns the subspace the rounds converge to by far less
+// than the oversampling and the Rayleigh-Ritz step, which works on the fp32 residual, absorb.  A workgroup owns TILES x 32
+// output indices (two tiles, so that an operand of X serves two, where the grid fills the chip with them) and four slices of
+// the reduction range, one for each of its wavefronts; they add up in LDS.  Bound by the loads of A, of which every wavefront
+// keeps 8 or 16 KiB in flight: 4096 x 4096 8 us a product (through LDS, from row-major copies: 11.5), 14336 x 4096 20 us (24-49).
+constexpr int kHAhead = 8;
+template <int TILES>
+__global__ __launch_bounds__(256) void k_dc_mulh(const uint4* A, const uint4* X, float* P, int M, int K, int steps_per_wave) {
+    __shared__ float red[4][TILES][16][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int steps = K >> 4, tile0 = blockIdx.x * TILES;
+    const int s_begin = min(steps, (int(blockIdx.y) * 4 + wave) * steps_per_wave), s_end = min(steps, s_begin + steps_per_wave);
+    const uint4* const x0 = X + lane;
+    const uint4* a0[TILES];
+    v16f acc[TILES];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int idx = tid + 256 * i, r = idx >> 4, q = idx & 15;   // row o0 + r, columns j0 + 4 q ..
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (o0 + r < out) v = *reinterpret_cast<const float4*>(R + size_t(o0 + r) * in + j0 + 4 * q);
-        const unsigned short h[4] = {bf16_of(fabsf(v.x)), bf16_of(fabsf(v.y)), bf16_of(fabsf(v.z)), bf16_of(fabsf(v.w))};
-        if (o0 + r < out)
-            *reinterpret_cast<uint2*>(Rh + size_t(o0 + r) * in + j0 + 4 * q) =
-                make_uint2(unsigned(h[0]) | unsigned(h[1]) << 16, unsigned(h[2]) | unsigned(h[3]) << 16);
+    for (int t = 0; t < TILES; ++t) {
+        a0[t] = A + size_t(min(tile0 + t, (M >> 5) - 1)) * steps * 64 + lane;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) Ts[4 * q + e][r] = h[e];
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
     }
+    auto products = [&](auto count, int st) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        uint4 a[N][TILES], x[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+#pragma unroll
+            for (int t = 0; t < TILES; ++t) a[u][t] = a0[t][size_t(st + u) * 64];
+            x[u] = x0[size_t(st + u) * 64];
+        }
+        __builtin_amdgcn_sched_barrier(0);   // all requests before the first product
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int t = 0; t < TILES; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[u][t]), __builtin_bit_cast(v8bf, x[u]), acc[t], 0, 0, 0);
+    };
+    int st = s_begin;
+    for (; st + kHAhead <= s_end; st += kHAhead) products(std::integral_constant<int, kHAhead>{}, st);
+    for (; st + 2 <= s_end; st += 2) products(std::integral_constant<int, 2>{}, st);   // K is a multiple of 32
+#pragma unroll
+    for (int t = 0; t < TILES; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[wave][t][v][lane] = acc[t][v];
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int idx = tid + 256 * i, c = idx >> 4, q = idx & 15;   // column j0 + c, rows o0 + 4 q ..
-        if (o0 + 4 * q < out)   // out is a multiple of 32: a group of four rows is inside or outside as a whole
-            *reinterpret_cast<uint2*>(RhT + size_t(j0 + c) * out + o0 + 4 * q) =
-                make_uint2(unsigned(Ts[c][4 * q]) | unsigned(Ts[c][4 * q + 1]) << 16,
-                           unsigned(Ts[c][4 * q + 2]) | unsigned(Ts[c][4 * q + 3]) << 16);
-    }
-}
-
-// The power rounds' tall products on the bf16 matrix cores: P[slice][m][c] = sum_{k in slice}
-// A[m][k] X[k][c] with A = Rh (M = out, K = in) or RhT (M = in, K = out), row-major with K
-// contiguous, X (K x kL, fp32) rounded to bf16 as it is staged.  A perturbation of |R| and of the
-// iterate of 2^-9 relative per element turns the subspace the rounds converge to by far less than
-// the oversampling and the Rayleigh-Ritz step, which works on the fp32 residual, absorb.  A
-// workgroup (4 wavefronts) owns 128 output indices and one slice of the reduction range, 64
-// reduction indices per LDS stage (K is a multiple of 32: a last half stage is filled with zeros).
-constexpr int kHChunk = 64;
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-__global__ __launch_bounds__(256) void k_dc_mulh(const unsigned short* A, const float* X, float* P, int M, int K,
-                                                 int chunks_per_slice) {
-    __shared__ __attribute__((aligned(16))) unsigned short As[kDcTile][kHChunk + 8];   // [m][k]
-    __shared__ __attribute__((aligned(16))) unsigned short Xs[kL][kHChunk + 8];        // [c][k]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int hl = lane >> 5, ln = lane & 31;
-    const int m0 = blockIdx.x * kDcTile;
-    const int chunks = (K + kHChunk - 1) / kHChunk;
-    const int c_begin = blockIdx.y * chunks_per_slice;
-    const int c_end = min(chunks, c_begin + chunks_per_slice);
-    v16f acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    for (int ch = c_begin; ch < c_end; ++ch) {
-        const int k0 = ch * kHChunk;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = tid + 256 * i, m = idx >> 3, q = idx & 7;   // row m0 + m, reduction indices k0 + 8 q ..
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (m0 + m < M && k0 + 8 * q < K) v = *reinterpret_cast<const uint4*>(A + size_t(m0 + m) * K + k0 + 8 * q);
-            *reinterpret_cast<uint4*>(&As[m][8 * q]) = v;
-        }
-        {
-            const int kk = tid >> 2, cq = tid & 3;   // reduction index k0 + kk, columns 8 cq ..
-            float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-            if (k0 + kk < K) {
-                a = *reinterpret_cast<const float4*>(X + size_t(k0 + kk) * kL + 8 * cq);
-                b = *reinterpret_cast<const float4*>(X + size_t(k0 + kk) * kL + 8 * cq + 4);
-            }
-            const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) Xs[8 * cq + e][kk] = bf16_of(x[e]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < kHChunk / 16; ++s) {
-            const v8bf a = *reinterpret_cast<const v8bf*>(&As[wave * 32 + ln][16 * s + 8 * hl]);
-            const v8bf b = *reinterpret_cast<const v8bf*>(&Xs[ln][16 * s + 8 * hl]);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // D[i = output index][n = column]: lane (column ln), register v holds index 8*(v/4) + 4*hl + v%4
+    // D[i = output index][n = column]: lane (column l % 32), register v holds index 8*(v/4) + 4*(l/32) + v%4
     float* Ps = P + size_t(blockIdx.y) * M * kL;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wave * 32 + 8 * (v >> 2) + 4 * hl + (v & 3);
-        if (m < M) Ps[size_t(m) * kL + ln] = acc[v];
+    for (int i = 0; i < TILES * 32 * kL / 256; ++i) {
+        const int o = tid + 256 * i, l = o & 63, v = (o >> 6) & 15, t = o >> 10;
+        const int m = (tile0 + t) * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
+        if (m < M) Ps[size_t(m) * kL + (l & 31)] = (red[0][t][v][l] + red[1][t][v][l]) + (red[2][t][v][l] + red[3][t][v][l]);
     }
 }
 
-// Y = sum of the product's slices (written out) and this workgroup's part of Y^T Y in fp64:
-// 128 rows of Y (m x kL) per workgroup in four stages of 32, every thread four columns of one row
-// with the loads of all slices in flight together.  The parts are added up in a fixed order by
-// the kernel that consumes the Gram matrix (no atomics: the decomposition is reproducible bit for
-// bit).  Gpart == nullptr: only the sum is wanted.
-constexpr int kGramRows = 128;
-__global__ __launch_bounds__(256) void k_dc_gram(const float* P, int slices, float* Y, int m, double* Gpart) {
+// four columns of one row of a product, its slices added up: in groups of four as they lie (the fp32 product's slices), or one
+// by one (slices that are such groups already); the order of the additions is that of four slices to a group either way
+__device__ __forceinline__ float4 slice_sum(const float* src, int slices, size_t n, bool grouped) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int sl = 0; sl < slices; sl += 4) {
+        float4 a[4];   // in flight together
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            a[u] = sl + u < slices ? *reinterpret_cast<const float4*>(src + size_t(sl + u) * n) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (grouped || sl + 4 > slices) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                v.x += a[u].x; v.y += a[u].y; v.z += a[u].z; v.w += a[u].w;
+            }
+        } else {
+            v.x += (a[0].x + a[1].x) + (a[2].x + a[3].x); v.y += (a[0].y + a[1].y) + (a[2].y + a[3].y);
+            v.z += (a[0].z + a[1].z) + (a[2].z + a[3].z); v.w += (a[0].w + a[1].w) + (a[2].w + a[3].w);
+        }
+    }
+    return v;
+}
+
+// 8 rows k8 of column c of a matrix in LDS (rows ld floats apart) as one piece of its transpose's fragment order
+__device__ __forceinline__ uint4 bf16_piece(const float* col, int ld) {
+    unsigned w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = bf16_of(col[2 * e * ld]) | bf16_of(col[(2 * e + 1) * ld]) << 16;
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// a product's slices added up and rounded to bf16 in fragment order, as the next product takes it; 32 rows per workgroup
+__global__ __launch_bounds__(256) void k_dc_sum(const float* P, int slices, uint4* Xf, int m) {
     __shared__ float Ys[32][kL + 1];
-    const int tid = threadIdx.x, r = tid >> 3, cq = tid & 7;
-    const int i = tid >> 3, jg = tid & 7;
-    const size_t n = size_t(m) * kL;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int st = 0; st < kGramRows / 32; ++st) {
-        const int row = blockIdx.x * kGramRows + st * 32 + r;
+    const int tid = threadIdx.x, r = tid >> 3, cq = tid & 7, row0 = blockIdx.x * 32;   // m is a multiple of 32
+    const float4 v = slice_sum(P + size_t(row0 + r) * kL + 4 * cq, slices, size_t(m) * kL, true);
+    Ys[r][4 * cq] = v.x; Ys[r][4 * cq + 1] = v.y; Ys[r][4 * cq + 2] = v.z; Ys[r][4 * cq + 3] = v.w;
+    __syncthreads();
+    if (tid < 4 * kL) {
+        const int c = tid % kL, k8 = tid / kL;
+        Xf[frag_piece(c, row0 / 8 + k8, m)] = bf16_piece(&Ys[8 * k8][c], kL + 1);
+    }
+}
+
+// Y = sum of the product's slices (written out) and this workgroup's part of Y^T Y in fp64: stages of 128 rows of Y (m x kL),
+// 16 wavefronts.  Wavefront w multiplies, on the fp64 matrix cores (v_mfma_f64_16x16x4_f64), a quarter of a stage's rows into
+// one of the four 16 x 16 tiles of the part; the quarters are added up in LDS.  The parts (at most kGramParts) are added up
+// in a fixed order by the kernel that consumes the Gram matrix (no atomics: the decomposition is reproducible bit for
+// bit).  4096 rows: 4.4 us (12 with 256 threads to 128 rows and fp64 vector arithmetic).
+constexpr int kGramRows = 128, kGramParts = 64;
+__host__ __device__ inline int gram_stages(int m) { return (m + kGramRows * kGramParts - 1) / (kGramRows * kGramParts); }
+inline int gram_parts(int m) { return (m + kGramRows * gram_stages(m) - 1) / (kGramRows * gram_stages(m)); }
+__global__ __launch_bounds__(1024) void k_dc_gram(const float* P, int slices, bool grouped, float* Y, int m, double* Gpart) {
+    __shared__ float Ys[kGramRows][kL + 1];
+    __shared__ double Gq[4][kL * kL];
+    const int tid = threadIdx.x, lane = tid & 63, r = tid >> 3, cq = tid & 7;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ti = (wave >> 1) & 1, tj = wave & 1, quarter = wave >> 2;
+    const int stages = gram_stages(m);
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+    for (int st = 0; st < stages; ++st) {
+        const int row = (blockIdx.x * stages + st) * kGramRows + r;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (row < m) {
-            const float* src = P + size_t(row) * kL + 4 * cq;
-            int sl = 0;
-            for (; sl + 4 <= slices; sl += 4) {
-                const float4 a = *reinterpret_cast<const float4*>(src + size_t(sl) * n);
-                const float4 b = *reinterpret_cast<const float4*>(src + size_t(sl + 1) * n);
-                const float4 c = *reinterpret_cast<const float4*>(src + size_t(sl + 2) * n);
-                const float4 d = *reinterpret_cast<const float4*>(src + size_t(sl + 3) * n);
-                v.x += (a.x + b.x) + (c.x + d.x); v.y += (a.y + b.y) + (c.y + d.y);
-                v.z += (a.z + b.z) + (c.z + d.z); v.w += (a.w + b.w) + (c.w + d.w);
-            }
-            for (; sl < slices; ++sl) {
-                const float4 a = *reinterpret_cast<const float4*>(src + size_t(sl) * n);
-                v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
-            }
+            v = slice_sum(P + size_t(row) * kL + 4 * cq, slices, size_t(m) * kL, grouped);
             *reinterpret_cast<float4*>(Y + size_t(row) * kL + 4 * cq) = v;
         }
-        if (Gpart == nullptr) continue;   // same for the whole grid
+        if (st) __syncthreads();
         Ys[r][4 * cq] = v.x; Ys[r][4 * cq + 1] = v.y; Ys[r][4 * cq + 2] = v.z; Ys[r][4 * cq + 3] = v.w;
         __syncthreads();
-#pragma unroll 8
-        for (int q = 0; q < 32; ++q) {
-            const double yi = double(Ys[q][i]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += yi * double(Ys[q][4 * jg + e]);
+        for (int q = 0; q < 8; ++q) {   // operands: lane l holds index l % 16 of row 4 q + l / 16
+            const float* const y = Ys[quarter * 32 + 4 * q + (lane >> 4)];
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(double(y[ti * 16 + (lane & 15)]), double(y[tj * 16 + (lane & 15)]), acc, 0, 0, 0);
         }
-        __syncthreads();
     }
-    if (Gpart == nullptr) return;
-    double* dst = Gpart + size_t(blockIdx.x) * (kL * kL) + i * kL + 4 * jg;
+    // D[i][j]: lane l, register v holds i = 4 v + l / 16, j = l % 16
 #pragma unroll
-    for (int e = 0; e < 4; ++e) dst[e] = acc[e];
+    for (int v = 0; v < 4; ++v) Gq[quarter][(ti * 16 + 4 * v + (lane >> 4)) * kL + tj * 16 + (lane & 15)] = acc[v];
+    __syncthreads();
+    Gpart[size_t(blockIdx.x) * (kL * kL) + tid] = (Gq[0][tid] + Gq[1][tid]) + (Gq[2][tid] + Gq[3][tid]);
 }
 
-// the Gram matrix from its parts, in a fixed order, into LDS: 1024 threads, one entry each, the loads
-// of up to 32 parts in flight together (one trip to memory per 32 parts instead of one per four)
-constexpr int kSmallThreads = kL * kL;
+// the Gram matrix from its parts, in a fixed order, into LDS: THREADS threads, the loads of up to 16 parts in flight together
+template <int THREADS>
 __device__ __forceinline__ void gram_sum(const double* Gpart, int parts, double (*Gs)[kL + 1]) {
-    const int e = threadIdx.x;
-    double acc = 0.0;
-    for (int p0 = 0; p0 < parts; p0 += 32) {
-        double v[32];
+    constexpr int N = kL * kL / THREADS;
+    double acc[N];
 #pragma unroll
-        for (int u = 0; u < 32; ++u) v[u] = p0 + u < parts ? Gpart[size_t(p0 + u) * (kL * kL) + e] : 0.0;
+    for (int i = 0; i < N; ++i) acc[i] = 0.0;
+    for (int p0 = 0; p0 < parts; p0 += 16) {
+        double v[16][N];
 #pragma unroll
-        for (int u = 0; u < 32; ++u) acc += v[u];   // the order of the additions is fixed
+        for (int u = 0; u < 16; ++u)
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[u][i] = p0 + u < parts ? Gpart[size_t(p0 + u) * (kL * kL) + i * THREADS + threadIdx.x] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] += v[u][i];   // the order of the additions is fixed
     }
-    Gs[e / kL][e % kL] = acc;
+#pragma unroll
+    for (int i = 0; i < N; ++i) Gs[(i * THREADS + threadIdx.x) / kL][(i * THREADS + threadIdx.x) % kL] = acc[i];
 }
 
-// G = L L^T (Cholesky, L lower triangular) so that Q = Y L^-T has orthonormal columns; the kernel that
-// applies it solves Q L^T = Y row by row.  Right-looking, one thread per matrix entry, fp64: at step
-// j the threads of column j publish their entries (final after the updates of the earlier steps)
-// and thread (j, j) the reciprocal of the pivot and its square root; after one barrier column j of
-// L is raw / sqrt(pivot) and every entry below and right of the pivot takes its rank-one update.
-// No chain of dependent operations longer than one division per step.
-//   Lout: kL x kL fp32, row-major, L[r][c] for c < r, and 1 / L[r][r] on the diagonal (what the
-//   substitution multiplies by); all zero for an all-zero Y (no direction to normalise: Q = 0).
-__global__ __launch_bounds__(kSmallThreads) void k_dc_chol(const double* Gpart, int parts, float* Lout) {
+// Columns made orthonormal: G = Y^T Y = L L^T (Cholesky), Q L^T = Y for every row of Y (m x kL), so that Q = Y L^-T.  Every
+// workgroup factors G by itself (256 KiB of parts from cache) and solves
+// its 256 rows, one per thread.
+//
+// The factorisation is one wavefront's, right-looking, fp64: lane (half h, row r) keeps columns h, h + 2, ... of row r in
+// registers, and a step publishes its column in LDS for all rows (no barrier: LDS operations of a wavefront are in order).
+// Per step a trip through LDS, one division and at most 16 updates; the square roots are taken together at the end.
+//   Ls: L[r][c] for c < r, and 1 / L[r][r] on the diagonal (what the substitution multiplies by); all zero for an
+//   all-zero Y (no direction to normalise: Q = 0).
+// The substitution q_c = (y_c - sum_{i < c} q_i L[c][i]) / L[c][c] runs by columns: once q_c is known it is taken off all later
+// entries, which do not depend on each other (the same operations on each entry in the same order as row by row).
+// 4096 rows: 16 us (factorisation and solve as two kernels: 15 + 7 us and a launch); bound by the chain of the 32 steps.
+// Q goes out as fp32 (Q, if not null) and as bf16 in fragment order (Xf).  Q and Y may be the same array.
+__global__ __launch_bounds__(256) void k_dc_orth(const double* Gpart, int parts, const float* Y, float* Q, uint4* Xf, int m) {
     __shared__ double Gs[kL][kL + 1];
-    __shared__ double colj[2][kL];
-    __shared__ double piv[2][2];
-    const int t = threadIdx.x, r = t / kL, c = t % kL;
-    gram_sum(Gpart, parts, Gs);
-    __syncthreads();
-    double tr = 0.0;
-#pragma unroll
-    for (int k = 0; k < kL; ++k) tr += Gs[k][k];
-    if (!(tr > 0.0)) {   // uniform over the workgroup
-        Lout[t] = 0.f;
-        return;
-    }
-    // a tiny ridge keeps the factorisation defined if the columns are (numerically) dependent
-    const double ridge = tr * 1e-13;
-    double a = Gs[r][c] + (r == c ? ridge : 0.0);
-    double mine = 0.0;   // my entry of L (r > c), or 1 / L[r][r]
-    for (int j = 0; j < kL; ++j) {
-        const int b = j & 1;
-        if (c == j && r >= j) {
-            colj[b][r] = a;
-            if (r == j) {
-                const double d = a > 0.0 ? a : ridge;
-                const double inv = 1.0 / d;
-                piv[b][0] = inv;
-                piv[b][1] = sqrt(inv);
-            }
-        }
-        __syncthreads();
-        if (c == j && r >= j) mine = r == j ? piv[b][1] : a * piv[b][1];   // 1 / sqrt(d), or a_rj / sqrt(d)
-        if (c > j && r >= c) a -= colj[b][r] * colj[b][c] * piv[b][0];
-    }
-    Lout[t] = r >= c ? float(mine) : 0.f;
-}
-
-// Q L^T = Y for every row of Y (m x kL), L as k_dc_chol leaves it (reciprocal pivots on the diagonal):
-// q_c = (y_c - sum_{i < c} q_i L[c][i]) / L[c][c].  One row per thread, L in LDS (all lanes read the
-// same entry: a broadcast).  Y and Q may be the same array.
-__global__ __launch_bounds__(256) void k_dc_solve(const float* Y, const float* Lg, float* Q, int m) {
-    __shared__ __attribute__((aligned(16))) float Ls[kL][kL];
-    for (int idx = threadIdx.x; idx < kL * kL; idx += 256) Ls[idx / kL][idx % kL] = Lg[idx];
-    __syncthreads();
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= m) return;
+    // passed between the lanes of a wavefront: volatile, and by LDS pointers (a volatile access to a shared array is a flat
+    // one); [parity of the step][kL], and a place for what the other half writes
+    __shared__ double col_lds[3 * kL];
+    lds_double* const col = (lds_double*)col_lds;
+    __shared__ __attribute__((aligned(16))) float Lt[kL][kL];   // Lt[c][r] = L[r][c]
+    __shared__ float Qs[256][kL + 1];
+    const int tid = threadIdx.x, row = blockIdx.x * 256 + tid;
     float q[kL];
 #pragma unroll
     for (int g = 0; g < kL / 4; ++g) {
-        const float4 v = *reinterpret_cast<const float4*>(Y + size_t(r) * kL + 4 * g);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (row < m) v = *reinterpret_cast<const float4*>(Y + size_t(row) * kL + 4 * g);
         q[4 * g] = v.x; q[4 * g + 1] = v.y; q[4 * g + 2] = v.z; q[4 * g + 3] = v.w;
     }
+    gram_sum<256>(Gpart, parts, Gs);
+    __syncthreads();
+    if (tid < 64) {
+        const int h = tid >> 5, r = tid & 31;
+        double tr = 0.0;
+#pragma unroll
+        for (int k = 0; k < kL; ++k) tr += Gs[k][k];
+        // a tiny ridge keeps the factorisation defined if the columns are (numerically) dependent
+        const double ridge = tr * 1e-13;
+        double a[kL / 2], inv[kL / 2] = {};   // inv: 1 / pivot of the columns
+#pragma unroll
+        for (int i = 0; i < kL / 2; ++i) a[i] = Gs[r][2 * i + h] + (r == 2 * i + h ? ridge : 0.0);
+        if (tr > 0.0) {   // uniform over the wavefront
+#pragma unroll
+            for (int j = 0; j < kL; ++j) {
+                lds_double* const cj = col + (j & 1) * kL;
+                (h == (j & 1) ? cj : col + 2 * kL)[r] = a[j >> 1];
+                const double d0 = cj[j], mine = cj[r];
+                const double d = d0 > 0.0 ? d0 : ridge;
+                const double w = 1.0 / d;
+                inv[j >> 1] = h == (j & 1) ? w : inv[j >> 1];
+                const double t = mine * w;
+#pragma unroll
+                for (int i = (j + 1) / 2; i < kL / 2; ++i) {
+                    const int c = 2 * i + h;
+                    const double cc = cj[c];
+                    if (c > j) a[i] = fma(-t, cc, a[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kL / 2; ++i) {
+                const int c = 2 * i + h;
+                const double root = sqrt(inv[i]);   // 1 / L[c][c]
+                Lt[c][r] = r > c ? float(a[i] * root) : r == c ? float(root) : 0.f;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kL / 2; ++i) Lt[2 * i + h][r] = 0.f;
+        }
+    }
+    __syncthreads();
 #pragma unroll
     for (int c = 0; c < kL; ++c) {
-        float v = q[c];
+        q[c] *= Lt[c][c];
 #pragma unroll
-        for (int i = 0; i < c; ++i) v = fmaf(-q[i], Ls[c][i], v);
-        q[c] = v * Ls[c][c];
+        for (int i = c + 1; i < kL; ++i) q[i] = fmaf(-q[c], Lt[c][i], q[i]);
+    }
+    if (Q && row < m) {
+#pragma unroll
+        for (int g = 0; g < kL / 4; ++g)
+            *reinterpret_cast<float4*>(Q + size_t(row) * kL + 4 * g) = make_float4(q[4 * g], q[4 * g + 1], q[4 * g + 2], q[4 * g + 3]);
     }
 #pragma unroll
-    for (int g = 0; g < kL / 4; ++g)
-        *reinterpret_cast<float4*>(Q + size_t(r) * kL + 4 * g) = make_float4(q[4 * g], q[4 * g + 1], q[4 * g + 2], q[4 * g + 3]);
+    for (int c = 0; c < kL; ++c) Qs[tid][c] = q[c];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int idx = tid + 256 * i, c = idx % kL, k8 = idx / kL;
+        if (int(blockIdx.x) * 256 + 8 * k8 < m) Xf[frag_piece(c, blockIdx.x * 32 + k8, m)] = bf16_piece(&Qs[8 * k8][c], kL + 1);
+    }
 }
 
 // Q[r][c] = sum_i Y[r][i] T[i][c], c < NC; fp32 or fp16 (round to nearest even) output
@@ -383,13 +498,24 @@ __global__ __launch_bounds__(256) void k_dc_apply(const float* Y, const float* T
     }
 }
 
+// 1 / sqrt(x) for x > 0 in fp64: the hardware's estimate and two Newton steps
+__device__ __forceinline__ double rsqrt64(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(y * 0.5, fma(-x * y, y, 1.0), y);
+    return y;
+}
+
 // Rayleigh-Ritz step.  With Q orthonormal (out x kL) and Z = |R|^T Q (in x kL), G = Z^T Z =
 // H diag(sigma^2) H^T gives the leading triplets of |R|: left vectors Q H, right vectors
 // Z H diag(1/sigma).  Tu = H_k diag(sqrt(sigma)), Tv = H_k diag(1/sqrt(sigma)) (Eq. 2's split):
 // U = Q Tu, V = Z Tv.  Jacobi rotations in fp64 in the round-robin ordering: 31 rounds of 16
-// disjoint pairs per sweep, the 16 rotations of a round applied together by 512 threads, one per
-// (line, pair); all 1024 add up the parts of G first.
-__global__ __launch_bounds__(kSmallThreads) void k_dc_ritz(const double* Gpart, int parts, float* Tu, float* Tv, int k) {
+// disjoint pairs per sweep.  The rotations of a round act on A from both sides, so A falls into 16 x 16 independent blocks of
+// 2 x 2 (rows of one pair, columns of another): 256 threads take one each, the other 256 two lines of H each, and a round
+// needs two barriers.  One launch of one workgroup, bound by the rounds' chain (rotation, barrier, update, barrier):
+// 227 -> 113 us with this, the rotations from two reciprocal square roots and the ordering by all threads.
+constexpr int kRitzThreads = 512;
+__global__ __launch_bounds__(kRitzThreads) void k_dc_ritz(const double* Gpart, int parts, float* Tu, float* Tv, int k) {
     __shared__ double A[kL][kL + 1];
     __shared__ double H[kL][kL + 1];
     __shared__ double cs[kL / 2][2];
@@ -397,11 +523,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_dc_ritz(const double* Gpart, 
     __shared__ int order[kL];
     __shared__ double offd[kL];
     const int t = threadIdx.x;
-    gram_sum(Gpart, parts, A);
-    H[t / kL][t % kL] = (t / kL == t % kL) ? 1.0 : 0.0;
+    gram_sum<kRitzThreads>(Gpart, parts, A);
+#pragma unroll
+    for (int i = t; i < kL * kL; i += kRitzThreads) H[i / kL][i % kL] = (i / kL == i % kL) ? 1.0 : 0.0;
+    if (t < kL) order[t] = t;
     __syncthreads();
-    // thread (line r, pair e) of the first 512 applies rotation e of a round to line r
-    const int r = t >> 4, e = t & (kL / 2 - 1);
+    const int e = t & (kL / 2 - 1), f = (t >> 4) & (kL / 2 - 1);   // pair of the columns, pair of the rows (or line of H)
     for (int sweep = 0; sweep < 10; ++sweep) {
         // converged?  (off-diagonal mass against the trace; falls quadratically once small)
         if (t < kL) {
@@ -429,11 +556,13 @@ __global__ __launch_bounds__(kSmallThreads) void k_dc_ritz(const double* Gpart, 
                 }
                 const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
                 double c = 1.0, s = 0.0;
-                if (fabs(apq) > 1e-300 && fabs(apq) > 1e-18 * sqrt(fabs(app * aqq))) {
-                    const double tau = (aqq - app) / (2.0 * apq);
-                    const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + tt * tt);
-                    s = tt * c;
+                if (fabs(apq) > 1e-300 && apq * apq > 1e-36 * fabs(app * aqq)) {
+                    // tan(2 theta) = b / d; the smaller angle: cos^2 = (1 + |d| / h) / 2, sin = b sign(d) / (2 h cos)
+                    const double d = aqq - app, b = 2.0 * apq;
+                    const double rh = rsqrt64(fma(d, d, b * b));
+                    const double c2 = fma(0.5 * fabs(d), rh, 0.5), rc = rsqrt64(c2);
+                    c = c2 * rc;
+                    s = (d >= 0.0 ? 0.5 : -0.5) * b * rh * rc;
                 }
                 pq[t][0] = p;
                 pq[t][1] = q;
@@ -441,75 +570,43 @@ __global__ __launch_bounds__(kSmallThreads) void k_dc_ritz(const double* Gpart, 
                 cs[t][1] = s;
             }
             __syncthreads();
-            // the 16 pairs of a round are disjoint: 512 threads, one (line, pair) each
             const int p = pq[e][0], q = pq[e][1];
             const double c = cs[e][0], sn = cs[e][1];
-            if (t < kL * kL / 2) {   // columns p, q of A and H: row r
-                const double ap = A[r][p], aq = A[r][q], hp = H[r][p], hq = H[r][q];
-                A[r][p] = c * ap - sn * aq;
-                A[r][q] = sn * ap + c * aq;
-                H[r][p] = c * hp - sn * hq;
-                H[r][q] = sn * hp + c * hq;
+            if (t < 256) {
+                const int g = pq[f][0], h = pq[f][1];
+                const double cr = cs[f][0], sr = cs[f][1];
+                const double gp = A[g][p], gq = A[g][q], hp = A[h][p], hq = A[h][q];
+                const double gp1 = c * gp - sn * gq, gq1 = sn * gp + c * gq, hp1 = c * hp - sn * hq, hq1 = sn * hp + c * hq;
+                A[g][p] = cr * gp1 - sr * hp1;
+                A[g][q] = cr * gq1 - sr * hq1;
+                A[h][p] = sr * gp1 + cr * hp1;
+                A[h][q] = sr * gq1 + cr * hq1;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int r = f + 16 * i;
+                    const double hp = H[r][p], hq = H[r][q];
+                    H[r][p] = c * hp - sn * hq;
+                    H[r][q] = sn * hp + c * hq;
+                }
             }
             __syncthreads();
-            if (t < kL * kL / 2) {   // rows p, q of A: column r
-                const double ap = A[p][r], aq = A[q][r];
-                A[p][r] = c * ap - sn * aq;
-                A[q][r] = sn * ap + c * aq;
-            }
-            __syncthreads();
         }
     }
-    if (t == 0) {   // eigenvalues in descending order
-        bool used[kL];
-        for (int i = 0; i < kL; ++i) used[i] = false;
-        for (int r = 0; r < kL; ++r) {
-            int best = -1;
-            for (int i = 0; i < kL; ++i)
-                if (!used[i] && (best < 0 || A[i][i] > A[best][best])) best = i;
-            used[best] = true;
-            order[r] = best;
-        }
+    if (t < kL) {   // eigenvalues in descending order (equal ones by their index)
+        const double mine = A[t][t];
+        int rank = 0;
+        for (int i = 0; i < kL; ++i) rank += (A[i][i] > mine || (A[i][i] == mine && i < t)) ? 1 : 0;
+        order[rank] = t;
     }
     __syncthreads();
-    if (t < kL)
-        for (int r = 0; r < k; ++r) {
-            const int e = order[r];
-            const double lam = A[e][e] > 0.0 ? A[e][e] : 0.0;
-            const double sig = sqrt(lam);
-            const double rt = sqrt(sig);
-            Tu[t * k + r] = float(H[t][e] * rt);
-            Tv[t * k + r] = rt > 0.0 ? float(H[t][e] / rt) : 0.f;
-        }
-}
-
-// R <- R - sign(R) (.) (U V^T) with the factors as stored (fp16); 32 rows x 64 columns per workgroup
-__global__ __launch_bounds__(256) void k_dc_update(float* R, const __half* U, const __half* V, int out, int in) {
-    __shared__ float Us[32][kRank + 1];
-    __shared__ float Vs[64][kRank + 1];
-    const int tid = threadIdx.x;
-    const int o0 = blockIdx.y * 32, j0 = blockIdx.x * 64;
-    for (int idx = tid; idx < 32 * kRank; idx += 256) {
-        const int r = idx / kRank, c = idx % kRank;
-        Us[r][c] = (o0 + r < out) ? __half2float(U[size_t(o0 + r) * kRank + c]) : 0.f;
-    }
-    for (int idx = tid; idx < 64 * kRank; idx += 256) {
-        const int r = idx / kRank, c = idx % kRank;
-        Vs[r][c] = (j0 + r < in) ? __half2float(V[size_t(j0 + r) * kRank + c]) : 0.f;
-    }
-    __syncthreads();
-    const int jl = tid & 63, rg = tid >> 6;   // column, group of 8 rows
-    if (j0 + jl >= in) return;
-#pragma unroll
-    for (int rr = 0; rr < 8; ++rr) {
-        const int o = o0 + rg * 8 + rr;
-        if (o >= out) break;
-        float m = 0.f;
-#pragma unroll
-        for (int r = 0; r < kRank; ++r) m = fmaf(Us[rg * 8 + rr][r], Vs[jl][r], m);
-        const size_t at = size_t(o) * in + j0 + jl;
-        const float x = R[at];
-        R[at] = (x < 0.0f) ? x + m : x - m;
+    for (int i = t; i < kL * k; i += kRitzThreads) {
+        const int r = i % k, line = i / k, o = order[r];
+        const double lam = A[o][o] > 0.0 ? A[o][o] : 0.0;
+        const double sig = sqrt(lam);
+        const double rt = sqrt(sig);
+        Tu[line * k + r] = float(H[line][o] * rt);
+        Tv[line * k + r] = rt > 0.0 ? float(H[line][o] / rt) : 0.f;
     }
 }
 
@@ -518,14 +615,15 @@ size_t decompose_workspace_bytes(int out, int in, int slices) {
     size_t b = align256(size_t(out) * in * 4);               // R
     b += 2 * align256(size_t(out) * in * 2);                 // |R| as bf16 and its transpose
     b += 2 * align256(size_t(out) * kL * 4);                 // Y, Q (out side)
-    b += 2 * align256(size_t(in) * kL * 4);                  // Z, Qz (in side)
+    b += align256(size_t(in) * kL * 4);                      // Z (in side)
+    b += align256(mx * kL * 2);                              // the iterate as bf16
     b += align256(size_t(slices) * mx * kL * 4);             // partial products
-    b += align256(((mx + kGramRows - 1) / kGramRows) * size_t(kL * kL * 8)) + 3 * align256(kL * kL * 4);  // Gram parts, T, Tu, Tv
+    b += align256(size_t(kGramParts) * (kL * kL * 8)) + 2 * align256(kL * kL * 4);  // Gram parts, Tu, Tv
     return b;
 }
 
 int decompose_slices(int out, int in) {
-    // enough workgroups for 256 compute units: 128 output indices x one slice each
+    // enough workgroups of the fp32 product for 256 compute units: 128 output indices x one slice each
     const int tiles = ((out < in ? out : in) + kDcTile - 1) / kDcTile;
     int s = 1;
     while (tiles * s < 512 && s < 16) s *= 2;
@@ -543,81 +641,73 @@ hipError_t launch_decompose(const float* W, const float* s, int out, int in, int
         return p;
     };
     float* R = reinterpret_cast<float*>(take(size_t(out) * in * 4));
-    unsigned short* Rh = reinterpret_cast<unsigned short*>(take(size_t(out) * in * 2));
-    unsigned short* RhT = reinterpret_cast<unsigned short*>(take(size_t(out) * in * 2));
+    uint4* Rh = reinterpret_cast<uint4*>(take(size_t(out) * in * 2));
+    uint4* RhT = reinterpret_cast<uint4*>(take(size_t(out) * in * 2));
     float* Y = reinterpret_cast<float*>(take(size_t(out) * kL * 4));
     float* Q = reinterpret_cast<float*>(take(size_t(out) * kL * 4));
     float* Z = reinterpret_cast<float*>(take(size_t(in) * kL * 4));
-    float* Qz = reinterpret_cast<float*>(take(size_t(in) * kL * 4));
+    uint4* X = reinterpret_cast<uint4*>(take(mx * kL * 2));   // of either side: a product has read it before the next one is made
     float* P = reinterpret_cast<float*>(take(size_t(slices) * mx * kL * 4));
-    double* G = reinterpret_cast<double*>(take(((mx + kGramRows - 1) / kGramRows) * size_t(kL * kL * 8)));
-    float* T = reinterpret_cast<float*>(take(kL * kL * 4));
+    double* G = reinterpret_cast<double*>(take(size_t(kGramParts) * (kL * kL * 8)));
     float* Tu = reinterpret_cast<float*>(take(kL * kL * 4));
     float* Tv = reinterpret_cast<float*>(take(kL * kL * 4));
 
-    const size_t total = size_t(out) * in;
-    hipLaunchKernelGGL(k_dc_scale, dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, W, s, R, total, in);
-
-    // P = slices of |R| X  (X: in x kL)  or of  |R|^T X  (X: out x kL)
-    // (exact: from the fp32 residual; otherwise from its bf16 copies, which the power rounds use)
-    auto mul = [&](bool trans, const float* X, bool exact) {
+    // P = slices of |R| X  (X: in x kL)  or of  |R|^T X  (X: out x kL), from the bf16 copies; four of `slices` to a workgroup.
+    // Two tiles to a wavefront from two workgroups per compute unit on.
+    const int groups = (slices + 3) / 4;
+    auto mul = [&](bool trans) {
         const int M = trans ? in : out, K = trans ? out : in;
-        dim3 grid((M + kDcTile - 1) / kDcTile, slices);
-        if (exact) {
-            const int chunks = K / kDcChunk;
-            const int per = (chunks + slices - 1) / slices;
-            if (trans)
-                hipLaunchKernelGGL(k_dc_mul<true>, grid, dim3(256), 0, st, R, X, P, out, in, per);
-            else
-                hipLaunchKernelGGL(k_dc_mul<false>, grid, dim3(256), 0, st, R, X, P, out, in, per);
-        } else {
-            const int chunks = (K + kHChunk - 1) / kHChunk;
-            const int per = (chunks + slices - 1) / slices;
-            hipLaunchKernelGGL(k_dc_mulh, grid, dim3(256), 0, st, trans ? RhT : Rh, X, P, M, K, per);
-        }
+        const int per = 4 * (((K + 63) / 64 + 4 * groups - 1) / (4 * groups));
+        if ((M + 63) / 64 * groups >= 512)
+            hipLaunchKernelGGL(k_dc_mulh<2>, dim3((M + 63) / 64, groups), dim3(256), 0, st, trans ? RhT : Rh, X, P, M, K, per);
+        else
+            hipLaunchKernelGGL(k_dc_mulh<1>, dim3(M / 32, groups), dim3(256), 0, st, trans ? RhT : Rh, X, P, M, K, per);
     };
-    // the product in P, added up into raw (m x kL), columns made orthonormal into dst: Cholesky
-    // QR with the Gram matrix in fp64 (factor, then a triangular solve per row); a second pass
-    // (twice = orthonormal to rounding) where asked
-    auto orth = [&](float* raw, float* dst, int m, bool twice) {
-        const int parts = (m + kGramRows - 1) / kGramRows;
-        hipLaunchKernelGGL(k_dc_gram, dim3(parts), dim3(256), 0, st, P, slices, raw, m, G);
-        hipLaunchKernelGGL(k_dc_chol, dim3(1), dim3(kSmallThreads), 0, st, G, parts, T);
-        hipLaunchKernelGGL(k_dc_solve, dim3((m + 255) / 256), dim3(256), 0, st, raw, T, dst, m);
+    auto gram = [&](const float* src, int sl, bool grouped, float* dst, int m) {
+        hipLaunchKernelGGL(k_dc_gram, dim3(gram_parts(m)), dim3(1024), 0, st, src, sl, grouped, dst, m, G);
+    };
+    // the product in P, added up, its columns made orthonormal into X (and Q): Cholesky QR with the Gram matrix in fp64; a
+    // second pass (twice = orthonormal to rounding) where asked
+    auto orth = [&](bool twice) {
+        gram(P, groups, true, Y, out);
+        hipLaunchKernelGGL(k_dc_orth, dim3((out + 255) / 256), dim3(256), 0, st, G, gram_parts(out), Y, twice ? Q : nullptr, X, out);
         if (twice) {
-            hipLaunchKernelGGL(k_dc_gram, dim3(parts), dim3(256), 0, st, dst, 1, raw, m, G);
-            hipLaunchKernelGGL(k_dc_chol, dim3(1), dim3(kSmallThreads), 0, st, G, parts, T);
-            hipLaunchKernelGGL(k_dc_solve, dim3((m + 255) / 256), dim3(256), 0, st, raw, T, dst, m);
+            gram(Q, 1, true, Y, out);
+            hipLaunchKernelGGL(k_dc_orth, dim3((out + 255) / 256), dim3(256), 0, st, G, gram_parts(out), Y, Q, X, out);
         }
     };
 
+    const dim3 tiles(in / kResCols, (out + kResRows - 1) / kResRows);
     for (int i = 0; i < n; ++i) {
         uint32_t* sw = sign_words + size_t(i) * out * (in / 32);
         __half* Ui = U + size_t(i) * out * kRank;
         __half* Vi = V + size_t(i) * in * kRank;
-        const size_t waves = size_t(out) * (in / 64);
-        hipLaunchKernelGGL(k_dc_signs, dim3(unsigned((waves + 3) / 4)), dim3(256), 0, st, R, sw, out, in);
-        if (iters > 0)
-            hipLaunchKernelGGL(k_dc_half, dim3(in / 64, (out + 63) / 64), dim3(256), 0, st, R, Rh, RhT, out, in);
+        if (i == 0)
+            hipLaunchKernelGGL(k_dc_residual<true>, tiles, dim3(256), 0, st, W, s, R, Ui, Vi, sw, Rh, RhT, out, in);
+        else
+            hipLaunchKernelGGL(k_dc_residual<false>, tiles, dim3(256), 0, st, W, s, R, Ui - size_t(out) * kRank,
+                               Vi - size_t(in) * kRank, sw, Rh, RhT, out, in);
         // start: random X (in x kL) -> Y = |R| X -> Q
-        hipLaunchKernelGGL(k_dc_random, dim3(unsigned((size_t(in) * kL + 255) / 256)), dim3(256), 0, st, Qz,
-                           size_t(in) * kL, 0x9e3779b9u * unsigned(i + 1));
-        mul(false, Qz, iters == 0);
-        orth(Y, Q, out, iters == 0);
+        hipLaunchKernelGGL(k_dc_random, dim3(unsigned((size_t(in) / 8 * kL + 255) / 256)), dim3(256), 0, st, X, in,
+                           0x9e3779b9u * unsigned(i + 1));
+        mul(false);
+        orth(false);
         // one round = |R| |R|^T applied to Q; only Q is made orthonormal again (the product in
         // between spreads the columns' lengths by sigma_0 / sigma_31 ~ 30, far inside fp32)
         for (int it = 0; it < iters; ++it) {
-            mul(true, Q, false);
-            hipLaunchKernelGGL(k_dc_gram, dim3((in + kGramRows - 1) / kGramRows), dim3(256), 0, st, P, slices, Z, in, static_cast<double*>(nullptr));
-            mul(false, Z, false);
-            orth(Y, Q, out, it == iters - 1);
+            mul(true);
+            hipLaunchKernelGGL(k_dc_sum, dim3(in / 32), dim3(256), 0, st, P, groups, X, in);
+            mul(false);
+            orth(it == iters - 1);
         }
-        mul(true, Q, true);   // the Rayleigh-Ritz step sees the fp32 residual
-        hipLaunchKernelGGL(k_dc_gram, dim3((in + kGramRows - 1) / kGramRows), dim3(256), 0, st, P, slices, Z, in, G);
-        hipLaunchKernelGGL(k_dc_ritz, dim3(1), dim3(kSmallThreads), 0, st, G, (in + kGramRows - 1) / kGramRows, Tu, Tv, kRank);
+        // the Rayleigh-Ritz step sees the fp32 residual
+        const int chunks = out / kDcChunk;
+        hipLaunchKernelGGL(k_dc_mul, dim3((in + kDcTile - 1) / kDcTile, slices), dim3(256), 0, st, R, Q, P, out, in,
+                           (chunks + slices - 1) / slices);
+        gram(P, slices, false, Z, in);
+        hipLaunchKernelGGL(k_dc_ritz, dim3(1), dim3(kRitzThreads), 0, st, G, gram_parts(in), Tu, Tv, kRank);
         hipLaunchKernelGGL((k_dc_apply<kRank, true>), dim3((out + 255) / 256), dim3(256), 0, st, Q, Tu, Ui, out);
         hipLaunchKernelGGL((k_dc_apply<kRank, true>), dim3((in + 255) / 256), dim3(256), 0, st, Z, Tv, Vi, in);
-        hipLaunchKernelGGL(k_dc_update, dim3((in + 63) / 64, (out + 31) / 32), dim3(256), 0, st, R, Ui, Vi, out, in);
     }
     return hipGetLastError();
 }
