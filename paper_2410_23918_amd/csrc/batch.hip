@@ -1,7 +1,8 @@
-// Batch kernel for 2 to 64 tokens on rebuilt weight units (rebuild.h): Y += X (W' diag(1/s))^T, W' of a unit summed over its
-// blocks in registers, multiplied with the activations from there and never stored.
+// Batch kernel for 2 to 64 tokens, and for up to 1024 in groups of 64, on rebuilt weight units (rebuild.h):
+// Y += X (W' diag(1/s))^T, W' of a unit summed over its blocks in registers, multiplied with the activations from there and
+// never stored.
 //
-// One workgroup = 64 output rows x all tokens; 8 wavefronts = 4 teams (column chunks) x 2 row tiles.  A wavefront rebuilds
+// One workgroup = 64 output rows x up to 64 tokens; 8 wavefronts = 4 teams (column chunks) x 2 row tiles.  A wavefront rebuilds
 // its unit of 32 rows x 256 columns block by block; a lane then holds 128 columns of one row, which, scaled by 1/s and
 // rounded to fp16, are the B operands of 16 products over 16 columns each, and the activations as they lie in memory (8
 // columns of a token: 16 bytes) the A operands.  So the weight costs the same for one token as for 64, and a block costs
@@ -12,8 +13,11 @@
 // 8 wavefronts and not two workgroups of 4: the teams' partial tiles meet in LDS, so a quarter of the workspace serves, and
 // the workspace is what limits the column split of small stacks (14336 x 4096, 3 blocks, 16 tokens: 28 us against 33).
 // 14336 x 4096, 16 blocks: 86 us for 2-32 tokens (k_fused 104), 98 us for 64 (k_fused 214, weight-tile kernel 152);
-// 28672 x 8192: 354 us for 16 tokens (462).  Bound by the issue of vector and matrix instructions: a step (8 tiles per wavefront,
-// two wavefronts per SIMD) takes 1.05-1.25 us, the same instructions without loads and barriers 0.92.
+// 28672 x 8192: 354 us for 16 tokens (462).  Beyond 64 tokens every group of 64 (a grid dimension) rebuilds the weight again,
+// on compute units that are idle otherwise: 4096 x 4096, 16 blocks: 90 us for 64 tokens, 99 for 256 (weight-tile kernel 139).
+// Groups of 96 or 128 would need more than the 256 registers that two wavefronts per SIMD leave (248 in use).
+//
+// Bound by the issue of vector and matrix instructions: a step (8 tiles per wavefront, two wavefronts per SIMD) takes 1.05-1.25 us, the same instructions without loads and barriers 0.92.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -47,6 +51,8 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     const int c_lo = int(blockIdx.y) * nch / ksplit, c_hi = (int(blockIdx.y) + 1) * nch / ksplit;
     const int iters = (c_hi - c_lo + TEAMS - 1) / TEAMS;
     const int rt = int(blockIdx.x) * RT + tile, rtc = min(rt, nrt - 1);
+    const int tok0 = int(blockIdx.z) * (TOK * GROUPS);   // this workgroup's tokens: tok0 .. tok_end - 1
+    const int tok_end = min(p.batch, tok0 + TOK * GROUPS);
 
     const unsigned stride = unsigned(p.block_stride);
     __amdgpu_buffer_rsrc_t rsrc =
@@ -83,7 +89,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
                 const int kk = k < 4 ? k : 3;
                 const int lin = kk * 64 + lane, t = tile * (4096 / kXRowBytes) + lin / (2 * kPieces);   // token of the group
                 const int j = (lin % (2 * kPieces)) ^ (t & 15);   // piece: [half][kPieces]
-                const int tok = min(g * TOK + t, p.batch - 1);
+                const int tok = min(tok0 + g * TOK + t, p.batch - 1);
                 const unsigned off = unsigned(tok) * unsigned(p.in) * 2u + unsigned(j / kPieces) * 256u + unsigned(j % kPieces + e0) * 16u;
                 load_to_lds<0>(x_rsrc, mine + kk * 1024, off, unsigned(ch) * 512u);
             }
@@ -206,8 +212,8 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
             float sum = 0.0f;
 #pragma unroll
             for (int w = 0; w < TEAMS; ++w) sum += red[((w * RT + (row >> 5)) * 16 + v) * 64 + l];
-            const int tok = g * TOK + t, r = int(blockIdx.x) * kRows + row;
-            if (tok < p.batch && r < p.out) {
+            const int tok = tok0 + g * TOK + t, r = int(blockIdx.x) * kRows + row;
+            if (tok < tok_end && r < p.out) {
                 if (ksplit == 1)
                     store_y(p, size_t(tok) * p.out + r, sum);
                 else   // write-through: the reader may sit on another XCD
@@ -223,7 +229,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     unsigned* const flag = reinterpret_cast<unsigned*>(smem + 8 * 4096);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // each wavefront's stores are acknowledged before it reaches the barrier
     __syncthreads();
-    unsigned* const ctr = p.ctr + blockIdx.x;
+    unsigned* const ctr = p.ctr + blockIdx.z * gridDim.x + blockIdx.x;
     if (tid == 0) {
         const unsigned old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *flag = (old + 1u == unsigned(ksplit)) ? 1u : 0u;
@@ -234,8 +240,8 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
         __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(p.part, 0, span, 0x00020000);
         constexpr int kAgentScope = 16;   // sc1
         // thread = (token, 4 consecutive rows)
-        for (int o = tid; o < p.batch * (kRows / 4); o += 512) {
-            const int tok = o / (kRows / 4), row = int(blockIdx.x) * kRows + 4 * (o & (kRows / 4 - 1));
+        for (int o = tid; o < (tok_end - tok0) * (kRows / 4); o += 512) {
+            const int tok = tok0 + o / (kRows / 4), row = int(blockIdx.x) * kRows + 4 * (o & (kRows / 4 - 1));
             if (row >= p.out) continue;   // out is a multiple of 32: a quad is inside or outside as a whole
             v4i v[8];
 #pragma unroll
@@ -262,10 +268,11 @@ constexpr int kBatchMaxSplit = 8;
 // hold a partial row per split and token).  The split with the fewest rounds x chunk iterations is taken, the smallest of
 // equals.
 static int batch_split(int out, int in, int batch, int part_slots) {
-    const int groups = (out + 63) / 64, nch = in / kChunkCols;
+    const int groups = (out + 63) / 64 * ((batch + 63) / 64), nch = in / kChunkCols;
     int best = 1;
     long best_cost = 0;
     for (int k = 1; k <= kBatchMaxSplit && k <= nch && (k == 1 || k * batch <= part_slots); ++k) {
+        if (k > 1 && size_t(k) * batch * out * 4 >= (size_t(1) << 32)) break;   // 32-bit offsets into the partial rows
         const long cost = long((groups * k + 255) / 256) * (((nch + k - 1) / k + 3) / 4);
         if (k == 1 || cost < best_cost) {
             best = k;
@@ -286,21 +293,27 @@ static hipError_t launch_batch_t(KParams p, hipStream_t st) {
         attr_set = true;
     }
     p.n_ks = batch_split(p.out, p.in, p.batch, p.part_slots);
-    hipLaunchKernelGGL((k_batch<TOK, GROUPS>), dim3((p.out + 63) / 64, p.n_ks), dim3(512), smem, st, p);
+    hipLaunchKernelGGL((k_batch<TOK, GROUPS>), dim3((p.out + 63) / 64, p.n_ks, (p.batch + TOK * GROUPS - 1) / (TOK * GROUPS)), dim3(512), smem, st, p);
     return hipGetLastError();
 }
 
 // Estimated duration (microseconds; fitted to 553 cases from 512 x 512 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens: 3.7 %
-// root mean square): per round and chunk iteration of a workgroup 1.05-1.25 us per block and ~2-4 us for scaling and product
+// root mean square; and to 720 cases of 65 to 1024 tokens, 4.5 %): per round and chunk iteration of a workgroup 1.05-1.25 us per
+// block and ~2-4 us for scaling and product
 double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
-    const int groups = (out + 63) / 64, nch = in / kChunkCols, split = batch_split(out, in, batch, part_slots);
+    const int groups = (out + 63) / 64 * ((batch + 63) / 64), nch = in / kChunkCols;
+    const int split = batch_split(out, in, batch, part_slots);
     const int wgs = groups * split, xsteps = batch > 32 ? 4 : batch > 16 ? 2 : 1;
     const double its = double((wgs + 255) / 256) * (((nch + split - 1) / split + 3) / 4), fill = wgs < 256 ? wgs / 256.0 : 1.0;
-    return 4.3 + its * (n_loaded * (1.05 + 0.2 * fill) + 1.2 + 0.63 * xsteps) + (split > 1 ? 1.9 + 0.018 * batch * split : 0.0);
+    const double again = batch > 64 ? 3.3 * ((wgs + 255) / 256 - 1) : 0.0;   // token groups in further rounds: their first loads
+    return 4.3 + its * (n_loaded * (1.05 + 0.2 * fill) + 1.2 + 0.63 * xsteps) + again +
+           (split > 1 ? 1.9 + 0.018 * (batch < 64 ? batch : 64) * split : 0.0);
 }
 
-bool batch_fits(const KParams& p) {   // one 32-bit buffer descriptor over the loaded blocks, one counter per row group
-    return size_t(p.n_loaded) * p.block_stride < (size_t(1) << 32) && (p.out + 63) / 64 <= kCounterSlots;
+// one 32-bit buffer descriptor each over the loaded blocks and the activations, one counter per row group and 64 tokens
+bool batch_fits(const KParams& p) {
+    return size_t(p.n_loaded) * p.block_stride < (size_t(1) << 32) && size_t(p.batch) * p.in * 2 < (size_t(1) << 32) &&
+           (size_t(p.out) + 63) / 64 * ((size_t(p.batch) + 63) / 64) <= size_t(kCounterSlots);
 }
 
 hipError_t launch_batch(const KParams& p, hipStream_t st) {

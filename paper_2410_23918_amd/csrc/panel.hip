@@ -1006,6 +1006,16 @@ double tile_time_us(int out, int in, int batch, int n_loaded) {
     return rounds * (15.0 + chunk_pairs * scale * (0.9 * n_loaded + (batch > 512 ? 14.0 : batch > 256 ? 12.0 : 6.5)));
 }
 
+// The weight-tile kernel against k_batch for 65 to 1024 tokens, fitted to 720 cases (12 shapes from 512 x 512 to 14336 x 4096, 1 to 24
+// blocks; 7 % root mean square; with batch_time_us the faster kernel was taken in each, to 1 %).  tile_time_us is up to 1.9 times too
+// high here, but the crossover to the materialising path is stated in terms of it.
+static double tile_launch_us(int out, int in, int batch, int n_loaded) {
+    const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 1.0 + 1.28 * (wgs / 256.0 - 1.0);
+    const double tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
+    return 14.8 + rounds * (chunk_pairs * ((0.65 + 0.09 * fill) * n_loaded + 3.85 + (2.8 + 2.13 * fill) * tokens) - 3.0);
+}
+
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     KParams p = make_params(a);
     if (a.n_loaded < 1 || a.batch < 1) return hipErrorInvalidValue;
@@ -1022,6 +1032,13 @@ hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
         if (take_batch) return launch_batch(p, st);
         if (tf != 0.0) return launch_fused(p, st);
     }
+    // 65 to 1024 tokens: where rows x 64 tokens leave compute units idle in the weight-tile kernel's grid of 64 rows x 512 tokens,
+    // k_batch's token groups and column split fill them (608 x 12032, 8 blocks, 96 tokens: 263 -> 59 us; 4096 x 14336, 16 blocks,
+    // 128 tokens: 449 -> 307; 4096 x 4096, 256 tokens: 139 -> 99, but 300 tokens 146 -> 189).  Also for stacks the
+    // weight-tile kernel cannot hold: k_panel is slower than its estimate
+    if (a.batch > kFusedMaxBatch && a.batch <= 1024 && batch_fits(p) &&
+        batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) < tile_launch_us(p.out, p.in, p.batch, p.n_loaded))
+        return launch_batch(p, st);
     if (a.batch > kFusedMaxBatch && tile_fits(p)) return launch_tile(p, st);
     if (a.batch > 256) return launch_panel_t<4>(p, st);
     if (a.batch > 128) return launch_panel_t<2>(p, st);

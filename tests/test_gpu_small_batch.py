@@ -15,12 +15,25 @@ pytestmark = pytest.mark.gpu
 ])
 @pytest.mark.parametrize("batch", [2, 16, 17, 32, 33, 64])
 def test_every_output_of_the_small_batch_kernel(out, inn, batch):
+    check(out, inn, 45, batch)
+
+
+@pytest.mark.parametrize("out,inn,n", [
+    (96, 1280, 60),    # enough workspace to split the columns of several token groups
+    (160, 2816, 12),
+])
+@pytest.mark.parametrize("batch", [65, 128, 129, 1000, 1024, 1025])
+def test_more_than_64_tokens_in_groups(out, inn, n, batch):
+    """Both sides of the 64-token groups, and of the 1024 tokens up to which they are taken."""
+    check(out, inn, n, batch)
+
+
+def check(out, inn, n, batch):
     import torch
     import paper_2410_23918_amd as B
-    n = 45
     g = torch.Generator(device="cuda:0").manual_seed(out + inn + batch)
     s = np.exp(0.5 * np.random.default_rng(batch).standard_normal(inn)).astype(np.float32)
-    ps = B.PackedStack.empty(out, inn, n, s, max_batch=64)
+    ps = B.PackedStack.empty(out, inn, n, s, max_batch=max(64, batch))
     w = torch.zeros((out, inn), device="cuda:0")
     mag = torch.zeros_like(w)   # sum over blocks of |U V^T|
     bits = torch.arange(32, device="cuda:0", dtype=torch.int32)
