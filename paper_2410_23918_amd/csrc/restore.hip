@@ -169,8 +169,8 @@ static int restore_groups_per_wg(int groups, int chunks) {
 }
 
 // The restoring part of the materialising path in the choice of kernel (microseconds): rounds of 256 workgroups of 64 rows x
-// a power of two of column slices, as the former kernel had them.  k_restore is 1.4-1.9 times faster; the choice stays
-// where both sides of it were measured.
+// a power of two of column slices, as the kernel before k_restore had them.  k_restore is 1.4-1.9 times faster, but the
+// crossovers that follow from this estimate are what bitstack_choose_kernel promises (tests/test_abi_host.py states them).
 double restore_time_us(int rows, int in, int n_loaded) {
     const int iters = (in / kChunkCols + 1) / 2, row_wgs = (rows + 63) / 64;
     double best = 0.0;
