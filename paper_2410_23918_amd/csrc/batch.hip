@@ -15,7 +15,7 @@
 // 14336 x 4096, 16 blocks: 86 us for 2-32 tokens (k_fused 104), 98 us for 64 (k_fused 214, weight-tile kernel 152);
 // 28672 x 8192: 354 us for 16 tokens (462).  Beyond 64 tokens every group of 64 (a grid dimension) rebuilds the weight again,
 // on compute units that are idle otherwise: 4096 x 4096, 16 blocks: 90 us for 64 tokens, 99 for 256 (weight-tile kernel 139).
-// Groups of 96 or 128 would need more than the 256 registers that two wavefronts per SIMD leave (248 in use).
+// Groups of 96 or 128 would need more than the 256 registers that two wavefronts per SIMD leave (all in use with 64).
 //
 // Bound by the issue of vector and matrix instructions: a step (8 tiles per wavefront, two wavefronts per SIMD) takes 1.05-1.25 us, the same instructions without loads and barriers 0.92.
 #include <hip/hip_fp16.h>
@@ -55,15 +55,13 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     const int tok_end = min(p.batch, tok0 + TOK * GROUPS);
 
     const unsigned stride = unsigned(p.block_stride);
-    __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(p.blocks), 0, unsigned(n) * stride, 0x00020000);
-    __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(p.x), 0,
-                                                                      unsigned(p.batch) * unsigned(p.in) * 2u, 0x00020000);
-    __amdgpu_buffer_rsrc_t rs_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.rs), 0, unsigned(p.in) * 4u, 0x00020000);
+    const v4i rsrc = buffer_over(p.blocks, unsigned(n) * stride);
+    const v4i x_rsrc = buffer_over(p.x, unsigned(p.batch) * unsigned(p.in) * 2u);
+    const v4i rs_rsrc = buffer_over(p.rs, unsigned(p.in) * 4u);
     const unsigned s_lane = unsigned(size_t(rtc) * nch * kUnitBytes) + unsigned(lane) * 16u;
     const unsigned v_lane = v_lane_offset<RT>(unsigned(p.off_v), unsigned(tile), unsigned(lane));
     const unsigned u_lane = u_lane_offset<RT>(unsigned(p.off_u), unsigned(rtc), unsigned(lane));
-    const unsigned lds0 = unsigned(reinterpret_cast<uintptr_t>((lds_void*)smem));
+    const unsigned lds0 = lds_address(smem);
     const unsigned v_rd = lds0 + unsigned(team) * L::kBytes + v_read_offset(unsigned(lane));
     const unsigned s_rd = lds0 + unsigned(wave) * L::kWaveBytes + unsigned(lane) * 16u;
     // x in LDS: a token's 2 kPieces 16-byte pieces in a row, piece j of token t at position j ^ (t & 15)
@@ -77,21 +75,20 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     auto request = [&]() {
         const int ch = min(c_lo + qit * TEAMS + team, c_hi - 1);
         if (qi < n) {
-            load_step<RT>(rsrc, smem + qbuf + wave * L::kWaveBytes, s_lane, v_lane, u_lane, qoff + unsigned(ch) * kUnitBytes,
+            load_step<RT>(rsrc, lds0 + qbuf + unsigned(wave) * L::kWaveBytes, s_lane, v_lane, u_lane, qoff + unsigned(ch) * kUnitBytes,
                           qoff + unsigned(ch) * kVChunkBytes, qoff);
             qoff += stride;
         } else {
-            // four loads of 1 KiB per wavefront (and, to keep the number of loads the same in every step, the last one again)
+            // four loads of 1 KiB per wavefront
             const int xs = qi - n, g = xs / kPerGroup, e0 = xs % kPerGroup * kPieces;
-            unsigned char* const mine = smem + qbuf + team * L::kBytes + tile * 4096;
+            const unsigned mine = lds0 + qbuf + unsigned(team) * L::kBytes + unsigned(tile) * 4096u;
 #pragma unroll
-            for (int k = 0; k < kStepLoads<RT>; ++k) {
-                const int kk = k < 4 ? k : 3;
-                const int lin = kk * 64 + lane, t = tile * (4096 / kXRowBytes) + lin / (2 * kPieces);   // token of the group
+            for (int k = 0; k < 4; ++k) {
+                const int lin = k * 64 + lane, t = tile * (4096 / kXRowBytes) + lin / (2 * kPieces);   // token of the group
                 const int j = (lin % (2 * kPieces)) ^ (t & 15);   // piece: [half][kPieces]
                 const int tok = min(tok0 + g * TOK + t, p.batch - 1);
                 const unsigned off = unsigned(tok) * unsigned(p.in) * 2u + unsigned(j / kPieces) * 256u + unsigned(j % kPieces + e0) * 16u;
-                load_to_lds<0>(x_rsrc, mine + kk * 1024, off, unsigned(ch) * 512u);
+                load_to_lds(x_rsrc, mine + unsigned(k) * 1024u, off, unsigned(ch) * 512u);
             }
         }
         if (++qi == n + kXSteps) {
@@ -107,7 +104,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
 #pragma unroll
         for (int k = 0; k < 4 / RT; ++k) {
             const unsigned part = unsigned(tile * (4 / RT) + k) * 256u;
-            load4_to_lds(rs_rsrc, smem + kRsLds + (it & 1) * (TEAMS * 1024) + team * 1024 + part, unsigned(lane) * 4u,
+            load4_to_lds(rs_rsrc, lds0 + kRsLds + unsigned(it & 1) * (TEAMS * 1024) + unsigned(team) * 1024u + part, unsigned(lane) * 4u,
                          unsigned(ch) * (kChunkCols * 4) + part);
         }
     };
@@ -127,7 +124,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     {
         FirstReads first;
         begin_reads<RT>(in, first, v_rd, s_rd);
-        wait_inputs(in, first.f7, first.signs);
+        take_reads(in, first);
     }
     for (int it = 0; it < iters; ++it) {
         auto step = [&](auto first) __attribute__((always_inline)) {
@@ -147,18 +144,14 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
         auto scale = [&](auto e) __attribute__((always_inline)) {
             constexpr int E = decltype(e)::value;
             v4f(&q)[2] = r[E & 1];
-            if constexpr (E < 15) {
-                read_scales<(E < 15 ? E + 1 : 15)>(r[(E + 1) & 1], rs_rd);
-                wait_scales<2>(q);
-            } else {
-                wait_scales<0>(q);
-            }
+            if constexpr (E < 15) read_scales(r[(E + 1) & 1], rs_rd, E + 1);
 #pragma unroll
             for (int t = 0; t < 8; t += 2)
                 b[E][t >> 1] = scaled_pair(acc[t][E >> 2][E & 3], acc[t + 1][E >> 2][E & 3], q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
+            asm volatile("" : "+v"(b[E]));   // made here: put off to the products, it would keep the scales in registers until then
             __builtin_amdgcn_sched_barrier(0);
         };
-        read_scales<0>(r[0], rs_rd);
+        read_scales(r[0], rs_rd, 0);
 #define BS_SCALE(E) scale(std::integral_constant<int, E>{});
         BS_SCALE(0) BS_SCALE(1) BS_SCALE(2) BS_SCALE(3) BS_SCALE(4) BS_SCALE(5) BS_SCALE(6) BS_SCALE(7)
         BS_SCALE(8) BS_SCALE(9) BS_SCALE(10) BS_SCALE(11) BS_SCALE(12) BS_SCALE(13) BS_SCALE(14) BS_SCALE(15)
@@ -178,9 +171,8 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const unsigned pos = unsigned(hl * kPieces + eq * 4 + k) ^ unsigned(ln & 15);
-                    read16<0>(a[k], x_rd + buf + pos * 16u);
+                    a[k] = read_lds<v4i>(x_rd + buf + pos * 16u);
                 }
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
                 if (valid) {
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
@@ -190,7 +182,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
             }
             buf = nb;
         }
-        wait_inputs(in, first.f7, first.signs);
+        take_reads(in, first);
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();

@@ -55,24 +55,51 @@ struct StepLayout {
     static constexpr int frag(int t) { return t / kClassesPerWave * kWaveBytes + kVOffset + t % kClassesPerWave * kVClassBytes; }
 };
 
-typedef __attribute__((address_space(3))) void lds_void;
+// LDS by its byte address
+template <class T>
+__device__ __forceinline__ T read_lds(unsigned addr) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) T*>(addr);
+}
+template <class T>
+__device__ __forceinline__ void write_lds(unsigned addr, T v) {
+    *reinterpret_cast<__attribute__((address_space(3))) T*>(addr) = v;
+}
+// What the lanes of a wavefront wrote before is what they read after, lane to lane: LDS operations of a wavefront execute in
+// order, so this only keeps the compiler from reordering them
+__device__ __forceinline__ void wavefront_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+__device__ __forceinline__ unsigned lds_address(const void* p) {
+    return unsigned(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
+}
 
-// All but the last N vector memory operations of this wavefront are complete, then the workgroup's barrier.  (The
-// fences of lds_barrier() would wait for every load to LDS in flight.)  The LDS reads before it must have been
-// consumed: it does not wait for them.
+// Loads to LDS are asynchronous and several steps ahead of the reads of what they bring.  They are inline assembly because
+// the compiler knows of its own ones only that they write LDS somewhere, and waits for all of them at every LDS read.
+// They write no register, so nothing of theirs can be taken for ready before it is: the reads are ordinary loads, whose
+// waits the compiler places, and no read passes loads_barrier() or a request ("memory").  The other way round -- reads
+// in assembly with a wait further down -- left it to chance that the compiler neither spilled nor copied a register between.
+//
+// All but the last N vector memory operations of this wavefront are complete, and its LDS reads; then the workgroup's
+// barrier.  (The fences of lds_barrier() in kparams.h are the compiler's: they do not know of these loads.)
 template <int N>
 __device__ __forceinline__ void loads_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// 16 (4) bytes per lane from the buffer to LDS, lane after lane (asynchronous, counted by vmcnt).  OFF is added to
-// both addresses.
-template <int OFF>
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rsrc, void* lds, unsigned lane_off, unsigned soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)lds, 16, lane_off, soff, OFF, 0);
+// raw buffer descriptor
+__device__ __forceinline__ v4i buffer_over(const void* p, unsigned bytes) {
+    const unsigned long long a = reinterpret_cast<uintptr_t>(p);
+    return v4i{int(unsigned(a)), int(unsigned(a >> 32)), int(bytes), 0x00020000};
 }
-__device__ __forceinline__ void load4_to_lds(__amdgpu_buffer_rsrc_t rsrc, void* lds, unsigned lane_off, unsigned soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)lds, 4, lane_off, soff, 0, 0);
+
+// 16 (4) bytes per lane from the buffer to LDS at the wavefront's byte address lds, lane after lane (counted by vmcnt).
+// s_nop 4: a memory instruction reads a scalar register five wait states after a vector instruction has written it at the
+// earliest, and M0 one after the scalar unit has; the compiler does not look into assembly for either.
+__device__ __forceinline__ void load_to_lds(v4i rsrc, unsigned lds, unsigned lane_off, unsigned soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(lane_off), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+__device__ __forceinline__ void load4_to_lds(v4i rsrc, unsigned lds, unsigned lane_off, unsigned soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(lane_off), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
 }
 
 // byte offset inside a class's KiB in memory of the 16-byte piece that lane u of a load to LDS fetches.  In LDS
@@ -87,49 +114,48 @@ __device__ __forceinline__ unsigned v_read_offset(unsigned lane) {
     return kg * 256 + rr * 64 + (pc & 1) * 32 + (grp * 2 + (pc >> 1)) * 8;
 }
 
-// The LDS reads of the pipeline below are inline assembly: for an ordinary LDS read the compiler would first wait for
-// every load to LDS that is in flight, and those are requested several steps ahead.  Their results are valid only after
-// a wait on them (wait_lds<N>: at most N reads requested since may be outstanding; LDS reads return in order).
+// A operand of the magnitude product of class T: two transposing reads
 struct VFrag {
     v2u q0, q1;
 };
-// A operand of the magnitude product of class T: two reads
+__device__ __forceinline__ v2u read_lds_turned(unsigned addr) {
+    typedef __fp16 v4f16 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4f16(reinterpret_cast<__attribute__((address_space(3))) v4f16*>(addr)));
+}
 template <int T, int RT>
-__device__ __forceinline__ void read_frag(VFrag& f, unsigned addr) {
-    asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
-                 : "=&v"(f.q0), "=&v"(f.q1)
-                 : "v"(addr), "n"(StepLayout<RT>::frag(T)), "n"(StepLayout<RT>::frag(T) + 512));
-}
-template <int OFF>
-__device__ __forceinline__ void read16(v4i& d, unsigned addr) {
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
-}
-template <int N>
-__device__ __forceinline__ void wait_lds(VFrag& f) {
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(f.q0), "+v"(f.q1) : "n"(N));
-}
-template <int N>
-__device__ __forceinline__ void wait_lds(v4i& d) {
-    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(d) : "n"(N));
+__device__ __forceinline__ VFrag read_frag(unsigned addr) {
+    constexpr unsigned off = StepLayout<RT>::frag(T);
+    return VFrag{read_lds_turned(addr + off), read_lds_turned(addr + off + 512)};
 }
 
-// One wavefront's part of a step's inputs: signs at s_off, V of its classes at v_off (class 0 of the chunk + the wavefront's
-// share), U at u_off.  (A load's constant offset counts in memory and in LDS: v_lane and u_lane have it taken off.)
+// One wavefront's part of a step's inputs, to its LDS byte address mine: signs at s_off, V of its classes at v_off (class 0 of
+// the chunk + the wavefront's share), U at u_off.  (A load's constant offset, at most 4095, counts in memory and in LDS: v_lane
+// and u_lane have it taken off.)
 template <int RT>
-__device__ __forceinline__ void load_step(__amdgpu_buffer_rsrc_t rsrc, unsigned char* mine, unsigned s_lane, unsigned v_lane,
-                                          unsigned u_lane, unsigned s_off, unsigned v_off, unsigned u_off) {
+__device__ __forceinline__ void load_step(v4i rsrc, unsigned mine, unsigned s_lane, unsigned v_lane, unsigned u_lane, unsigned s_off,
+                                          unsigned v_off, unsigned u_off) {
     typedef StepLayout<RT> L;
-    load_to_lds<0>(rsrc, mine, s_lane, s_off);
-    load_to_lds<L::kVOffset>(rsrc, mine, v_lane, v_off);
-    load_to_lds<L::kVOffset + kVClassBytes>(rsrc, mine, v_lane, v_off);
-    if constexpr (RT == 4) {
-        load_to_lds<L::kUOffset>(rsrc, mine, u_lane, u_off);
-    } else {   // (constant offsets reach 4095)
-        static_assert(RT == 4 || RT == 2, "");
-        load_to_lds<L::kVOffset + 2 * kVClassBytes>(rsrc, mine, v_lane, v_off);
-        load_to_lds<0>(rsrc, mine + 4096, v_lane, v_off + 4096u);
-        load_to_lds<L::kUOffset - 4096>(rsrc, mine + 4096, u_lane, u_off);
-    }
+    static_assert(RT == 4 || RT == 2, "");
+    static_assert(L::kVOffset == 1024 && L::kUOffset == (RT == 4 ? 3072 : 4096 + 1024), "");
+    if constexpr (RT == 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                     "buffer_load_dwordx4 %1, %4, %5 offen lds\n\t"
+                     "buffer_load_dwordx4 %2, %4, %6 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %2, %4, %6 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %3, %4, %7 offen offset:3072 lds" ::"s"(mine),
+                     "v"(s_lane), "v"(v_lane), "v"(u_lane), "s"(rsrc), "s"(s_off), "s"(v_off), "s"(u_off)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                     "buffer_load_dwordx4 %2, %5, %6 offen lds\n\t"
+                     "buffer_load_dwordx4 %3, %5, %7 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %3, %5, %7 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %3, %5, %7 offen offset:3072 lds\n\t"
+                     "s_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                     "buffer_load_dwordx4 %3, %5, %8 offen lds\n\t"
+                     "buffer_load_dwordx4 %4, %5, %9 offen offset:1024 lds" ::"s"(mine),
+                     "s"(mine + 4096u), "v"(s_lane), "v"(v_lane), "v"(u_lane), "s"(rsrc), "s"(s_off), "s"(v_off), "s"(v_off + 4096u), "s"(u_off)
+                     : "memory", "m0");
 }
 template <int RT>
 constexpr int kStepLoads = kClasses / RT + 2;
@@ -166,23 +192,17 @@ __device__ __forceinline__ v16f zero16() {
     return z;
 }
 
-// 1/s of the eight columns of byte E: addr = LDS byte address of the lane's half of a chunk's 256 scales
-template <int E>
-__device__ __forceinline__ void read_scales(v4f (&d)[2], unsigned addr) {
-    asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
-                 : "=&v"(d[0]), "=&v"(d[1])
-                 : "v"(addr), "n"(E * 32), "n"(E * 32 + 16));
+// 1/s of the eight columns of byte e: addr = LDS byte address of the lane's half of a chunk's 256 scales
+__device__ __forceinline__ void read_scales(v4f (&d)[2], unsigned addr, int e) {
+    d[0] = read_lds<v4f>(addr + unsigned(e) * 32u);
+    d[1] = read_lds<v4f>(addr + unsigned(e) * 32u + 16u);
 }
-template <int N>
-__device__ __forceinline__ void wait_scales(v4f (&d)[2]) {
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(d[0]), "+v"(d[1]) : "n"(N));
-}
-// fp16 pair (a ra, b rb), product and conversion in one instruction each
+// fp16 pair (a ra, b rb)
 __device__ __forceinline__ int scaled_pair(float a, float b, float ra, float rb) {
-    int d;
-    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(d) : "v"(a), "v"(ra));
-    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(d) : "v"(b), "v"(rb));
-    return d;
+    v2h c;
+    c[0] = _Float16(__builtin_fmaf(a, ra, 0.0f));
+    c[1] = _Float16(__builtin_fmaf(b, rb, 0.0f));
+    return __builtin_bit_cast(int, c);
 }
 
 // acc[t][w][b]: column 128 g + 32 w + 8 b + t of row lane % 32, g = lane / 32
@@ -204,30 +224,24 @@ __device__ __forceinline__ v16f magnitude(const VFrag& f, const v4i& u) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, both), __builtin_bit_cast(v8h, u), zero16(), 0, 0, 0);
 }
 
-// wait for all of a step's first reads; nothing that is still under way crosses a loop's back edge, where the compiler
-// may move values between registers
-__device__ __forceinline__ void wait_inputs(StepInputs& in, VFrag& f7, v4i& signs) {
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(in.u), "+v"(in.f.q0), "+v"(in.f.q1), "+v"(f7.q0), "+v"(f7.q1), "+v"(signs));
-    in.m = magnitude(f7, in.u);
-    // (a real copy: merged with the registers the reads fill, it would have to be made before they are filled)
-    const v2u lo = {unsigned(signs[0]), unsigned(signs[1])}, hi = {unsigned(signs[2]), unsigned(signs[3])};
-    asm("v_mov_b64 %0, %1" : "=v"(in.s[0]) : "v"(lo));
-    asm("v_mov_b64 %0, %1" : "=v"(in.s[1]) : "v"(hi));
-}
-
-// The first reads of a step that no step precedes: requested by begin_reads, taken over by wait_inputs.  vaddr: LDS byte
-// address of its V panel + v_read_offset; saddr: of the lane's 16 bytes of signs (its 16 bytes of U are kUOffset further on)
+// The first reads of a step that no step precedes.  vaddr: LDS byte address of its V panel + v_read_offset; saddr: of the
+// lane's 16 bytes of signs (its 16 bytes of U are kUOffset further on)
 struct FirstReads {
     VFrag f7;
     v4i signs;
 };
 template <int RT>
 __device__ __forceinline__ void begin_reads(StepInputs& in, FirstReads& r, unsigned vaddr, unsigned saddr) {
-    read_frag<7, RT>(r.f7, vaddr);
-    read16<StepLayout<RT>::kUOffset>(in.u, saddr);
-    read16<0>(r.signs, saddr);
-    read_frag<6, RT>(in.f, vaddr);
+    r.f7 = read_frag<7, RT>(vaddr);
+    in.u = read_lds<v4i>(saddr + StepLayout<RT>::kUOffset);
+    r.signs = read_lds<v4i>(saddr);
+    in.f = read_frag<6, RT>(vaddr);
+}
+// the first magnitude product from them
+__device__ __forceinline__ void take_reads(StepInputs& in, const FirstReads& r) {
+    in.m = magnitude(r.f7, in.u);
+    in.s[0] = v2u{unsigned(r.signs[0]), unsigned(r.signs[1])};
+    in.s[1] = v2u{unsigned(r.signs[2]), unsigned(r.signs[3])};
 }
 
 // One block onto the wavefront's unit.  vnext, snext: addresses of the next step.  FIRST: the accumulators start
@@ -275,13 +289,12 @@ __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned
     v16f n;
 #define BS_CLASS(T, CUR, NXT, F0, F1)                     \
     {                                                     \
-        read_frag<T - 2, RT>(F0, vaddr);                  \
-        wait_lds<2>(F1);                                  \
+        F0 = read_frag<T - 2, RT>(vaddr);                 \
         NXT = magnitude(F1, in.u);                        \
         __builtin_amdgcn_sched_barrier(0);                \
         apply(acc[T], CUR, true);                         \
     }
-    read_frag<5, RT>(f, vaddr);
+    f = read_frag<5, RT>(vaddr);
     n = magnitude(in.f, in.u);
     __builtin_amdgcn_sched_barrier(0);
     apply(acc[7], in.m, true);
@@ -291,17 +304,14 @@ __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned
     BS_CLASS(3, in.m, n, f, in.f)
     BS_CLASS(2, n, in.m, in.f, f)
 #undef BS_CLASS
-    wait_lds<0>(in.f);
     n = magnitude(in.f, in.u);
     __builtin_amdgcn_sched_barrier(0);
     apply(acc[1], in.m, true);
-    v4i signs;
-    read_frag<7, RT>(f, vnext);
-    read16<StepLayout<RT>::kUOffset>(in.u, snext);
-    read16<0>(signs, snext);
-    read_frag<6, RT>(in.f, vnext);
+    FirstReads next;
+    begin_reads<RT>(in, next, vnext, snext);
+    __builtin_amdgcn_sched_barrier(0);
     apply(acc[0], n, false);
-    wait_inputs(in, f, signs);
+    take_reads(in, next);
     __builtin_amdgcn_sched_barrier(0);
 }
 

@@ -45,13 +45,12 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     const int nrt = p.out / kTileRows, rt_first = p.row_begin / kTileRows + wave;
 
     const unsigned stride = unsigned(p.block_stride);
-    __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(p.blocks), 0, unsigned(n) * stride, 0x00020000);
-    __amdgpu_buffer_rsrc_t rs_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.rs), 0, unsigned(p.in) * 4u, 0x00020000);
+    const v4i rsrc = buffer_over(p.blocks, unsigned(n) * stride);
+    const v4i rs_rsrc = buffer_over(p.rs, unsigned(p.in) * 4u);
     const unsigned s_lane = unsigned(ch) * kUnitBytes + unsigned(lane) * 16u;
     const unsigned v_lane = v_lane_offset<kRebuildWaves>(unsigned(p.off_v), unsigned(wave), unsigned(lane)) + unsigned(ch) * kVChunkBytes;
     const unsigned u_lane = u_lane_offset<kRebuildWaves>(unsigned(p.off_u), 0u, unsigned(lane));
-    const unsigned lds0 = unsigned(reinterpret_cast<uintptr_t>((lds_void*)smem));
+    const unsigned lds0 = lds_address(smem);
     const unsigned v_rd = lds0 + v_read_offset(unsigned(lane));
     const unsigned s_rd = lds0 + unsigned(wave) * Step::kWaveBytes + unsigned(lane) * 16u;
     const v4h ident = accumulate_matrix(unsigned(lane));
@@ -63,7 +62,7 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     unsigned qv = 0, qs = unsigned(row_tile(rg0)) * unsigned(nch) * kUnitBytes, qu = unsigned(row_tile(rg0)) * 1024u;
     unsigned qbuf = 0;
     auto request = [&]() {
-        load_step<kRebuildWaves>(rsrc, smem + qbuf + wave * Step::kWaveBytes, s_lane, v_lane, u_lane, qs, qv, qu);
+        load_step<kRebuildWaves>(rsrc, lds0 + qbuf + unsigned(wave) * Step::kWaveBytes, s_lane, v_lane, u_lane, qs, qv, qu);
         qv += stride;
         qs += stride;
         qu += stride;
@@ -81,7 +80,7 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     UnitAcc acc;
     StepInputs in;
     unsigned buf = 0;
-    load4_to_lds(rs_rsrc, smem + kRsLds + wave * 256, unsigned(lane) * 4u, unsigned(ch) * (kChunkCols * 4) + unsigned(wave) * 256u);
+    load4_to_lds(rs_rsrc, lds0 + kRsLds + unsigned(wave) * 256u, unsigned(lane) * 4u, unsigned(ch) * (kChunkCols * 4) + unsigned(wave) * 256u);
     request();
     request();
     loads_barrier<kInFlight>();
@@ -89,7 +88,7 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     {
         FirstReads first;
         begin_reads<kRebuildWaves>(in, first, v_rd, s_rd);
-        wait_inputs(in, first.f7, first.signs);
+        take_reads(in, first);
     }
     auto step = [&](auto first) __attribute__((always_inline)) {
         // the next step's inputs have landed (this wavefront's loads, then everybody's), and nobody reads the previous
@@ -114,37 +113,27 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
         unsigned char* const dst16 = dst + size_t(p.in) * 32;   // 16 rows further down
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            v4f r[4][2];
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
-                             : "=&v"(r[b][0]), "=&v"(r[b][1])
-                             : "v"(rs_rd), "n"((w * 4 + b) * 32), "n"((w * 4 + b) * 32 + 16));
-            asm volatile("s_waitcnt lgkmcnt(0)"
-                         : "+v"(r[0][0]), "+v"(r[0][1]), "+v"(r[1][0]), "+v"(r[1][1]), "+v"(r[2][0]), "+v"(r[2][1]), "+v"(r[3][0]),
-                           "+v"(r[3][1]));
             v4i o[4];
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
+            for (int b = 0; b < 4; ++b) {
+                v4f r[2];
+                read_scales(r, rs_rd, w * 4 + b);
 #pragma unroll
-                for (int t = 0; t < 8; t += 2) {   // (product and conversion in one instruction)
-                    int d;
-                    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(d) : "v"(acc[t][w][b]), "v"(r[b][t >> 2][t & 3]));
-                    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(d) : "v"(acc[t + 1][w][b]), "v"(r[b][t >> 2][(t & 3) + 1]));
-                    o[b][t >> 1] = d;
-                }
+                for (int t = 0; t < 8; t += 2)
+                    o[b][t >> 1] = scaled_pair(acc[t][w][b], acc[t + 1][w][b], r[t >> 2][t & 3], r[t >> 2][(t & 3) + 1]);
+            }
             v4i q[4];
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 if (hl == half) {
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) asm volatile("ds_write_b128 %0, %1" ::"v"(wr + ((unsigned(b) ^ swz) * 16u)), "v"(o[b]));
+                    for (int b = 0; b < 4; ++b) write_lds(wr + ((unsigned(b) ^ swz) * 16u), o[b]);
                 }
-                asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:1024"
-                             : "=&v"(q[2 * half]), "=&v"(q[2 * half + 1])
-                             : "v"(rd));
+                wavefront_lds_order();
+                q[2 * half] = read_lds<v4i>(rd);
+                q[2 * half + 1] = read_lds<v4i>(rd + 1024u);
+                wavefront_lds_order();
             }
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]));
             *reinterpret_cast<v4i*>(dst + w * 64) = q[0];
             *reinterpret_cast<v4i*>(dst16 + w * 64) = q[1];
             *reinterpret_cast<v4i*>(dst + 256 + w * 64) = q[2];
