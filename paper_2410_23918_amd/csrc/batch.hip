@@ -40,7 +40,8 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     constexpr unsigned kStep = TEAMS * L::kBytes;
     // an activation step brings TOK tokens x kPieces columns of eight per half, 8 KiB per team
     constexpr int kPieces = 256 / TOK, kPerGroup = 16 / kPieces, kXSteps = GROUPS * kPerGroup, kXRowBytes = kPieces * 32;
-    constexpr unsigned kRsLds = kRing * kStep;   // [2][TEAMS][256] floats
+    // behind the ring: 1/s [2][TEAMS][256], 128 ones, a flag
+    constexpr unsigned kRsLds = kRing * kStep, kOnesLds = kRsLds + 2 * TEAMS * 1024, kFlagLds = kOnesLds + 512;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -109,83 +110,124 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
         }
     };
 
-    v16f yacc[GROUPS];
-#pragma unroll
-    for (int g = 0; g < GROUPS; ++g) yacc[g] = zero16();
+    // the lane's half, made anew: kept, it would cost the loop a register it does not have
+    auto own_half = [&]() {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l >> 5;
+    };
 
+    v16f yacc[GROUPS];
     UnitAcc acc;
     StepInputs in;
     unsigned buf = 0;
-    request_rs(0);
-    // step s's inputs are requested two steps ahead
-    request();
-    loads_barrier<0>();
-    request();
-    {
-        FirstReads first;
-        begin_reads<RT>(in, first, v_rd, s_rd);
-        take_reads(in, first);
-    }
-    for (int it = 0; it < iters; ++it) {
-        auto step = [&](auto first) __attribute__((always_inline)) {
-            loads_barrier<0>();
-            request();
-            const unsigned nb = next_buf(buf);
-            add_block<decltype(first)::value, RT>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
-            buf = nb;
-        };
-        step(std::true_type{});
-        for (int i = 1; i < n; ++i) step(std::false_type{});
-        // (what the last step read ahead was activations: read again below)
-        const bool valid = c_lo + it * TEAMS + team < c_hi;   // uniform over the wavefront
-        const unsigned rs_rd = lds0 + kRsLds + unsigned(it & 1) * (TEAMS * 1024) + unsigned(team) * 1024u + unsigned(hl) * 512u;
-        v4i b[16];   // W' diag(1/s) of the unit as B operands: step e = columns 8 e .. 8 e + 7 of both halves
-        v4f r[2][2];
-        auto scale = [&](auto e) __attribute__((always_inline)) {
-            constexpr int E = decltype(e)::value;
-            v4f(&q)[2] = r[E & 1];
-            if constexpr (E < 15) read_scales(r[(E + 1) & 1], rs_rd, E + 1);
+    if (tid < 128) write_lds(lds0 + kOnesLds + unsigned(tid) * 4u, 1.0f);
+    if (tid == 0) write_lds(lds0 + kFlagLds, 0u);
+
+    auto accumulate = [&](auto on_x) __attribute__((always_inline)) {
+        constexpr bool kScaleX = decltype(on_x)::value;
+        const int hl = own_half();
 #pragma unroll
-            for (int t = 0; t < 8; t += 2)
-                b[E][t >> 1] = scaled_pair(acc[t][E >> 2][E & 3], acc[t + 1][E >> 2][E & 3], q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
-            asm volatile("" : "+v"(b[E]));   // made here: put off to the products, it would keep the scales in registers until then
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        read_scales(r[0], rs_rd, 0);
-#define BS_SCALE(E) scale(std::integral_constant<int, E>{});
-        BS_SCALE(0) BS_SCALE(1) BS_SCALE(2) BS_SCALE(3) BS_SCALE(4) BS_SCALE(5) BS_SCALE(6) BS_SCALE(7)
-        BS_SCALE(8) BS_SCALE(9) BS_SCALE(10) BS_SCALE(11) BS_SCALE(12) BS_SCALE(13) BS_SCALE(14) BS_SCALE(15)
-#undef BS_SCALE
-        FirstReads first;
-#pragma unroll
-        for (int xs = 0; xs < kXSteps; ++xs) {
-            const int g = xs / kPerGroup, e0 = xs % kPerGroup * kPieces;
-            loads_barrier<0>();
-            if (xs == 0) request_rs(it + 1);
-            request();
-            const unsigned nb = next_buf(buf);
-            if (xs == kXSteps - 1) begin_reads<RT>(in, first, v_rd + nb, s_rd + nb);   // the next chunk's first step
-#pragma unroll
-            for (int eq = 0; eq < kPieces / 4; ++eq) {
-                v4i a[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const unsigned pos = unsigned(hl * kPieces + eq * 4 + k) ^ unsigned(ln & 15);
-                    a[k] = read_lds<v4i>(x_rd + buf + pos * 16u);
-                }
-                if (valid) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        yacc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a[k]),
-                                                                         __builtin_bit_cast(v8h, b[e0 + eq * 4 + k]), yacc[g], 0, 0, 0);
-                }
-            }
-            buf = nb;
+        for (int g = 0; g < GROUPS; ++g) yacc[g] = zero16();
+        request_rs(0);
+        // step s's inputs are requested two steps ahead
+        request();
+        loads_barrier<0>();
+        request();
+        {
+            FirstReads first;
+            begin_reads<RT>(in, first, v_rd, s_rd);
+            take_reads(in, first);
         }
-        take_reads(in, first);
-    }
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        for (int it = 0; it < iters; ++it) {
+            auto step = [&](auto first) __attribute__((always_inline)) {
+                loads_barrier<0>();
+                request();
+                const unsigned nb = next_buf(buf);
+                add_block<decltype(first)::value, RT>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
+                buf = nb;
+            };
+            step(std::true_type{});
+            for (int i = 1; i < n; ++i) step(std::false_type{});
+            // (what the last step read ahead was activations: read again below)
+            const bool valid = c_lo + it * TEAMS + team < c_hi;   // uniform over the wavefront
+            const unsigned rs_rd = lds0 + kRsLds + unsigned(it & 1) * (TEAMS * 1024) + unsigned(team) * 1024u + unsigned(hl) * 512u;
+            const unsigned b_rd = kScaleX ? lds0 + kOnesLds : rs_rd;
+            v4i b[16];   // W' diag(1/s) of the unit as B operands: step e = columns 8 e .. 8 e + 7 of both halves
+            v4f r[2][2];
+            auto scale = [&](auto e) __attribute__((always_inline)) {
+                constexpr int E = decltype(e)::value;
+                v4f(&q)[2] = r[E & 1];
+                if constexpr (E < 15) read_scales(r[(E + 1) & 1], b_rd, E + 1);
+#pragma unroll
+                for (int t = 0; t < 8; t += 2)
+                    b[E][t >> 1] = scaled_pair(acc[t][E >> 2][E & 3], acc[t + 1][E >> 2][E & 3], q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
+                asm volatile("" : "+v"(b[E]));   // made here: put off to the products, it would keep the scales in registers until then
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            read_scales(r[0], b_rd, 0);
+#define BS_SCALE(E) scale(std::integral_constant<int, E>{});
+            BS_SCALE(0) BS_SCALE(1) BS_SCALE(2) BS_SCALE(3) BS_SCALE(4) BS_SCALE(5) BS_SCALE(6) BS_SCALE(7)
+            BS_SCALE(8) BS_SCALE(9) BS_SCALE(10) BS_SCALE(11) BS_SCALE(12) BS_SCALE(13) BS_SCALE(14) BS_SCALE(15)
+#undef BS_SCALE
+            FirstReads first;
+#pragma unroll
+            for (int xs = 0; xs < kXSteps; ++xs) {
+                const int g = xs / kPerGroup, e0 = xs % kPerGroup * kPieces;
+                loads_barrier<0>();
+                if (xs == 0) request_rs(it + 1);
+                request();
+                const unsigned nb = next_buf(buf);
+                if (xs == kXSteps - 1) begin_reads<RT>(in, first, v_rd + nb, s_rd + nb);   // the next chunk's first step
+#pragma unroll
+                for (int eq = 0; eq < kPieces / 4; ++eq) {
+                    v4i a[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const unsigned pos = unsigned(hl * kPieces + eq * 4 + k) ^ unsigned(ln & 15);
+                        a[k] = read_lds<v4i>(x_rd + buf + pos * 16u);
+                    }
+                    if constexpr (kScaleX) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            v4f q[2];
+                            read_scales(q, rs_rd, e0 + eq * 4 + k);
+                            const v8h h = __builtin_bit_cast(v8h, a[k]);
+#pragma unroll
+                            for (int t = 0; t < 8; t += 2)
+                                a[k][t >> 1] = scaled_pair(float(h[t]), float(h[t + 1]), q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
+                        }
+                    }
+                    if (valid) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            yacc[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a[k]),
+                                                                             __builtin_bit_cast(v8h, b[e0 + eq * 4 + k]), yacc[g], 0, 0, 0);
+                    }
+                }
+                buf = nb;
+            }
+            take_reads(in, first);
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    };
+    accumulate(std::false_type{});
+    // A weight over its scale need not be an fp16 number where the weight and the activation over the scale are (a channel
+    // scaled far down whose activations are tiny, or zero): then y is not finite, and the workgroup starts over with 1/s on the
+    // activations.  Not so in the first place: large scales would take the activations out of fp16's range.
+    float rest = 0.0f;   // 0 * y: NaN for infinities and NaN
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) rest = __builtin_fmaf(yacc[g][v], 0.0f, rest);
+    if (rest != 0.0f) write_lds(lds0 + kFlagLds, 1u);
     __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(int(read_lds<unsigned>(lds0 + kFlagLds)))) {
+        qi = qit = 0;
+        qbuf = qoff = buf = 0u;
+        accumulate(std::true_type{});
+        __syncthreads();
+    }
 
     // the teams' partial tiles meet in LDS; D[i = token][n = row]: lane (row ln), register v holds token
     // 8 (v / 4) + 4 hl + v % 4 of the group
@@ -276,7 +318,7 @@ static int batch_split(int out, int in, int batch, int part_slots) {
 
 template <int TOK, int GROUPS>
 static hipError_t launch_batch_t(KParams p, hipStream_t st) {
-    const size_t smem = size_t(3) * 4 * StepLayout<2>::kBytes + 2 * 4 * kChunkCols * 4;
+    const size_t smem = size_t(3) * 4 * StepLayout<2>::kBytes + 2 * 4 * kChunkCols * 4 + 512 + 16;
     static std::atomic<bool> attr_set{false};   // setting the attribute twice is harmless
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch<TOK, GROUPS>),

@@ -28,11 +28,23 @@ def test_more_than_64_tokens_in_groups(out, inn, n, batch):
     check(out, inn, n, batch)
 
 
-def check(out, inn, n, batch):
+@pytest.mark.parametrize("batch", [2, 17, 64, 130])
+def test_weights_over_their_scales_out_of_fp16_range(batch):
+    """Four channels scaled down by 2^-30 whose activations are tiny or zero: a weight over its scale is beyond fp16's largest value
+    there (W' is of the order of 0.2), the activation over the scale is not."""
+    check(96, 1280, 45, batch, small=(5, 300, 511, 1279))
+
+
+def test_an_infinite_activation_stays_with_its_token():
+    check(96, 1280, 45, 20, infinite=7)
+
+
+def check(out, inn, n, batch, small=(), infinite=None):
     import torch
     import paper_2410_23918_amd as B
     g = torch.Generator(device="cuda:0").manual_seed(out + inn + batch)
     s = np.exp(0.5 * np.random.default_rng(batch).standard_normal(inn)).astype(np.float32)
+    s[list(small)] = 2.0**-30
     ps = B.PackedStack.empty(out, inn, n, s, max_batch=max(64, batch))
     w = torch.zeros((out, inn), device="cuda:0")
     mag = torch.zeros_like(w)   # sum over blocks of |U V^T|
@@ -49,16 +61,27 @@ def check(out, inn, n, batch):
     w *= rs
     mag *= rs
     x = torch.randn((batch, inn), generator=g, device="cuda:0").half()
+    for k, c in enumerate(small):
+        x[:, c] = 0.0 if k % 2 else 2.0**-24 * torch.randint(-3, 4, (batch,), generator=g, device="cuda:0").half()
+    if infinite is not None:
+        x[infinite, 100] = float("inf")
+    finite = torch.isfinite(x).all(dim=1)
     y = torch.full((batch, out), float("nan"), device="cuda:0")
     for _ in range(2):   # the second call finds the counters as the first left them
         ps.linear_batched(x, n, y=y, kernel=B.KERNEL_PANEL)
         torch.cuda.synchronize()
-        xa = x.float().abs().double()
-        want = x.double() @ w.double().t().contiguous()
+        assert not torch.isfinite(y[~finite]).any()
+        xa = x[finite].float().abs().double()
+        want = x[finite].double() @ w.double().t().contiguous()
         # magnitudes rounded to fp16 (2^-11 of each), their sum times 1/s rounded once more; then fp32 sums of 16-column
         # products: at most in / 16 + 16 roundings of 2^-24 of the sum of absolute values
         werr = 2.0**-11 * (mag + w.abs()) * 1.01 + 2.0**-20 * rs + 2.0**-24
         bound = xa @ werr.double().t().contiguous() + (inn / 16 + 16) * 2.0**-24 * (xa @ w.abs().double().t().contiguous())
-        worst = ((y.double() - want).abs() / bound).max().item()
+        if small or infinite is not None:
+            # 1/s may be on the activations instead: x/s rounded to fp16 (2^-11 of it, or half the spacing of subnormals) and the sum
+            # of the magnitudes rounded before the scale (2^-11 of it is in werr, half a subnormal spacing is not)
+            wp, xs = (w / rs).abs().double(), xa * rs.double()
+            bound += (2.0**-11 * xs + 2.0**-25) @ wp.t().contiguous() + 2.0**-25 * xs.sum(dim=1, keepdim=True)
+        worst = ((y[finite].double() - want).abs() / bound).max().item()
         print(f"{out}x{inn} batch {batch}: largest error {worst:.3f} of its bound", flush=True)
         assert worst <= 1.0   # also false for an element that was not written (NaN)
