@@ -1016,6 +1016,19 @@ static double tile_launch_us(int out, int in, int batch, int n_loaded) {
     return 14.8 + rounds * (chunk_pairs * ((0.65 + 0.09 * fill) * n_loaded + 3.85 + (2.8 + 2.13 * fill) * tokens) - 3.0);
 }
 
+// k_fused against k_batch where k_fused's workgroups run few steps (column pairs x blocks) in one round: its loop is unrolled three
+// times and ends with a whole turn.  fused_time_us is up to 1.5 times too high there (three steps: 10 us for 6.7, k_batch 8.8).
+// Fitted to 1052 cases of up to 18 steps, 0.36 us root mean square; with 8 < steps <= 18 and a column split it is no better than
+// fused_time_us.  Of 800 cases (64 x 256 to 28672 x 8192, 1 to 24
+// blocks, 2 to 64 tokens; both kernels timed) eight are then 3 to 8 % slower on k_batch than on k_fused; by fused_time_us alone 103, by up to 32 %.
+static double fused_launch_us(int out, int in, int batch, int n_loaded, int part_slots) {
+    const int split = small_batch_split(out, in, batch, part_slots), wgs = (out + 63) / 64 * ((batch + 31) / 32) * split;
+    const int pairs = ((in / kChunkCols + 1) / 2 + split - 1) / split, steps = n_loaded * pairs;
+    if (wgs > 256 || steps > (split > 1 ? 8 : 18)) return fused_time_us(out, in, batch, n_loaded, part_slots);
+    return (batch > 32 ? 4.0 : 4.3) + 0.62 * ((steps + 2) / 3 * 3 + pairs) + (steps % 3 ? 0.7 : 0.0) + (steps == 1 ? 0.4 : 0.0) +
+           1.3 * wgs / 256 + (split > 1 ? 1.8 : 0.0);
+}
+
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     KParams p = make_params(a);
     if (a.n_loaded < 1 || a.batch < 1) return hipErrorInvalidValue;
@@ -1025,7 +1038,7 @@ hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
         // tokens; the weight-tile kernel is a candidate from 33 tokens on
         const bool batch_ok = batch_fits(p);
         const double tb = batch_ok ? batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 0.0;
-        const double tf = fused_fits(p) ? fused_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 0.0;
+        const double tf = fused_fits(p) ? fused_launch_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 0.0;
         const bool take_batch = batch_ok && (tf == 0.0 || tb < tf);
         if (a.batch > 32 && tile_fits(p) && tile_time_us(p.out, p.in, p.batch, p.n_loaded) < (take_batch ? tb : tf))
             return launch_tile(p, st);

@@ -35,6 +35,31 @@ def test_weights_over_their_scales_out_of_fp16_range(batch):
     check(96, 1280, 45, batch, small=(5, 300, 511, 1279))
 
 
+@pytest.mark.parametrize("out,inn,n,batch,fused", [
+    (736, 512, 3, 4, True),       # three steps: 6.7 us, k_batch 8.7
+    (5376, 512, 3, 16, True),     # 7.0, 9.2
+    (96, 512, 2, 30, True),       # two steps: 7.4, 8.7
+    (832, 768, 3, 50, True),      # six steps, two token groups: 9.7, 11.7
+    (384, 1024, 8, 3, True),      # eight steps, two column ranges: 12.5, 14.2
+    (448, 256, 1, 4, False),      # one step: 8.0, 6.7
+    (4096, 4096, 16, 16, False),
+])
+def test_the_kernel_taken_for_few_steps(out, inn, n, batch, fused):
+    """k_fused rounds x/s to fp16, k_batch W'/s: with weights n, scales 7 and activations 7 the one is exact, the other is not."""
+    import torch
+    import paper_2410_23918_amd as B
+    ps = B.PackedStack.empty(out, inn, n, np.full(inn, 7.0, np.float32), max_batch=64)
+    for _ in range(n):
+        ps.push_block_device(torch.full((out, inn // 32), -1, dtype=torch.int32, device="cuda:0"),
+                             torch.full((out, 16), 0.25, dtype=torch.float16, device="cuda:0"),
+                             torch.full((inn, 16), 0.25, dtype=torch.float16, device="cuda:0"))
+    y = torch.full((batch, out), float("nan"), device="cuda:0")
+    ps.linear_batched(torch.full((batch, inn), 7.0, dtype=torch.float16, device="cuda:0"), n, y=y, kernel=B.KERNEL_PANEL)
+    want = float(n * inn if fused else torch.tensor(n / 7.0).half()) * (1 if fused else 7 * inn)
+    # the sums are of equal numbers: exact for k_fused, for k_batch within fp32's rounding of in / 16 + 16 additions
+    assert (y - want).abs().max().item() <= (0.0 if fused else (inn / 16 + 16) * 2.0**-24 * want)
+
+
 def test_an_infinite_activation_stays_with_its_token():
     check(96, 1280, 45, 20, infinite=7)
 
