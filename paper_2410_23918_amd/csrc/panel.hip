@@ -1008,19 +1008,21 @@ double tile_time_us(int out, int in, int batch, int n_loaded) {
 
 // The weight-tile kernel against k_batch for 65 to 1024 tokens, fitted to 720 cases (12 shapes from 512 x 512 to 14336 x 4096, 1 to 24
 // blocks; 7 % root mean square; with batch_time_us the faster kernel was taken in each, to 1 %).  tile_time_us is up to 1.9 times too
-// high here, but the crossover to the materialising path is stated in terms of it.
+// high here, but the crossover to the materialising path is stated in terms of it.  A single column chunk, of which one team has
+// none, is 2.5 us less (3264 x 256, 12 blocks, 220 tokens: 25 us for 22).
 static double tile_launch_us(int out, int in, int batch, int n_loaded) {
     const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
     const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 1.0 + 1.28 * (wgs / 256.0 - 1.0);
     const double tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
-    return 14.8 + rounds * (chunk_pairs * ((0.65 + 0.09 * fill) * n_loaded + 3.85 + (2.8 + 2.13 * fill) * tokens) - 3.0);
+    return 14.8 + rounds * (chunk_pairs * ((0.65 + 0.09 * fill) * n_loaded + 3.85 + (2.8 + 2.13 * fill) * tokens) - 3.0) -
+           (in == kChunkCols ? 2.5 : 0.0);
 }
 
 // k_fused against k_batch where k_fused's workgroups run few steps (column pairs x blocks) in one round: its loop is unrolled three
 // times and ends with a whole turn.  fused_time_us is up to 1.5 times too high there (three steps: 10 us for 6.7, k_batch 8.8).
 // Fitted to 1052 cases of up to 18 steps, 0.36 us root mean square; with 8 < steps <= 18 and a column split it is no better than
-// fused_time_us.  Of 800 cases (64 x 256 to 28672 x 8192, 1 to 24
-// blocks, 2 to 64 tokens; both kernels timed) eight are then 3 to 8 % slower on k_batch than on k_fused; by fused_time_us alone 103, by up to 32 %.
+// fused_time_us.  Of 800 cases (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens; both kernels timed) eight are then 3 to
+// 8 % slower on k_batch than on k_fused; by fused_time_us alone 103, by up to 32 %.
 static double fused_launch_us(int out, int in, int batch, int n_loaded, int part_slots) {
     const int split = small_batch_split(out, in, batch, part_slots), wgs = (out + 63) / 64 * ((batch + 31) / 32) * split;
     const int pairs = ((in / kChunkCols + 1) / 2 + split - 1) / split, steps = n_loaded * pairs;
@@ -1049,8 +1051,11 @@ hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     // k_batch's token groups and column split fill them (608 x 12032, 8 blocks, 96 tokens: 263 -> 59 us; 4096 x 14336, 16 blocks,
     // 128 tokens: 449 -> 307; 4096 x 4096, 256 tokens: 139 -> 99, but 300 tokens 146 -> 189).  Also for stacks the
     // weight-tile kernel cannot hold: k_panel is slower than its estimate
+    // (estimates within 5 % of each other say nothing: there the weight-tile kernel, which k_batch was up to 15 % slower than; in
+    // 680 cases given to k_batch by this rule it is at most 7 % slower, and up to 7 times faster)
+    const double margin = tile_fits(p) ? 0.95 : 1.0;
     if (a.batch > kFusedMaxBatch && a.batch <= 1024 && batch_fits(p) &&
-        batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) < tile_launch_us(p.out, p.in, p.batch, p.n_loaded))
+        batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) < margin * tile_launch_us(p.out, p.in, p.batch, p.n_loaded))
         return launch_batch(p, st);
     if (a.batch > kFusedMaxBatch && tile_fits(p)) return launch_tile(p, st);
     if (a.batch > 256) return launch_panel_t<4>(p, st);

@@ -60,6 +60,30 @@ def test_the_kernel_taken_for_few_steps(out, inn, n, batch, fused):
     assert (y - want).abs().max().item() <= (0.0 if fused else (inn / 16 + 16) * 2.0**-24 * want)
 
 
+@pytest.mark.parametrize("out,inn,n,batch,tile", [
+    (3264, 256, 12, 220, True),    # one column chunk: 21.9 us, k_batch 24.7
+    (5312, 1536, 2, 249, True),    # estimates within 1 %: 30.7, 35.2
+    (11424, 768, 5, 78, True),     # 27.7, 30.0
+    (864, 256, 9, 124, False),     # 19.4, 19.2
+    (768, 12032, 18, 84, False),   # 410, 57
+])
+def test_the_kernel_taken_beyond_64_tokens(out, inn, n, batch, tile):
+    """k_tile rearranges the activations in the image's scratch, k_batch reads them where they are."""
+    import torch
+    import paper_2410_23918_amd as B
+    ps = B.PackedStack.empty(out, inn, n, np.full(inn, 7.0, np.float32), max_batch=1024)
+    for _ in range(n):
+        ps.push_block_device(torch.full((out, inn // 32), -1, dtype=torch.int32, device="cuda:0"),
+                             torch.full((out, 16), 0.25, dtype=torch.float16, device="cuda:0"),
+                             torch.full((inn, 16), 0.25, dtype=torch.float16, device="cuda:0"))
+    torch.cuda.synchronize()
+    end = ps.buf.numel() // 256 * 256
+    scratch = ps.buf[end - 1024 * inn * 2:end]   # the image's last 1024 x in fp16 values
+    scratch.zero_()
+    ps.linear_batched(torch.full((batch, inn), 7.0, dtype=torch.float16, device="cuda:0"), n, kernel=B.KERNEL_PANEL)
+    assert bool(scratch.any()) == tile
+
+
 def test_an_infinite_activation_stays_with_its_token():
     check(96, 1280, 45, 20, infinite=7)
 
