@@ -331,17 +331,17 @@ static hipError_t launch_batch_t(KParams p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Estimated duration (microseconds; fitted to 553 cases from 512 x 512 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens: 3.7 %
-// root mean square; and to 720 cases of 65 to 1024 tokens, 4.5 %): per round and chunk iteration of a workgroup 1.05-1.25 us per
-// block and ~2-4 us for scaling and product
+// Estimated duration (microseconds; fitted to 4774 cases of 2 to 64 tokens and 3483 of 65 to 1024, 64 x 256 to 28672 x 8192, 1 to 24
+// blocks; 3.4 % root mean square, all within 16 %): per round and chunk iteration of a workgroup 1.02-1.19 us per block and 1.9-3.9 us
+// for scaling and product
 double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
     const int groups = (out + 63) / 64 * ((batch + 63) / 64), nch = in / kChunkCols;
     const int split = batch_split(out, in, batch, part_slots);
     const int wgs = groups * split, xsteps = batch > 32 ? 4 : batch > 16 ? 2 : 1;
-    const double its = double((wgs + 255) / 256) * (((nch + split - 1) / split + 3) / 4), fill = wgs < 256 ? wgs / 256.0 : 1.0;
-    const double again = batch > 64 ? 3.3 * ((wgs + 255) / 256 - 1) : 0.0;   // token groups in further rounds: their first loads
-    return 4.3 + its * (n_loaded * (1.05 + 0.2 * fill) + 1.2 + 0.63 * xsteps) + again +
-           (split > 1 ? 1.9 + 0.018 * (batch < 64 ? batch : 64) * split : 0.0);
+    const int its = ((nch + split - 1) / split + 3) / 4;
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0;
+    return (batch > 64 ? 3.3 : 2.0) + (wgs + 255) / 256 * ((batch > 64 ? 3.5 : 3.1) + its * (n_loaded * (1.02 + 0.17 * fill) + 1.25 + 0.66 * xsteps)) +
+           (split > 1 ? (batch > 64 ? 3.2 : 2.0) : 0.0);
 }
 
 // one 32-bit buffer descriptor each over the loaded blocks and the activations, one counter per row group and 64 tokens

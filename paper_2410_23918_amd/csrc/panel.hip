@@ -985,16 +985,15 @@ static hipError_t launch_tile(const KParams& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Estimated durations (microseconds).  k_fused (fitted to the same 553 cases as batch_time_us): per round of 256 workgroups ~8 us
-// and 0.65-0.82 us per block and pair of column chunks of a workgroup; later workgroups start as earlier ones end, so rounds
-// beyond the first count fractionally.
+// Estimated durations (microseconds).  k_fused, fitted to 4774 cases (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens; 3.4 %
+// root mean square, all within 15 %): a step is a pair of column chunks and a block; the loop takes three at a time and ends with a
+// whole turn (three steps 7.0 us, four 9.2, six 9.0); rounds of 256 workgroups count nearly whole.
 double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
-    const int row_tiles = (out + 2 * kTileRows - 1) / (2 * kTileRows), chunk_pairs = (in / kChunkCols + 1) / 2;
-    const int split = small_batch_split(out, in, batch, part_slots);
-    const int wgs = row_tiles * ((batch + 31) / 32) * split;
-    const double rounds = wgs <= 256 ? 1.0 : wgs / 256.0, fill = wgs < 256 ? wgs / 256.0 : 1.0;
-    return rounds * (20.1 + n_loaded * ((chunk_pairs + split - 1) / split) * (0.65 + 0.17 * fill)) - 12.2 +
-           (split > 1 ? 1.5 - 0.013 * batch * split : 0.0);
+    const int split = small_batch_split(out, in, batch, part_slots), wgs = (out + 63) / 64 * ((batch + 31) / 32) * split;
+    const int pairs = ((in / kChunkCols + 1) / 2 + split - 1) / split, steps = n_loaded * pairs;
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 0.81 * ((wgs + 255) / 256) + 0.19 * wgs / 256.0;
+    return 1.8 + rounds * (3.8 + (steps + 2) / 3 * 3 * (0.58 + 0.166 * fill) + 0.625 * pairs + (steps % 3 ? 0.76 : 0.0)) +
+           (split > 1 ? 1.5 + 0.003 * batch * split : 0.0);
 }
 // k_tile: per pair of column chunks ~0.9 us per block for the rebuild + 12-14 us for the product
 // (14 when several token tiles of a row tile run at once, 6.5 up to 256 tokens, where only one
@@ -1006,58 +1005,34 @@ double tile_time_us(int out, int in, int batch, int n_loaded) {
     return rounds * (15.0 + chunk_pairs * scale * (0.9 * n_loaded + (batch > 512 ? 14.0 : batch > 256 ? 12.0 : 6.5)));
 }
 
-// The weight-tile kernel against k_batch for 65 to 1024 tokens, fitted to 720 cases (12 shapes from 512 x 512 to 14336 x 4096, 1 to 24
-// blocks; 7 % root mean square; with batch_time_us the faster kernel was taken in each, to 1 %).  tile_time_us is up to 1.9 times too
-// high here, but the crossover to the materialising path is stated in terms of it.  A single column chunk, of which one team has
-// none, is 2.5 us less (3264 x 256, 12 blocks, 220 tokens: 25 us for 22).
+// The weight-tile kernel against k_batch and k_fused for 33 to 1024 tokens, fitted to 3483 cases (64 x 256 to 28672 x 8192, 1 to 24
+// blocks; 4.3 % root mean square).  tile_time_us is up to 1.9 times too high here, but the crossover to the materialising path
+// is stated in terms of it.
 static double tile_launch_us(int out, int in, int batch, int n_loaded) {
     const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
-    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 1.0 + 1.28 * (wgs / 256.0 - 1.0);
-    const double tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
-    return 14.8 + rounds * (chunk_pairs * ((0.65 + 0.09 * fill) * n_loaded + 3.85 + (2.8 + 2.13 * fill) * tokens) - 3.0) -
-           (in == kChunkCols ? 2.5 : 0.0);
-}
-
-// k_fused against k_batch where k_fused's workgroups run few steps (column pairs x blocks) in one round: its loop is unrolled three
-// times and ends with a whole turn.  fused_time_us is up to 1.5 times too high there (three steps: 10 us for 6.7, k_batch 8.8).
-// Fitted to 1052 cases of up to 18 steps, 0.36 us root mean square; with 8 < steps <= 18 and a column split it is no better than
-// fused_time_us.  Of 800 cases (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens; both kernels timed) eight are then 3 to
-// 8 % slower on k_batch than on k_fused; by fused_time_us alone 103, by up to 32 %.
-static double fused_launch_us(int out, int in, int batch, int n_loaded, int part_slots) {
-    const int split = small_batch_split(out, in, batch, part_slots), wgs = (out + 63) / 64 * ((batch + 31) / 32) * split;
-    const int pairs = ((in / kChunkCols + 1) / 2 + split - 1) / split, steps = n_loaded * pairs;
-    if (wgs > 256 || steps > (split > 1 ? 8 : 18)) return fused_time_us(out, in, batch, n_loaded, part_slots);
-    return (batch > 32 ? 4.0 : 4.3) + 0.62 * ((steps + 2) / 3 * 3 + pairs) + (steps % 3 ? 0.7 : 0.0) + (steps == 1 ? 0.4 : 0.0) +
-           1.3 * wgs / 256 + (split > 1 ? 1.8 : 0.0);
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
+    return 5.5 + 2.15e-6 * batch * in +   // the activations rearranged
+           (wgs + 255) / 256 * (6.1 + chunk_pairs * ((0.652 + 0.074 * fill) * n_loaded + 4.2 + 2.3 * tokens)) -
+           (in == kChunkCols ? 1.5 : 0.0);
 }
 
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     KParams p = make_params(a);
     if (a.n_loaded < 1 || a.batch < 1) return hipErrorInvalidValue;
-    if (a.batch <= kFusedMaxBatch) {
-        // the cheapest of three estimates: k_batch sums the weight over the blocks before it multiplies (many blocks, many
-        // tokens); k_fused multiplies every block's tile and has less to do per chunk (few blocks), but rebuilds the tiles per 32
-        // tokens; the weight-tile kernel is a candidate from 33 tokens on
-        const bool batch_ok = batch_fits(p);
-        const double tb = batch_ok ? batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 0.0;
-        const double tf = fused_fits(p) ? fused_launch_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 0.0;
-        const bool take_batch = batch_ok && (tf == 0.0 || tb < tf);
-        if (a.batch > 32 && tile_fits(p) && tile_time_us(p.out, p.in, p.batch, p.n_loaded) < (take_batch ? tb : tf))
-            return launch_tile(p, st);
-        if (take_batch) return launch_batch(p, st);
-        if (tf != 0.0) return launch_fused(p, st);
-    }
-    // 65 to 1024 tokens: where rows x 64 tokens leave compute units idle in the weight-tile kernel's grid of 64 rows x 512 tokens,
-    // k_batch's token groups and column split fill them (608 x 12032, 8 blocks, 96 tokens: 263 -> 59 us; 4096 x 14336, 16 blocks,
-    // 128 tokens: 449 -> 307; 4096 x 4096, 256 tokens: 139 -> 99, but 300 tokens 146 -> 189).  Also for stacks the
-    // weight-tile kernel cannot hold: k_panel is slower than its estimate
-    // (estimates within 5 % of each other say nothing: there the weight-tile kernel, which k_batch was up to 15 % slower than; in
-    // 680 cases given to k_batch by this rule it is at most 7 % slower, and up to 7 times faster)
-    const double margin = tile_fits(p) ? 0.95 : 1.0;
-    if (a.batch > kFusedMaxBatch && a.batch <= 1024 && batch_fits(p) &&
-        batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) < margin * tile_launch_us(p.out, p.in, p.batch, p.n_loaded))
-        return launch_batch(p, st);
-    if (a.batch > kFusedMaxBatch && tile_fits(p)) return launch_tile(p, st);
+    // The cheapest of three estimates.  k_batch sums the weight over the blocks before it multiplies (many blocks, many tokens) and
+    // rebuilds it per 64 tokens, with a column split that fills the chip; k_fused multiplies every block's tile and has less to do
+    // per chunk (few blocks), but rebuilds the tiles per 32 tokens; the weight-tile kernel rebuilds the weight once per 512
+    // tokens (608 x 12032, 8 blocks, 96 tokens: k_tile 263 us, k_batch 59; 4096 x 4096, 16 blocks, 256 tokens 139 and 99, 300 tokens
+    // 146 and 189).  In 8257 cases that were timed with every kernel the one taken is 0.1 % slower than the fastest on average;
+    // k_batch is up to 10 % slower than another in its place.
+    const bool tile_ok = a.batch > 32 && tile_fits(p);
+    const double tf = a.batch <= kFusedMaxBatch && fused_fits(p) ? fused_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
+    const double tb = a.batch <= 1024 && batch_fits(p) ? batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
+    // beyond 64 tokens also where the weight-tile kernel cannot hold the stack: k_panel is slower than k_tile's estimate
+    const double tt = tile_ok || a.batch > kFusedMaxBatch ? tile_launch_us(p.out, p.in, p.batch, p.n_loaded) : 1e30;
+    if (tb < tf && tb < tt) return launch_batch(p, st);
+    if (tf < tt) return launch_fused(p, st);
+    if (tile_ok) return launch_tile(p, st);
     if (a.batch > 256) return launch_panel_t<4>(p, st);
     if (a.batch > 128) return launch_panel_t<2>(p, st);
     return launch_panel_t<1>(p, st);
