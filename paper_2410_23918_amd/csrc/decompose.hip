@@ -466,11 +466,10 @@ __global__ __launch_bounds__(256) void k_dc_orth(const double* Gpart, int parts,
     }
 }
 
-// Q[r][c] = sum_i Y[r][i] T[i][c], c < NC; fp32 or fp16 (round to nearest even) output
-template <int NC, bool HALF_OUT>
-__global__ __launch_bounds__(256) void k_dc_apply(const float* Y, const float* T, void* Qv, int m) {
-    __shared__ float Ts[kL][NC];
-    for (int idx = threadIdx.x; idx < kL * NC; idx += 256) Ts[idx / NC][idx % NC] = T[idx];
+// Q[r][c] = sum_i Y[r][i] T[i][c], c < kRank, rounded to fp16 (nearest even)
+__global__ __launch_bounds__(256) void k_dc_apply(const float* Y, const float* T, __half* Q, int m) {
+    __shared__ float Ts[kL][kRank];
+    for (int idx = threadIdx.x; idx < kL * kRank; idx += 256) Ts[idx / kRank][idx % kRank] = T[idx];
     __syncthreads();
     const int r = blockIdx.x * 256 + threadIdx.x;
     if (r >= m) return;
@@ -480,22 +479,15 @@ __global__ __launch_bounds__(256) void k_dc_apply(const float* Y, const float* T
         const float4 v = *reinterpret_cast<const float4*>(Y + size_t(r) * kL + 4 * q);
         y[4 * q] = v.x; y[4 * q + 1] = v.y; y[4 * q + 2] = v.z; y[4 * q + 3] = v.w;
     }
-    float o[NC];
+    float o[kRank];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) o[c] = 0.f;
+    for (int c = 0; c < kRank; ++c) o[c] = 0.f;
 #pragma unroll
     for (int i = 0; i < kL; ++i)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) o[c] = fmaf(y[i], Ts[i][c], o[c]);
-    if (HALF_OUT) {
-        __half* Q = static_cast<__half*>(Qv);
+        for (int c = 0; c < kRank; ++c) o[c] = fmaf(y[i], Ts[i][c], o[c]);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) Q[size_t(r) * NC + c] = __float2half_rn(o[c]);
-    } else {
-        float* Q = static_cast<float*>(Qv);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) Q[size_t(r) * NC + c] = o[c];
-    }
+    for (int c = 0; c < kRank; ++c) Q[size_t(r) * kRank + c] = __float2half_rn(o[c]);
 }
 
 // 1 / sqrt(x) for x > 0 in fp64: the hardware's estimate and two Newton steps
@@ -706,8 +698,8 @@ hipError_t launch_decompose(const float* W, const float* s, int out, int in, int
                            (chunks + slices - 1) / slices);
         gram(P, slices, false, Z, in);
         hipLaunchKernelGGL(k_dc_ritz, dim3(1), dim3(kRitzThreads), 0, st, G, gram_parts(in), Tu, Tv, kRank);
-        hipLaunchKernelGGL((k_dc_apply<kRank, true>), dim3((out + 255) / 256), dim3(256), 0, st, Q, Tu, Ui, out);
-        hipLaunchKernelGGL((k_dc_apply<kRank, true>), dim3((in + 255) / 256), dim3(256), 0, st, Z, Tv, Vi, in);
+        hipLaunchKernelGGL(k_dc_apply, dim3((out + 255) / 256), dim3(256), 0, st, Q, Tu, Ui, out);
+        hipLaunchKernelGGL(k_dc_apply, dim3((in + 255) / 256), dim3(256), 0, st, Z, Tv, Vi, in);
     }
     return hipGetLastError();
 }

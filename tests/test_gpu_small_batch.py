@@ -1,7 +1,7 @@
 """The batch kernel for up to 64 tokens at the edges of its tiling: row counts that end inside a workgroup, chunk counts that
 leave teams without a chunk, both sides of its 16- and 32-token groups, with and without a column split (whose partial
-tiles meet in the workspace).  45 blocks: more than the other small-batch kernel holds, so this one runs.  Every
-element of y in fp32."""
+tiles meet in the workspace).  45 blocks: more than the other small-batch kernel holds, so this one runs; the cases of one
+and two blocks are among those that are seen to take it.  Every element of y in fp32."""
 import numpy as np
 import pytest
 
@@ -16,6 +16,22 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("batch", [2, 16, 17, 32, 33, 64])
 def test_every_output_of_the_small_batch_kernel(out, inn, batch):
     check(out, inn, 45, batch)
+
+
+@pytest.mark.parametrize("inn,batch", [(8192, 2), (8192, 33), (7168, 16), (5120, 17)])
+def test_many_column_ranges(inn, batch):
+    """32, 28 and 20 column chunks in eight, seven and five ranges: the last workgroup to arrive adds that many partial tiles."""
+    check(32, inn, 45, batch)
+
+
+# one block (a step of the ring, then the activations and the next scales at once) and two, in one and two chunk iterations
+FEW_BLOCKS = [(448, 256, 1, 16), (96, 1024, 1, 32), (64, 512, 1, 24), (512, 1024, 2, 8), (512, 1024, 2, 24), (9056, 2048, 1, 20),
+              (14336, 2048, 2, 8), (9056, 1280, 2, 60)]
+
+
+@pytest.mark.parametrize("out,inn,n,batch", FEW_BLOCKS)
+def test_few_blocks(out, inn, n, batch):
+    check(out, inn, n, batch)
 
 
 @pytest.mark.parametrize("out,inn,n", [
@@ -43,6 +59,7 @@ def test_weights_over_their_scales_out_of_fp16_range(batch):
     (384, 1024, 8, 3, True),      # eight steps, two column ranges: 12.5, 14.2
     (448, 256, 1, 4, False),      # one step: 8.0, 6.7
     (4096, 4096, 16, 16, False),
+    *((*c, False) for c in FEW_BLOCKS),
 ])
 def test_the_kernel_taken_for_few_steps(out, inn, n, batch, fused):
     """k_fused rounds x/s to fp16, k_batch W'/s: with weights n, scales 7 and activations 7 the one is exact, the other is not."""
