@@ -222,8 +222,9 @@ def batch_table(B, torch, dev, n):
             us = timed(lambda: ps.linear_batched(x, n, y=y), 10 if b <= 64 else 3)
             tf = 2.0 * o * i * b / us / 1e6
             kern = names[B.choose_kernel(o, i, n, max(batches), b, n)] or (
-                "k_fused" if b <= 32 else "k_fused or k_xpack + k_tile, the launcher's estimate" if b <= 64
-                else "k_xpack + k_tile")
+                "k_batch or k_fused, the launcher's estimate" if b <= 32
+                else "k_batch, k_fused or k_xpack + k_tile, the launcher's estimate" if b <= 64
+                else "k_batch or k_xpack + k_tile, the launcher's estimate" if b <= 1024 else "k_xpack + k_tile")
             log(f"[bench] batch path {o}x{i} n={n} tokens={b} ({kern}): {us:.1f} us, {tf:.1f} useful TFLOP/s")
             rows.append({"shape": f"{o}x{i}", "tokens": b, "kernel": kern, "us": round(us, 1),
                          "useful_TFLOPs": round(tf, 2)})
@@ -241,7 +242,7 @@ def batch_table(B, torch, dev, n):
                 ur = timed(lambda: ps.restore_weight(n, wd), 3)
                 tfm = 2.0 * o * i * b / um / 1e6
                 diff = (y2.float() - y.float()).abs().max().item() / y.float().abs().max().item()
-                log(f"[bench] materialising path {o}x{i} n={n} tokens={b} (k_tile<restore> + k_gemm): "
+                log(f"[bench] materialising path {o}x{i} n={n} tokens={b} (k_restore + k_gemm): "
                     f"{um:.1f} us ({ur:.1f} us of it restoring), {tfm:.1f} useful TFLOP/s; "
                     f"max |difference| to the batch kernel / max |y| = {diff:.1e}")
                 rows.append({"shape": f"{o}x{i}", "tokens": b, "kernel": "restore + k_gemm", "us": round(um, 1),
@@ -265,10 +266,10 @@ def batch_table(B, torch, dev, n):
 
 def decompose_table(B, torch, dev, iterations=16):
     """The decomposition on the device (bitstack_decompose): time per residual block at the 4096x4096
-    and 14336x4096 shapes.  Bytes per block as the kernels move them: the fp32 residual is read by
-    the sign packing, by the conversion to bf16 (which writes |R| and its transpose), by the
-    Rayleigh-Ritz product, and read and written by the residual update (5 x 4 bytes per element);
-    the 2 * iterations + 1 tall products of the power rounds read one bf16 copy each."""
+    and 14336x4096 shapes.  Bytes per block as the kernels move them: the fp32 residual (the first time the
+    weight) is read and written by the residual pass, which also writes |R| and its transpose as bf16, and read by
+    the Rayleigh-Ritz product (3 x 4 bytes per element); the 2 * iterations + 1 tall products of the power
+    rounds read one bf16 copy each."""
     from workloads import synth as W
     rows = []
     for cfg, (o, i), nblk in ((2, (4096, 4096), 4), (3, (14336, 4096), 2)):
@@ -282,7 +283,7 @@ def decompose_table(B, torch, dev, iterations=16):
         t0 = time.perf_counter()
         sw, U, V = B.decompose(Wd, s, nblk, iterations=iterations)   # synchronises before returning
         ms = (time.perf_counter() - t0) * 1e3 / nblk
-        bytes_per_block = (5 * 4 + (2 + 2 * iterations + 1) * 2) * o * i
+        bytes_per_block = (3 * 4 + (2 + 2 * iterations + 1) * 2) * o * i
         gbs = bytes_per_block / ms / 1e6
         log(f"[bench] decomposition on the device {o}x{i}, {iterations} iterations: {ms:.1f} ms per block, "
             f"{gbs:.0f} GB/s of residual traffic, fp32 and bf16 passes ({gbs / HBM_PEAK_GBS * 100:.1f}% of 8 TB/s)")

@@ -78,7 +78,7 @@ inline KParams make_params(const LaunchArgs& a) {
     return p;
 }
 
-// batch kernel for up to 64 tokens (batch.hip)
+// batch kernel for 2 to 1024 tokens, in groups of 64 (batch.hip)
 bool batch_fits(const KParams& p);
 hipError_t launch_batch(const KParams& p, hipStream_t st);
 

@@ -158,8 +158,8 @@ static int restore_groups_per_wg(int groups, int chunks) {
 }
 
 // The restoring part of the materialising path in the choice of kernel (microseconds): rounds of 256 workgroups of 64 rows x
-// a power of two of column slices, as the kernel before k_restore had them.  k_restore is 1.4-1.9 times faster, but the
-// crossovers that follow from this estimate are what bitstack_choose_kernel promises (tests/test_abi_host.py states them).
+// a power of two of column slices, as the kernel before k_restore had them.  k_restore is 1.0 (one block of a large matrix) to 2.2
+// times faster, but the crossovers that follow from this estimate are what tests/test_abi_host.py states.
 double restore_time_us(int rows, int in, int n_loaded) {
     const int iters = (in / kChunkCols + 1) / 2, row_wgs = (rows + 63) / 64;
     double best = 0.0;
@@ -170,8 +170,8 @@ double restore_time_us(int rows, int in, int n_loaded) {
     return best;
 }
 
-// restored blocks are limited by what the weight-tile kernel holds, whose place this path takes; the kernel reaches the
-// loaded blocks through one buffer descriptor with 32-bit offsets
+// The block count is what bitstack_restore_max_blocks has always answered (the kernel before k_restore kept every block's U in LDS);
+// k_restore has no such limit.  It reaches the loaded blocks through one buffer descriptor with 32-bit offsets.
 int restore_max_blocks() { return kRestoreMaxBlocks; }
 bool restore_fits(size_t block_stride, int n_loaded) {
     return n_loaded <= kRestoreMaxBlocks && size_t(n_loaded) * block_stride < (size_t(1) << 32);
