@@ -18,7 +18,7 @@ def test_every_output_of_the_small_batch_kernel(out, inn, batch):
     check(out, inn, 45, batch)
 
 
-@pytest.mark.parametrize("inn,batch", [(8192, 2), (8192, 33), (7168, 16), (5120, 17)])
+@pytest.mark.parametrize("inn,batch", [(8192, 1), (8192, 2), (8192, 33), (7168, 16), (5120, 17)])
 def test_many_column_ranges(inn, batch):
     """32, 28 and 20 column chunks in eight, seven and five ranges: the last workgroup to arrive adds that many partial tiles."""
     check(32, inn, 45, batch)
