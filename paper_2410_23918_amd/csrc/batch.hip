@@ -44,8 +44,8 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     constexpr unsigned kStep = TEAMS * L::kBytes;
     // an activation step brings TOK tokens x kPieces columns of eight per half, 8 KiB per team
     constexpr int kPieces = 256 / TOK, kPerGroup = 16 / kPieces, kXSteps = GROUPS * kPerGroup, kXRowBytes = kPieces * 32;
-    // behind the ring: 1/s [2][TEAMS][256], 128 ones, a flag
-    constexpr unsigned kRsLds = kRing * kStep, kOnesLds = kRsLds + 2 * TEAMS * 1024, kFlagLds = kOnesLds + 512;
+    constexpr unsigned kRsLds = kRing * kStep;   // [2][TEAMS][256] floats
+    constexpr unsigned kFlagLds = 8 * 4096;   // two words behind the partial tiles, in the ring when it is idle
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -114,23 +114,21 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
         }
     };
 
-    // the lane's half, made anew: kept, it would cost the loop a register it does not have
-    auto own_half = [&]() {
-        int l = lane;
-        asm volatile("" : "+v"(l));
-        return l >> 5;
+    // the thread's number, made anew: what is derived from it outside the loop would cost the loop registers it does not have
+    auto own_id = [&]() {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        return t;
     };
 
     v16f yacc[GROUPS];
     UnitAcc acc;
     StepInputs in;
     unsigned buf = 0;
-    if (tid < 128) write_lds(lds0 + kOnesLds + unsigned(tid) * 4u, 1.0f);
-    if (tid == 0) write_lds(lds0 + kFlagLds, 0u);
 
     auto accumulate = [&](auto on_x) __attribute__((always_inline)) {
         constexpr bool kScaleX = decltype(on_x)::value;
-        const int hl = own_half();
+        const int hl = (own_id() >> 5) & 1;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) yacc[g] = zero16();
         request_rs(0);
@@ -156,20 +154,20 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
             // (what the last step read ahead was activations: read again below)
             const bool valid = c_lo + it * TEAMS + team < c_hi;   // uniform over the wavefront
             const unsigned rs_rd = lds0 + kRsLds + unsigned(it & 1) * (TEAMS * 1024) + unsigned(team) * 1024u + unsigned(hl) * 512u;
-            const unsigned b_rd = kScaleX ? lds0 + kOnesLds : rs_rd;
             v4i b[16];   // W' diag(1/s) of the unit as B operands: step e = columns 8 e .. 8 e + 7 of both halves
             v4f r[2][2];
             auto scale = [&](auto e) __attribute__((always_inline)) {
                 constexpr int E = decltype(e)::value;
                 v4f(&q)[2] = r[E & 1];
-                if constexpr (E < 15) read_scales(r[(E + 1) & 1], b_rd, E + 1);
+                if constexpr (kScaleX) q[0] = q[1] = v4f{1.0f, 1.0f, 1.0f, 1.0f};
+                else if constexpr (E < 15) read_scales(r[(E + 1) & 1], rs_rd, E + 1);
 #pragma unroll
                 for (int t = 0; t < 8; t += 2)
                     b[E][t >> 1] = scaled_pair(acc[t][E >> 2][E & 3], acc[t + 1][E >> 2][E & 3], q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
                 asm volatile("" : "+v"(b[E]));   // made here: put off to the products, it would keep the scales in registers until then
                 __builtin_amdgcn_sched_barrier(0);
             };
-            read_scales(r[0], b_rd, 0);
+            if constexpr (!kScaleX) read_scales(r[0], rs_rd, 0);
 #define BS_SCALE(E) scale(std::integral_constant<int, E>{});
             BS_SCALE(0) BS_SCALE(1) BS_SCALE(2) BS_SCALE(3) BS_SCALE(4) BS_SCALE(5) BS_SCALE(6) BS_SCALE(7)
             BS_SCALE(8) BS_SCALE(9) BS_SCALE(10) BS_SCALE(11) BS_SCALE(12) BS_SCALE(13) BS_SCALE(14) BS_SCALE(15)
@@ -215,58 +213,62 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
         }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     };
-    accumulate(std::false_type{});
-    // A weight over its scale need not be an fp16 number where the weight and the activation over the scale are (a channel
-    // scaled far down whose activations are tiny, or zero): then y is not finite, and the workgroup starts over with 1/s on the
-    // activations.  Not so in the first place: large scales would take the activations out of fp16's range.
-    float rest = 0.0f;   // 0 * y: NaN for infinities and NaN
-#pragma unroll
-    for (int g = 0; g < GROUPS; ++g)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) rest = __builtin_fmaf(yacc[g][v], 0.0f, rest);
-    if (rest != 0.0f) write_lds(lds0 + kFlagLds, 1u);
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(int(read_lds<unsigned>(lds0 + kFlagLds)))) {
-        qi = qit = 0;
-        qbuf = qoff = buf = 0u;
-        accumulate(std::true_type{});
-        __syncthreads();
-    }
 
     // the teams' partial tiles meet in LDS; D[i = token][n = row]: lane (row ln), register v holds token
     // 8 (v / 4) + 4 hl + v % 4 of the group
     float* const red = reinterpret_cast<float*>(smem);   // [wave][16][64]
     float* const mine = p.part + size_t(blockIdx.y) * p.batch * p.out;
+    auto store = [&]() __attribute__((always_inline)) {
+        const int tid = own_id(), lane = tid & 63;
+        float rest = 0.0f;   // 0 * y: NaN for infinities and NaN
 #pragma unroll
-    for (int g = 0; g < GROUPS; ++g) {
-        if (g) __syncthreads();
+        for (int g = 0; g < GROUPS; ++g) {
+            __syncthreads();
+            if (g == 0 && tid == 0) write_lds(lds0 + kFlagLds, 0u);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = yacc[g][v];
-        __syncthreads();
-        // thread = (row, token): consecutive lanes take consecutive rows
-        for (int o = tid; o < kRows * TOK; o += 512) {
-            const int row = o & (kRows - 1), t = o / kRows;   // token of the group
-            const int v = (t >> 3) * 4 + (t & 3), l = ((t >> 2) & 1) * 32 + (row & 31);
-            float sum = 0.0f;
+            for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = yacc[g][v];
+            __syncthreads();
+            // thread = (row, token): consecutive lanes take consecutive rows
+            for (int o = tid; o < kRows * TOK; o += 512) {
+                const int row = o & (kRows - 1), t = o / kRows;   // token of the group
+                const int v = (t >> 3) * 4 + (t & 3), l = ((t >> 2) & 1) * 32 + (row & 31);
+                float sum = 0.0f;
 #pragma unroll
-            for (int w = 0; w < TEAMS; ++w) sum += red[((w * RT + (row >> 5)) * 16 + v) * 64 + l];
-            const int tok = tok0 + g * TOK + t, r = int(blockIdx.x) * kRows + row;
-            if (tok < tok_end && r < p.out) {
-                if (ksplit == 1)
-                    store_y(p, size_t(tok) * p.out + r, sum);
-                else   // write-through: the reader may sit on another XCD
-                    __hip_atomic_store(mine + size_t(tok) * p.out + r, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (int w = 0; w < TEAMS; ++w) sum += red[((w * RT + (row >> 5)) * 16 + v) * 64 + l];
+                const int tok = tok0 + g * TOK + t, r = int(blockIdx.x) * kRows + row;
+                if (tok < tok_end && r < p.out) {
+                    rest = __builtin_fmaf(sum, 0.0f, rest);
+                    if (ksplit == 1)
+                        store_y(p, size_t(tok) * p.out + r, sum);
+                    else   // write-through: the reader may sit on another XCD
+                        __hip_atomic_store(mine + size_t(tok) * p.out + r, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
         }
+        if (rest != 0.0f) write_lds(lds0 + kFlagLds, 1u);
+        if (ksplit > 1) __builtin_amdgcn_s_waitcnt(0x0F70);   // each wavefront's stores are acknowledged before it reaches the barrier
+        __syncthreads();
+    };
+
+    accumulate(std::false_type{});
+    store();
+    // A weight over its scale need not be an fp16 number where the weight and the activation over the scale are (a channel
+    // scaled far down whose activations are tiny, or zero): then y is not finite, and the workgroup starts over with 1/s on the
+    // activations, its stores replaced by the same threads.  Not so in the first place: large scales would take the activations out
+    // of fp16's range.  The question costs 0.2-0.3 us a call (448 x 256, 1 block, 4 tokens: 5.9 -> 6.2).
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(int(read_lds<unsigned>(lds0 + kFlagLds))), 0)) {
+        __syncthreads();   // everybody has seen it
+        qi = qit = 0;
+        qbuf = qoff = buf = 0u;
+        accumulate(std::true_type{});
+        store();
     }
     if (ksplit == 1) return;
 
     // column split: the last workgroup of this row group adds the ksplit partial tiles in a fixed order and stores y (same
     // protocol as the decode kernel: write-through stores, one relaxed agent-scope counter after a barrier, agent-scope
     // loads by the last one)
-    unsigned* const flag = reinterpret_cast<unsigned*>(smem + 8 * 4096);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // each wavefront's stores are acknowledged before it reaches the barrier
-    __syncthreads();
+    unsigned* const flag = reinterpret_cast<unsigned*>(smem + kFlagLds + 4);
     unsigned* const ctr = p.ctr + blockIdx.z * gridDim.x + blockIdx.x;
     if (tid == 0) {
         const unsigned old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -322,7 +324,7 @@ static int batch_split(int out, int in, int batch, int part_slots) {
 
 template <int TOK, int GROUPS>
 static hipError_t launch_batch_t(KParams p, hipStream_t st) {
-    const size_t smem = size_t(3) * 4 * StepLayout<2>::kBytes + 2 * 4 * kChunkCols * 4 + 512 + 16;
+    const size_t smem = size_t(3) * 4 * StepLayout<2>::kBytes + 2 * 4 * kChunkCols * 4;
     static std::atomic<bool> attr_set{false};   // setting the attribute twice is harmless
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch<TOK, GROUPS>),
