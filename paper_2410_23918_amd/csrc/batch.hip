@@ -71,7 +71,6 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
     const unsigned s_rd = lds0 + unsigned(wave) * L::kWaveBytes + unsigned(lane) * 16u;
     // x in LDS: a token's 2 kPieces 16-byte pieces in a row, piece j of token t at position j ^ (t & 15)
     const unsigned x_rd = lds0 + unsigned(team) * L::kBytes + unsigned(ln % TOK) * unsigned(kXRowBytes);
-    const v4h ident = accumulate_matrix(unsigned(lane));
 
     // steps of a chunk: its n blocks, then kXSteps steps of activations
     int qi = 0, qit = 0;
@@ -136,21 +135,19 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
         request();
         loads_barrier<0>();
         request();
-        {
-            FirstReads first;
-            begin_reads<RT>(in, first, v_rd, s_rd);
-            take_reads(in, first);
-        }
+        begin_reads<RT>(in, v_rd, s_rd);
+        in.last = in.s;
         for (int it = 0; it < iters; ++it) {
             auto step = [&](auto first) __attribute__((always_inline)) {
                 loads_barrier<0>();
                 request();
                 const unsigned nb = next_buf(buf);
-                add_block<decltype(first)::value, RT>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
+                add_block<decltype(first)::value, RT>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb);
                 buf = nb;
             };
             step(std::true_type{});
             for (int i = 1; i < n; ++i) step(std::false_type{});
+            finish_unit(acc, in);
             // (what the last step read ahead was activations: read again below)
             const bool valid = c_lo + it * TEAMS + team < c_hi;   // uniform over the wavefront
             const unsigned rs_rd = lds0 + kRsLds + unsigned(it & 1) * (TEAMS * 1024) + unsigned(team) * 1024u + unsigned(hl) * 512u;
@@ -163,7 +160,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
                 else if constexpr (E < 15) read_scales(r[(E + 1) & 1], rs_rd, E + 1);
 #pragma unroll
                 for (int t = 0; t < 8; t += 2)
-                    b[E][t >> 1] = scaled_pair(acc[t][E >> 2][E & 3], acc[t + 1][E >> 2][E & 3], q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
+                    b[E][t >> 1] = scaled_pair(acc[t][E], acc[t + 1][E], q[t >> 2][t & 3], q[t >> 2][(t & 3) + 1]);
                 asm volatile("" : "+v"(b[E]));   // made here: put off to the products, it would keep the scales in registers until then
                 __builtin_amdgcn_sched_barrier(0);
             };
@@ -172,7 +169,6 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
             BS_SCALE(0) BS_SCALE(1) BS_SCALE(2) BS_SCALE(3) BS_SCALE(4) BS_SCALE(5) BS_SCALE(6) BS_SCALE(7)
             BS_SCALE(8) BS_SCALE(9) BS_SCALE(10) BS_SCALE(11) BS_SCALE(12) BS_SCALE(13) BS_SCALE(14) BS_SCALE(15)
 #undef BS_SCALE
-            FirstReads first;
 #pragma unroll
             for (int xs = 0; xs < kXSteps; ++xs) {
                 const int g = xs / kPerGroup, e0 = xs % kPerGroup * kPieces;
@@ -180,7 +176,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
                 if (xs == 0) request_rs(it + 1);
                 request();
                 const unsigned nb = next_buf(buf);
-                if (xs == kXSteps - 1) begin_reads<RT>(in, first, v_rd + nb, s_rd + nb);   // the next chunk's first step
+                if (xs == kXSteps - 1) begin_reads<RT>(in, v_rd + nb, s_rd + nb);   // the next chunk's first step
 #pragma unroll
                 for (int eq = 0; eq < kPieces / 4; ++eq) {
                     v4i a[4];
@@ -209,7 +205,6 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
                 }
                 buf = nb;
             }
-            take_reads(in, first);
         }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     };

@@ -10,15 +10,16 @@
 //     per byte e and half) one v_mfma_f32_32x32x16_f16 over the 16 ranks.  The A operand's rows are the class's
 //     columns, ordered so that lane (g, j) receives, in register e, column (g, e, t) of row j: the columns of its own
 //     sign words, in the order of their bytes;
-//   * sign: registers e and e + 2 of a word sit 16 bits apart in it.  They are packed to a pair of fp16
-//     (convert-pack), and one three-input bit operation flips the pair's signs by bits 15 and 31 of a copy
-//     of the word that moves up by one bit per class (two words per instruction: v_lshl_add_u64; the bit that
-//     crosses from one word into the other stays below bit 8);
-//   * sum: v_mfma_f32_4x4x4_16b_f16 with a permutation matrix as A adds the four fp16 values a lane holds to
-//     four of its own fp32 accumulators: 256 elements in 8 cycles, where a 32x32x16 product with an identity
-//     takes 32 cycles for 512.
-// Registers only, that is 56 ns per 32 x 32 tile, block and SIMD (the former scheme with a shift per pair and two
-// 32x32x16 identity products: 77).
+//   * sign and sum: s_i W_i = s_i W_{i-1} + M_i with M_i the magnitudes and s_i s_i = 1, so the accumulator holds s_i times the sum.
+//     Before a block's product its sign bits are flipped where s_i and s_{i-1} differ, and the product adds M_i to it as its third
+//     operand: one vector instruction per element and block, no conversion, fp32 throughout.  A flip is an exclusive-or of the
+//     register's top byte with a byte of a copy of the word in which the class's bits stand at bit 7 of the bytes and the others are
+//     cleared (v_xor_b32_sdwa); the copy moves up by one bit per class, two words per instruction (v_lshl_add_u64: the bit that
+//     crosses from one word into the other stays below bit 7).  After the last block s_n is taken off.
+// Registers only, that is 48 ns per 32 x 32 tile, block and SIMD, bound by the issue of vector instructions (22 per tile, most of them
+// four cycles; the matrix product takes one slot more).  Rounding the signed magnitudes to fp16 pairs, flipping two signs at
+// a time and summing by v_mfma_f32_4x4x4_16b_f16 takes as many slots, 50 ns, but 24 registers more; a shift per pair and two 32x32x16
+// identity products 77.
 //
 // V needs its 16 x 16 pieces (16 ranks x 16 columns of one half and class) turned from rank rows, as they lie in
 // memory, into "8 ranks of one column".  The V panel goes to LDS without passing through registers
@@ -168,23 +169,6 @@ __device__ __forceinline__ unsigned u_lane_offset(unsigned off_u, unsigned row_t
     return off_u + (row_tile * kTileRows + (lane & 31)) * 32u + (lane >> 5) * 16u - unsigned(StepLayout<RT>::kUOffset % 4096);
 }
 
-// A operand of the accumulating product: output row i of a lane's group takes slot 0, 2, 1, 3 (the pairs hold
-// bytes (0, 2) and (1, 3) of a word)
-__device__ __forceinline__ v4h accumulate_matrix(unsigned lane) {
-    const unsigned i = lane & 3, slot = i == 1 ? 2u : i == 2 ? 1u : i;
-    v4h a;
-#pragma unroll
-    for (unsigned s = 0; s < 4; ++s) a[s] = _Float16(s == slot ? 1.0f : 0.0f);
-    return a;
-}
-
-__device__ __forceinline__ unsigned signed_pair(float a, float b, unsigned bits) {
-    v2h c;
-    c[0] = _Float16(a);
-    c[1] = _Float16(b);
-    return __builtin_bit_cast(unsigned, c) ^ (~bits & 0x80008000u);   // a cleared bit marks a negative sign
-}
-
 __device__ __forceinline__ v16f zero16() {
     v16f z;
 #pragma unroll
@@ -205,114 +189,151 @@ __device__ __forceinline__ int scaled_pair(float a, float b, float ra, float rb)
     return __builtin_bit_cast(int, c);
 }
 
-// acc[t][w][b]: column 128 g + 32 w + 8 b + t of row lane % 32, g = lane / 32
-typedef v4f UnitAcc[kClasses][4];
+// acc[t][4 w + b]: column 128 g + 32 w + 8 b + t of row lane % 32, g = lane / 32; between blocks times the sign of the block
+// added last (finish_unit takes it off)
+typedef v16f UnitAcc[kClasses];
 
-// What one step hands to the next: its inputs come from LDS, and the first reads and the first magnitude product of a
-// step are issued inside the step before, so that no step starts with an empty pipeline.
-struct StepInputs {
-    v4i u;          // U: row lane % 32, ranks 8 (lane / 32) on
-    v2u s[2];       // sign words
-    VFrag f;        // fragment of class 6
-    v16f m;         // magnitudes of class 7
+// Sign words of a lane: 128 columns of its row
+struct SignWords {
+    v2u w[2];
 };
 
-__device__ __forceinline__ v16f magnitude(const VFrag& f, const v4i& u) {
+// What one step hands to the next: its inputs come from LDS, and the first reads of a step are issued inside the step
+// before, so that no step starts with an empty pipeline.
+struct StepInputs {
+    v4i u;             // U: row lane % 32, ranks 8 (lane / 32) on
+    SignWords s;       // signs of the step's block
+    SignWords last;    // signs of the block before it
+    VFrag f7, f6;      // fragments of the first two classes
+};
+
+__device__ __forceinline__ v16f magnitude(const VFrag& f, const v4i& u, const v16f& c) {
     struct {
         v2u a, b;
     } both = {f.q0, f.q1};
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, both), __builtin_bit_cast(v8h, u), zero16(), 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, both), __builtin_bit_cast(v8h, u), c, 0, 0, 0);
 }
 
-// The first reads of a step that no step precedes.  vaddr: LDS byte address of its V panel + v_read_offset; saddr: of the
-// lane's 16 bytes of signs (its 16 bytes of U are kUOffset further on)
-struct FirstReads {
-    VFrag f7;
-    v4i signs;
-};
+// The first reads of a step.  vaddr: LDS byte address of its V panel + v_read_offset; saddr: of the lane's 16 bytes of signs (its
+// 16 bytes of U are kUOffset further on)
 template <int RT>
-__device__ __forceinline__ void begin_reads(StepInputs& in, FirstReads& r, unsigned vaddr, unsigned saddr) {
-    r.f7 = read_frag<7, RT>(vaddr);
+__device__ __forceinline__ void begin_reads(StepInputs& in, unsigned vaddr, unsigned saddr) {
+    in.f7 = read_frag<7, RT>(vaddr);
     in.u = read_lds<v4i>(saddr + StepLayout<RT>::kUOffset);
-    r.signs = read_lds<v4i>(saddr);
-    in.f = read_frag<6, RT>(vaddr);
+    const v4i signs = read_lds<v4i>(saddr);
+    in.f6 = read_frag<6, RT>(vaddr);
+    in.s.w[0] = v2u{unsigned(signs[0]), unsigned(signs[1])};
+    in.s.w[1] = v2u{unsigned(signs[2]), unsigned(signs[3])};
 }
-// the first magnitude product from them
-__device__ __forceinline__ void take_reads(StepInputs& in, const FirstReads& r) {
-    in.m = magnitude(r.f7, in.u);
-    in.s[0] = v2u{unsigned(r.signs[0]), unsigned(r.signs[1])};
-    in.s[1] = v2u{unsigned(r.signs[2]), unsigned(r.signs[3])};
+
+// a's sign bit flipped where bit 7 of byte B of m is set (B < 3: the other bits of the byte are clear): the top byte of the
+// register, exclusive-or with that byte; byte 3 is where it has to be already (a three-input operation with vector operands
+// takes two thirds of the time).  The compiler does not know that these are vector instructions: whoever uses them keeps them
+// sixteen instructions from a matrix product that writes a and two from one that reads it.
+template <int B>
+__device__ __forceinline__ float flip_sign(float a, unsigned m, unsigned top_bit) {
+    static_assert(B >= 0 && B < 4, "");
+    if constexpr (B == 0)
+        asm("v_xor_b32_sdwa %0, %0, %1 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_0" : "+v"(a) : "v"(m));
+    else if constexpr (B == 1)
+        asm("v_xor_b32_sdwa %0, %0, %1 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_1" : "+v"(a) : "v"(m));
+    else if constexpr (B == 2)
+        asm("v_xor_b32_sdwa %0, %0, %1 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_2" : "+v"(a) : "v"(m));
+    else
+        asm("v_bitop3_b32 %0, %0, %1, %2 bitop3:0x78" : "+v"(a) : "v"(m), "v"(top_bit));   // a ^ (m & top_bit)
+    return a;
+}
+
+// The sixteen values of the class whose bits stand at bit 7 of the bytes of d
+struct FlipMasks {
+    unsigned w[4];
+};
+__device__ __forceinline__ FlipMasks flip_masks(const SignWords& d) {
+    return FlipMasks{{d.w[0][0] & 0x80808080u, d.w[0][1] & 0x80808080u, d.w[1][0] & 0x80808080u, d.w[1][1] & 0x80808080u}};
+}
+__device__ __forceinline__ void flip_class(v16f& a, const FlipMasks& m) {
+    unsigned top = 0x80000000u;
+    asm("" : "+v"(top));   // a vector register
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        a[4 * w + 0] = flip_sign<0>(a[4 * w + 0], m.w[w], top);
+        a[4 * w + 1] = flip_sign<1>(a[4 * w + 1], m.w[w], top);
+        a[4 * w + 2] = flip_sign<2>(a[4 * w + 2], m.w[w], top);
+        a[4 * w + 3] = flip_sign<3>(a[4 * w + 3], m.w[w], top);
+    }
+}
+// the next lower class to bit 7 (the bit that crosses from one word into the other stays below it)
+__device__ __forceinline__ void next_class(SignWords& d) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        unsigned long long v = __builtin_bit_cast(unsigned long long, d.w[k]);
+        asm("v_lshl_add_u64 %0, %0, 1, 0" : "+v"(v));
+        d.w[k] = __builtin_bit_cast(v2u, v);
+    }
 }
 
 // One block onto the wavefront's unit.  vnext, snext: addresses of the next step.  FIRST: the accumulators start
-// from zero.  A SIMD issues one vector or matrix instruction per four cycles, and with two wavefronts to it a
-// wavefront issues one instruction of any kind per eight: what counts is the number of instructions.
+// from zero.  A SIMD issues one vector or matrix instruction per four cycles: what counts is the number of instructions, 23
+// per class.
 template <bool FIRST, int RT>
-__device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned vaddr, unsigned vnext, unsigned snext, v4h ident) {
-    typedef unsigned long long u64;
-    // per pair of words, for the class at hand: bytes 1, 3 (hi) and 0, 2 (lo) of each word at its bits 15, 31
-    u64 hi[2], lo[2];
+__device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned vaddr, unsigned vnext, unsigned snext) {
+    SignWords d;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        hi[k] = __builtin_bit_cast(u64, in.s[k]);
-        asm("v_lshlrev_b64 %0, 8, %1" : "=v"(lo[k]) : "v"(hi[k]));
+    for (int k = 0; k < 2; ++k) d.w[k] = in.s.w[k] ^ in.last.w[k];
+    in.last = in.s;
+    const v4i u = in.u;
+    // a class's fragment is requested two classes ahead; its product is issued after the signs of the next class have been
+    // made ready, six instructions after its last flip
+    VFrag f[kClasses];
+    f[7] = in.f7;
+    f[6] = in.f6;
+#define BS_CLASS(T)                                                                        \
+    {                                                                                      \
+        if constexpr (T >= 2) f[T >= 2 ? T - 2 : 0] = read_frag<(T >= 2 ? T - 2 : 0), RT>(vaddr); \
+        if constexpr (T < 2) {                                                             \
+            if constexpr (T == 1) begin_reads<RT>(in, vnext, snext);                       \
+        }                                                                                  \
+        if constexpr (FIRST) {                                                             \
+            acc[T] = magnitude(f[T], u, zero16());                                         \
+        } else {                                                                           \
+            const FlipMasks m = flip_masks(d);                                             \
+            if constexpr (T > 0) next_class(d);                                            \
+            __builtin_amdgcn_sched_barrier(0);                                             \
+            if constexpr (T < 7) acc[T < 7 ? T + 1 : 7] = magnitude(f[T < 7 ? T + 1 : 7], u, acc[T < 7 ? T + 1 : 7]); \
+            flip_class(acc[T], m);                                                         \
+        }                                                                                  \
+        __builtin_amdgcn_sched_barrier(0);                                                 \
     }
-    auto apply = [&](v4f (&a)[4], const v16f& mg, bool more) __attribute__((always_inline)) {
-        v2u p[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const int sh = (w & 1) * 32;
-            p[w][0] = signed_pair(mg[4 * w], mg[4 * w + 2], unsigned(lo[w >> 1] >> sh));
-            p[w][1] = signed_pair(mg[4 * w + 1], mg[4 * w + 3], unsigned(hi[w >> 1] >> sh));
-        }
-        __builtin_amdgcn_sched_barrier(0);   // (products behind all of this: no wait states between a pair and its product)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const v4f z = {0.0f, 0.0f, 0.0f, 0.0f};
-            a[w] = __builtin_amdgcn_mfma_f32_4x4x4f16(ident, __builtin_bit_cast(v4h, p[w]), FIRST ? z : a[w], 0, 0, 0);
-        }
-        if (more) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                u64 h = hi[k], l = lo[k];
-                asm("v_lshl_add_u64 %0, %0, 1, 0" : "+v"(h));
-                asm("v_lshl_add_u64 %0, %0, 1, 0" : "+v"(l));
-                hi[k] = h;
-                lo[k] = l;
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    // the magnitudes of the next class are under way while this one's signs are applied, its fragment was requested one
-    // class earlier still
-    VFrag f;
-    v16f n;
-#define BS_CLASS(T, CUR, NXT, F0, F1)                     \
-    {                                                     \
-        F0 = read_frag<T - 2, RT>(vaddr);                 \
-        NXT = magnitude(F1, in.u);                        \
-        __builtin_amdgcn_sched_barrier(0);                \
-        apply(acc[T], CUR, true);                         \
-    }
-    f = read_frag<5, RT>(vaddr);
-    n = magnitude(in.f, in.u);
-    __builtin_amdgcn_sched_barrier(0);
-    apply(acc[7], in.m, true);
-    BS_CLASS(6, n, in.m, in.f, f)
-    BS_CLASS(5, in.m, n, f, in.f)
-    BS_CLASS(4, n, in.m, in.f, f)
-    BS_CLASS(3, in.m, n, f, in.f)
-    BS_CLASS(2, n, in.m, in.f, f)
+    BS_CLASS(7)
+    BS_CLASS(6)
+    BS_CLASS(5)
+    BS_CLASS(4)
+    BS_CLASS(3)
+    BS_CLASS(2)
+    BS_CLASS(1)
+    BS_CLASS(0)
 #undef BS_CLASS
-    n = magnitude(in.f, in.u);
+    if constexpr (!FIRST) {
+        asm volatile("s_nop 3");
+        __builtin_amdgcn_sched_barrier(0);
+        acc[0] = magnitude(f[0], u, acc[0]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// After the last block: the sign of that block off the sums
+__device__ __forceinline__ void finish_unit(UnitAcc& acc, const StepInputs& in) {
+    SignWords d;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) d.w[k] = ~in.last.w[k];   // a cleared bit marks a negative sign
     __builtin_amdgcn_sched_barrier(0);
-    apply(acc[1], in.m, true);
-    FirstReads next;
-    begin_reads<RT>(in, next, vnext, snext);
-    __builtin_amdgcn_sched_barrier(0);
-    apply(acc[0], n, false);
-    take_reads(in, next);
-    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = kClasses - 1; t >= 0; --t) {
+        const FlipMasks m = flip_masks(d);
+        if (t > 0) next_class(d);
+        flip_class(acc[t], m);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 }  // namespace bitstack

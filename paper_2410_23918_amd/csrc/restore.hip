@@ -53,7 +53,6 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     const unsigned lds0 = lds_address(smem);
     const unsigned v_rd = lds0 + v_read_offset(unsigned(lane));
     const unsigned s_rd = lds0 + unsigned(wave) * Step::kWaveBytes + unsigned(lane) * 16u;
-    const v4h ident = accumulate_matrix(unsigned(lane));
 
     // a step = (row group, block), row groups outermost; its inputs are requested three steps ahead, into a ring of
     // four buffers in LDS.  Rows past the end of the matrix repeat its last tile: computed, never stored.
@@ -85,18 +84,15 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     request();
     loads_barrier<kInFlight>();
     request();
-    {
-        FirstReads first;
-        begin_reads<kRebuildWaves>(in, first, v_rd, s_rd);
-        take_reads(in, first);
-    }
+    begin_reads<kRebuildWaves>(in, v_rd, s_rd);
+    in.last = in.s;
     auto step = [&](auto first) __attribute__((always_inline)) {
         // the next step's inputs have landed (this wavefront's loads, then everybody's), and nobody reads the previous
         // step's any more
         loads_barrier<kInFlight>();
         request();
         const unsigned nb = (buf + kStepBytes) & (kRing * kStepBytes - 1);
-        add_block<decltype(first)::value, kRebuildWaves>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb, ident);
+        add_block<decltype(first)::value, kRebuildWaves>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb);
         buf = nb;
     };
     // The unit times 1/s (Eq. 4 folded into the columns), as fp16 to the dense matrix.  A lane holds 256
@@ -120,7 +116,7 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
                 read_scales(r, rs_rd, w * 4 + b);
 #pragma unroll
                 for (int t = 0; t < 8; t += 2)
-                    o[b][t >> 1] = scaled_pair(acc[t][w][b], acc[t + 1][w][b], r[t >> 2][t & 3], r[t >> 2][(t & 3) + 1]);
+                    o[b][t >> 1] = scaled_pair(acc[t][4 * w + b], acc[t + 1][4 * w + b], r[t >> 2][t & 3], r[t >> 2][(t & 3) + 1]);
             }
             v4i q[4];
 #pragma unroll
@@ -143,6 +139,7 @@ __global__ __launch_bounds__(kRebuildWaves * 64, 2) void k_restore(KParams p, in
     for (int rg = rg0; rg < rg1; ++rg) {
         step(std::true_type{});
         for (int i = 1; i < n; ++i) step(std::false_type{});
+        finish_unit(acc, in);
         const int rt = rt_first + rg * kRebuildWaves;
         if (rt < nrt) flush(rt);
     }
