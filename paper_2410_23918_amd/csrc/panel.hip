@@ -26,11 +26,10 @@
 #include "kernels.h"
 #include "kparams.h"
 #include "layout.h"
+#include "rebuild.h"
 
 namespace bitstack {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 constexpr int kPanelRows = 64;        // output rows per workgroup
 constexpr int kPanelLd = 264;         // fp16 elements per LDS row of a 256-column tile (+8: bank spread)
@@ -640,11 +639,10 @@ static hipError_t launch_fused(KParams p, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Many tokens (prefill): the weight tile is kept, but built the way the small-batch kernel builds
-// its signed tiles.  Per block, the signed fp16 tile (same 1.5 vector instructions per element) is
-// multiplied by a permuted identity on the matrix cores, which adds it to an fp32 accumulator tile
-// in the same register layout; after the last block the tile is scaled by 1/s (Eq. 4 moved from the
-// activations to the weight columns, so that activation fragments come from memory untouched),
+// Many tokens (prefill): the weight tile is kept, in fp32 accumulators that hold it times the sign of the block added last (rebuild.h):
+// a block flips the signs that change and its magnitude product adds in place.  (Signed fp16 tiles, added by products with permuted
+// identities, took 157 us where this takes 137: 14336 x 4096, 16 blocks, 300 tokens.)  After the last block the tile is scaled by 1/s
+// (Eq. 4 moved from the activations to the weight columns, so that activation fragments come from memory untouched),
 // rounded to fp16 and parked in LDS.  Then every wavefront multiplies the two parked tiles (64 rows
 // x 2 x 256 columns) with its own 64 of the workgroup's 512 tokens.  Same teams, private LDS
 // pieces, U cache and three-deep input rotation as k_fused; two LDS-only barriers per pair of
@@ -779,16 +777,6 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
         return *reinterpret_cast<const v8h*>(ucache + ((i * 64 + rg * 32 + ln) * 2 + hl) * 16);
     };
 
-    // permuted identities: A[i'][slot s of half hl] = 1 where i' is the column that slot s of the
-    // signed tile holds (8*mf + 4*hl + s/2 + 16*(s%2)), so that identity x tile = tile in the
-    // accumulator layout "register v <-> column 8*(v/4) + 4*hl + v%4"
-    v8h ident[2];
-#pragma unroll
-    for (int mf = 0; mf < 2; ++mf)
-#pragma unroll
-        for (int sl = 0; sl < 8; ++sl)
-            ident[mf][sl] = _Float16(ln == 8 * mf + 4 * hl + (sl >> 1) + 16 * (sl & 1) ? 1.0f : 0.0f);
-
     v16f wacc[2][2];   // [tile][row group]: the weight tile of this chunk, fp32 (starts at a chunk's first block)
     v16f yacc[2][2];   // [row group][token group of my 64 tokens]
 #pragma unroll
@@ -798,52 +786,57 @@ __global__ __launch_bounds__(512) void k_tile(KParams p) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) yacc[a][b][v] = 0.0f;
 
-    // the sign bits of a register pair (word bits 8*mf + k + 4*hl and that + 16) go to bits 15 and 31: the word is
-    // moved down by 4*hl, the shifts from there are immediates
-
-    // first = the chunk's first block: the accumulator starts from zero instead of being cleared
+    // One block onto the four tiles (tb = 2 * tile + row group): the accumulator holds the sum times the sign of the block added
+    // last (rebuild.h): flip where this block's differs, then the product adds its magnitudes.  Register 4 b + k of a lane is bit
+    // 8 b + 4 hl + k of its word.  first = the chunk's first block: the accumulator starts from zero instead of being cleared
     // beforehand, so that its 64 registers are free during the product stage
-    auto magnitude = [&](int tb, v8h uf0, v8h uf1, v8h vf0, v8h vf1) -> v16f {
+    unsigned last[2][2];   // [row group][tile]: sign words of the block added last
+    auto flip = [&](v16f& a, unsigned d) __attribute__((always_inline)) {
+        d <<= 4 - 4 * hl;   // bits 4 .. 7 of every byte: k = 0 .. 3
+        unsigned top = 0x80000000u;
+        asm("" : "+v"(top));   // a vector register
+#pragma unroll
+        for (int k = 3; k >= 0; --k) {
+            const unsigned m = (d << (3 - k)) & 0x80808080u;
+            a[k] = flip_sign<0>(a[k], m, top);
+            a[4 + k] = flip_sign<1>(a[4 + k], m, top);
+            a[8 + k] = flip_sign<2>(a[8 + k], m, top);
+            a[12 + k] = flip_sign<3>(a[12 + k], m, top);
+        }
+    };
+    auto product = [&](auto first, int tb, v8h uf, v8h vf) __attribute__((always_inline)) {
         v16f z;
 #pragma unroll
         for (int v = 0; v < 16; ++v) z[v] = 0.0f;
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16((tb >> 1) ? vf1 : vf0, (tb & 1) ? uf1 : uf0, z, 0, 0, 0);
+        v16f& w = wacc[tb >> 1][tb & 1];
+        w = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, uf, decltype(first)::value ? z : w, 0, 0, 0);
     };
-    auto sign_and_add = [&](auto first, int tb, const v16f& m, const SIn& sg) {
-        const int tile = tb >> 1, rg = tb & 1;
-        const unsigned wrd = unsigned(tile ? sg.w[rg].y : sg.w[rg].x) >> (4 * hl);
-#pragma unroll
-        for (int mf = 0; mf < 2; ++mf) {
-            unsigned r4[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-                h2 c;
-                c[0] = _Float16(m[4 * mf + k]);
-                c[1] = _Float16(m[4 * mf + k + 8]);
-                const unsigned flip = ~(wrd << (15 - 8 * mf - k)) & 0x80008000u;   // a cleared bit marks a negative sign
-                r4[k] = __builtin_bit_cast(unsigned, c) ^ flip;
-            }
-            if (decltype(first)::value && mf == 0) {
-                v16f z;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) z[v] = 0.0f;
-                wacc[tile][rg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ident[mf], __builtin_bit_cast(v8h, r4), z, 0, 0, 0);
-            } else {
-                wacc[tile][rg] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ident[mf], __builtin_bit_cast(v8h, r4),
-                                                                        wacc[tile][rg], 0, 0, 0);
-            }
-        }
-    };
-    // tile-blocks tb = 2 * tile + row group
     auto rebuild = [&](auto first, const SIn& sg, v8h uf0, v8h uf1, v8h vf0, v8h vf1) {
+        // a tile's product is issued behind the flips of the next tile, and the flips of a step come long after the last step's products
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb) sign_and_add(first, tb, magnitude(tb, uf0, uf1, vf0, vf1), sg);
+        for (int tb = 0; tb < 4; ++tb) {
+            const int tile = tb >> 1, rg = tb & 1;
+            const unsigned w = unsigned(tile ? sg.w[rg].y : sg.w[rg].x);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!decltype(first)::value) flip(wacc[tile][rg], w ^ last[rg][tile]);
+            last[rg][tile] = w;
+            __builtin_amdgcn_sched_barrier(0);
+            if (tb > 0) product(first, tb - 1, ((tb - 1) & 1) ? uf1 : uf0, ((tb - 1) >> 1) ? vf1 : vf0);
+        }
+        asm volatile("s_nop 3");
+        __builtin_amdgcn_sched_barrier(0);
+        product(first, 3, uf1, vf1);
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     // end of a chunk: park my piece of W' diag(1/s) in LDS, then the product stage for both teams' chunks
     auto flush_and_multiply = [&](int it) {
         const int ch = min(2 * it + team, nch - 1);
+        asm volatile("s_nop 15\n\ts_nop 15");   // the last products (the compiler does not look into flip_sign)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) flip(wacc[tb >> 1][tb & 1], ~last[tb & 1][tb >> 1]);   // a cleared bit marks a negative sign
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int tile = 0; tile < 2; ++tile)
 #pragma unroll
