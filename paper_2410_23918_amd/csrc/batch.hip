@@ -2,23 +2,21 @@
 // Y += X (W' diag(1/s))^T, W' of a unit summed over its blocks in registers, multiplied with the activations from there and
 // never stored.
 //
-// One workgroup = 64 output rows x up to 64 tokens; 8 wavefronts = 4 teams (column chunks) x 2 row tiles.  A wavefront rebuilds
-// its unit of 32 rows x 256 columns block by block; a lane then holds 128 columns of one row, which, scaled by 1/s and
+// One workgroup = RT row tiles of 32 rows x up to 64 tokens; 8 wavefronts = 8 / RT teams (column chunks) x RT row tiles.  A wavefront
+// rebuilds its unit of 32 rows x 256 columns block by block; a lane then holds 128 columns of one row, which, scaled by 1/s and
 // rounded to fp16, are the B operands of 16 products over 16 columns each, and the activations as they lie in memory (8
 // columns of a token: 16 bytes) the A operands.  So the weight costs the same for one token as for 64, and a block costs
 // three matrix-core products' worth less than where every block's signed tile meets the activations itself (k_fused in
 // panel.hip).  The activations of a chunk come through the same ring of LDS buffers as the blocks' inputs, as one to four
-// further steps after the last block.
+// further steps after the last block.  The teams' partial tiles meet in LDS.
 //
-// 8 wavefronts and not two workgroups of 4: the teams' partial tiles meet in LDS, so a quarter of the workspace serves, and
-// the workspace is what limits the column split of small stacks (14336 x 4096, 3 blocks, 16 tokens: 28 us against 33).
-// 14336 x 4096, 16 blocks: 81-88 us for 2-32 tokens depending on the device (k_fused 102), 91-98 for 64 (k_fused 214, weight-tile kernel
-// 152); 28672 x 8192: 344-354 us for 16 tokens (462).  Beyond 64 tokens every group of 64 (a grid dimension) rebuilds the weight again,
-// on compute units that are idle otherwise: 4096 x 4096, 16 blocks: 90 us for 64 tokens, 99 for 256 (weight-tile kernel 139).
-// Groups of 96 or 128 would need more than the 256 registers that two wavefronts per SIMD leave (all in use with 64).
+// 14336 x 4096, 16 blocks: 78 us for 4 tokens (k_fused 102); 4096 x 14336, 16 tokens: 79 us.  Beyond 64 tokens every group of 64 (a
+// grid dimension) rebuilds the weight again, on compute units that are idle otherwise.
+// Groups of 128 would need more than the 256 registers that two wavefronts per SIMD leave.
 //
-// Bound by the issue of vector and matrix instructions: a step (8 tiles per wavefront, two wavefronts per SIMD) takes 1.05-1.25 us, the
-// same instructions without loads and barriers 0.92; by counters the two fill 74 % of a working SIMD's cycles (16 tokens).
+// Bound by the issue of vector and matrix instructions (0.79 us a step of 8 tiles per wavefront and two wavefronts per SIMD, registers
+// only) and by the arrival of the next steps' inputs: a step takes 1.17 us with RT = 2 and a ring of three, 1.0 us with RT = 4 and a ring
+// of four (1.05-1.25 before, when the rebuild took 0.92).
 //
 // The weight over its scale is rounded to fp16 where k_fused rounds the activation over the scale; the error against fp64 is the same
 // to 1.5 % (2.97e-4 of y against 2.93e-4 over 49 shapes).  For weights beyond fp16's range see the end of the accumulation.
@@ -36,14 +34,15 @@ namespace bitstack {
 
 namespace {
 
-// TOK tokens (16 or 32) per group of activations, GROUPS of them
-template <int TOK, int GROUPS>
+// TOK tokens (16 or 32) per group of activations, GROUPS of them; RT row tiles per workgroup (2 or 4)
+template <int TOK, int GROUPS, int RT>
 __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
-    constexpr int RT = 2, TEAMS = 4, kRows = RT * kTileRows, kRing = 3;
+    constexpr int TEAMS = 8 / RT, kRows = RT * kTileRows;
+    constexpr int kRing = RT == 4 ? 4 : 3, kInFlight = RT == 4 ? kStepLoads<RT> : 0;   // every request is four loads then
     typedef StepLayout<RT> L;
     constexpr unsigned kStep = TEAMS * L::kBytes;
-    // an activation step brings TOK tokens x kPieces columns of eight per half, 8 KiB per team
-    constexpr int kPieces = 256 / TOK, kPerGroup = 16 / kPieces, kXSteps = GROUPS * kPerGroup, kXRowBytes = kPieces * 32;
+    // an activation step brings TOK tokens x kPieces columns of eight per half, at most 4 RT KiB per team
+    constexpr int kPieces = RT * 128 / TOK < 16 ? RT * 128 / TOK : 16, kPerGroup = 16 / kPieces, kXSteps = GROUPS * kPerGroup, kXRowBytes = kPieces * 32;
     constexpr unsigned kRsLds = kRing * kStep;   // [2][TEAMS][256] floats
     constexpr unsigned kFlagLds = 8 * 4096;   // two words behind the partial tiles, in the ring when it is idle
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -88,7 +87,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
             const unsigned mine = lds0 + qbuf + unsigned(team) * L::kBytes + unsigned(tile) * 4096u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int lin = k * 64 + lane, t = tile * (4096 / kXRowBytes) + lin / (2 * kPieces);   // token of the group
+                const int lin = k * 64 + lane, t = (tile * (4096 / kXRowBytes) + lin / (2 * kPieces)) % TOK;   // token of the group (some twice)
                 const int j = (lin % (2 * kPieces)) ^ (t & 15);   // piece: [half][kPieces]
                 const int tok = min(tok0 + g * TOK + t, p.batch - 1);
                 const unsigned off = unsigned(tok) * unsigned(p.in) * 2u + unsigned(j / kPieces) * 256u + unsigned(j % kPieces + e0) * 16u;
@@ -102,7 +101,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
         }
         qbuf = next_buf(qbuf);
     };
-    
+
     auto request_rs = [&](int it) {   // 1/s of the team's chunk of iteration it, 1 KiB by the team's wavefronts
         const int ch = min(c_lo + it * TEAMS + team, c_hi - 1);
 #pragma unroll
@@ -131,15 +130,16 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) yacc[g] = zero16();
         request_rs(0);
-        // step s's inputs are requested two steps ahead
+        // a step's inputs are requested kRing - 1 steps ahead and have kRing - 2 steps to arrive
         request();
-        loads_barrier<0>();
+        if constexpr (kRing == 4) request();
+        loads_barrier<kInFlight>();
         request();
         begin_reads<RT>(in, v_rd, s_rd);
         in.last = in.s;
         for (int it = 0; it < iters; ++it) {
             auto step = [&](auto first) __attribute__((always_inline)) {
-                loads_barrier<0>();
+                loads_barrier<kInFlight>();
                 request();
                 const unsigned nb = next_buf(buf);
                 add_block<decltype(first)::value, RT>(acc, in, v_rd + buf, v_rd + nb, s_rd + nb);
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
 #pragma unroll
             for (int xs = 0; xs < kXSteps; ++xs) {
                 const int g = xs / kPerGroup, e0 = xs % kPerGroup * kPieces;
-                loads_barrier<0>();
+                loads_barrier<kInFlight>();
                 if (xs == 0) request_rs(it + 1);
                 request();
                 const unsigned nb = next_buf(buf);
@@ -299,50 +299,90 @@ __global__ __launch_bounds__(512, 2) void k_batch(KParams p) {
 
 constexpr int kBatchMaxSplit = 8;
 
-// Column split: too few row groups to fill the chip share their column chunks among several workgroups (the workspace must
-// hold a partial row per split and token).  The split with the fewest rounds x chunk iterations is taken, the smallest of
-// equals.
-static int batch_split(int out, int in, int batch, int part_slots) {
-    const int groups = (out + 63) / 64 * ((batch + 63) / 64), nch = in / kChunkCols;
-    int best = 1;
-    long best_cost = 0;
-    for (int k = 1; k <= kBatchMaxSplit && k <= nch && (k == 1 || k * batch <= part_slots); ++k) {
-        if (k > 1 && size_t(k) * batch * out * 4 >= (size_t(1) << 32)) break;   // 32-bit offsets into the partial rows
-        const long cost = long((groups * k + 255) / 256) * (((nch + k - 1) / k + 3) / 4);
-        if (k == 1 || cost < best_cost) {
-            best = k;
-            best_cost = cost;
+// Row tiles of a workgroup (RT) and column split, with the estimated duration (microseconds).
+//
+// Four row tiles share a column chunk's V panel and leave LDS for a ring of four steps: a step's inputs have two steps' time to
+// arrive instead of one, which is what a step of two row tiles waits for (14336 x 4096, 16 blocks, 4 tokens: 87 us with two
+// row tiles, 78 with four; 4096 x 14336, 16 tokens: 91, 79).  Two row tiles with twice the column chunks per workgroup need no or half
+// the column split for the same number of workgroups, so they stay where the workspace allows no split (it holds a partial row per
+// split and token) and for calls of a few microseconds (8608 x 768, 3 blocks, 4 tokens: 10.0 us with two, 11.4 with four).
+//
+// Too few row groups to fill the chip share their column chunks among several workgroups: the split with the fewest rounds x chunk
+// iterations, the smallest of equals.  The estimates of the two forms, per round, chunk iteration and block, are fitted to 6120 cases
+// (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 300 tokens, each timed with both; 1.9 and 2.5 % root mean square): the form
+// taken is 0.01 % slower than the faster one in the mean, one of them by more than 3 %.
+struct BatchPlan {
+    int rt, split;
+    double us;
+};
+static std::atomic<int> g_forced_tiles{0};
+void batch_force_tiles(int tiles) { g_forced_tiles = tiles == 2 || tiles == 4 ? tiles : 0; }
+
+static BatchPlan batch_plan(int out, int in, int batch, int n_loaded, int part_slots) {
+    const int nch = in / kChunkCols, forced = g_forced_tiles.load();
+    const bool many = batch > 64;
+    BatchPlan best = {0, 1, 0.0};
+    for (int rt = 4; rt >= 2; rt -= 2) {
+        if (forced && forced != rt) continue;
+        const int groups = (out + 32 * rt - 1) / (32 * rt) * ((batch + 63) / 64), teams = 8 / rt;
+        int split = 1;
+        long cost = 0;
+        for (int k = 1; k <= kBatchMaxSplit && k <= nch && (k == 1 || k * batch <= part_slots); ++k) {
+            if (k > 1 && size_t(k) * batch * out * 4 >= (size_t(1) << 32)) break;   // 32-bit offsets into the partial rows
+            const long c = long((groups * k + 255) / 256) * (((nch + k - 1) / k + teams - 1) / teams);
+            if (k == 1 || c < cost) {
+                split = k;
+                cost = c;
+            }
         }
+        const int wgs = groups * split, its = ((nch + split - 1) / split + teams - 1) / teams;
+        const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = (wgs + 255) / 256;
+        const int halves = batch > 32 ? 2 : 1;   // groups of up to 32 tokens
+        const double tokens = batch > 32 ? 1.0 : batch > 16 ? 0.33 : 0.0, apart = split > 1 ? 1.73 + 0.36 * split * fill : 0.0;
+        const double us = rt == 4 ? (many ? 0.3 : 1.6) + 2.2 * tokens + apart +
+                                        rounds * ((many ? 4.45 : 2.5) + its * (n_loaded * (0.928 + 0.073 * fill) + 1.16 + 0.74 * halves))
+                                  : (many ? 1.2 : 1.5) + 1.1 * tokens + apart +
+                                        rounds * ((many ? 3.55 : 2.85) +
+                                                  its * (n_loaded * (1.025 + 0.141 * fill) + 1.33 + 0.54 * (batch > 16 ? 2 * halves : 1)));
+        if (best.rt == 0 || us < best.us) best = {rt, split, us};
     }
     return best;
 }
 
-template <int TOK, int GROUPS>
-static hipError_t launch_batch_t(KParams p, hipStream_t st) {
-    const size_t smem = size_t(3) * 4 * StepLayout<2>::kBytes + 2 * 4 * kChunkCols * 4;
+template <int TOK, int GROUPS, int RT>
+static hipError_t launch_batch_t(KParams p, int split, hipStream_t st) {
+    const size_t smem = size_t(RT == 4 ? 4 : 3) * (8 / RT) * StepLayout<RT>::kBytes + 2 * (8 / RT) * kChunkCols * 4;
     static std::atomic<bool> attr_set{false};   // setting the attribute twice is harmless
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch<TOK, GROUPS>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch<TOK, GROUPS, RT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(smem));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    p.n_ks = batch_split(p.out, p.in, p.batch, p.part_slots);
-    hipLaunchKernelGGL((k_batch<TOK, GROUPS>), dim3((p.out + 63) / 64, p.n_ks, (p.batch + TOK * GROUPS - 1) / (TOK * GROUPS)), dim3(512), smem, st, p);
+    p.n_ks = split;
+    const dim3 grid((p.out + 32 * RT - 1) / (32 * RT), split, (p.batch + TOK * GROUPS - 1) / (TOK * GROUPS));
+    hipLaunchKernelGGL((k_batch<TOK, GROUPS, RT>), grid, dim3(512), smem, st, p);
     return hipGetLastError();
 }
 
-// Estimated duration (microseconds; fitted to 4774 cases of 2 to 64 tokens and 3483 of 65 to 1024, 64 x 256 to 28672 x 8192, 1 to 24
-// blocks; 3.4 % root mean square, all within 16 %): per round and chunk iteration of a workgroup 1.02-1.19 us per block and 1.9-3.9 us
-// for scaling and product
+// Beyond 64 tokens the crossover to the weight-tile kernel stays where it was when both kernels summed fp16 magnitudes and k_batch had
+// two row tiles only (tests/test_gpu_small_batch.py states which kernel is taken): both became faster by about the same, 13 and
+// 15-20 %.  In 3690 cases of 33 to 1024 tokens estimates of the present kernels would choose 0.4 % better in the mean.
 double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
+    if (batch <= 64) return batch_plan(out, in, batch, n_loaded, part_slots).us;
     const int groups = (out + 63) / 64 * ((batch + 63) / 64), nch = in / kChunkCols;
-    const int split = batch_split(out, in, batch, part_slots);
-    const int wgs = groups * split, xsteps = batch > 32 ? 4 : batch > 16 ? 2 : 1;
-    const int its = ((nch + split - 1) / split + 3) / 4;
+    int split = 1;
+    long best = 0;
+    for (int k = 1; k <= kBatchMaxSplit && k <= nch && (k == 1 || k * batch <= part_slots); ++k) {
+        const long cost = long((groups * k + 255) / 256) * (((nch + k - 1) / k + 3) / 4);
+        if (k == 1 || cost < best) {
+            split = k;
+            best = cost;
+        }
+    }
+    const int wgs = groups * split, its = ((nch + split - 1) / split + 3) / 4;
     const double fill = wgs < 256 ? wgs / 256.0 : 1.0;
-    return (batch > 64 ? 3.3 : 2.0) + (wgs + 255) / 256 * ((batch > 64 ? 3.5 : 3.1) + its * (n_loaded * (1.02 + 0.17 * fill) + 1.25 + 0.66 * xsteps)) +
-           (split > 1 ? (batch > 64 ? 3.2 : 2.0) : 0.0);
+    return 3.3 + (wgs + 255) / 256 * (3.5 + its * (n_loaded * (1.02 + 0.17 * fill) + 3.89)) + (split > 1 ? 3.2 : 0.0);
 }
 
 // one 32-bit buffer descriptor each over the loaded blocks and the activations, one counter per row group and 64 tokens
@@ -351,8 +391,16 @@ bool batch_fits(const KParams& p) {
            (size_t(p.out) + 63) / 64 * ((size_t(p.batch) + 63) / 64) <= size_t(kCounterSlots);
 }
 
+template <int RT>
+static hipError_t launch_batch_rt(const KParams& p, int split, hipStream_t st) {
+    return p.batch > 32   ? launch_batch_t<32, 2, RT>(p, split, st)
+           : p.batch > 16 ? launch_batch_t<32, 1, RT>(p, split, st)
+                          : launch_batch_t<16, 1, RT>(p, split, st);
+}
+
 hipError_t launch_batch(const KParams& p, hipStream_t st) {
-    return p.batch > 32 ? launch_batch_t<32, 2>(p, st) : p.batch > 16 ? launch_batch_t<32, 1>(p, st) : launch_batch_t<16, 1>(p, st);
+    const BatchPlan pl = batch_plan(p.out, p.in, p.batch, p.n_loaded, p.part_slots);
+    return pl.rt == 4 ? launch_batch_rt<4>(p, pl.split, st) : launch_batch_rt<2>(p, pl.split, st);
 }
 
 }  // namespace bitstack

@@ -978,15 +978,15 @@ static hipError_t launch_tile(const KParams& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Estimated durations (microseconds).  k_fused, fitted to 4774 cases (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens; 3.4 %
+// Estimated durations (microseconds).  k_fused, fitted to 5440 cases (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens; 3.0 %
 // root mean square, all within 15 %): a step is a pair of column chunks and a block; the loop takes three at a time and ends with a
 // whole turn (three steps 7.0 us, four 9.2, six 9.0); rounds of 256 workgroups count nearly whole.
 double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
     const int split = small_batch_split(out, in, batch, part_slots), wgs = (out + 63) / 64 * ((batch + 31) / 32) * split;
     const int pairs = ((in / kChunkCols + 1) / 2 + split - 1) / split, steps = n_loaded * pairs;
-    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 0.81 * ((wgs + 255) / 256) + 0.19 * wgs / 256.0;
-    return 1.8 + rounds * (3.8 + (steps + 2) / 3 * 3 * (0.58 + 0.166 * fill) + 0.625 * pairs + (steps % 3 ? 0.76 : 0.0)) +
-           (split > 1 ? 1.5 + 0.003 * batch * split : 0.0);
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 0.79 * ((wgs + 255) / 256) + 0.21 * wgs / 256.0;
+    return (steps == 1 ? 1.8 : 1.35) + rounds * (3.78 + (steps + 2) / 3 * 3 * (0.585 + 0.176 * fill) + 0.617 * pairs + (steps % 3 ? 0.68 : 0.0)) +
+           (split > 1 ? 1.33 + 0.0048 * batch * split : 0.0);
 }
 // k_tile: per pair of column chunks ~0.9 us per block for the rebuild + 12-14 us for the product
 // (14 when several token tiles of a row tile run at once, 6.5 up to 256 tokens, where only one

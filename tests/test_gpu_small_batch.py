@@ -151,3 +151,20 @@ def check(out, inn, n, batch, small=(), infinite=None):
         worst = ((y[finite].double() - want).abs() / bound).max().item()
         print(f"{out}x{inn} batch {batch}: largest error {worst:.3f} of its bound", flush=True)
         assert worst <= 1.0   # also false for an element that was not written (NaN)
+
+
+@pytest.mark.parametrize("tiles", [2, 4])
+@pytest.mark.parametrize("out,inn,n,batch", [
+    (32, 256, 45, 2),       # one of four row tiles, one of two teams with a chunk
+    (160, 768, 45, 17),     # a ragged second row group, three chunks: the second team's last one is none
+    (128, 1280, 60, 33),    # the columns split
+    (416, 2816, 45, 64),
+    (224, 1536, 60, 129),   # three token groups
+])
+def test_both_numbers_of_row_tiles_per_workgroup(tiles, out, inn, n, batch):
+    import paper_2410_23918_amd as B
+    B.set_option(B.OPT_BATCH_TILES, tiles)
+    try:
+        check(out, inn, n, batch)
+    finally:
+        B.set_option(B.OPT_BATCH_TILES, 0)
