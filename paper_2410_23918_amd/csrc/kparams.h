@@ -46,9 +46,14 @@ struct DecodeLaunch {
     KGroup grp;
     unsigned wgs;
     int tiles, early;
+    bool token;   // k_token instead
 };
 hipError_t prepare_decode_group(const LaunchArgs* a, int count, DecodeLaunch* d);
 hipError_t run_decode_launch(const DecodeLaunch& d, hipStream_t st);
+// one token through small stacks that read the same vector (token.hip); token_time_us: microseconds, 0: not served
+double token_time_us(const LaunchArgs* a, int count);
+void prepare_token(const LaunchArgs* a, int count, DecodeLaunch* d);
+hipError_t launch_token(const DecodeLaunch& d, hipStream_t st);
 
 inline KParams make_params(const LaunchArgs& a) {
     KParams p;
