@@ -468,6 +468,8 @@ class PackedStack:
     def _stream(self, stream):
         import torch
         if stream is None:
+            if self.device.index is not None:   # the handle alone: a stream object costs as much as a small launch
+                return C.c_void_p(torch._C._cuda_getCurrentRawStream(self.device.index))
             stream = torch.cuda.current_stream(self.device)
         return C.c_void_p(stream.cuda_stream)
 

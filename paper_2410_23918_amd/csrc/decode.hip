@@ -1015,6 +1015,7 @@ double decode_tokens_time_us(const Geometry& g, int batch, int n_loaded) {
 // A small batch through the decode kernel: one to four tokens per launch, each a member of the
 // group with its own x row, y row and share of the stack's workspace.
 hipError_t launch_decode_tokens(const LaunchArgs& a, hipStream_t st) {
+    if (a.batch == 1) return launch_decode_group(&a, 1, st);   // nothing to cut: pricing the cuts took 1-3.5 us of host time a call
     const size_t xbytes = size_t(a.geo.in) * 2, ybytes = size_t(a.geo.out) * (a.y_f32 ? 4 : 2);
     int sizes[kPlanTokens], n_launches = 0, head_size = 1, head_launches = 0;
     plan_decode_tokens(a.geo, a.batch, a.n_loaded, sizes, &n_launches, &head_size, &head_launches);
