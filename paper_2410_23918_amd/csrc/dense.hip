@@ -20,18 +20,16 @@
 // leaves in 16-byte pieces.  Workgroup ids map to tiles so that all token tiles of a row tile run
 // on one XCD (one L2 pulls that part of the weight).  Two more instantiations, with tiles of 128
 // rows x 256 tokens and of 128 x 128, fill the chip for shapes with few tiles (row slabs, small
-// batches; chosen per launch on the host).
+// batches; chosen per launch on the host); k_gemm_split takes the 128 x 128 tiles of long rows.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
 #include "kparams.h"
 #include "layout.h"
+#include "rebuild.h"
 
 namespace bitstack {
-
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 constexpr int kGemmRows = 256;              // output rows per workgroup (128 in the narrow variant)
 constexpr int kGemmTokens = 256;            // tokens per workgroup
@@ -278,6 +276,196 @@ __global__ __launch_bounds__(512, KSPLIT ? 4 : 1) void k_gemm(KParams p) {
     }
 }
 
+// The 128 x 128 tile where k_gemm's is bound by the arrival of its operands: long rows, and no more tiles than compute units (a slab of
+// 2048 rows x 2048 tokens is 256 of them).  2048 x 8192, 2048 tokens: 82 -> 71 us; 4096 x 14336, 1024 tokens: 134 -> 114.
+// Without its loads it takes 52 us there, without its products 49: streams and products overlap in part.
+// k_gemm<2, true> stays for short rows, where the exchange of four column quarters costs more than is gained (1024 x 1024, 1024 tokens:
+// 11.5 us, this kernel 13.5), and for more tiles than compute units, where two of its workgroups share one (6144 x 2048, 1500
+// tokens: 53 and 63).
+// Eight wavefronts = two token halves x four column quarters: a wavefront multiplies 128 rows x 64 tokens over 32 columns at a time,
+// so that twelve fragments read from LDS feed 32 products (64 x 64 tiles over two column halves: eight feed 16, and the
+// LDS, whose reads and writes both count, would be the bound by half as much again).
+//   Steps of 64 columns (32 KiB of both operands) through a ring of five in LDS, loaded there directly.  Wavefronts 0-3 take the even
+//   steps, 4-7 (the other ones of each SIMD) the odd ones, one half of the columns each; a step's products last two steps.  Its
+//   fragments are read two steps ahead, into a second set of registers, which frees its buffer: a step is requested five steps ahead
+//   and has three to arrive, 96-128 KiB in flight per compute unit.  One barrier per step.
+//   LDS: row r of a step in 128 bytes, its 16-byte piece q at position q ^ (r / 2 % 8): a fragment read of sixteen rows touches every
+//   bank once, and a load's 1 KiB are eight rows.
+// 16x16x32 products: with random operands the chip holds 1.96 PFLOP/s of them and 1.69 of 32x32x16 ones (registers only).
+constexpr unsigned kSplitTile = 128 * 128, kSplitStep = 2 * kSplitTile;   // bytes of an operand's step, of both
+constexpr int kSplitRing = 5, kSplitLds = kSplitRing * kSplitStep;
+constexpr int kSplitYLd = 128 + 8;
+static_assert(4 * 128 * 64 * 4 <= kSplitLds && 128 * kSplitYLd * 2 <= kSplitLds, "the exchange and the output tile reuse the ring");
+__global__ __launch_bounds__(512, 2) void k_gemm_split(KParams p) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int th = wave & 1, cq = wave >> 1;   // token half, column quarter
+    const int ln = lane & 15, kg = lane >> 4;
+    // ids are dealt round-robin to the 8 XCDs, whose L2s each fetch what their tiles read: every fourth row tile x every second token tile
+    // to one of them
+    const int ntt = (p.batch + 127) / 128, nrt = (p.out + 127) / 128, per_row = (ntt + 1) / 2;
+    const int xcd = blockIdx.x & 7, place = blockIdx.x >> 3;
+    const int rt = (xcd >> 1) + 4 * (place / per_row), tt = (xcd & 1) + 2 * (place % per_row);
+    if (rt >= nrt || tt >= ntt) return;
+    const int row0 = rt * 128, tok0 = tt * 128;
+    const int steps = p.in / 64;   // a multiple of 4
+    const v4i w_rsrc = buffer_over(p.wdense, unsigned(size_t(p.out) * p.in * 2));
+    const v4i x_rsrc = buffer_over(p.x, unsigned(size_t(p.batch) * p.in * 2));
+    const unsigned lds0 = lds_address(smem);
+    // this wavefront brings rows / tokens 16 wave .. + 15 of a step, eight per load; past the end the last one is repeated (computed,
+    // never stored)
+    unsigned w_off[2], x_off[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = 8 * i + (lane >> 3), piece = (lane & 7) ^ (r >> 1);
+        w_off[i] = unsigned(size_t(min(row0 + 16 * wave + r, p.out - 1)) * p.in * 2) + unsigned(piece) * 16u;
+        x_off[i] = unsigned(size_t(min(tok0 + 16 * wave + r, p.batch - 1)) * p.in * 2) + unsigned(piece) * 16u;
+    }
+    int q = 0;                                   // next step to request; past the last one the last one again, harmlessly
+    unsigned q_dst = lds0 + unsigned(wave) * 2048u;
+    auto after = [&](unsigned at, unsigned base) { return at == base + (kSplitRing - 1) * kSplitStep ? base : at + kSplitStep; };
+    auto request = [&]() __attribute__((always_inline)) {
+        const unsigned col = unsigned(min(q, steps - 1)) * 128u;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            load_to_lds(w_rsrc, q_dst + unsigned(i) * 1024u, w_off[i], col);
+            load_to_lds(x_rsrc, q_dst + kSplitTile + unsigned(i) * 1024u, x_off[i], col);
+        }
+        ++q;
+        q_dst = after(q_dst, lds0 + unsigned(wave) * 2048u);
+    };
+    const unsigned frag = lds0 + unsigned(ln) * 128u + (unsigned(4 * (cq & 1) + kg) ^ unsigned(ln >> 1)) * 16u;
+    unsigned r_src = frag;                       // fragments of the step to be read next
+    struct Frags {
+        v8h w[8], x[4];
+    };
+    auto read = [&](Frags& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) f.x[t] = __builtin_bit_cast(v8h, read_lds<v4i>(r_src + kSplitTile + unsigned(th * 4 + t) * 2048u));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f.w[j] = __builtin_bit_cast(v8h, read_lds<v4i>(r_src + unsigned(j) * 2048u));
+    };
+    v4f acc[8][4];   // [16 rows][16 tokens]
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[j][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    auto products = [&](const Frags& f, int j0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = j0; j < j0 + 4; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(f.x[t], f.w[j], acc[j][t], 0, 0, 0);
+    };
+    // the first half of a step's products, its successor's fragments read meanwhile (at step h: of step h + 2)
+    auto first = [&](const Frags& now, Frags& next) __attribute__((always_inline)) {
+        loads_barrier<8>();   // step h + 2 has arrived; step h is in its wavefronts' registers
+        request();            // step h + 5, into step h's place
+        r_src = after(after(r_src, frag), frag);
+        read(next);
+        products(now, 0);
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one matrix-core instruction
+        }
+    };
+    auto second = [&](const Frags& now) __attribute__((always_inline)) {
+        loads_barrier<8>();
+        request();
+        products(now, 4);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Frags fa, fb;
+#pragma unroll
+    for (int i = 0; i < kSplitRing; ++i) request();
+    loads_barrier<12>();   // steps 0 and 1
+    // (both sides meet the same barriers)
+    if (cq < 2) {
+        read(fa);
+        for (int h = 0; h < steps; h += 4) {
+            first(fa, fb);
+            second(fa);
+            first(fb, fa);
+            second(fb);
+        }
+    } else {
+        r_src += kSplitStep;
+        read(fa);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) fb.x[t] = v8h{};   // no step before the first
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fb.w[j] = v8h{};
+        for (int h = 0; h < steps; h += 4) {
+            second(fb);
+            first(fa, fb);
+            second(fa);
+            first(fb, fa);
+        }
+        products(fb, 4);
+    }
+    loads_barrier<0>();   // nothing may land in LDS any more
+
+    // the column quarters meet: 2 and 3 park their sums, 0 and 1 add them, then 1 parks and 0 adds
+    float* const red = reinterpret_cast<float*>(smem) + (wave & 3) * (128 * 64) + lane;   // [4][128 registers][64 lanes]
+    auto park = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[((j * 4 + t) * 4 + v) * 64] = acc[j][t][v];
+    };
+    auto add = [&](const float* from) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[j][t][v] += from[((j * 4 + t) * 4 + v) * 64];
+    };
+    if (cq >= 2) park();
+    lds_barrier();
+    if (cq < 2) add(red);
+    lds_barrier();
+    if (cq == 1) park();
+    lds_barrier();
+    if (cq == 0) add(red + 2 * (128 * 64));
+    lds_barrier();
+    // D[i = token][n = row]: lane (row ln), register v holds token 4 kg + v of the group
+    if (p.y_f32) {
+        if (cq != 0) return;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int tok = tok0 + th * 64 + t * 16 + 4 * kg + v, row = row0 + j * 16 + ln;
+                    if (tok < p.batch && row < p.out) static_cast<float*>(p.y)[size_t(tok) * p.y_ld + row] = acc[j][t][v];
+                }
+        return;
+    }
+    _Float16* const yl = reinterpret_cast<_Float16*>(smem);   // [128 tokens][kSplitYLd]: leaves in 16-byte pieces
+    if (cq == 0) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) yl[(th * 64 + t * 16 + 4 * kg + v) * kSplitYLd + j * 16 + ln] = _Float16(acc[j][t][v]);
+    }
+    lds_barrier();
+    __half* const y = static_cast<__half*>(p.y);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int idx = tid + 512 * k, tok = idx / 16, piece = idx % 16;
+        const uint4 v = *reinterpret_cast<const uint4*>(yl + tok * kSplitYLd + piece * 8);
+        if (tok0 + tok < p.batch && row0 + piece * 8 < p.out)
+            *reinterpret_cast<uint4*>(y + size_t(tok0 + tok) * p.y_ld + row0 + piece * 8) = v;
+    }
+}
+
 hipError_t launch_dense_zero(const LaunchArgs& a, hipStream_t st) {
     const size_t n16 = size_t(a.geo.out) * size_t(a.geo.in) * 2 / 16;
     hipLaunchKernelGGL(k_dense_zero, dim3(unsigned((n16 + 255) / 256)), dim3(256), 0, st,
@@ -290,11 +478,12 @@ hipError_t launch_dense_zero(const LaunchArgs& a, hipStream_t st) {
 // chip runs each tile faster (clock, shared caches) - with (a, b) = (0.0196, 0.0148) for 256-row
 // tiles, (0.0111, 0.0089) for 128-row tiles and (0.0068, 0.0032) for 128 x 128 tiles.  The
 // launcher takes the cheapest tile.
-enum GemmTile { kTile256 = 1, kTile128 = 2, kTile128x128 = 3 };
+enum GemmTile { kTile256 = 1, kTile128 = 2, kTile128x128 = 3, kTileSplit = 4 };
 static std::atomic<int> g_forced_tile{0};   // measurement hook: 0 = the estimate's choice
 void dense_force_tile(int tile) { g_forced_tile = tile; }
 
 static double tile_rounds_time_us(int out, int in, int batch, int tile) {
+    if (tile == kTileSplit) tile = kTile128x128;   // what the crossovers between the paths are stated in
     const int rows = tile == kTile256 ? 256 : 128, toks = tile == kTile128x128 ? 128 : kGemmTokens;
     const int tiles = ((out + rows - 1) / rows) * ((batch + toks - 1) / toks);
     const double a = tile == kTile256 ? 0.0196 : tile == kTile128 ? 0.0111 : 0.0068;
@@ -304,10 +493,11 @@ static double tile_rounds_time_us(int out, int in, int batch, int tile) {
 }
 static int dense_tile(int out, int in, int batch) {
     const int forced = g_forced_tile.load();
-    if (forced >= kTile256 && forced <= kTile128x128) return forced;
+    if (forced >= kTile256 && forced <= kTileSplit) return forced;
     int best = kTile256;
     for (int t = kTile128; t <= kTile128x128; ++t)
         if (tile_rounds_time_us(out, in, batch, t) < tile_rounds_time_us(out, in, batch, best)) best = t;
+    if (best == kTile128x128 && in >= 4096 && (out + 127) / 128 * ((batch + 127) / 128) <= 256) return kTileSplit;
     return best;
 }
 double dense_time_us(int out, int in, int batch) {
@@ -340,14 +530,18 @@ hipError_t launch_dense(const LaunchArgs& a, hipStream_t st) {
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<2, true>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLdsSmall);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_split), hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int tile = dense_tile(p.out, p.in, p.batch);
-    const int rows = tile == kTile256 ? 256 : 128, toks = tile == kTile128x128 ? 128 : kGemmTokens;
+    const int rows = tile == kTile256 ? 256 : 128, toks = tile >= kTile128x128 ? 128 : kGemmTokens;
     const int ntt = (p.batch + toks - 1) / toks, nrt = (p.out + rows - 1) / rows;
     const unsigned wgs = unsigned(8 * ((nrt + 7) / 8) * ntt);
-    if (tile == kTile128x128)
+    if (tile == kTileSplit)
+        hipLaunchKernelGGL(k_gemm_split, dim3(unsigned(8 * ((nrt + 3) / 4) * ((ntt + 1) / 2))), dim3(512), kSplitLds, st, p);
+    else if (tile == kTile128x128)
         hipLaunchKernelGGL((k_gemm<2, true>), dim3(wgs), dim3(512), kGemmLdsSmall, st, p);
     else if (tile == kTile128)
         hipLaunchKernelGGL((k_gemm<2, false>), dim3(wgs), dim3(512), kGemmLds, st, p);

@@ -62,7 +62,7 @@ hipError_t launch_restore(const LaunchArgs& a, hipStream_t st);
 hipError_t launch_dense_zero(const LaunchArgs& a, hipStream_t st);
 hipError_t launch_dense(const LaunchArgs& a, hipStream_t st);
 // k_gemm's tile choice (128-row tiles or 256-row ones) and its estimated duration
-void dense_force_tile(int tile);   // measurement hook: 1 = 256-row tiles, 2 = 128-row tiles, 3 = 128 x 128 tiles, 0 = the estimate's choice
+void dense_force_tile(int tile);   // measurement hook: 1 = 256-row tiles, 2 = 128-row tiles, 3 = 128 x 128 tiles, 4 = those of long rows, 0 = the estimate's choice
 void batch_force_tiles(int tiles);   // measurement hook: row tiles per workgroup of k_batch, 0 = the plan's choice
 double dense_time_us(int out, int in, int batch);
 double restore_time_us(int rows, int in, int n_loaded);
