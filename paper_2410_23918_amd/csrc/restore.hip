@@ -6,10 +6,9 @@
 // columns (rebuild.h); a workgroup is four of them, 128 rows x one column chunk, and two workgroups share a compute
 // unit, so that one's barrier or turn through LDS is covered by the other's arithmetic.
 //
-// 14336 x 4096, 16 blocks: 78 us (before, with the weight-tile kernel's rebuild stage: 145); 28672 x 8192, 16 blocks: 346 us
-// (490-530); 2048 x 8192, 16 blocks: 27 us (40).  What bounds it: issue of vector and matrix instructions (64 of these us at
-// 14336 x 4096 with every input from cache and nothing stored) and the traffic of signs, U, V and dense rows, which overlap
-// in part.
+// 14336 x 4096, 16 blocks: 76-81 us; 28672 x 8192: 312-350; 2048 x 8192: 25-28 (with magnitudes rounded to fp16 and added by products of
+// their own 78-82, 329-368, 26-28).  What bounds it: on whole matrices the issue of vector instructions (half of all cycles) and
+// the traffic of signs, U, V and dense rows, which overlap in part; in slabs the first loads and last stores of 512 workgroups at once.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
