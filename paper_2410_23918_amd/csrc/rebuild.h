@@ -287,9 +287,18 @@ __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned
     VFrag f[kClasses];
     f[7] = in.f7;
     f[6] = in.f6;
+    if constexpr (FIRST) {   // nothing but products: all fragments at once (two classes ahead is less than an LDS read takes then)
+        f[5] = read_frag<5, RT>(vaddr);
+        f[4] = read_frag<4, RT>(vaddr);
+        f[3] = read_frag<3, RT>(vaddr);
+        f[2] = read_frag<2, RT>(vaddr);
+        f[1] = read_frag<1, RT>(vaddr);
+        f[0] = read_frag<0, RT>(vaddr);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #define BS_CLASS(T)                                                                        \
     {                                                                                      \
-        if constexpr (T >= 2) f[T >= 2 ? T - 2 : 0] = read_frag<(T >= 2 ? T - 2 : 0), RT>(vaddr); \
+        if constexpr (T >= 2 && !FIRST) f[T >= 2 ? T - 2 : 0] = read_frag<(T >= 2 ? T - 2 : 0), RT>(vaddr); \
         if constexpr (T < 2) {                                                             \
             if constexpr (T == 1) begin_reads<RT>(in, vnext, snext);                       \
         }                                                                                  \
