@@ -2,23 +2,25 @@
 // latency are all there is.
 //
 // k_decode (decode.hip) needs three barriers before its first product (x/s table, exact maxima, quantised panel) because an
-// integer panel wants one scale per column range.  Here the activation goes onto V as an fp16 factor, which needs a scale only to
-// stay in range, and a wavefront takes one sign unit (32 rows x 256 columns of one block) from its loads to its row sums alone:
-//   * every load is issued at entry: V of the chunk to LDS, signs, U, x and 1/s of the lane's columns to registers;
-//   * per column class t: A = V (8 ranks of one column, turned by the transposing LDS read) times x/s of that column, which is the
-//     lane's own (the columns that a lane holds for the eight classes are eight neighbours); B = U of the row; the product is the
-//     contribution of the class's 32 columns to 32 rows, before the sign;
-//   * sign and sum as in rebuild.h: the accumulator holds the sum times the sign of the class added last, so a class flips the
-//     signs that differ and its product adds in place.  Two accumulators take turns, so that one's product covers the other's flips.
+// integer panel wants one scale per column range.  Here nothing is quantised, and a wavefront takes one sign unit (32 rows x 256
+// columns of one block) from its loads to its row sums alone:
+//   * every load is issued at entry: V of the chunk to LDS, signs, U, x and 1/s of eight columns per lane to registers;
+//   * per column class t the magnitudes of its 32 columns x 32 rows by one matrix product, V (8 ranks of one column, turned by the
+//     transposing LDS read) times U, exactly as they are stored;
+//   * a lane then holds sixteen columns of its row: their signs are flipped by the bytes of its sign words (rebuild.h), and
+//     sum += magnitude * x/s in fp32.  x/s of the sixteen columns is the same for all rows; each row of sixteen lanes keeps it with one
+//     column per lane and class, and the multiply-add takes it from there (row_newbcast).
 // A workgroup is eight units of one row tile; more than eight meet in the workspace (k_decode's protocol: write-through stores, one
 // relaxed agent-scope counter, the last arriver adds the partial rows in a fixed order).
 //
-// 512 x 512, 4 blocks: 9.3 -> 4.5 us; 1024 x 4096, 3 blocks: 10.9 -> 6.2 (k_decode, this kernel; graph replay).  Bound by launch, one
+// 512 x 512, 4 blocks: 9.1 and 4.4 us; 1024 x 4096, 3 blocks: 10.8 and 5.9 (k_decode, this kernel; graph replay).  Bound by launch, one
 // memory latency and, with partial rows, the protocol's two more; on larger stacks by V, which every row tile loads again (1024 x
-// 4096, 16 blocks: 12.1 and 12.5).
+// 4096, 12 blocks: 11.9 and 10.1).  Putting x/s onto V as an fp16 factor before the product, so that signs and sums stay in the
+// accumulator (rebuild.h), takes 4 % longer and needs a scale: one from separate maxima of |x/s| and |V| loses every column where the
+// loudest channel has no weight.
 //
-// Error: V and x/s are multiplied in fp16 (x/s rounded, the product rounded), as in k_decode's quantiser, whose fixed point comes on
-// top there: 3.6e-4 of y where k_decode has 4.0e-4 (41 drawn stacks against fp64); sums are fp32.
+// Error: sums and products in fp32 and nothing rounded before y: 1.5e-7 of y where k_decode's fixed point has 3.4e-4 (41 drawn stacks
+// against fp64, fp32 outputs).
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -33,14 +35,33 @@ namespace {
 
 constexpr int kTokenWaves = 8;
 
-// largest of the non-negative floats of a wavefront's lanes (as integers), in all lanes
-__device__ __forceinline__ int wave_max(int v) {
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false));   // row_ror:8
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false));   // row_ror:4
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, false));   // row_ror:2
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, false));   // row_ror:1
-    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+// s += sum of a x/s over the sixteen columns of one class, a the magnitudes of the lane's row with their signs taken from m: the class's
+// bits stand at bit 7 of the bytes (set: negative; the other bits of bytes 0 to 2 cleared).  Lane e of a row of sixteen has register e's x/s.
+// The compiler places the wait states behind a matrix product where an instruction of its own reads the result, but does not look into
+// assembly.  So the first flip is its own, and the others take that one as an operand; the rest is one statement that keeps its own
+// distances (one instruction between a sub-dword operation and a reader, two between a vector instruction and a row operation).
+__device__ __forceinline__ void add_class(float (&s)[4], v16f a, const FlipMasks& m, float xs) {
+    const unsigned top = 0x80000000u;
+    a[3] = __int_as_float(__float_as_int(a[3]) ^ int(m.w[0] & top));
+#define BS_FLIP(E, M, B) "v_xor_b32_sdwa " E ", " E ", " M " dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_" B "\n\t"
+#define BS_ADD(S, E, N) "v_fmac_f32_dpp " S ", %[xs], " E " row_newbcast:" N " row_mask:0xf bank_mask:0xf\n\t"
+    asm(BS_FLIP("%4", "%[m0]", "0") BS_FLIP("%5", "%[m0]", "1") BS_FLIP("%6", "%[m0]", "2")
+        BS_FLIP("%7", "%[m1]", "0") BS_FLIP("%8", "%[m1]", "1") BS_FLIP("%9", "%[m1]", "2")
+        BS_FLIP("%11", "%[m2]", "0") BS_FLIP("%12", "%[m2]", "1") BS_FLIP("%13", "%[m2]", "2")
+        BS_FLIP("%15", "%[m3]", "0") BS_FLIP("%16", "%[m3]", "1") BS_FLIP("%17", "%[m3]", "2")
+        "v_bitop3_b32 %10, %10, %[m1], %[top] bitop3:0x78\n\t"   // a ^ (m & top)
+        "v_bitop3_b32 %14, %14, %[m2], %[top] bitop3:0x78\n\t"
+        "v_bitop3_b32 %18, %18, %[m3], %[top] bitop3:0x78\n\t"
+        BS_ADD("%0", "%4", "0") BS_ADD("%1", "%5", "1") BS_ADD("%2", "%6", "2") BS_ADD("%3", "%[a3]", "3")
+        BS_ADD("%0", "%7", "4") BS_ADD("%1", "%8", "5") BS_ADD("%2", "%9", "6") BS_ADD("%3", "%10", "7")
+        BS_ADD("%0", "%11", "8") BS_ADD("%1", "%12", "9") BS_ADD("%2", "%13", "10") BS_ADD("%3", "%14", "11")
+        BS_ADD("%0", "%15", "12") BS_ADD("%1", "%16", "13") BS_ADD("%2", "%17", "14") BS_ADD("%3", "%18", "15")
+        : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]),
+          "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]),
+          "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15])
+        : [m0] "v"(m.w[0]), [m1] "v"(m.w[1]), [m2] "v"(m.w[2]), [m3] "v"(m.w[3]), [a3] "v"(a[3]), [top] "v"(top), [xs] "v"(xs));
+#undef BS_FLIP
+#undef BS_ADD
 }
 
 // one workgroup: part `part` of p.n_ks of row tile rt
@@ -63,92 +84,44 @@ __device__ __forceinline__ void token_part(const KParams& p, int rt, int part) {
 #pragma unroll
         for (int t = 0; t < kClasses; ++t)
             load_to_lds(rsrc, lds + unsigned(t) * kVClassBytes, v_piece_offset(unsigned(lane)), unsigned(ch) * kVChunkBytes + unsigned(t) * kVClassBytes);
-        // column of row m of the A operand in class t: the first of the eight + t
-        const int col = ch * kChunkCols + ((m >> 2) & 1) * 128 + (m >> 3) * 32 + (m & 3) * 8;
+        // the eight columns, one per class, that this lane keeps x/s of for its row of sixteen lanes: lane e has register e's
+        const int col = ch * kChunkCols + hl * 128 + (lane & 15) * 8;
         const v4i xw = *reinterpret_cast<const v4i*>(p.x + col);
         const v4f r0 = *reinterpret_cast<const v4f*>(p.rs + col), r1 = *reinterpret_cast<const v4f*>(p.rs + col + 4);
-        const v2u vm = *reinterpret_cast<const v2u*>(p.vmax + size_t(blk) * p.in + ch * kChunkCols + lane * 4);
         const v4i sw = *reinterpret_cast<const v4i*>(block + (size_t(rt) * nch + ch) * kUnitBytes + lane * 16);
         const v4i u = *reinterpret_cast<const v4i*>(block + p.off_u + size_t(rt * kTileRows + m) * 32 + hl * 16);
 
         float xs[8];
-        int xm = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int two = xw[k];   // (a copy: a cast of a vector's element takes element 0)
             const v2h h = __builtin_bit_cast(v2h, two);
             xs[2 * k] = float(h[0]) * (k < 2 ? r0[2 * k] : r1[2 * k - 4]);
             xs[2 * k + 1] = float(h[1]) * (k < 2 ? r0[2 * k + 1] : r1[2 * k - 3]);
-            xm = max(xm, max(__float_as_int(fabsf(xs[2 * k])), __float_as_int(fabsf(xs[2 * k + 1]))));
         }
-        // max_r |V| of the chunk's channels: fp16 magnitudes compare like their bits
-        const int vb = wave_max(int(max(max(vm[0] & 0xFFFFu, vm[0] >> 16), max(vm[1] & 0xFFFFu, vm[1] >> 16))));
-        const float vmax = fmaxf(float(__builtin_bit_cast(_Float16, (unsigned short)vb)), 1.0f);
-        // x/s times 2^k below 2^14, and times V too: products of 2^-28 of the largest are still normal numbers
-        const int bound = __float_as_int(__int_as_float(wave_max(xm)) * vmax);
-        const int k = min(13 - ((bound >> 23) - 127), 126);
-        const float f = __int_as_float((k + 127) << 23);
-        v2h xh[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) xh[t][0] = xh[t][1] = _Float16(xs[t] * f);
-
-        // bit t of a byte: does the sign of class t differ from that of class t + 2 (t < 6), the class before it on its accumulator
-        SignWords w, d;
-        w.w[0] = v2u{unsigned(sw[0]), unsigned(sw[1])};
-        w.w[1] = v2u{unsigned(sw[2]), unsigned(sw[3])};
-#pragma unroll
-        for (int q = 0; q < 2; ++q) d.w[q] = (w.w[q] ^ (w.w[q] >> 2)) << 2;   // class 5 at bit 7
+        SignWords d;   // negative signs; class 7 at bit 7 of the bytes
+        d.w[0] = v2u{~unsigned(sw[0]), ~unsigned(sw[1])};
+        d.w[1] = v2u{~unsigned(sw[2]), ~unsigned(sw[3])};
         const unsigned rd = lds + v_read_offset(unsigned(lane));
-        auto factor = [&](int t) __attribute__((always_inline)) -> VFrag {
-            VFrag a{read_lds_turned(rd + unsigned(t) * kVClassBytes), read_lds_turned(rd + unsigned(t) * kVClassBytes + 512u)};
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const unsigned v0 = a.q0[q], v1 = a.q1[q];
-                a.q0[q] = __builtin_bit_cast(unsigned, __builtin_bit_cast(v2h, v0) * xh[t]);
-                a.q1[q] = __builtin_bit_cast(unsigned, __builtin_bit_cast(v2h, v1) * xh[t]);
-            }
-            return a;
-        };
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // V is in LDS (this wavefront's own loads)
-        VFrag a[8];
+        VFrag a[kClasses];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) a[t] = factor(t);
-        __builtin_amdgcn_sched_barrier(0);
-        v16f acc[2];   // [t & 1]
-        acc[1] = magnitude(a[7], u, zero16());
-        acc[0] = magnitude(a[6], u, zero16());
-        asm volatile("s_nop 15");   // the first product (the compiler does not look into the flips)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 5; t >= 0; --t) {
-            const FlipMasks mk = flip_masks(d);
-            next_class(d);
-            flip_class(acc[t & 1], mk);
-            asm volatile("s_nop 3");
-            __builtin_amdgcn_sched_barrier(0);
-            acc[t & 1] = magnitude(a[t], u, acc[t & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // the signs of classes 1 and 0 off the sums; a cleared bit marks a negative sign
-        SignWords s0, s1;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            s0.w[q] = ~w.w[q] << 7;
-            s1.w[q] = ~w.w[q] << 6;
-        }
-        const FlipMasks m0 = flip_masks(s0), m1 = flip_masks(s1);
-        asm volatile("s_nop 15");
-        __builtin_amdgcn_sched_barrier(0);
-        flip_class(acc[1], m1);
-        __builtin_amdgcn_sched_barrier(0);
-        flip_class(acc[0], m0);
+        for (int t = 0; t < kClasses; ++t) a[t] = VFrag{read_lds_turned(rd + unsigned(t) * kVClassBytes), read_lds_turned(rd + unsigned(t) * kVClassBytes + 512u)};
         __builtin_amdgcn_sched_barrier(0);
         float s4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        v16f w[2];   // a class's product is under way while the one before it is added up
+        w[1] = magnitude(a[7], u, zero16());
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s4[v & 3] += acc[0][v] + acc[1][v];
+        for (int t = kClasses - 1; t >= 0; --t) {
+            if (t > 0) w[(t - 1) & 1] = magnitude(a[t - 1], u, zero16());
+            __builtin_amdgcn_sched_barrier(0);
+            const FlipMasks mk = flip_masks(d);
+            next_class(d);
+            add_class(s4, w[t & 1], mk, xs[t]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         sum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
         sum += __shfl_xor(sum, 32);
-        sum *= __int_as_float((127 - k) << 23);
     }
     if (hl == 0) red[wave][m] = sum;
     __syncthreads();
