@@ -568,8 +568,7 @@ def test_cfg4_layer_through_one_native_call_with_merged_launches(B):
 def test_restored_weight_matches_eq8(B, out, inn, n):
     """The dense matrix the restore kernel writes against Eq. 8 with the scaling of Eq. 4 folded
     into the columns, element by element: per output row, max_j |w - w_ref| / max_j |w_ref|
-    (the weight is rounded to fp16 once; every block's magnitudes once more before they are
-    summed in fp32)."""
+    (the blocks are summed in fp32, the weight is rounded to fp16 once)."""
     import torch
     st = synth_stack(3, out, inn, n)
     ps = _pack(B, st, max_batch=65)

@@ -1,6 +1,6 @@
 """The restore kernel at the edges of its tiling: row counts that end inside a row tile's workgroup, one and several column
 chunks, one block and more (the pipeline runs three steps ahead), several row groups per workgroup.  Every element
-against Eq. 8 in fp32 on the device."""
+against Eq. 8 in fp64 on the device."""
 import numpy as np
 import pytest
 
@@ -21,29 +21,28 @@ def test_every_element_of_the_restored_weight(out, inn, n):
     g = torch.Generator(device="cuda:0").manual_seed(out + inn + n)
     s = np.exp(0.5 * np.random.default_rng(n).standard_normal(inn)).astype(np.float32)
     ps = B.PackedStack.empty(out, inn, n, s)
-    w = torch.zeros((out, inn), device="cuda:0")
-    mag = torch.zeros_like(w)   # sum over blocks of |U V^T|
+    w = torch.zeros((out, inn), device="cuda:0", dtype=torch.float64)
+    mag = torch.zeros((out, inn), device="cuda:0")   # sum over blocks of |U| |V|^T
     bits = torch.arange(32, device="cuda:0", dtype=torch.int32)
     for _ in range(n):
         words = torch.randint(-2**31, 2**31, (out, inn // 32), generator=g, device="cuda:0", dtype=torch.int64).to(torch.int32)
         u = (0.1 * torch.randn((out, 16), generator=g, device="cuda:0")).half()
         v = (0.1 * torch.randn((inn, 16), generator=g, device="cuda:0")).half()
         ps.push_block_device(words, u, v)
-        m = u.float() @ v.float().t().contiguous()
+        m = u.double() @ v.double().t().contiguous()
         for r in range(0, out, 4096):
             plus = ((words[r:r + 4096, :, None] >> bits) & 1).reshape(-1, inn).bool()
             w[r:r + 4096] += torch.where(plus, m[r:r + 4096], -m[r:r + 4096])
-        mag += m.abs()
+        mag += u.float().abs() @ v.float().abs().t().contiguous()
     rs = torch.from_numpy(1.0 / s).to("cuda:0")
     w *= rs
     mag *= rs
     got = torch.full((out, inn), float("nan"), dtype=torch.float16, device="cuda:0")
     ps.restore_weight(n, got)
     torch.cuda.synchronize()
-    # every magnitude is rounded to fp16 once (half a unit: 2^-11 of it), the sum is rounded to fp16 once more; products and
-    # sums are fp32, |u| |v| over the 16 ranks is at most ~50 times |m| here and 2^-24 of it far below half a percent of the rest;
-    # 2^-24: half the spacing of fp16 subnormals
-    bound = 2.0**-11 * (mag + w.abs()) * 1.01 + 2.0**-20 * rs + 2.0**-24
-    worst = ((got.float() - w).abs() / bound).max().item()
+    # n blocks of 16 ranks added in fp32 (at most n + 16 roundings of 2^-23 of the sum of absolute values; a matrix product may cut
+    # off) and times 1/s, rounded to fp16 once: 2^-11 of it, or half the spacing of subnormals
+    bound = 2.0**-11 * w.abs() * 1.01 + (n + 16) * 2.0**-23 * mag + 2.0**-25
+    worst = ((got.double() - w).abs() / bound).max().item()
     print(f"{out}x{inn} n={n}: largest error {worst:.2f} of its bound", flush=True)
     assert worst <= 1.0   # also false for an element that was not written (NaN)

@@ -112,18 +112,18 @@ def check(out, inn, n, batch, small=(), infinite=None):
     s = np.exp(0.5 * np.random.default_rng(batch).standard_normal(inn)).astype(np.float32)
     s[list(small)] = 2.0**-30
     ps = B.PackedStack.empty(out, inn, n, s, max_batch=max(64, batch))
-    w = torch.zeros((out, inn), device="cuda:0")
-    mag = torch.zeros_like(w)   # sum over blocks of |U V^T|
+    w = torch.zeros((out, inn), device="cuda:0", dtype=torch.float64)
+    mag = torch.zeros_like(w)   # sum over blocks of |U| |V|^T
     bits = torch.arange(32, device="cuda:0", dtype=torch.int32)
     for _ in range(n):
         words = torch.randint(-2**31, 2**31, (out, inn // 32), generator=g, device="cuda:0", dtype=torch.int64).to(torch.int32)
         u = (0.1 * torch.randn((out, 16), generator=g, device="cuda:0")).half()
         v = (0.1 * torch.randn((inn, 16), generator=g, device="cuda:0")).half()
         ps.push_block_device(words, u, v)
-        m = u.float() @ v.float().t().contiguous()
+        m = u.double() @ v.double().t().contiguous()
         w += torch.where(((words[:, :, None] >> bits) & 1).reshape(out, inn).bool(), m, -m)
-        mag += m.abs()
-    rs = torch.from_numpy(1.0 / s).to("cuda:0")
+        mag += u.double().abs() @ v.double().abs().t().contiguous()
+    rs = torch.from_numpy(1.0 / s).to("cuda:0").double()
     w *= rs
     mag *= rs
     x = torch.randn((batch, inn), generator=g, device="cuda:0").half()
@@ -138,15 +138,16 @@ def check(out, inn, n, batch, small=(), infinite=None):
         torch.cuda.synchronize()
         assert not torch.isfinite(y[~finite]).any()
         xa = x[finite].float().abs().double()
-        want = x[finite].double() @ w.double().t().contiguous()
-        # magnitudes rounded to fp16 (2^-11 of each), their sum times 1/s rounded once more; then fp32 sums of 16-column
+        want = x[finite].double() @ w.t().contiguous()
+        # a weight: n blocks of 16 ranks added in fp32 (at most n + 16 roundings of 2^-23 of the sum of absolute values; a matrix product
+        # may cut off), times 1/s, rounded to fp16 once (2^-11 of it, or half the spacing of subnormals); then fp32 sums of 16-column
         # products: at most in / 16 + 16 roundings of 2^-24 of the sum of absolute values
-        werr = 2.0**-11 * (mag + w.abs()) * 1.01 + 2.0**-20 * rs + 2.0**-24
-        bound = xa @ werr.double().t().contiguous() + (inn / 16 + 16) * 2.0**-24 * (xa @ w.abs().double().t().contiguous())
-        if small or infinite is not None:
-            # 1/s may be on the activations instead: x/s rounded to fp16 (2^-11 of it, or half the spacing of subnormals) and the sum
+        werr = 2.0**-11 * w.abs() * 1.01 + (n + 16) * 2.0**-23 * mag + 2.0**-25
+        bound = xa @ werr.t().contiguous() + (inn / 16 + 16) * 2.0**-24 * (xa @ w.abs().t().contiguous())
+        if small or infinite is not None or (batch > 1024 and n > 29):
+            # 1/s may be on the activations instead (always in the kernel for many tokens and tall stacks): x/s rounded to fp16 (2^-11 of it, or half the spacing of subnormals) and the sum
             # of the magnitudes rounded before the scale (2^-11 of it is in werr, half a subnormal spacing is not)
-            wp, xs = (w / rs).abs().double(), xa * rs.double()
+            wp, xs = (w / rs).abs(), xa * rs
             bound += (2.0**-11 * xs + 2.0**-25) @ wp.t().contiguous() + 2.0**-25 * xs.sum(dim=1, keepdim=True)
         worst = ((y[finite].double() - want).abs() / bound).max().item()
         print(f"{out}x{inn} batch {batch}: largest error {worst:.3f} of its bound", flush=True)
