@@ -596,10 +596,10 @@ def test_restored_weight_matches_eq8(B, out, inn, n):
 def test_materialised_path_every_tile_variant(B, out, inn, n):
     """Restore + dense product against the oracle for batches on both sides of the product
     kernel's tiles (32-token fragments, 64 tokens per wavefront, 128 or 256 per workgroup), with
-    ragged row tiles (out not a multiple of 128 or 256), both output types and each of the three
+    ragged row tiles (out not a multiple of 128 or 256), both output types and each of the four
     output tiles of the product forced in turn (256 x 256, 128 x 256, 128 x 128 with the columns
-    of a chunk split over the two halves of the workgroup), then the launcher's own choice; the
-    two-step form (restore once, multiply many times) gives the same bits as the combined call."""
+    of a chunk split over the two halves of the workgroup, 128 x 128 with the columns split over
+    four pairs of wavefronts), then the launcher's own choice; the two-step form (restore once, multiply many times) gives the same bits as the combined call."""
     import torch
     st = synth_stack(3, out, inn, n)
     batches = (1, 31, 33, 64, 65, 255, 256, 257, 513)
@@ -610,7 +610,7 @@ def test_materialised_path_every_tile_variant(B, out, inn, n):
     for b in batches:
         xd = _to_dev(x[:b])
         for dt in (torch.float16, torch.float32):
-            for tile in (1, 2, 3, 0):
+            for tile in (1, 2, 3, 4, 0):
                 B.set_option(B.OPT_DENSE_TILE, tile)
                 try:
                     y = ps.linear_materialised(xd, n, wd, out_dtype=dt)
@@ -728,14 +728,15 @@ def test_materialised_path_through_the_images_own_scratch(B):
     for b in (70, 1100):
         xd = _to_dev(x[:b])
         for dt in (torch.float16, torch.float32):
-            B.set_option(B.OPT_DENSE_TILE, 3)
-            try:
-                y_full = ps.linear_materialised(xd, n, full, out_dtype=dt)
-                y_img = ps.linear_batched(xd, n, out_dtype=dt, kernel=B.KERNEL_MATERIALISE)
-                torch.cuda.synchronize()
-            finally:
-                B.set_option(B.OPT_DENSE_TILE, 0)
-            assert torch.equal(y_full, y_img), (b, dt)
+            for tile in (3, 4):
+                B.set_option(B.OPT_DENSE_TILE, tile)
+                try:
+                    y_full = ps.linear_materialised(xd, n, full, out_dtype=dt)
+                    y_img = ps.linear_batched(xd, n, out_dtype=dt, kernel=B.KERNEL_MATERIALISE)
+                    torch.cuda.synchronize()
+                finally:
+                    B.set_option(B.OPT_DENSE_TILE, 0)
+                assert torch.equal(y_full, y_img), (b, dt, tile)
             y_img = ps.linear_batched(xd, n, out_dtype=dt, kernel=B.KERNEL_MATERIALISE)
             y_tile = ps.linear_batched(xd, n, out_dtype=dt, kernel=B.KERNEL_PANEL)
             torch.cuda.synchronize()
@@ -754,9 +755,9 @@ def test_materialised_path_through_the_images_own_scratch(B):
 
 def test_materialised_path_in_row_slabs_through_a_small_scratch(B):
     """A scratch with room for fewer rows than the weight has: the weight is restored and multiplied
-    slab by slab through it.  With the dense product's output tile held fixed (each of its three
+    slab by slab through it.  With the dense product's output tile held fixed (each of its four
     tiles in turn: 256 x 256, 128 x 256, 128 x 128 with the columns of a chunk split over two
-    halves of the workgroup) the bits are those of a scratch for the whole matrix -- the same
+    halves of the workgroup, 128 x 128 for long rows) the bits are those of a scratch for the whole matrix -- the same
     kernel does the same arithmetic per row -- for a slab count that leaves a short last slab and
     both output types; with the launcher's own choice of tile per slab the result holds the
     parity bound; a scratch below 1024 rows is refused."""
@@ -772,7 +773,7 @@ def test_materialised_path_in_row_slabs_through_a_small_scratch(B):
         for b in (70, 600):
             xd = _to_dev(x[:b])
             for dt in (torch.float16, torch.float32):
-                for tile in (1, 2, 3, 0):
+                for tile in (1, 2, 3, 4, 0):
                     B.set_option(B.OPT_DENSE_TILE, tile)
                     try:
                         y_full = ps.linear_materialised(xd, n, full, out_dtype=dt)

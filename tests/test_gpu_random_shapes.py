@@ -41,7 +41,7 @@ def _draw(rng):
     if mode == 5:                               # needs the activation scratch of an image packed for many tokens:
         max_batch = max(max_batch, 1024)        # at least 1024 rows of the dense weight fit it
     f32 = bool(rng.integers(0, 2))
-    tile = int(rng.integers(0, 4))              # dense product's output tile on the materialising paths (0: its own choice)
+    tile = int(rng.integers(0, 5))              # dense product's output tile on the materialising paths (0: its own choice)
     return out, inn, n, max_batch, batch, n_loaded, mode, f32, tile
 
 
