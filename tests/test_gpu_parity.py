@@ -308,10 +308,20 @@ def test_small_batch_through_the_decode_kernel(B, out, inn, n_slots):
         assert O.relative_error(y1, ref[:1]) <= TOL
 
 
-def test_degenerate_activations(B):
+@pytest.mark.parametrize("tiles", [0, 2, 4])
+def test_degenerate_activations(B, tiles):
     """x = 0 gives y = 0 exactly (the panel's quantisation scale is zero: nothing may divide by
     it); a one-hot x picks one column of W' diag(1/s); a huge and a tiny x keep the relative error
-    (the panel is quantised against its own maximum per block and column slab)."""
+    (the panel is quantised against its own maximum per block and column slab).  One token through this
+    stack is k_token's; a forced work split sends it to k_decode."""
+    B.set_option(B.OPT_DECODE_TILES, tiles)
+    try:
+        degenerate_activations(B)
+    finally:
+        B.set_option(B.OPT_DECODE_TILES, 0)
+
+
+def degenerate_activations(B):
     import torch
     out, inn, n = 1056, 2048, 3
     st = synth_stack(3, out, inn, n)
