@@ -276,8 +276,8 @@ __global__ __launch_bounds__(512, KSPLIT ? 4 : 1) void k_gemm(KParams p) {
     }
 }
 
-// The 128 x 128 tile where k_gemm's is bound by the arrival of its operands: long rows, and no more tiles than compute units (a slab of
-// 2048 rows x 2048 tokens is 256 of them).  2048 x 8192, 2048 tokens: 82 -> 71 us; 4096 x 14336, 1024 tokens: 134 -> 114.
+// The 128 x 128 tile where k_gemm's is bound by the arrival of its operands: long rows, and no more tiles for an XCD than it has compute
+// units (a slab of 2048 rows x 2048 tokens is 256 of them).  2048 x 8192, 2048 tokens: 82 -> 71 us; 4096 x 14336, 1024 tokens: 134 -> 114.
 // Without its loads it takes 52 us there, without its products 49: streams and products overlap in part.
 // k_gemm<2, true> stays for short rows, where the exchange of four column quarters costs more than is gained (1024 x 1024, 1024 tokens:
 // 11.5 us, this kernel 13.5), and for more tiles than compute units, where two of its workgroups share one (6144 x 2048, 1500
@@ -497,7 +497,11 @@ static int dense_tile(int out, int in, int batch) {
     int best = kTile256;
     for (int t = kTile128; t <= kTile128x128; ++t)
         if (tile_rounds_time_us(out, in, batch, t) < tile_rounds_time_us(out, in, batch, best)) best = t;
-    if (best == kTile128x128 && in >= 4096 && (out + 127) / 128 * ((batch + 127) / 128) <= 256) return kTileSplit;
+    // 333 random shapes with rows of 4096 columns and more: 0.90 of k_gemm<2, true>'s time in the mean, none above 1.013 of it.  An XCD
+    // has 32 compute units and takes every fourth row tile x every second token tile: where that is more than 32 tiles (odd numbers of
+    // token tiles) it takes two rounds, 5376 x 5888, 580 tokens: 82 us against 52.
+    const int per_xcd = ((out + 127) / 128 + 3) / 4 * (((batch + 127) / 128 + 1) / 2);
+    if (best == kTile128x128 && in >= 4096 && per_xcd <= 32) return kTileSplit;
     return best;
 }
 double dense_time_us(int out, int in, int batch) {

@@ -44,10 +44,11 @@ def test_a_long_row_takes_it():
     import torch
     import paper_2410_23918_amd as B
     g = torch.Generator(device="cuda:0").manual_seed(1)
-    for inn, split in ((4096, True), (2048, False)):
-        ps = B.PackedStack.empty(512, inn, 1, np.ones(inn, np.float32), max_batch=256)
-        wd = torch.randn((512, inn), generator=g, device="cuda:0").half()
-        x = torch.randn((256, inn), generator=g, device="cuda:0").half()
+    # 4224 rows x 800 tokens: 231 tiles, but 36 of them would be one XCD's, which has 32 compute units
+    for out, inn, batch, split in ((512, 4096, 256, True), (512, 2048, 256, False), (4224, 4096, 800, False), (4096, 4096, 900, True)):
+        ps = B.PackedStack.empty(out, inn, 1, np.ones(inn, np.float32), max_batch=batch)
+        wd = torch.randn((out, inn), generator=g, device="cuda:0").half()
+        x = torch.randn((batch, inn), generator=g, device="cuda:0").half()
         auto = ps.linear_dense(x, wd, out_dtype=torch.float32).clone()
         forced = {}
         try:
