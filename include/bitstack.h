@@ -247,6 +247,9 @@ int bitstack_linear(const void* x, const bitstack_weight_t* blocks, int n_loaded
  * each with its own n_loaded as the sorted stack leaves them, Section 2.2).
  * Same results as calling bitstack_linear(jobs[i].x, jobs[i].blocks, jobs[i].n_loaded,
  * jobs[i].y, stream) for i = 0..count-1, the whole list `repeat` times.
+ * (A merged launch has its own work split and one kernel for all its jobs, which need not be
+ * those of a job by itself: the order of the sums and the rounding may differ, y by no more
+ * than either may differ from the exact value, 2e-3 of its largest element.)
  * Up to four consecutive jobs that read the same x (the q/k/v or the gate/up projections
  * of a decoder layer) are independent of each other and are merged into one kernel
  * launch, provided they use different stacks, their outputs overlap neither each other

@@ -192,7 +192,9 @@ static int token_parts(int out, int in, int n_loaded, int part_slots) {
 
 // Estimated duration (microseconds; fitted to 900 stacks of 32 x 256 to 16384 x 14336 with up to 24 blocks): one workgroup per row tile
 // 4.4, with partial rows 6.1; two workgroups to a compute unit 1.2-2.1 more; from 512 workgroups on their number counts, V being
-// loaded anew for every row tile.
+// loaded anew for every row tile.  Merged launches (184 of 2 to 4 stacks) take 3 % longer than that, up to 17 % beyond 512 workgroups, and
+// what k_decode takes for the same is estimated too high: of 38 whose estimates were less than 3 us apart one was 24 % slower than
+// through k_decode and the mean 3 % faster, so these go there.
 double token_time_us(const LaunchArgs* a, int count) {
     long wgs = 0;
     int most = 1;
@@ -204,7 +206,7 @@ double token_time_us(const LaunchArgs* a, int count) {
         wgs += long(a[i].geo.out / kTileRows) * parts;
         most = parts > most ? parts : most;
     }
-    if (wgs > 512) return 5.2 + 0.0088 * wgs + 0.015 * most;
+    if (wgs > 512) return 5.2 + 0.0088 * wgs + 0.015 * most + (count > 1 ? 2.0 : 0.0);
     return (most == 1 ? 4.4 : 6.1) + (wgs > 256 ? 1.2 + 0.9 * (wgs - 256) / 256 : 0.0);
 }
 

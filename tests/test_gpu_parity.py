@@ -255,7 +255,8 @@ def test_blocks_loaded_and_offloaded_one_at_a_time(B):
 def test_job_list_merging_rules(B):
     """Jobs that read one x are merged four at a time; a stack that appears twice, an output that
     overlaps x or another output, or a different input width end a group.  Whatever the grouping,
-    every job's output must equal that of its own single launch."""
+    every job's output must equal that of its own single launch (all of these take the same kernel
+    with one partial row order either way; stacks of mixed sizes: tests/test_gpu_token.py)."""
     import torch
     stacks = [_pack(B, synth_stack(3, 160, 1024, 3, tag=t)) for t in range(6)]
     wide = _pack(B, synth_stack(3, 96, 2048, 2, tag=7))

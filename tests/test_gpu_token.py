@@ -126,3 +126,48 @@ def test_what_is_not_finite_stays_so(bad):
     y = ps.linear(x, 2)
     assert not torch.isfinite(y).any()
     assert not ps.linear(torch.zeros_like(x), 2).any()
+
+
+@pytest.mark.parametrize("inn,shapes,token", [
+    (1024, ((160, 3), (64, 2), (1056, 1)), True),
+    (2048, ((96, 9), (1024, 2)), True),
+    (4096, ((1024, 9), (4096, 9)), False),                   # the first alone is k_token's
+    (12288, ((256, 5), (320, 5), (1312, 1)), False),         # 786 workgroups: 14.7 us, through k_decode 12.0
+])
+def test_merged_launches(inn, shapes, token):
+    """A launch has one kernel for all its stacks: every output against fp64 and against the stack's own launch, which may be the
+    other kernel's."""
+    import torch
+    import paper_2410_23918_amd as B
+    g = torch.Generator(device="cuda:0").manual_seed(inn)
+    x = torch.randn((inn,), generator=g, device="cuda:0").half()
+    bits = torch.arange(32, device="cuda:0", dtype=torch.int32)
+    items, wants = [], []
+    for out, n in shapes:
+        ps = B.PackedStack.empty(out, inn, n, np.ones(inn, np.float32))
+        want = torch.zeros(out, device="cuda:0", dtype=torch.float64)
+        for _ in range(n):
+            words = torch.randint(-2**31, 2**31, (out, inn // 32), generator=g, device="cuda:0", dtype=torch.int64).to(torch.int32)
+            u = (0.1 * torch.randn((out, 16), generator=g, device="cuda:0")).half()
+            v = (0.1 * torch.randn((inn, 16), generator=g, device="cuda:0")).half()
+            ps.push_block_device(words, u, v)
+            m = u.double() @ v.double().t().contiguous()
+            want += torch.where(((words[:, :, None] >> bits) & 1).reshape(out, inn).bool(), m, -m) @ x.double()
+        items.append((x, ps, n, torch.full((out,), float("nan"), dtype=torch.float16, device="cuda:0")))
+        wants.append(want)
+    plan = B.TokenPlan(B.make_jobs(items))
+    assert plan.steps == 1
+    plan.launch()
+    got = [y.clone() for *_, y in items]
+    single = [ps.linear(x, n).clone() for _, ps, n, _ in items]
+    B.set_option(B.OPT_DECODE_EARLY, 3)   # what k_decode takes by itself
+    try:
+        B.TokenPlan(B.make_jobs(items)).launch()
+        torch.cuda.synchronize()
+    finally:
+        B.set_option(B.OPT_DECODE_EARLY, 0)
+    assert all(torch.equal(a, y) for a, (*_, y) in zip(got, items)) != token
+    for a, b, want in zip(got, single, wants):
+        # either kernel's error is 2e-3 of the largest output at most
+        assert (a.double() - want).abs().max() <= 2e-3 * want.abs().max()
+        assert (a.double() - b.double()).abs().max() <= 2e-3 * want.abs().max()
