@@ -43,25 +43,41 @@ constexpr int kTokenWaves = 8;
 __device__ __forceinline__ void add_class(float (&s)[4], v16f a, const FlipMasks& m, float xs) {
     const unsigned top = 0x80000000u;
     a[3] = __int_as_float(__float_as_int(a[3]) ^ int(m.w[0] & top));
-#define BS_FLIP(E, M, B) "v_xor_b32_sdwa " E ", " E ", " M " dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_" B "\n\t"
-#define BS_ADD(S, E, N) "v_fmac_f32_dpp " S ", %[xs], " E " row_newbcast:" N " row_mask:0xf bank_mask:0xf\n\t"
-    asm(BS_FLIP("%4", "%[m0]", "0") BS_FLIP("%5", "%[m0]", "1") BS_FLIP("%6", "%[m0]", "2")
-        BS_FLIP("%7", "%[m1]", "0") BS_FLIP("%8", "%[m1]", "1") BS_FLIP("%9", "%[m1]", "2")
-        BS_FLIP("%11", "%[m2]", "0") BS_FLIP("%12", "%[m2]", "1") BS_FLIP("%13", "%[m2]", "2")
-        BS_FLIP("%15", "%[m3]", "0") BS_FLIP("%16", "%[m3]", "1") BS_FLIP("%17", "%[m3]", "2")
+    asm("v_xor_b32_sdwa %4, %4, %[m0] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_0\n\t"
+        "v_xor_b32_sdwa %5, %5, %[m0] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_1\n\t"
+        "v_xor_b32_sdwa %6, %6, %[m0] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_2\n\t"
+        "v_xor_b32_sdwa %7, %7, %[m1] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_0\n\t"
+        "v_xor_b32_sdwa %8, %8, %[m1] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_1\n\t"
+        "v_xor_b32_sdwa %9, %9, %[m1] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_2\n\t"
+        "v_xor_b32_sdwa %11, %11, %[m2] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_0\n\t"
+        "v_xor_b32_sdwa %12, %12, %[m2] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_1\n\t"
+        "v_xor_b32_sdwa %13, %13, %[m2] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_2\n\t"
+        "v_xor_b32_sdwa %15, %15, %[m3] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_0\n\t"
+        "v_xor_b32_sdwa %16, %16, %[m3] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_1\n\t"
+        "v_xor_b32_sdwa %17, %17, %[m3] dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_2\n\t"
         "v_bitop3_b32 %10, %10, %[m1], %[top] bitop3:0x78\n\t"   // a ^ (m & top)
         "v_bitop3_b32 %14, %14, %[m2], %[top] bitop3:0x78\n\t"
         "v_bitop3_b32 %18, %18, %[m3], %[top] bitop3:0x78\n\t"
-        BS_ADD("%0", "%4", "0") BS_ADD("%1", "%5", "1") BS_ADD("%2", "%6", "2") BS_ADD("%3", "%[a3]", "3")
-        BS_ADD("%0", "%7", "4") BS_ADD("%1", "%8", "5") BS_ADD("%2", "%9", "6") BS_ADD("%3", "%10", "7")
-        BS_ADD("%0", "%11", "8") BS_ADD("%1", "%12", "9") BS_ADD("%2", "%13", "10") BS_ADD("%3", "%14", "11")
-        BS_ADD("%0", "%15", "12") BS_ADD("%1", "%16", "13") BS_ADD("%2", "%17", "14") BS_ADD("%3", "%18", "15")
+        "v_fmac_f32_dpp %0, %[xs], %4 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %[xs], %5 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %[xs], %6 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %[xs], %[a3] row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %[xs], %7 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %[xs], %8 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %[xs], %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %[xs], %10 row_newbcast:7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %[xs], %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %[xs], %12 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %[xs], %13 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %[xs], %14 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %[xs], %15 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %[xs], %16 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %[xs], %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %[xs], %18 row_newbcast:15 row_mask:0xf bank_mask:0xf"
         : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]),
           "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]), "+v"(a[10]),
           "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15])
         : [m0] "v"(m.w[0]), [m1] "v"(m.w[1]), [m2] "v"(m.w[2]), [m3] "v"(m.w[3]), [a3] "v"(a[3]), [top] "v"(top), [xs] "v"(xs));
-#undef BS_FLIP
-#undef BS_ADD
 }
 
 // one workgroup: part `part` of p.n_ks of row tile rt
