@@ -305,9 +305,9 @@ int bitstack_weight_shape(const bitstack_weight_t* w, int* out, int* in, int* k,
 // dense weight, restoring it once and one dense product wins for prefill-sized batches.
 // Up to 64 tokens these are the estimates that launch_panel decides by.  Beyond, the choice between the batch path and restoring
 // compares tile_time_us, which is up to 1.9 times too high up to 1024 tokens and does not know k_batch, with restore_time_us, which
-// describes a slower kernel than k_restore, and dense_time_us, which is up to 3 times too low for small matrices: of 3497 random cases of 16
-// to 2048 tokens with a scratch for the whole weight the path taken is 6.5 % slower than the other on average, and
-// 306 times by more than 30 % (up to 2.7 times), mostly by restoring a matrix of few rows or few blocks.
+// describes a slower kernel than k_restore, and dense_time_us, which is up to 3 times too low for small matrices: of 800 random cases of 16
+// to 2048 tokens with a scratch for the whole weight the path taken is 3.8 % slower than the other on average, and
+// 45 times by more than 30 % (up to 1.8 times), mostly by restoring a matrix of few rows or few blocks.
 // Rows of the weight a scratch buffer of this size holds at a time on the materialising path
 // (multiples of 256, the dense kernel's tile height; the whole matrix if it fits; 0: too small to
 // be worth it -- below 1024 rows the dense product no longer fills the chip).

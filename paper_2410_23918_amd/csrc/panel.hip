@@ -988,9 +988,9 @@ double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
     return (steps == 1 ? 1.8 : 1.35) + rounds * (3.78 + (steps + 2) / 3 * 3 * (0.585 + 0.176 * fill) + 0.617 * pairs + (steps % 3 ? 0.68 : 0.0)) +
            (split > 1 ? 1.33 + 0.0048 * batch * split : 0.0);
 }
-// k_tile: per pair of column chunks ~0.9 us per block for the rebuild + 12-14 us for the product
-// (14 when several token tiles of a row tile run at once, 6.5 up to 256 tokens, where only one
-// wavefront per SIMD has tokens to multiply); 15 % less of both when the chip is not full.
+// What the choice between k_tile and the other paths goes by: constants of the dispatch, fitted when a pair of column chunks took
+// ~0.9 us per block for the rebuild (0.63 now) + 12-14 us for the product (14 when several token tiles of a row tile run at once, 6.5
+// up to 256 tokens, where only one wavefront per SIMD has tokens to multiply); 15 % less of both when the chip is not full.
 double tile_time_us(int out, int in, int batch, int n_loaded) {
     const int row_tiles = (out + 2 * kTileRows - 1) / (2 * kTileRows), chunk_pairs = (in / kChunkCols + 1) / 2;
     const int wgs = row_tiles * ((batch + kTileTokens - 1) / kTileTokens);

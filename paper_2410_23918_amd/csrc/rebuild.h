@@ -37,7 +37,6 @@ namespace bitstack {
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
@@ -274,8 +273,8 @@ __device__ __forceinline__ void next_class(SignWords& d) {
 }
 
 // One block onto the wavefront's unit.  vnext, snext: addresses of the next step.  FIRST: the accumulators start
-// from zero.  A SIMD issues one vector or matrix instruction per four cycles: what counts is the number of instructions, 23
-// per class.
+// from zero.  A SIMD issues one vector or matrix instruction per four cycles: what counts is the number of instructions, 22
+// vector ones and a product per class.
 template <bool FIRST, int RT>
 __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned vaddr, unsigned vnext, unsigned snext) {
     SignWords d;
