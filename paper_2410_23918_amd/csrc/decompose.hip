@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "kparams.h"
 #include "layout.h"
 
 namespace bitstack {
@@ -27,7 +28,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef double v4d __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) volatile double lds_double;
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 constexpr int kL = 32;        // subspace width: rank 16 + 16 columns of oversampling
 constexpr int kDcTile = 128;  // output indices per workgroup of the fp32 product
@@ -171,7 +172,8 @@ __global__ __launch_bounds__(256) void k_dc_residual(const float* W, const float
 // indices x 32 columns, two reduction indices per instruction):
 //   P[slice][j][c] = sum_{o in slice} |R[o][j]| X[o][c]     (M = in, K = out)
 // A workgroup (4 wavefronts) owns 128 output indices and one slice of the reduction range; the residual chunk goes to LDS
-// as As[reduction index][output index] (|.| applied on the way).  The slices are added up by the kernel that reads the product.
+// as As[reduction index][output index] (|.| applied on the way), the next chunk's loads in flight during the products (4096 x 4096: 22
+// -> 17 us).  The slices are added up by the kernel that reads the product.
 __global__ __launch_bounds__(256) void k_dc_mul(const float* R, const float* X, float* P, int out, int in, int chunks_per_slice) {
     __shared__ float As[kDcChunk][kDcTile + 4];
     __shared__ float Xs[kDcChunk][kL];
@@ -184,24 +186,31 @@ __global__ __launch_bounds__(256) void k_dc_mul(const float* R, const float* X, 
     v16f acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    for (int ch = c_begin; ch < c_end; ++ch) {
+    float4 a[4], x;
+    auto request = [&](int ch) {
         const int k0 = ch * kDcChunk;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int idx = tid + 256 * i, kk = idx >> 5, q = idx & 31;   // row k0 + kk, columns m0 + 4 q ..
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (m0 + 4 * q < in) v = *reinterpret_cast<const float4*>(R + size_t(k0 + kk) * in + m0 + 4 * q);
-            *reinterpret_cast<float4*>(&As[kk][4 * q]) = make_float4(fabsf(v.x), fabsf(v.y), fabsf(v.z), fabsf(v.w));
+            a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (m0 + 4 * q < in) a[i] = *reinterpret_cast<const float4*>(R + size_t(k0 + kk) * in + m0 + 4 * q);
         }
-        {
-            const int kk = tid >> 3, q = tid & 7;
-            *reinterpret_cast<float4*>(&Xs[kk][4 * q]) = *reinterpret_cast<const float4*>(X + size_t(k0 + kk) * kL + 4 * q);
+        x = *reinterpret_cast<const float4*>(X + size_t(k0 + (tid >> 3)) * kL + 4 * (tid & 7));
+    };
+    if (c_begin < c_end) request(c_begin);
+    for (int ch = c_begin; ch < c_end; ++ch) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int idx = tid + 256 * i, kk = idx >> 5, q = idx & 31;
+            *reinterpret_cast<float4*>(&As[kk][4 * q]) = make_float4(fabsf(a[i].x), fabsf(a[i].y), fabsf(a[i].z), fabsf(a[i].w));
         }
-        __syncthreads();
+        *reinterpret_cast<float4*>(&Xs[tid >> 3][4 * (tid & 7)]) = x;
+        lds_barrier();
+        if (ch + 1 < c_end) request(ch + 1);
 #pragma unroll
         for (int kk = 0; kk < kDcChunk; kk += 2)
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[kk + hl][wave * 32 + ln], Xs[kk + hl][ln], acc, 0, 0, 0);
-        __syncthreads();
+        lds_barrier();
     }
     // D[i = output index][n = column]: lane (column ln), register v holds index 8*(v/4) + 4*hl + v%4
     float* Ps = P + size_t(blockIdx.y) * in * kL;
@@ -219,9 +228,9 @@ __global__ __launch_bounds__(256) void k_dc_mul(const float* R, const float* X, 
 // than the oversampling and the Rayleigh-Ritz step, which works on the fp32 residual, absorb.  A workgroup owns TILES x 32
 // output indices (two tiles, so that an operand of X serves two, where the grid fills the chip with them) and four slices of
 // the reduction range, one for each of its wavefronts; they add up in LDS.  Bound by the loads of A, of which every wavefront
-// keeps 8 or 16 KiB in flight: 4096 x 4096 8 us a product (through LDS, from row-major copies: 11.5), 14336 x 4096 20 us (24-49).
-constexpr int kHAhead = 8;
-template <int TILES>
+// keeps 16 KiB in flight: 4096 x 4096 8.4 us a product (8.9 with 8 KiB; through LDS, from row-major copies: 11.5), 14336 x 4096 20 us
+// (24-49).
+template <int TILES, int AHEAD>
 __global__ __launch_bounds__(256) void k_dc_mulh(const uint4* A, const uint4* X, float* P, int M, int K, int steps_per_wave) {
     __shared__ float red[4][TILES][16][64];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -254,7 +263,7 @@ __global__ __launch_bounds__(256) void k_dc_mulh(const uint4* A, const uint4* X,
                 acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[u][t]), __builtin_bit_cast(v8bf, x[u]), acc[t], 0, 0, 0);
     };
     int st = s_begin;
-    for (; st + kHAhead <= s_end; st += kHAhead) products(std::integral_constant<int, kHAhead>{}, st);
+    for (; st + AHEAD <= s_end; st += AHEAD) products(std::integral_constant<int, AHEAD>{}, st);
     for (; st + 2 <= s_end; st += 2) products(std::integral_constant<int, 2>{}, st);   // K is a multiple of 32
 #pragma unroll
     for (int t = 0; t < TILES; ++t)
@@ -353,141 +362,220 @@ __global__ __launch_bounds__(1024) void k_dc_gram(const float* P, int slices, bo
     Gpart[size_t(blockIdx.x) * (kL * kL) + tid] = (Gq[0][tid] + Gq[1][tid]) + (Gq[2][tid] + Gq[3][tid]);
 }
 
-// the Gram matrix from its parts, in a fixed order, into LDS: THREADS threads, the loads of up to 16 parts in flight together
-template <int THREADS>
+// the Gram matrix from its parts, in a fixed order, into LDS: THREADS threads, the loads of 32 values in flight together.  Buffer
+// loads: past the last part they bring zeros.  LOWER: without the tile above the diagonal (columns 16 on of rows 0-15), by the first
+// 768 of 1024 threads: what a compute unit can take in (256 KiB from 32 parts) is half of the time.
+template <int THREADS, bool LOWER>
 __device__ __forceinline__ void gram_sum(const double* Gpart, int parts, double (*Gs)[kL + 1]) {
-    constexpr int N = kL * kL / THREADS;
+    static_assert(!LOWER || THREADS == kL * kL, "");
+    constexpr int N = kL * kL / THREADS, kAhead = 32 / N;
+    __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(Gpart), 0, parts * (kL * kL * 8), 0x00020000);
+    const int t = int(threadIdx.x);
+    int at = t;
+    if constexpr (LOWER) {
+        if (t >= 768) return;
+        at = (t < 256 ? t >> 4 : 16 + ((t >> 4) & 15)) * kL + (t < 512 ? 0 : 16) + (t & 15);
+    }
     double acc[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) acc[i] = 0.0;
-    for (int p0 = 0; p0 < parts; p0 += 16) {
-        double v[16][N];
+#pragma unroll 1
+    for (int p0 = 0; p0 < parts; p0 += kAhead) {
+        v2u v[kAhead][N];
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
+        for (int u = 0; u < kAhead; ++u)
 #pragma unroll
-            for (int i = 0; i < N; ++i) v[u][i] = p0 + u < parts ? Gpart[size_t(p0 + u) * (kL * kL) + i * THREADS + threadIdx.x] : 0.0;
+            for (int i = 0; i < N; ++i)
+                v[u][i] = __builtin_amdgcn_raw_buffer_load_b64(src, at * 8, (p0 + u) * (kL * kL * 8) + i * THREADS * 8, 0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
+        for (int u = 0; u < kAhead; ++u)
 #pragma unroll
-            for (int i = 0; i < N; ++i) acc[i] += v[u][i];   // the order of the additions is fixed
+            for (int i = 0; i < N; ++i) acc[i] += __builtin_bit_cast(double, v[u][i]);   // the order of the additions is fixed
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) Gs[(i * THREADS + threadIdx.x) / kL][(i * THREADS + threadIdx.x) % kL] = acc[i];
+    for (int i = 0; i < N; ++i) Gs[(i * THREADS + at) / kL][(i * THREADS + at) % kL] = acc[i];
 }
 
-// Columns made orthonormal: G = Y^T Y = L L^T (Cholesky), Q L^T = Y for every row of Y (m x kL), so that Q = Y L^-T.  Every
-// workgroup factors G by itself (256 KiB of parts from cache) and solves
-// its 256 rows, one per thread.
-//
-// The factorisation is one wavefront's, right-looking, fp64: lane (half h, row r) keeps columns h, h + 2, ... of row r in
-// registers, and a step publishes its column in LDS for all rows (no barrier: LDS operations of a wavefront are in order).
-// Per step a trip through LDS, one division and at most 16 updates; the square roots are taken together at the end.
-//   Ls: L[r][c] for c < r, and 1 / L[r][r] on the diagonal (what the substitution multiplies by); all zero for an
-//   all-zero Y (no direction to normalise: Q = 0).
-// The substitution q_c = (y_c - sum_{i < c} q_i L[c][i]) / L[c][c] runs by columns: once q_c is known it is taken off all later
-// entries, which do not depend on each other (the same operations on each entry in the same order as row by row).
-// 4096 rows: 16 us (factorisation and solve as two kernels: 15 + 7 us and a launch); bound by the chain of the 32 steps.
-// Q goes out as fp32 (Q, if not null) and as bf16 in fragment order (Xf).  Q and Y may be the same array.
-__global__ __launch_bounds__(256) void k_dc_orth(const double* Gpart, int parts, const float* Y, float* Q, uint4* Xf, int m) {
-    __shared__ double Gs[kL][kL + 1];
-    // passed between the lanes of a wavefront: volatile, and by LDS pointers (a volatile access to a shared array is a flat
-    // one); [parity of the step][kL], and a place for what the other half writes
-    __shared__ double col_lds[3 * kL];
-    lds_double* const col = (lds_double*)col_lds;
-    __shared__ __attribute__((aligned(16))) float Lt[kL][kL];   // Lt[c][r] = L[r][c]
-    __shared__ float Qs[256][kL + 1];
-    const int tid = threadIdx.x, row = blockIdx.x * 256 + tid;
-    float q[kL];
+// G = Y^T Y = L D L^T (fp64), by one wavefront, G in LDS: in lds.pivoted the columns of L D below (and on) the diagonal, in lds.over the
+// reciprocal pivots.  False for an all-zero Y (no direction to normalise).
+// The matrix stays in the accumulators of the fp64 matrix cores and is eliminated four columns at a time: every lane takes the four
+// columns of its row (lanes 32 on: the same rows again) and the 4 x 4 diagonal block from LDS, eliminates within them by itself, and
+// one 16x16x4 product per tile (its four terms one after the other) takes the four columns off what is left.  Each entry meets the same operations in the same order as
+// column by column; but there are eight trips through LDS instead of 32, and a loop's code instead of that of 32 steps.
+struct FactorLds {
+    double panel[kL][4], scaled[kL][4];   // [row][column of the four]: as they are, eliminated and over their pivots
+    double pivoted[kL / 4][kL][4];        // [four columns][row][column]: eliminated
+    double over[kL];
+};
+__device__ __forceinline__ bool gram_factor(const double (*Gs)[kL + 1], FactorLds& lds) {
+    auto order = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); };   // LDS operations of a wavefront execute in order
+    const int lane = threadIdx.x & 63, row = lane >> 4, col = lane & 15, r = lane & 31;
+    double tr = 0.0;
 #pragma unroll
-    for (int g = 0; g < kL / 4; ++g) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row < m) v = *reinterpret_cast<const float4*>(Y + size_t(row) * kL + 4 * g);
-        q[4 * g] = v.x; q[4 * g + 1] = v.y; q[4 * g + 2] = v.z; q[4 * g + 3] = v.w;
-    }
-    gram_sum<256>(Gpart, parts, Gs);
-    __syncthreads();
-    if (tid < 64) {
-        const int h = tid >> 5, r = tid & 31;
-        double tr = 0.0;
+    for (int k = 0; k < kL; ++k) tr += Gs[k][k];
+    if (!(tr > 0.0)) return false;   // uniform over the wavefront
+    const double ridge = tr * 1e-13;   // a tiny ridge keeps the factorisation defined if the columns are (numerically) dependent
+    // tiles (0, 0), (1, 0), (1, 1), register v: row 16 rt + 4 v + row, column 16 ct + col
+    v4d acc[3];
 #pragma unroll
-        for (int k = 0; k < kL; ++k) tr += Gs[k][k];
-        // a tiny ridge keeps the factorisation defined if the columns are (numerically) dependent
-        const double ridge = tr * 1e-13;
-        double a[kL / 2], inv[kL / 2] = {};   // inv: 1 / pivot of the columns
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int i = 0; i < kL / 2; ++i) a[i] = Gs[r][2 * i + h] + (r == 2 * i + h ? ridge : 0.0);
-        if (tr > 0.0) {   // uniform over the wavefront
+        for (int v = 0; v < 4; ++v) {
+            const int i = (k ? 16 : 0) + 4 * v + row, j = (k == 2 ? 16 : 0) + col;
+            acc[k][v] = Gs[i][j] + (i == j ? ridge : 0.0);
+        }
 #pragma unroll
-            for (int j = 0; j < kL; ++j) {
-                lds_double* const cj = col + (j & 1) * kL;
-                (h == (j & 1) ? cj : col + 2 * kL)[r] = a[j >> 1];
-                const double d0 = cj[j], mine = cj[r];
-                const double d = d0 > 0.0 ? d0 : ridge;
-                const double w = 1.0 / d;
-                inv[j >> 1] = h == (j & 1) ? w : inv[j >> 1];
-                const double t = mine * w;
+    for (int ct = 0; ct < 2; ++ct)
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+            const int jb = 4 * ct + q;
+            order();
+            if ((col >> 2) == q) {
 #pragma unroll
-                for (int i = (j + 1) / 2; i < kL / 2; ++i) {
-                    const int c = 2 * i + h;
-                    const double cc = cj[c];
-                    if (c > j) a[i] = fma(-t, cc, a[i]);
+                for (int v = 0; v < 4; ++v) {
+                    if (ct == 0) lds.panel[4 * v + row][col & 3] = acc[0][v];
+                    lds.panel[16 + 4 * v + row][col & 3] = acc[ct ? 2 : 1][v];
+                }
+            }
+            order();
+            double d[4][4], p[4];   // the diagonal block's lower half, the lane's row
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                p[a] = lds.panel[r][a];
+#pragma unroll
+                for (int b = 0; b <= a; ++b) d[a][b] = lds.panel[4 * jb + a][b];
+            }
+            double w[4], t[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                w[k] = 1.0 / (d[k][k] > 0.0 ? d[k][k] : ridge);
+                t[k] = p[k] * w[k];
+#pragma unroll
+                for (int b = k + 1; b < 4; ++b) {
+                    p[b] = fma(-t[k], d[b][k], p[b]);
+#pragma unroll
+                    for (int a = b; a < 4; ++a) d[a][b] = fma(-(d[a][k] * w[k]), d[b][k], d[a][b]);
                 }
             }
 #pragma unroll
-            for (int i = 0; i < kL / 2; ++i) {
-                const int c = 2 * i + h;
-                const double root = sqrt(inv[i]);   // 1 / L[c][c]
-                Lt[c][r] = r > c ? float(a[i] * root) : r == c ? float(root) : 0.f;
+            for (int k = 0; k < 4; ++k) {
+                lds.scaled[r][k] = t[k];
+                lds.pivoted[jb][r][k] = p[k];
             }
-        } else {
+            if (lane == 0) {
 #pragma unroll
-            for (int i = 0; i < kL / 2; ++i) Lt[2 * i + h][r] = 0.f;
+                for (int k = 0; k < 4; ++k) lds.over[4 * jb + k] = w[k];
+            }
+            order();
+            // operands: lane l holds index l % 16 of column l / 16
+            const double s1 = -lds.scaled[16 + col][row], p1 = lds.pivoted[jb][16 + col][row];
+            if (ct == 0) {
+                const double s0 = -lds.scaled[col][row], p0 = lds.pivoted[jb][col][row];
+                acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(s0, p0, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(s1, p0, acc[1], 0, 0, 0);
+            }
+            acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(s1, p1, acc[2], 0, 0, 0);
         }
+    return true;
+}
+
+// q_I += l_I minus for I = C + 1 .. 31, l_I in lane I % 16 of every row of sixteen lanes (lo: I < 16, hi).  The compiler does not fold
+// the row operation into the multiply-add, and it does not know that the statement is a vector instruction: lo and hi come from LDS, and
+// the values of q are read two instructions behind at the earliest (tests/test_asm_distances_decompose.py).
+template <int I>
+__device__ __forceinline__ void fma_row_lane(float& q, float l, float minus) {
+    asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(q) : "v"(l), "v"(minus), "n"(I % 16));
+}
+template <int C, int I = C + 1>
+__device__ __forceinline__ void take_off(float (&q)[kL], float lo, float hi, float minus) {
+    if constexpr (I < kL) {
+        fma_row_lane<I>(q[I], I < 16 ? lo : hi, minus);
+        take_off<C, I + 1>(q, lo, hi, minus);
     }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < kL; ++c) {
-        q[c] *= Lt[c][c];
-#pragma unroll
-        for (int i = c + 1; i < kL; ++i) q[i] = fmaf(-q[c], Lt[c][i], q[i]);
+}
+// columns C to END - 1; their rows of L are requested together
+template <int C, int END>
+__device__ __forceinline__ void substitute(float (&q)[kL], const float (&lo)[8], const float (&hi)[8], const float (&diagonal)[8]) {
+    if constexpr (C < END) {
+        q[C] *= diagonal[C % 8];
+        take_off<C>(q, lo[C % 8], hi[C % 8], -q[C]);
+        substitute<C + 1, END>(q, lo, hi, diagonal);
     }
-    if (Q && row < m) {
+}
+template <int C>
+__device__ __forceinline__ void read_columns(const float (*Lt)[kL], int i, float (&lo)[8], float (&hi)[8], float (&diagonal)[8]) {
 #pragma unroll
-        for (int g = 0; g < kL / 4; ++g)
-            *reinterpret_cast<float4*>(Q + size_t(row) * kL + 4 * g) = make_float4(q[4 * g], q[4 * g + 1], q[4 * g + 2], q[4 * g + 3]);
-    }
-#pragma unroll
-    for (int c = 0; c < kL; ++c) Qs[tid][c] = q[c];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int idx = tid + 256 * i, c = idx % kL, k8 = idx / kL;
-        if (int(blockIdx.x) * 256 + 8 * k8 < m) Xf[frag_piece(c, blockIdx.x * 32 + k8, m)] = bf16_piece(&Qs[8 * k8][c], kL + 1);
+    for (int k = 0; k < 8; ++k) {
+        lo[k] = Lt[C + k][i];
+        hi[k] = Lt[C + k][16 + i];
+        diagonal[k] = Lt[C + k][C + k];
     }
 }
 
-// Q[r][c] = sum_i Y[r][i] T[i][c], c < kRank, rounded to fp16 (nearest even)
-__global__ __launch_bounds__(256) void k_dc_apply(const float* Y, const float* T, __half* Q, int m) {
-    __shared__ float Ts[kL][kRank];
-    for (int idx = threadIdx.x; idx < kL * kRank; idx += 256) Ts[idx / kRank][idx % kRank] = T[idx];
-    __syncthreads();
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= m) return;
-    float y[kL];
+// Columns made orthonormal: G = Y^T Y = L L^T, Q L^T = Y for every row of Y (m x kL), so that Q = Y L^-T.  Every workgroup factors G by
+// itself (parts from cache, summed by 768 threads with 32 loads each in flight) and solves kOrthRows rows, one per thread.  4096 rows:
+// 12.3 us, of which the parts take 3.9, the factorisation 4.9 and the substitution 2.0 (16.3 with the factorisation by columns, 4.9 and
+// more for its code, and L broadcast from LDS).  Bound by those three chains.
+//
+// The substitution q_c = (y_c - sum_{i < c} q_i L[c][i]) / L[c][c] runs by columns: once q_c is known it is taken off all later
+// entries, which do not depend on each other (the same operations on each entry in the same order as row by row).  A row of sixteen
+// lanes keeps a column of L in two registers and the multiply-adds take it from there: read from LDS as every lane needs it, the 528
+// broadcast values took 3.7 us.
+// Q goes out as fp32 (Q, if not null) and as bf16 in fragment order (Xf).  Q and Y may be the same array.
+constexpr int kOrthThreads = 1024, kOrthRows = 128;
+__global__ __launch_bounds__(kOrthThreads) void k_dc_orth(const double* Gpart, int parts, const float* Y, float* Q, uint4* Xf, int m) {
+    __shared__ double Gs[kL][kL + 1];
+    __shared__ FactorLds lds;
+    __shared__ __attribute__((aligned(16))) float Lt[kL][kL];   // Lt[c][r] = L[r][c] for c < r, 1 / L[r][r] on the diagonal
+    __shared__ float Qs[kOrthRows][kL + 1];
+    __shared__ int nonzero;
+    const int tid = threadIdx.x, row = blockIdx.x * kOrthRows + tid;
+    const bool mine = tid < kOrthRows && row < m;
+    float q[kL];
+    if (tid < kOrthRows) {
 #pragma unroll
-    for (int q = 0; q < kL / 4; ++q) {
-        const float4 v = *reinterpret_cast<const float4*>(Y + size_t(r) * kL + 4 * q);
-        y[4 * q] = v.x; y[4 * q + 1] = v.y; y[4 * q + 2] = v.z; y[4 * q + 3] = v.w;
+        for (int g = 0; g < kL / 4; ++g) {
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (mine) v = *reinterpret_cast<const float4*>(Y + size_t(row) * kL + 4 * g);
+            q[4 * g] = v.x; q[4 * g + 1] = v.y; q[4 * g + 2] = v.z; q[4 * g + 3] = v.w;
+        }
     }
-    float o[kRank];
+    gram_sum<kOrthThreads, true>(Gpart, parts, Gs);
+    __syncthreads();
+    if (tid < 64) {
+        const bool ok = gram_factor(Gs, lds);
+        if (tid == 0) nonzero = ok;
+    }
+    __syncthreads();
+    {
+        const int c = tid / kL, r = tid % kL;
+        const double root = nonzero ? sqrt(lds.over[c]) : 0.0;   // 1 / L[c][c]
+        Lt[c][r] = !nonzero ? 0.f : r > c ? float(lds.pivoted[c / 4][r][c % 4] * root) : r == c ? float(root) : 0.f;
+    }
+    __syncthreads();
+    if (tid < kOrthRows) {
+        const int i = tid & 15;
+        float lo[2][8], hi[2][8], diagonal[2][8];
+        read_columns<0>(Lt, i, lo[0], hi[0], diagonal[0]);
+        read_columns<8>(Lt, i, lo[1], hi[1], diagonal[1]);
+        substitute<0, 8>(q, lo[0], hi[0], diagonal[0]);
+        read_columns<16>(Lt, i, lo[0], hi[0], diagonal[0]);
+        substitute<8, 16>(q, lo[1], hi[1], diagonal[1]);
+        read_columns<24>(Lt, i, lo[1], hi[1], diagonal[1]);
+        substitute<16, 24>(q, lo[0], hi[0], diagonal[0]);
+        substitute<24, 32>(q, lo[1], hi[1], diagonal[1]);
 #pragma unroll
-    for (int c = 0; c < kRank; ++c) o[c] = 0.f;
-#pragma unroll
-    for (int i = 0; i < kL; ++i)
-#pragma unroll
-        for (int c = 0; c < kRank; ++c) o[c] = fmaf(y[i], Ts[i][c], o[c]);
-#pragma unroll
-    for (int c = 0; c < kRank; ++c) Q[size_t(r) * kRank + c] = __float2half_rn(o[c]);
+        for (int c = 0; c < kL; ++c) Qs[tid][c] = q[c];
+    }
+    __syncthreads();
+    const int c = tid % kL, k8 = tid / kL;
+    if (k8 < kOrthRows / 8 && int(blockIdx.x) * kOrthRows + 8 * k8 < m)
+        Xf[frag_piece(c, blockIdx.x * (kOrthRows / 8) + k8, m)] = bf16_piece(&Qs[8 * k8][c], kL + 1);
+    if (Q) {
+        const int r = tid >> 3, g = tid & 7, at = int(blockIdx.x) * kOrthRows + r;
+        if (at < m) *reinterpret_cast<float4*>(Q + size_t(at) * kL + 4 * g) = make_float4(Qs[r][4 * g], Qs[r][4 * g + 1], Qs[r][4 * g + 2], Qs[r][4 * g + 3]);
+    }
 }
 
 // 1 / sqrt(x) for x > 0 in fp64: the hardware's estimate and two Newton steps
@@ -498,82 +586,130 @@ __device__ __forceinline__ double rsqrt64(double x) {
     return y;
 }
 
+// U = Q Tu, V = Z Tv (kRank columns), rounded to fp16 (nearest even); 64 rows per workgroup, the out side's first, thread = four
+// columns of a row.  One launch for both, 4.5 us at 4096 x 4096; a launch each with a row per thread took 6.3 twice.
+__global__ __launch_bounds__(256) void k_dc_apply(const float* Q, const float* Tu, __half* U, int out, const float* Z, const float* Tv,
+                                                  __half* V, int in) {
+    __shared__ __attribute__((aligned(16))) float Ts[kL][kRank];
+    __shared__ float Ys[64][kL + 1];
+    const int tid = threadIdx.x, wgs = (out + 63) / 64;
+    const bool first = int(blockIdx.x) < wgs;
+    const float* const Y = first ? Q : Z;
+    const int m = first ? out : in, row0 = (int(blockIdx.x) - (first ? 0 : wgs)) * 64;
+    for (int idx = tid; idx < kL * kRank; idx += 256) Ts[idx / kRank][idx % kRank] = (first ? Tu : Tv)[idx];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int idx = tid + 256 * i, r = idx >> 3, q = idx & 7;
+        const float4 v = *reinterpret_cast<const float4*>(Y + size_t(min(row0 + r, m - 1)) * kL + 4 * q);
+        Ys[r][4 * q] = v.x; Ys[r][4 * q + 1] = v.y; Ys[r][4 * q + 2] = v.z; Ys[r][4 * q + 3] = v.w;
+    }
+    __syncthreads();
+    const int r = tid >> 2, c = 4 * (tid & 3);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int i = 0; i < kL; ++i) {
+        const float y = Ys[r][i];
+        const float4 w = *reinterpret_cast<const float4*>(&Ts[i][c]);
+        o.x = fmaf(y, w.x, o.x); o.y = fmaf(y, w.y, o.y); o.z = fmaf(y, w.z, o.z); o.w = fmaf(y, w.w, o.w);
+    }
+    if (row0 + r >= m) return;
+    __half* const dst = (first ? U : V) + size_t(row0 + r) * kRank + c;   // the caller's arrays: two-byte alignment
+    dst[0] = __float2half_rn(o.x); dst[1] = __float2half_rn(o.y); dst[2] = __float2half_rn(o.z); dst[3] = __float2half_rn(o.w);
+}
+
 // Rayleigh-Ritz step.  With Q orthonormal (out x kL) and Z = |R|^T Q (in x kL), G = Z^T Z =
 // H diag(sigma^2) H^T gives the leading triplets of |R|: left vectors Q H, right vectors
 // Z H diag(1/sigma).  Tu = H_k diag(sqrt(sigma)), Tv = H_k diag(1/sqrt(sigma)) (Eq. 2's split):
 // U = Q Tu, V = Z Tv.  Jacobi rotations in fp64 in the round-robin ordering: 31 rounds of 16
 // disjoint pairs per sweep.  The rotations of a round act on A from both sides, so A falls into 16 x 16 independent blocks of
-// 2 x 2 (rows of one pair, columns of another): 256 threads take one each, the other 256 two lines of H each, and a round
-// needs two barriers.  One launch of one workgroup, bound by the rounds' chain (rotation, barrier, update, barrier):
-// 227 -> 113 us with this, the rotations from two reciprocal square roots and the ordering by all threads.
+// 2 x 2 (rows of one pair, columns of another): 256 threads take one each and A goes from one buffer to another; the other 256
+// take two lines of H each, one round behind, with the rotations that the first left in LDS.  A thread makes its column pair's
+// rotation by itself and has its row pair's from the lane that makes that one, so a round needs one barrier.  One launch of one
+// workgroup, bound by the rounds' chain (rotation, update, barrier) and their LDS traffic: 100 us (107 with 16 threads making the
+// rotations and two barriers a round; 122 with every thread making both of its rotations).
 constexpr int kRitzThreads = 512;
 __global__ __launch_bounds__(kRitzThreads) void k_dc_ritz(const double* Gpart, int parts, float* Tu, float* Tv, int k) {
-    __shared__ double A[kL][kL + 1];
+    __shared__ double A2[2][kL][kL + 1];
     __shared__ double H[kL][kL + 1];
-    __shared__ double cs[kL / 2][2];
-    __shared__ int pq[kL / 2][2];
+    __shared__ double cs[2][kL / 2][2];
     __shared__ int order[kL];
-    __shared__ double offd[kL];
+    __shared__ double sums[kRitzThreads / 64][2];
     const int t = threadIdx.x;
-    gram_sum<kRitzThreads>(Gpart, parts, A);
+    gram_sum<kRitzThreads, false>(Gpart, parts, A2[0]);
 #pragma unroll
     for (int i = t; i < kL * kL; i += kRitzThreads) H[i / kL][i % kL] = (i / kL == i % kL) ? 1.0 : 0.0;
     if (t < kL) order[t] = t;
     __syncthreads();
     const int e = t & (kL / 2 - 1), f = (t >> 4) & (kL / 2 - 1);   // pair of the columns, pair of the rows (or line of H)
+    // pair i of a round: (kL - 1, round) and ((round + i) mod 31, (round - i) mod 31), the smaller index first
+    auto pair = [](int round, int i, int& p, int& q) {
+        const int a = i == 0 ? kL - 1 : round + i < kL - 1 ? round + i : round + i - (kL - 1);
+        const int b = round >= i ? round - i : round - i + (kL - 1);
+        p = min(a, b);
+        q = max(a, b);
+    };
+    auto rotation = [](double app, double aqq, double apq, double& c, double& s) {
+        // tan(2 theta) = b / d; the smaller angle: cos^2 = (1 + |d| / h) / 2, sin = b sign(d) / (2 h cos)
+        const double d = aqq - app, b = 2.0 * apq;
+        const double rh = rsqrt64(fma(d, d, b * b));
+        const double c2 = fma(0.5 * fabs(d), rh, 0.5), rc = rsqrt64(c2);
+        const bool turn = fabs(apq) > 1e-300 && apq * apq > 1e-36 * fabs(app * aqq);
+        c = turn ? c2 * rc : 1.0;
+        s = turn ? (d >= 0.0 ? 0.5 : -0.5) * b * rh * rc : 0.0;
+    };
+    int cur = 0;
     for (int sweep = 0; sweep < 10; ++sweep) {
         // converged?  (off-diagonal mass against the trace; falls quadratically once small)
-        if (t < kL) {
-            double o = 0.0;
-            for (int c = 0; c < kL; ++c) o += (c == t) ? 0.0 : A[t][c] * A[t][c];
-            offd[t] = o;
-        }
-        __syncthreads();
         double off = 0.0, tr = 0.0;
-        for (int c = 0; c < kL; ++c) {
-            off += offd[c];
-            tr += fabs(A[c][c]);
+#pragma unroll
+        for (int i = t; i < kL * kL; i += kRitzThreads) {
+            const double v = A2[cur][i / kL][i % kL];
+            if (i / kL == i % kL) tr += fabs(v);
+            else off += v * v;
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            off += __shfl_xor(off, d);
+            tr += __shfl_xor(tr, d);
+        }
+        if ((t & 63) == 0) {
+            sums[t >> 6][0] = off;
+            sums[t >> 6][1] = tr;
         }
         __syncthreads();
+        off = tr = 0.0;
+#pragma unroll
+        for (int w = 0; w < kRitzThreads / 64; ++w) {
+            off += sums[w][0];
+            tr += sums[w][1];
+        }
         if (off <= 1e-26 * tr * tr) break;   // same for every thread
-        for (int round = 0; round < kL - 1; ++round) {
-            if (t < kL / 2) {
-                // pair t of this round: (kL - 1, round) and ((round + t) mod 31, (round - t) mod 31)
-                int p = (t == 0) ? kL - 1 : (round + t) % (kL - 1);
-                int q = (t == 0) ? round : (round - t + (kL - 1)) % (kL - 1);
-                if (p > q) {
-                    const int x = p;
-                    p = q;
-                    q = x;
-                }
-                const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
-                double c = 1.0, s = 0.0;
-                if (fabs(apq) > 1e-300 && apq * apq > 1e-36 * fabs(app * aqq)) {
-                    // tan(2 theta) = b / d; the smaller angle: cos^2 = (1 + |d| / h) / 2, sin = b sign(d) / (2 h cos)
-                    const double d = aqq - app, b = 2.0 * apq;
-                    const double rh = rsqrt64(fma(d, d, b * b));
-                    const double c2 = fma(0.5 * fabs(d), rh, 0.5), rc = rsqrt64(c2);
-                    c = c2 * rc;
-                    s = (d >= 0.0 ? 0.5 : -0.5) * b * rh * rc;
-                }
-                pq[t][0] = p;
-                pq[t][1] = q;
-                cs[t][0] = c;
-                cs[t][1] = s;
-            }
-            __syncthreads();
-            const int p = pq[e][0], q = pq[e][1];
-            const double c = cs[e][0], sn = cs[e][1];
+        for (int round = 0; round < kL; ++round) {   // H is a round behind
+            int p, q;
             if (t < 256) {
-                const int g = pq[f][0], h = pq[f][1];
-                const double cr = cs[f][0], sr = cs[f][1];
-                const double gp = A[g][p], gq = A[g][q], hp = A[h][p], hq = A[h][q];
-                const double gp1 = c * gp - sn * gq, gq1 = sn * gp + c * gq, hp1 = c * hp - sn * hq, hq1 = sn * hp + c * hq;
-                A[g][p] = cr * gp1 - sr * hp1;
-                A[g][q] = cr * gq1 - sr * hq1;
-                A[h][p] = sr * gp1 + cr * hp1;
-                A[h][q] = sr * gq1 + cr * hq1;
-            } else {
+                if (round < kL - 1) {
+                    double(*const A)[kL + 1] = A2[cur];
+                    double(*const next)[kL + 1] = A2[cur ^ 1];
+                    int g, h;
+                    pair(round, e, p, q);
+                    pair(round, f, g, h);
+                    const double gp = A[g][p], gq = A[g][q], hp = A[h][p], hq = A[h][q];
+                    double c, sn;
+                    rotation(A[p][p], A[q][q], A[p][q], c, sn);
+                    if (t < kL / 2) {
+                        cs[round & 1][t][0] = c;
+                        cs[round & 1][t][1] = sn;
+                    }
+                    const double cr = __shfl(c, f, 16), sr = __shfl(sn, f, 16);   // lane e = f of the same row of sixteen lanes
+                    const double gp1 = c * gp - sn * gq, gq1 = sn * gp + c * gq, hp1 = c * hp - sn * hq, hq1 = sn * hp + c * hq;
+                    next[g][p] = cr * gp1 - sr * hp1;
+                    next[g][q] = cr * gq1 - sr * hq1;
+                    next[h][p] = sr * gp1 + cr * hp1;
+                    next[h][q] = sr * gq1 + cr * hq1;
+                }
+            } else if (round > 0) {
+                pair(round - 1, e, p, q);
+                const double c = cs[(round - 1) & 1][e][0], sn = cs[(round - 1) & 1][e][1];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const int r = f + 16 * i;
@@ -583,8 +719,10 @@ __global__ __launch_bounds__(kRitzThreads) void k_dc_ritz(const double* Gpart, i
                 }
             }
             __syncthreads();
+            if (round < kL - 1) cur ^= 1;
         }
     }
+    double(*const A)[kL + 1] = A2[cur];
     if (t < kL) {   // eigenvalues in descending order (equal ones by their index)
         const double mine = A[t][t];
         int rank = 0;
@@ -651,9 +789,9 @@ hipError_t launch_decompose(const float* W, const float* s, int out, int in, int
         const int M = trans ? in : out, K = trans ? out : in;
         const int per = 4 * (((K + 63) / 64 + 4 * groups - 1) / (4 * groups));
         if ((M + 63) / 64 * groups >= 512)
-            hipLaunchKernelGGL(k_dc_mulh<2>, dim3((M + 63) / 64, groups), dim3(256), 0, st, trans ? RhT : Rh, X, P, M, K, per);
+            hipLaunchKernelGGL((k_dc_mulh<2, 8>), dim3((M + 63) / 64, groups), dim3(256), 0, st, trans ? RhT : Rh, X, P, M, K, per);
         else
-            hipLaunchKernelGGL(k_dc_mulh<1>, dim3(M / 32, groups), dim3(256), 0, st, trans ? RhT : Rh, X, P, M, K, per);
+            hipLaunchKernelGGL((k_dc_mulh<1, 16>), dim3(M / 32, groups), dim3(256), 0, st, trans ? RhT : Rh, X, P, M, K, per);
     };
     auto gram = [&](const float* src, int sl, bool grouped, float* dst, int m) {
         hipLaunchKernelGGL(k_dc_gram, dim3(gram_parts(m)), dim3(1024), 0, st, src, sl, grouped, dst, m, G);
@@ -662,10 +800,10 @@ hipError_t launch_decompose(const float* W, const float* s, int out, int in, int
     // second pass (twice = orthonormal to rounding) where asked
     auto orth = [&](bool twice) {
         gram(P, groups, true, Y, out);
-        hipLaunchKernelGGL(k_dc_orth, dim3((out + 255) / 256), dim3(256), 0, st, G, gram_parts(out), Y, twice ? Q : nullptr, X, out);
+        hipLaunchKernelGGL(k_dc_orth, dim3((out + kOrthRows - 1) / kOrthRows), dim3(kOrthThreads), 0, st, G, gram_parts(out), Y, twice ? Q : nullptr, X, out);
         if (twice) {
             gram(Q, 1, true, Y, out);
-            hipLaunchKernelGGL(k_dc_orth, dim3((out + 255) / 256), dim3(256), 0, st, G, gram_parts(out), Y, Q, X, out);
+            hipLaunchKernelGGL(k_dc_orth, dim3((out + kOrthRows - 1) / kOrthRows), dim3(kOrthThreads), 0, st, G, gram_parts(out), Y, Q, X, out);
         }
     };
 
@@ -698,8 +836,7 @@ hipError_t launch_decompose(const float* W, const float* s, int out, int in, int
                            (chunks + slices - 1) / slices);
         gram(P, slices, false, Z, in);
         hipLaunchKernelGGL(k_dc_ritz, dim3(1), dim3(kRitzThreads), 0, st, G, gram_parts(in), Tu, Tv, kRank);
-        hipLaunchKernelGGL(k_dc_apply, dim3((out + 255) / 256), dim3(256), 0, st, Q, Tu, Ui, out);
-        hipLaunchKernelGGL(k_dc_apply, dim3((in + 255) / 256), dim3(256), 0, st, Z, Tv, Vi, in);
+        hipLaunchKernelGGL(k_dc_apply, dim3((out + 63) / 64 + (in + 63) / 64), dim3(256), 0, st, Q, Tu, Ui, out, Z, Tv, Vi, in);
     }
     return hipGetLastError();
 }
