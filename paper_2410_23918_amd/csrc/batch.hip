@@ -385,6 +385,9 @@ double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
     return 3.3 + (wgs + 255) / 256 * (3.5 + its * (n_loaded * (1.02 + 0.17 * fill) + 3.89)) + (split > 1 ? 3.2 : 0.0);
 }
 
+// what the launch takes, beyond 64 tokens too
+double batch_plan_time_us(int out, int in, int batch, int n_loaded, int part_slots) { return batch_plan(out, in, batch, n_loaded, part_slots).us; }
+
 // one 32-bit buffer descriptor each over the loaded blocks and the activations, one counter per row group and 64 tokens
 bool batch_fits(const KParams& p) {
     return size_t(p.n_loaded) * p.block_stride < (size_t(1) << 32) && size_t(p.batch) * p.in * 2 < (size_t(1) << 32) &&

@@ -477,7 +477,7 @@ hipError_t launch_dense_zero(const LaunchArgs& a, hipStream_t st) {
 // in x (a + b x the fraction of the 256 compute units that have a workgroup) - a partly filled
 // chip runs each tile faster (clock, shared caches) - with (a, b) = (0.0196, 0.0148) for 256-row
 // tiles, (0.0111, 0.0089) for 128-row tiles and (0.0068, 0.0032) for 128 x 128 tiles.  The
-// launcher takes the cheapest tile.
+// launcher takes the cheapest tile (dense_time_us below prices it more closely).
 enum GemmTile { kTile256 = 1, kTile128 = 2, kTile128x128 = 3, kTileSplit = 4 };
 static std::atomic<int> g_forced_tile{0};   // measurement hook: 0 = the estimate's choice
 void dense_force_tile(int tile) { g_forced_tile = tile; }
@@ -504,12 +504,21 @@ static int dense_tile(int out, int in, int batch) {
     if (best == kTile128x128 && in >= 4096 && per_xcd <= 32) return kTileSplit;
     return best;
 }
+// Duration (microseconds) of the tile taken, for the choice between the paths: rounds of 256 workgroups as above, one pass over both
+// operands, the outputs.  Fitted to 7053 cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192), 9.1, 7.2, 7.3 and 4.6 % root mean square
+// for the four tiles.
 double dense_time_us(int out, int in, int batch) {
-    // never below one pass over both operands at ~3.5 TB/s (few tokens: every tile reads its own rows
-    // of the weight once and nothing is reused)
-    const double t = tile_rounds_time_us(out, in, batch, dense_tile(out, in, batch));
-    const double stream = (double(out) + batch) * in * 2.0 / 3.5e6;
-    return t > stream ? t : stream;
+    const int tile = dense_tile(out, in, batch);
+    const int rows = tile == kTile256 ? 256 : 128, toks = tile == kTile256 || tile == kTile128 ? kGemmTokens : 128;
+    const int tiles = ((out + rows - 1) / rows) * ((batch + toks - 1) / toks), full = tiles / 256, rest = tiles % 256;
+    struct Fit {
+        double fixed, a, b, operands, outputs;
+    };
+    static constexpr Fit kFits[] = {{2.14, 0.0011, 0.0304, 0.0097, 0.544}, {3.26, 0.00705, 0.00908, 0.0174, 0.437},
+                                    {4.53, 0.00613, 0.00224, 0.0024, 0.356}, {7.74, 0.00522, 0.00112, 0.0386, 0.0437}};
+    const Fit& f = kFits[tile - kTile256];
+    return f.fixed + in * (full * (f.a + f.b) + (rest ? f.a + f.b * rest / 256.0 : 0.0)) +
+           1e-6 * (f.operands * 2.0 * (double(out) + batch) * in + f.outputs * double(out) * batch);
 }
 
 hipError_t launch_dense(const LaunchArgs& a, hipStream_t st) {

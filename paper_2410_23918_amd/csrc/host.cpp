@@ -303,11 +303,6 @@ int bitstack_weight_shape(const bitstack_weight_t* w, int* out, int* in, int* k,
 // launch streams the blocks once per token; the batch path rebuilds the weight on chip per group of 64
 // tokens (k_batch), 32 (k_fused) or 512 (k_tile); with a scratch buffer for the
 // dense weight, restoring it once and one dense product wins for prefill-sized batches.
-// Up to 64 tokens these are the estimates that launch_panel decides by.  Beyond, the choice between the batch path and restoring
-// compares tile_time_us, which is up to 1.9 times too high up to 1024 tokens and does not know k_batch, with restore_time_us, which
-// describes a slower kernel than k_restore, and dense_time_us, which is up to 3 times too low for small matrices: of 800 random cases of 16
-// to 2048 tokens with a scratch for the whole weight the path taken is 3.8 % slower than the other on average, and
-// 45 times by more than 30 % (up to 1.8 times), mostly by restoring a matrix of few rows or few blocks.
 // Rows of the weight a scratch buffer of this size holds at a time on the materialising path
 // (multiples of 256, the dense kernel's tile height; the whole matrix if it fits; 0: too small to
 // be worth it -- below 1024 rows the dense product no longer fills the chip).
@@ -329,31 +324,26 @@ static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t work
     if (batch == 1) return BITSTACK_KERNEL_DECODE;
     workspace_bytes = scratch_bytes(g, workspace_bytes);
     const double t_decode = decode_tokens_time_us(g, batch, n_loaded);   // up to four tokens per launch
-    double t_panel;
-    if (batch <= kSmallBatch) {
-        t_panel = fused_time_us(g.out, g.in, batch, n_loaded, g.part_slots);
-        const double t_batch = batch_time_us(g.out, g.in, batch, n_loaded, g.part_slots);   // launch_panel takes the cheapest
-        t_panel = t_batch < t_panel ? t_batch : t_panel;
-        if (batch > 32 && g.xpack_bytes) {
-            const double t_tile = tile_time_us(g.out, g.in, batch, n_loaded);
-            t_panel = t_tile < t_panel ? t_tile : t_panel;
-        }
-    } else {
-        t_panel = tile_time_us(g.out, g.in, batch, n_loaded);
-    }
+    const double t_panel = panel_time_us(g.out, g.in, batch, n_loaded, g.part_slots, g.xpack_bytes != 0);
     int kernel = t_decode <= t_panel ? BITSTACK_KERNEL_DECODE : BITSTACK_KERNEL_PANEL;
     const double t_best = t_decode <= t_panel ? t_decode : t_panel;
     const int slab = slab_rows(g, workspace_bytes);
     // (the dense product addresses x and a slab of the dense weight with 32-bit byte offsets)
     const bool dense_ok = size_t(batch) * g.in * 2 <= 0xffffffffull && size_t(slab) * g.in * 2 <= 0xffffffffull;
     if (restore_fits(g.block_stride, n_loaded) && slab > 0 && dense_ok) {
-        // per slab of rows: restore + product, two launches (~4 us each between kernels of one stream)
+        // per slab of rows: restore + product.  7053 cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks), timed both
+        // ways: with a scratch for the whole weight the path taken is 0.3 % slower than the other in the mean, two times by more than 30 %
+        // (0.1 % and none through the image's own scratch of 2048 rows).  The estimates before, of slower kernels, gave 6.6 % and 617,
+        // up to 2.35 times, mostly by restoring a matrix of few rows or few blocks.
         double t_mat = 0.0;
         for (int r0 = 0; r0 < g.out; r0 += slab) {
             const int rows = slab < g.out - r0 ? slab : g.out - r0;
-            t_mat += 8.0 + restore_time_us(rows, g.in, n_loaded) + dense_time_us(rows, g.in, batch);
+            t_mat += 1.7 + restore_time_us(rows, g.in, n_loaded) + dense_time_us(rows, g.in, batch);
         }
-        if (t_mat < t_best) kernel = BITSTACK_KERNEL_MATERIALISE;
+        // A dense weight of a quarter of the last-level cache and more takes the place of what the program's other kernels left there: for
+        // few tokens it has to be worth it (14336 x 4096, 16 blocks, 128 tokens: 121 us, 133 without; the caller's next kernels pay for the rest)
+        const bool displaces = size_t(slab) * g.in * 2 > (size_t(64) << 20) && batch <= 256;
+        if (t_mat * (displaces ? 1.15 : 1.0) < t_best) kernel = BITSTACK_KERNEL_MATERIALISE;
     }
     return kernel;
 }

@@ -68,8 +68,8 @@ double dense_time_us(int out, int in, int batch);
 double restore_time_us(int rows, int in, int n_loaded);
 // estimated durations of the batch kernels (microseconds); launch_panel takes the cheapest
 double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots);
-double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots);
-double tile_time_us(int out, int in, int batch, int n_loaded);
+double batch_plan_time_us(int out, int in, int batch, int n_loaded, int part_slots);   // what the launch takes, also beyond 64 tokens
+double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok);
 int restore_max_blocks();
 // can the restore kernel take n_loaded blocks of this stride? (block count, and their bytes below 4 GiB)
 bool restore_fits(size_t block_stride, int n_loaded);

@@ -19,6 +19,7 @@
 //   3. per tile of 128 tokens: x/s for the chunk goes to LDS as fp16, token-major, and meets the
 //      weight tile on the matrix cores (fp32 accumulate).  The weight tile is built once per
 //      chunk for all token tiles of the workgroup.
+#include <algorithm>
 #include <hip/hip_fp16.h>
 #include <type_traits>
 #include <hip/hip_runtime.h>
@@ -981,32 +982,36 @@ static hipError_t launch_tile(const KParams& p, hipStream_t st) {
 // Estimated durations (microseconds).  k_fused, fitted to 5440 cases (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens; 3.0 %
 // root mean square, all within 15 %): a step is a pair of column chunks and a block; the loop takes three at a time and ends with a
 // whole turn (three steps 7.0 us, four 9.2, six 9.0); rounds of 256 workgroups count nearly whole.
-double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
+static double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
     const int split = small_batch_split(out, in, batch, part_slots), wgs = (out + 63) / 64 * ((batch + 31) / 32) * split;
     const int pairs = ((in / kChunkCols + 1) / 2 + split - 1) / split, steps = n_loaded * pairs;
     const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 0.79 * ((wgs + 255) / 256) + 0.21 * wgs / 256.0;
     return (steps == 1 ? 1.8 : 1.35) + rounds * (3.78 + (steps + 2) / 3 * 3 * (0.585 + 0.176 * fill) + 0.617 * pairs + (steps % 3 ? 0.68 : 0.0)) +
            (split > 1 ? 1.33 + 0.0048 * batch * split : 0.0);
 }
-// What the choice between k_tile and the other paths goes by: constants of the dispatch, fitted when a pair of column chunks took
-// ~0.9 us per block for the rebuild (0.63 now) + 12-14 us for the product (14 when several token tiles of a row tile run at once, 6.5
-// up to 256 tokens, where only one wavefront per SIMD has tokens to multiply); 15 % less of both when the chip is not full.
-double tile_time_us(int out, int in, int batch, int n_loaded) {
-    const int row_tiles = (out + 2 * kTileRows - 1) / (2 * kTileRows), chunk_pairs = (in / kChunkCols + 1) / 2;
-    const int wgs = row_tiles * ((batch + kTileTokens - 1) / kTileTokens);
-    const double rounds = wgs <= 256 ? 1.0 : wgs / 256.0, scale = wgs <= 256 ? 0.85 : 1.0;
-    return rounds * (15.0 + chunk_pairs * scale * (0.9 * n_loaded + (batch > 512 ? 14.0 : batch > 256 ? 12.0 : 6.5)));
-}
-
 // The weight-tile kernel against k_batch and k_fused for 33 to 1024 tokens, fitted to 3483 cases (64 x 256 to 28672 x 8192, 1 to 24
-// blocks; 4.3 % root mean square).  tile_time_us is up to 1.9 times too high here, but the crossover to the materialising path
-// is stated in terms of it.
+// blocks; 4.3 % root mean square) before the sign stayed in the accumulator; the crossover to k_batch stays where it was then.
 static double tile_launch_us(int out, int in, int batch, int n_loaded) {
     const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
     const double fill = wgs < 256 ? wgs / 256.0 : 1.0, tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
     return 5.5 + 2.15e-6 * batch * in +   // the activations rearranged
            (wgs + 255) / 256 * (6.1 + chunk_pairs * ((0.652 + 0.074 * fill) * n_loaded + 4.2 + 2.3 * tokens)) -
            (in == kChunkCols ? 1.5 : 0.0);
+}
+
+// Duration of what launch_panel takes, for the choice between it and the other paths.  Up to 64 tokens that choice goes by the same
+// estimates; beyond, by those that its crossover is stated in, and the kernel taken is priced as it is now: k_tile fitted to 4269
+// cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks; 5.1 % root mean square: activations rearranged, rounds of
+// workgroups over pairs of column chunks, outputs written), k_batch by its plan (4.4 % over 2784).
+double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok) {
+    const double tt = batch > 32 && tile_ok ? tile_launch_us(out, in, batch, n_loaded) : 1e30;
+    const double tb = batch <= 1024 ? batch_time_us(out, in, batch, n_loaded, part_slots) : 1e30;
+    if (batch <= kFusedMaxBatch) return std::min(std::min(fused_time_us(out, in, batch, n_loaded, part_slots), tb), tt);
+    if (tb < tile_launch_us(out, in, batch, n_loaded)) return batch_plan_time_us(out, in, batch, n_loaded, part_slots);
+    const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
+    return 8.0 + 1.5e-6 * batch * in + 0.98e-6 * out * batch +
+           (wgs + 255) / 256 * (0.24 + chunk_pairs * ((0.575 + 0.085 * fill) * n_loaded + 4.32 + 1.78 * tokens + 0.14 * fill));
 }
 
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {

@@ -153,17 +153,13 @@ static int restore_groups_per_wg(int groups, int chunks) {
     return per < 1 ? 1 : per > 4 ? 4 : per;
 }
 
-// The restoring part of the materialising path in the choice of kernel (microseconds): rounds of 256 workgroups of 64 rows x
-// a power of two of column slices, as the kernel before k_restore had them.  k_restore is 1.0 (one block of a large matrix) to 2.2
-// times faster, but the crossovers that follow from this estimate are what tests/test_abi_host.py states.
+// Duration (microseconds), for the choice of kernel: rounds of 512 workgroups, part of each shared with the next, and the traffic of the
+// dense rows.  Fitted to 7053 cases (512 x 512 to 28672 x 8192, 1 to 24 blocks; 6.7 % root mean square).
 double restore_time_us(int rows, int in, int n_loaded) {
-    const int iters = (in / kChunkCols + 1) / 2, row_wgs = (rows + 63) / 64;
-    double best = 0.0;
-    for (int sl = 1; sl <= iters; sl *= 2) {
-        const double t = double((row_wgs * sl + 255) / 256) * (((iters + sl - 1) / sl) * (0.93 * n_loaded + 2.5) + 3.0);
-        if (sl == 1 || t < best) best = t;
-    }
-    return best;
+    const int groups = (rows + kRestoreRows - 1) / kRestoreRows, chunks = in / kChunkCols, per = restore_groups_per_wg(groups, chunks);
+    const int wgs = chunks * ((groups + per - 1) / per);
+    const double fill = wgs < 512 ? wgs / 512.0 : 1.0, rounds = 0.36 * ((wgs + 511) / 512) + 0.64 * (wgs < 512 ? 1.0 : wgs / 512.0);
+    return 3.27 + rounds * (per * (n_loaded * (0.496 + 0.558 * fill) + 3.49) - 2.78) + 0.267e-6 * rows * in;
 }
 
 // The block count is what bitstack_restore_max_blocks has always answered (the kernel before k_restore kept every block's U in LDS);
