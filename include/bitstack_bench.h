@@ -24,7 +24,8 @@ enum {
     BITSTACK_OPT_DECODE_KS_CHUNKS = 5,    /* 256-column chunks per workgroup: 1..32 */
     BITSTACK_OPT_DECODE_EARLY = 6,        /* value - 1 = chunks of the first sign window requested at entry: 0, 2, 4 */
     BITSTACK_OPT_DENSE_TILE = 7,          /* output tile of the dense product: 1 = 256 rows x 256 tokens, 2 = 128 x 256,
-                                             3 = 128 x 128, 4 = 128 x 128 for long rows */
+                                             3 = 128 x 128, 4 = 128 x 128 for long rows, 5 = 64 x 64 (sums in
+                                             the order of 3), 6 = 64 x 64 (of 4) */
     BITSTACK_OPT_BATCH_TILES = 8          /* row tiles per workgroup of the batch kernel: 2 or 4 (64 / 128 rows) */
 };
 int bitstack_set_option(int option, int value);

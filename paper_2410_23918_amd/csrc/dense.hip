@@ -20,7 +20,8 @@
 // leaves in 16-byte pieces.  Workgroup ids map to tiles so that all token tiles of a row tile run
 // on one XCD (one L2 pulls that part of the weight).  Two more instantiations, with tiles of 128
 // rows x 256 tokens and of 128 x 128, fill the chip for shapes with few tiles (row slabs, small
-// batches; chosen per launch on the host); k_gemm_split takes the 128 x 128 tiles of long rows.
+// batches; chosen per launch on the host); k_gemm_split takes the 128 x 128 tiles of long rows, k_gemm_64 (64 x 64) the products that
+// larger tiles leave most of the chip idle on.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -466,6 +467,174 @@ __global__ __launch_bounds__(512, 2) void k_gemm_split(KParams p) {
     }
 }
 
+// The 64 x 64 tile, wherever these leave no XCD with more tiles than it has compute units: a product that small is bound by the arrival of a
+// tile's operands, which are half as many as a 128 x 128 tile's, and takes 0.43 (long rows, few tiles) to 0.64 (rows of 512-1024 columns,
+// 32 tiles per XCD) of the time of the larger tiles (4143 products of 512 x 512 to 28672 x 14336, 20 to 2048 tokens; 0.82 at most, one
+// of 1.09 apart; 512 x 4096, 256 tokens: 28 us, 12 now).  Beyond 32 tiles per XCD it is 0.91 to 1.04 in the mean and up to 1.4.
+// A step is 128 columns (32 KiB of both operands) in a ring of five in LDS, loaded there directly; its fragments are read one step ahead
+// into a second set of registers, which frees its buffer: a step is requested five steps ahead and has four to arrive.  One barrier per step.
+// Eight wavefronts, and the order of the sums of the larger tile that would be taken instead (the same bits):
+//   QUARTERS: two token halves x four column quarters with 16x16x32 products, as k_gemm_split; a wavefront multiplies 64 rows x 32 tokens
+//     over its quarter of every step, six fragments feeding 8 products;
+//   else: two row halves x two token halves x the two halves of every 64 columns with 32x32x16 products, as k_gemm<2, true>; 32 rows x 32
+//     tokens, eight fragments feeding 4 products.
+// LDS: row r of a step in 256 bytes, its 16-byte piece q at position q ^ (r % 16); a load's 1 KiB are four rows.
+constexpr unsigned k64Tile = 64 * 256, k64Step = 2 * k64Tile;
+constexpr int k64Ld = 64 + 4;
+static_assert(kSplitRing * k64Step == kSplitLds && 4 * 64 * k64Ld * 4 <= kSplitLds, "the partial tiles reuse the ring");
+template <bool QUARTERS>
+__global__ __launch_bounds__(512, 2) void k_gemm_64(KParams p) {
+    constexpr int kSlices = QUARTERS ? 4 : 2;   // of the columns
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int th = wave & 1, rh = QUARTERS ? 0 : (wave >> 1) & 1, slice = QUARTERS ? wave >> 1 : wave >> 2;   // token half, row half, columns
+    constexpr int kSide = QUARTERS ? 16 : 32;   // rows and tokens of a fragment
+    const int ln = lane & (kSide - 1), kg = lane / kSide;
+    // the 8 XCDs, to which ids are dealt round-robin, share the tiles as (8 / n_ks) x n_ks: every (8 / n_ks)-th row tile x every n_ks-th token
+    // tile to one of them
+    const int ntt = (p.batch + 63) / 64, nrt = (p.out + 63) / 64, per_row = (ntt + p.n_ks - 1) / p.n_ks;
+    const int xcd = blockIdx.x & 7, place = blockIdx.x >> 3;
+    const int rt = xcd / p.n_ks + 8 / p.n_ks * (place / per_row), tt = xcd % p.n_ks + p.n_ks * (place % per_row);
+    if (rt >= nrt || tt >= ntt) return;
+    const int row0 = rt * 64, tok0 = tt * 64;
+    const int steps = p.in / 128;   // even
+    const v4i w_rsrc = buffer_over(p.wdense, unsigned(size_t(p.out) * p.in * 2));
+    const v4i x_rsrc = buffer_over(p.x, unsigned(size_t(p.batch) * p.in * 2));
+    const unsigned lds0 = lds_address(smem);
+    // this wavefront brings rows / tokens 8 wave .. + 7 of a step, four per load; past the end the last one is repeated (computed, never
+    // stored)
+    unsigned w_off[2], x_off[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = 8 * wave + 4 * i + (lane >> 4), piece = (lane & 15) ^ (r & 15);
+        w_off[i] = unsigned(size_t(min(row0 + r, p.out - 1)) * p.in * 2) + unsigned(piece) * 16u;
+        x_off[i] = unsigned(size_t(min(tok0 + r, p.batch - 1)) * p.in * 2) + unsigned(piece) * 16u;
+    }
+    int q = 0;                                   // next step to request; past the last one the last one again, harmlessly
+    unsigned q_dst = lds0 + unsigned(wave) * 2048u;
+    auto after = [&](unsigned at, unsigned base) { return at == base + (kSplitRing - 1) * k64Step ? base : at + k64Step; };
+    auto request = [&]() __attribute__((always_inline)) {
+        const unsigned col = unsigned(min(q, steps - 1)) * 256u;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            load_to_lds(w_rsrc, q_dst + unsigned(i) * 1024u, w_off[i], col);
+            load_to_lds(x_rsrc, q_dst + k64Tile + unsigned(i) * 1024u, x_off[i], col);
+        }
+        ++q;
+        q_dst = after(q_dst, lds0 + unsigned(wave) * 2048u);
+    };
+    // fragment f of a step: pieces kg on of 32 columns (quarters) or 16 columns (halves: two of each 64)
+    constexpr int kCols = QUARTERS ? 1 : 4, kRowFrags = QUARTERS ? 4 : 1, kTokFrags = QUARTERS ? 2 : 1;
+    unsigned from[kCols];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+        const int piece = QUARTERS ? 4 * slice + kg : 8 * (c >> 1) + 4 * slice + 2 * (c & 1) + kg;
+        from[c] = unsigned(ln) * 256u + unsigned(piece ^ (ln & 15)) * 16u;
+    }
+    unsigned r_src = lds0;                       // the step to be read next
+    struct Frags {
+        v8h w[kCols][kRowFrags], x[kCols][kTokFrags];
+    };
+    auto read = [&](Frags& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) {
+#pragma unroll
+            for (int t = 0; t < kTokFrags; ++t)
+                f.x[c][t] = __builtin_bit_cast(v8h, read_lds<v4i>(r_src + from[c] + k64Tile + unsigned(th * 32 + t * kSide) * 256u));
+#pragma unroll
+            for (int j = 0; j < kRowFrags; ++j)
+                f.w[c][j] = __builtin_bit_cast(v8h, read_lds<v4i>(r_src + from[c] + unsigned(rh * 32 + j * kSide) * 256u));
+        }
+        r_src = after(r_src, lds0);
+    };
+    v4f acc[QUARTERS ? 4 : 1][2];   // [16 rows][16 tokens]
+    v16f acc32;                     // 32 x 32
+    if constexpr (QUARTERS) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) acc[j][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    } else {
+        acc32 = zero16();
+    }
+    auto step = [&](const Frags& now, Frags& next) __attribute__((always_inline)) {   // step h
+        loads_barrier<12>();   // step h + 1 has arrived; step h is in the wavefronts' registers
+        request();             // step h + 5, into step h's place
+        read(next);            // past the last step: the last one again, not used
+        if constexpr (QUARTERS) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(now.x[0][t], now.w[0][j], acc[j][t], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one matrix-core instruction
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc32 = __builtin_amdgcn_mfma_f32_32x32x16_f16(now.x[c][0], now.w[c][0], acc32, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Frags fa, fb;
+#pragma unroll
+    for (int i = 0; i < kSplitRing; ++i) request();
+    loads_barrier<16>();   // step 0
+    read(fa);
+    for (int h = 0; h < steps; h += 2) {
+        step(fa, fb);
+        step(fb, fa);
+    }
+    loads_barrier<0>();   // nothing may land in LDS any more
+
+    // the column slices meet.  D[i = token][n = row]: lane (row ln), register v holds token 4 kg + v of 16, or 8 (v / 4) + 4 kg + v % 4 of 32
+    float* const red = reinterpret_cast<float*>(smem) + slice * 64 * k64Ld;   // [kSlices][64 tokens][k64Ld]
+    if constexpr (QUARTERS) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) red[(th * 32 + t * 16 + 4 * kg + v) * k64Ld + j * 16 + ln] = acc[j][t][v];
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[(th * 32 + 8 * (v >> 2) + 4 * kg + (v & 3)) * k64Ld + rh * 32 + ln] = acc32[v];
+    }
+    lds_barrier();
+    const int tok = tid >> 3, row = 8 * (tid & 7);   // eight rows of a token; out is a multiple of 32
+    float sum[8];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        v4f part[kSlices];
+#pragma unroll
+        for (int c = 0; c < kSlices; ++c) part[c] = *reinterpret_cast<const v4f*>(reinterpret_cast<const float*>(smem) + (c * 64 + tok) * k64Ld + row + 4 * k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (QUARTERS) sum[4 * k + e] = (part[0][e] + part[2][e]) + (part[1][e] + part[3][e]);
+            else sum[4 * k + e] = part[0][e] + part[1][e];
+        }
+    }
+    if (tok0 + tok >= p.batch || row0 + row >= p.out) return;
+    const size_t at = size_t(tok0 + tok) * p.y_ld + row0 + row;
+    if (p.y_f32) {
+        v4f* const y = reinterpret_cast<v4f*>(static_cast<float*>(p.y) + at);
+        y[0] = v4f{sum[0], sum[1], sum[2], sum[3]};
+        y[1] = v4f{sum[4], sum[5], sum[6], sum[7]};
+    } else {
+        v8h o;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) o[k] = _Float16(sum[k]);
+        *reinterpret_cast<v8h*>(static_cast<__half*>(p.y) + at) = o;
+    }
+}
+
 hipError_t launch_dense_zero(const LaunchArgs& a, hipStream_t st) {
     const size_t n16 = size_t(a.geo.out) * size_t(a.geo.in) * 2 / 16;
     hipLaunchKernelGGL(k_dense_zero, dim3(unsigned((n16 + 255) / 256)), dim3(256), 0, st,
@@ -478,7 +647,7 @@ hipError_t launch_dense_zero(const LaunchArgs& a, hipStream_t st) {
 // chip runs each tile faster (clock, shared caches) - with (a, b) = (0.0196, 0.0148) for 256-row
 // tiles, (0.0111, 0.0089) for 128-row tiles and (0.0068, 0.0032) for 128 x 128 tiles.  The
 // launcher takes the cheapest tile (dense_time_us below prices it more closely).
-enum GemmTile { kTile256 = 1, kTile128 = 2, kTile128x128 = 3, kTileSplit = 4 };
+enum GemmTile { kTile256 = 1, kTile128 = 2, kTile128x128 = 3, kTileSplit = 4, kTile64 = 5, kTile64Split = 6 };
 static std::atomic<int> g_forced_tile{0};   // measurement hook: 0 = the estimate's choice
 void dense_force_tile(int tile) { g_forced_tile = tile; }
 
@@ -491,9 +660,25 @@ static double tile_rounds_time_us(int out, int in, int batch, int tile) {
     const int full = tiles / 256, rest = tiles % 256;
     return in * (full * (a + b) + (rest ? a + b * rest / 256.0 : 0.0));
 }
+// The most 64 x 64 tiles that an XCD gets, and how many ways the token tiles are shared among the XCDs for that (2: what an L2 fetches is
+// least; 1 and 4 where 2 would leave XCDs with fewer tiles than others)
+static int tiles64_of_xcd(int out, int batch, int* ways) {
+    const int nrt = (out + 63) / 64, ntt = (batch + 63) / 64;
+    int best = 0;
+    for (int w : {2, 1, 4}) {
+        const int n = (nrt + 8 / w - 1) / (8 / w) * ((ntt + w - 1) / w);
+        if (best == 0 || n < best) {
+            best = n;
+            *ways = w;
+        }
+    }
+    return best;
+}
 static int dense_tile(int out, int in, int batch) {
     const int forced = g_forced_tile.load();
-    if (forced >= kTile256 && forced <= kTileSplit) return forced;
+    if (forced >= kTile256 && forced <= kTile64Split) return forced;
+    int ways;
+    if (tiles64_of_xcd(out, batch, &ways) <= 32) return in >= 4096 ? kTile64Split : kTile64;
     int best = kTile256;
     for (int t = kTile128; t <= kTile128x128; ++t)
         if (tile_rounds_time_us(out, in, batch, t) < tile_rounds_time_us(out, in, batch, best)) best = t;
@@ -506,16 +691,17 @@ static int dense_tile(int out, int in, int batch) {
 }
 // Duration (microseconds) of the tile taken, for the choice between the paths: rounds of 256 workgroups as above, one pass over both
 // operands, the outputs.  Fitted to 7053 cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192), 9.1, 7.2, 7.3 and 4.6 % root mean square
-// for the four tiles.
+// for the first four tiles, the 64 x 64 ones to 4143 of 20 to 2048 tokens, 4.3 and 8.3 %.
 double dense_time_us(int out, int in, int batch) {
     const int tile = dense_tile(out, in, batch);
-    const int rows = tile == kTile256 ? 256 : 128, toks = tile == kTile256 || tile == kTile128 ? kGemmTokens : 128;
+    const int rows = tile == kTile256 ? 256 : tile >= kTile64 ? 64 : 128, toks = tile <= kTile128 ? kGemmTokens : tile >= kTile64 ? 64 : 128;
     const int tiles = ((out + rows - 1) / rows) * ((batch + toks - 1) / toks), full = tiles / 256, rest = tiles % 256;
     struct Fit {
         double fixed, a, b, operands, outputs;
     };
-    static constexpr Fit kFits[] = {{2.14, 0.0011, 0.0304, 0.0097, 0.544}, {3.26, 0.00705, 0.00908, 0.0174, 0.437},
-                                    {4.53, 0.00613, 0.00224, 0.0024, 0.356}, {7.74, 0.00522, 0.00112, 0.0386, 0.0437}};
+    static constexpr Fit kFits[] = {{2.14, 0.0011, 0.0304, 0.0097, 0.544},   {3.26, 0.00705, 0.00908, 0.0174, 0.437},
+                                    {4.53, 0.00613, 0.00224, 0.0024, 0.356}, {7.74, 0.00522, 0.00112, 0.0386, 0.0437},
+                                    {4.02, 0.00203, 0.00118, 0.0109, 0.0},   {3.31, 0.00211, 0.00081, 0.0194, 2.78}};
     const Fit& f = kFits[tile - kTile256];
     return f.fixed + in * (full * (f.a + f.b) + (rest ? f.a + f.b * rest / 256.0 : 0.0)) +
            1e-6 * (f.operands * 2.0 * (double(out) + batch) * in + f.outputs * double(out) * batch);
@@ -545,10 +731,20 @@ hipError_t launch_dense(const LaunchArgs& a, hipStream_t st) {
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kGemmLdsSmall);
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_split), hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_64<false>), hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_64<true>), hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int tile = dense_tile(p.out, p.in, p.batch);
+    if (tile == kTile64 || tile == kTile64Split) {
+        const unsigned tiles = unsigned(8 * tiles64_of_xcd(p.out, p.batch, &p.n_ks));
+        if (tile == kTile64) hipLaunchKernelGGL(k_gemm_64<false>, dim3(tiles), dim3(512), kSplitLds, st, p);
+        else hipLaunchKernelGGL(k_gemm_64<true>, dim3(tiles), dim3(512), kSplitLds, st, p);
+        return hipGetLastError();
+    }
     const int rows = tile == kTile256 ? 256 : 128, toks = tile >= kTile128x128 ? 128 : kGemmTokens;
     const int ntt = (p.batch + toks - 1) / toks, nrt = (p.out + rows - 1) / rows;
     const unsigned wgs = unsigned(8 * ((nrt + 7) / 8) * ntt);
