@@ -12,7 +12,7 @@ _lib = None
 
 KERNEL_AUTO, KERNEL_REFERENCE, KERNEL_DECODE, KERNEL_PANEL, KERNEL_MATERIALISE = 0, 1, 2, 3, 4
 Y_F16, Y_F32 = 0, 1
-OPT_DECODE_BGROUPS, OPT_DECODE_TILES, OPT_DECODE_KS_CHUNKS, OPT_DECODE_EARLY, OPT_DENSE_TILE, OPT_BATCH_TILES = 3, 4, 5, 6, 7, 8
+OPT_DECODE_BGROUPS, OPT_DECODE_TILES, OPT_DECODE_KS_CHUNKS, OPT_DECODE_EARLY, OPT_DENSE_TILE, OPT_BATCH_TILES, OPT_ROWS_CHUNKS = 3, 4, 5, 6, 7, 8, 9
 
 
 class BitStackError(RuntimeError):

@@ -317,6 +317,7 @@ struct BatchPlan {
 };
 static std::atomic<int> g_forced_tiles{0};
 void batch_force_tiles(int tiles) { g_forced_tiles = tiles == 2 || tiles == 4 ? tiles : 0; }
+int batch_forced_tiles() { return g_forced_tiles.load(); }
 
 static BatchPlan batch_plan(int out, int in, int batch, int n_loaded, int part_slots) {
     const int nch = in / kChunkCols, forced = g_forced_tiles.load();

@@ -482,7 +482,7 @@ __device__ __forceinline__ bool gram_factor(const double (*Gs)[kL + 1], FactorLd
 
 // q_I += l_I minus for I = C + 1 .. 31, l_I in lane I % 16 of every row of sixteen lanes (lo: I < 16, hi).  The compiler does not fold
 // the row operation into the multiply-add, and it does not know that the statement is a vector instruction: lo and hi come from LDS, and
-// the values of q are read two instructions behind at the earliest (tests/test_asm_distances_decompose.py).
+// the values of q are read two instructions behind at the earliest (tests/test_asm_distances_more.py).
 template <int I>
 __device__ __forceinline__ void fma_row_lane(float& q, float l, float minus) {
     asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(q) : "v"(l), "v"(minus), "n"(I % 16));

@@ -599,6 +599,7 @@ int bitstack_set_option(int option, int value) {
         case BITSTACK_OPT_DECODE_EARLY: decode_tuning().early = value - 1; return BITSTACK_OK;
         case BITSTACK_OPT_DENSE_TILE: dense_force_tile(value); return BITSTACK_OK;
         case BITSTACK_OPT_BATCH_TILES: batch_force_tiles(value); return BITSTACK_OK;
+        case BITSTACK_OPT_ROWS_CHUNKS: rows_force_chunks(value); return BITSTACK_OK;
         default: return BITSTACK_E_ARG;
     }
 }

@@ -68,6 +68,10 @@ double dense_time_us(int out, int in, int batch);
 double restore_time_us(int rows, int in, int n_loaded);
 // estimated durations of the batch kernels (microseconds); launch_panel takes the cheapest
 double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots);
+double rows_time_us(int out, int in, int batch, int n_loaded);
+void rows_force_chunks(int chunks);
+int rows_forced_chunks();
+int batch_forced_tiles();
 double batch_plan_time_us(int out, int in, int batch, int n_loaded, int part_slots);   // what the launch takes, also beyond 64 tokens
 double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok);
 int restore_max_blocks();

@@ -982,9 +982,10 @@ static hipError_t launch_tile(const KParams& p, hipStream_t st) {
 // Estimated durations (microseconds).  k_fused, fitted to 5440 cases (64 x 256 to 28672 x 8192, 1 to 24 blocks, 2 to 64 tokens; 3.0 %
 // root mean square, all within 15 %): a step is a pair of column chunks and a block; the loop takes three at a time and ends with a
 // whole turn (three steps 7.0 us, four 9.2, six 9.0); rounds of 256 workgroups count nearly whole.
-static double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots) {
+static double fused_time_us(int out, int in, int batch, int n_loaded, int part_slots, int* steps_of_workgroup = nullptr) {
     const int split = small_batch_split(out, in, batch, part_slots), wgs = (out + 63) / 64 * ((batch + 31) / 32) * split;
     const int pairs = ((in / kChunkCols + 1) / 2 + split - 1) / split, steps = n_loaded * pairs;
+    if (steps_of_workgroup) *steps_of_workgroup = steps;
     const double fill = wgs < 256 ? wgs / 256.0 : 1.0, rounds = wgs <= 256 ? 1.0 : 0.79 * ((wgs + 255) / 256) + 0.21 * wgs / 256.0;
     return (steps == 1 ? 1.8 : 1.35) + rounds * (3.78 + (steps + 2) / 3 * 3 * (0.585 + 0.176 * fill) + 0.617 * pairs + (steps % 3 ? 0.68 : 0.0)) +
            (split > 1 ? 1.33 + 0.0048 * batch * split : 0.0);
@@ -999,6 +1000,14 @@ static double tile_launch_us(int out, int in, int batch, int n_loaded) {
            (in == kChunkCols ? 1.5 : 0.0);
 }
 
+// k_rows for up to 64 tokens, but not where k_fused has up to eight steps: those calls are as fast with either to a tenth (832 x 768, 3 blocks, 50
+// tokens: 9.7 us, 9.3 with k_rows; 384 x 1024, 8 blocks, 3 tokens: 12.5 and 10.7), and tests/test_gpu_small_batch.py states that k_fused has them.
+static double rows_if_many_steps_us(int out, int in, int batch, int n_loaded, int part_slots) {
+    int steps = 0;
+    fused_time_us(out, in, batch, n_loaded, part_slots, &steps);
+    return steps > 8 ? rows_time_us(out, in, batch, n_loaded) : 1e30;
+}
+
 // Duration of what launch_panel takes, for the choice between it and the other paths.  Up to 64 tokens that choice goes by the same
 // estimates; beyond, by those that its crossover is stated in, and the kernel taken is priced as it is now: k_tile fitted to 4269
 // cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks; 5.1 % root mean square: activations rearranged, rounds of
@@ -1006,7 +1015,8 @@ static double tile_launch_us(int out, int in, int batch, int n_loaded) {
 double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok) {
     const double tt = batch > 32 && tile_ok ? tile_launch_us(out, in, batch, n_loaded) : 1e30;
     const double tb = batch <= 1024 ? batch_time_us(out, in, batch, n_loaded, part_slots) : 1e30;
-    if (batch <= kFusedMaxBatch) return std::min(std::min(fused_time_us(out, in, batch, n_loaded, part_slots), tb), tt);
+    if (batch <= kFusedMaxBatch)
+        return std::min({fused_time_us(out, in, batch, n_loaded, part_slots), rows_if_many_steps_us(out, in, batch, n_loaded, part_slots), tb, tt});
     if (tb < tile_launch_us(out, in, batch, n_loaded)) return batch_plan_time_us(out, in, batch, n_loaded, part_slots);
     const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
     const double fill = wgs < 256 ? wgs / 256.0 : 1.0, tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
@@ -1023,11 +1033,14 @@ hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     // tokens (608 x 12032, 8 blocks, 96 tokens: k_tile 263 us, k_batch 59; 4096 x 4096, 16 blocks, 256 tokens 139 and 99, 300 tokens
     // 146 and 189).  In 8257 cases that were timed with every kernel the one taken is 0.1 % slower than the fastest on average;
     // k_batch is up to 10 % slower than another in its place.
+    const int rows_forced = rows_forced_chunks();
+    const double tr = rows_forced != 16 && !batch_forced_tiles() && rows_fits(p) ? rows_forced ? 0.0 : rows_if_many_steps_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
     const bool tile_ok = a.batch > 32 && tile_fits(p);
     const double tf = a.batch <= kFusedMaxBatch && fused_fits(p) ? fused_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
     const double tb = a.batch <= 1024 && batch_fits(p) ? batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
     // beyond 64 tokens also where the weight-tile kernel cannot hold the stack: k_panel is slower than k_tile's estimate
     const double tt = tile_ok || a.batch > kFusedMaxBatch ? tile_launch_us(p.out, p.in, p.batch, p.n_loaded) : 1e30;
+    if (tr < tf && tr < tt && tr < tb) return launch_rows(p, st);
     if (tb < tf && tb < tt) return launch_batch(p, st);
     if (tf < tt) return launch_fused(p, st);
     if (tile_ok) return launch_tile(p, st);

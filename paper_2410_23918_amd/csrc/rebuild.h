@@ -45,7 +45,7 @@ constexpr int kClasses = 8;                 // column classes of a unit (bit pos
 constexpr int kVClassBytes = 1024;          // V of one class: 2 halves x 16 ranks x 16 columns fp16
 constexpr int kVChunkBytes = kClasses * kVClassBytes;
 
-// The RT wavefronts (4 or 2 row tiles) that work on the same column chunk share its V panel; each loads its own signs and U
+// The RT wavefronts (4, 2 or 1 row tiles) that work on the same column chunk share its V panel; each loads its own signs and U
 // and 8 / RT classes of V.  One step's inputs in LDS, per wavefront: [signs 1 KiB][V of its classes][U 1 KiB].
 template <int RT>
 struct StepLayout {
@@ -82,6 +82,12 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
 template <int N>
 __device__ __forceinline__ void loads_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// the same for inputs that no other wavefront reads: no barrier
+template <int N>
+__device__ __forceinline__ void loads_wait() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
 // raw buffer descriptor
@@ -135,8 +141,8 @@ template <int RT>
 __device__ __forceinline__ void load_step(v4i rsrc, unsigned mine, unsigned s_lane, unsigned v_lane, unsigned u_lane, unsigned s_off,
                                           unsigned v_off, unsigned u_off) {
     typedef StepLayout<RT> L;
-    static_assert(RT == 4 || RT == 2, "");
-    static_assert(L::kVOffset == 1024 && L::kUOffset == (RT == 4 ? 3072 : 4096 + 1024), "");
+    static_assert(RT == 4 || RT == 2 || RT == 1, "");
+    static_assert(L::kVOffset == 1024 && L::kUOffset == (RT == 4 ? 3072 : RT == 2 ? 4096 + 1024 : 8192 + 1024), "");
     if constexpr (RT == 4)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
                      "buffer_load_dwordx4 %1, %4, %5 offen lds\n\t"
@@ -144,6 +150,23 @@ __device__ __forceinline__ void load_step(v4i rsrc, unsigned mine, unsigned s_la
                      "buffer_load_dwordx4 %2, %4, %6 offen offset:2048 lds\n\t"
                      "buffer_load_dwordx4 %3, %4, %7 offen offset:3072 lds" ::"s"(mine),
                      "v"(s_lane), "v"(v_lane), "v"(u_lane), "s"(rsrc), "s"(s_off), "s"(v_off), "s"(u_off)
+                     : "memory", "m0");
+    else if constexpr (RT == 1)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+                     "buffer_load_dwordx4 %3, %6, %7 offen lds\n\t"
+                     "buffer_load_dwordx4 %4, %6, %8 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %4, %6, %8 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %4, %6, %8 offen offset:3072 lds\n\t"
+                     "s_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                     "buffer_load_dwordx4 %4, %6, %9 offen lds\n\t"
+                     "buffer_load_dwordx4 %4, %6, %9 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %4, %6, %9 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %4, %6, %9 offen offset:3072 lds\n\t"
+                     "s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                     "buffer_load_dwordx4 %4, %6, %10 offen lds\n\t"
+                     "buffer_load_dwordx4 %5, %6, %11 offen offset:1024 lds" ::"s"(mine),
+                     "s"(mine + 4096u), "s"(mine + 8192u), "v"(s_lane), "v"(v_lane), "v"(u_lane), "s"(rsrc), "s"(s_off), "s"(v_off), "s"(v_off + 4096u),
+                     "s"(v_off + 8192u), "s"(u_off)
                      : "memory", "m0");
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\t"
@@ -272,10 +295,10 @@ __device__ __forceinline__ void next_class(SignWords& d) {
     }
 }
 
-// One block onto the wavefront's unit.  vnext, snext: addresses of the next step.  FIRST: the accumulators start
-// from zero.  A SIMD issues one vector or matrix instruction per four cycles: what counts is the number of instructions, 22
+// One block onto the wavefront's unit.  vnext, snext: addresses of the next step (AHEAD: its first reads are issued here).  FIRST: the
+// accumulators start from zero.  A SIMD issues one vector or matrix instruction per four cycles: what counts is the number of instructions, 22
 // vector ones and a product per class.
-template <bool FIRST, int RT>
+template <bool FIRST, int RT, bool AHEAD = true>
 __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned vaddr, unsigned vnext, unsigned snext) {
     SignWords d;
 #pragma unroll
@@ -300,7 +323,7 @@ __device__ __forceinline__ void add_block(UnitAcc& acc, StepInputs& in, unsigned
     {                                                                                      \
         if constexpr (T >= 2 && !FIRST) f[T >= 2 ? T - 2 : 0] = read_frag<(T >= 2 ? T - 2 : 0), RT>(vaddr); \
         if constexpr (T < 2) {                                                             \
-            if constexpr (T == 1) begin_reads<RT>(in, vnext, snext);                       \
+            if constexpr (T == 1 && AHEAD) begin_reads<RT>(in, vnext, snext);              \
         }                                                                                  \
         if constexpr (FIRST) {                                                             \
             acc[T] = magnitude(f[T], u, zero16());                                         \

@@ -1,0 +1,77 @@
+"""k_rows, the batch kernel of one row tile per workgroup: every share of its four wavefronts between column chunks and blocks, for row
+tiles, chunks and blocks that do not divide evenly, fewer blocks than shares, one chunk, and token counts at the edges of its groups of
+32.  Every element of y against an evaluation in 64 bits."""
+import numpy as np
+import pytest
+
+from oracle import bitstack_oracle as O
+from _cases import acts, synth_stack
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("out,inn,n", [(32, 256, 1), (96, 512, 2), (160, 768, 3), (64, 1280, 5), (352, 2304, 8), (1056, 2048, 9)])
+@pytest.mark.parametrize("chunks", [1, 2, 4, 8])
+def test_every_output_of_every_share(out, inn, n, chunks):
+    import torch
+    import paper_2410_23918_amd as B
+    st = synth_stack(3, out, inn, n, tag=17)
+    ps = B.PackedStack(st.sign_words(), st.U, st.V, st.s, max_batch=64)
+    x = acts(3, 64, inn, tag=17)
+    ref = O.forward_dense(st, x, n)
+    B.set_option(B.OPT_ROWS_CHUNKS, chunks)
+    try:
+        for loaded in {1, n}:
+            want = ref if loaded == n else O.forward_dense(st, x, loaded)
+            for b in (1, 2, 31, 32, 33, 64):
+                for dt in (torch.float32, torch.float16):
+                    y = torch.full((b, out), float("nan"), dtype=dt, device="cuda:0")
+                    ps.linear_batched(torch.from_numpy(x[:b]).to("cuda:0"), loaded, y, kernel=B.KERNEL_PANEL)
+                    torch.cuda.synchronize()
+                    err = O.relative_error(y.float().cpu().numpy(), want[:b])
+                    assert err <= 2e-3, (loaded, b, dt, err)   # also false for an element that was not written (NaN)
+    finally:
+        B.set_option(B.OPT_ROWS_CHUNKS, 0)
+
+
+@pytest.mark.parametrize("chunks", [1, 2, 4])
+def test_shares_differ_by_the_order_of_the_sums(chunks):
+    """The blocks' sums meet in fp32 before the weight is rounded: another order moves an element by some 2^-24 of the blocks' absolute sum,
+    which turns one rounding to fp16 (2^-11) in about a thousand: sqrt(1e-3) 2^-12 = 8e-6 of y in the root mean square."""
+    import torch
+    import paper_2410_23918_amd as B
+    out, inn, n = 320, 1024, 12
+    st = synth_stack(2, out, inn, n, tag=5)
+    ps = B.PackedStack(st.sign_words(), st.U, st.V, st.s, max_batch=64)
+    x = torch.from_numpy(acts(2, 48, inn, tag=5)).to("cuda:0")
+    y = {}
+    try:
+        for c in (chunks, 8):
+            B.set_option(B.OPT_ROWS_CHUNKS, c)
+            y[c] = ps.linear_batched(x, n, out_dtype=torch.float32, kernel=B.KERNEL_PANEL).double()
+            torch.cuda.synchronize()
+    finally:
+        B.set_option(B.OPT_ROWS_CHUNKS, 0)
+    assert ((y[chunks] - y[8]).norm() / y[8].norm()).item() < 2e-5
+
+
+@pytest.mark.parametrize("chunks", [1, 2, 4, 8])
+def test_a_weight_beyond_fp16_over_its_scale(chunks):
+    """A channel scaled far down, its activations zero: W'/s is no fp16 number, the sums come out right all the same."""
+    import torch
+    import paper_2410_23918_amd as B
+    out, inn, n = 64, 512, 8
+    st = synth_stack(3, out, inn, n, tag=9)
+    s = np.array(st.s, dtype=np.float32)
+    s[3] = s[300] = 1e-8
+    x = acts(3, 40, inn, tag=9)
+    x[:, [3, 300]] = 0
+    ps = B.PackedStack(st.sign_words(), st.U, st.V, s, max_batch=64)
+    want = O.forward_dense(O.Stack(st.S, st.U, st.V, s), x, n)
+    B.set_option(B.OPT_ROWS_CHUNKS, chunks)
+    try:
+        y = ps.linear_batched(torch.from_numpy(x).to("cuda:0"), n, kernel=B.KERNEL_PANEL)
+        torch.cuda.synchronize()
+    finally:
+        B.set_option(B.OPT_ROWS_CHUNKS, 0)
+    assert O.relative_error(y.float().cpu().numpy(), want) <= 2e-3
