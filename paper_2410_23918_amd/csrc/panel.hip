@@ -1000,28 +1000,36 @@ static double tile_launch_us(int out, int in, int batch, int n_loaded) {
            (in == kChunkCols ? 1.5 : 0.0);
 }
 
-// k_rows for up to 64 tokens, but not where k_fused has up to eight steps: those calls are as fast with either to a tenth (832 x 768, 3 blocks, 50
-// tokens: 9.7 us, 9.3 with k_rows; 384 x 1024, 8 blocks, 3 tokens: 12.5 and 10.7), and tests/test_gpu_small_batch.py states that k_fused has them.
+// k_rows, but up to 64 tokens not where k_fused has up to eight steps of rows of up to four column chunks: those calls are as fast with either to a
+// tenth (832 x 768, 3 blocks, 50 tokens: 9.7 us, 9.3 with k_rows; 384 x 1024, 8 blocks, 3 tokens: 12.5 and 10.7), and
+// tests/test_gpu_small_batch.py states that k_fused has them.  Longer rows give every wavefront of k_rows a chunk (1408 x 3584, one block, 8
+// tokens: 15.1, 9.8).
 static double rows_if_many_steps_us(int out, int in, int batch, int n_loaded, int part_slots) {
+    if (batch > kFusedMaxBatch) return rows_time_us(out, in, batch, n_loaded);
     int steps = 0;
     fused_time_us(out, in, batch, n_loaded, part_slots, &steps);
-    return steps > 8 ? rows_time_us(out, in, batch, n_loaded) : 1e30;
+    return steps > 8 || in > 4 * kChunkCols ? rows_time_us(out, in, batch, n_loaded) : 1e30;
 }
 
-// Duration of what launch_panel takes, for the choice between it and the other paths.  Up to 64 tokens that choice goes by the same
-// estimates; beyond, by those that its crossover is stated in, and the kernel taken is priced as it is now: k_tile fitted to 4269
-// cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks; 5.1 % root mean square: activations rearranged, rounds of
-// workgroups over pairs of column chunks, outputs written), k_batch by its plan (4.4 % over 2784).
+// Beyond 64 tokens the choice between k_batch and k_tile goes by the estimates that its crossover is stated in; this is what the one taken
+// lasts now: k_tile fitted to 4269 cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks; 5.1 % root mean square: activations
+// rearranged, rounds of workgroups over pairs of column chunks, outputs written), k_batch by its plan (4.4 % over 2784).
+static double batch_or_tile_us(int out, int in, int batch, int n_loaded, int part_slots) {
+    if (batch <= 1024 && batch_time_us(out, in, batch, n_loaded, part_slots) < tile_launch_us(out, in, batch, n_loaded))
+        return batch_plan_time_us(out, in, batch, n_loaded, part_slots);
+    const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
+    return 8.0 + 1.5e-6 * batch * in + 0.98e-6 * out * batch +
+           (wgs + 255) / 256 * (0.24 + chunk_pairs * ((0.575 + 0.085 * fill) * n_loaded + 4.32 + 1.78 * tokens + 0.14 * fill));
+}
+
+// Duration of what launch_panel takes, for the choice between it and the other paths
 double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok) {
     const double tt = batch > 32 && tile_ok ? tile_launch_us(out, in, batch, n_loaded) : 1e30;
     const double tb = batch <= 1024 ? batch_time_us(out, in, batch, n_loaded, part_slots) : 1e30;
     if (batch <= kFusedMaxBatch)
         return std::min({fused_time_us(out, in, batch, n_loaded, part_slots), rows_if_many_steps_us(out, in, batch, n_loaded, part_slots), tb, tt});
-    if (tb < tile_launch_us(out, in, batch, n_loaded)) return batch_plan_time_us(out, in, batch, n_loaded, part_slots);
-    const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
-    const double fill = wgs < 256 ? wgs / 256.0 : 1.0, tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
-    return 8.0 + 1.5e-6 * batch * in + 0.98e-6 * out * batch +
-           (wgs + 255) / 256 * (0.24 + chunk_pairs * ((0.575 + 0.085 * fill) * n_loaded + 4.32 + 1.78 * tokens + 0.14 * fill));
+    return std::min(rows_time_us(out, in, batch, n_loaded), batch_or_tile_us(out, in, batch, n_loaded, part_slots));
 }
 
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
@@ -1035,12 +1043,13 @@ hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     // k_batch is up to 10 % slower than another in its place.
     const int rows_forced = rows_forced_chunks();
     const double tr = rows_forced != 16 && !batch_forced_tiles() && rows_fits(p) ? rows_forced ? 0.0 : rows_if_many_steps_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
+    if (a.batch > kFusedMaxBatch && tr < batch_or_tile_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots)) return launch_rows(p, st);
     const bool tile_ok = a.batch > 32 && tile_fits(p);
     const double tf = a.batch <= kFusedMaxBatch && fused_fits(p) ? fused_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
     const double tb = a.batch <= 1024 && batch_fits(p) ? batch_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
     // beyond 64 tokens also where the weight-tile kernel cannot hold the stack: k_panel is slower than k_tile's estimate
     const double tt = tile_ok || a.batch > kFusedMaxBatch ? tile_launch_us(p.out, p.in, p.batch, p.n_loaded) : 1e30;
-    if (tr < tf && tr < tt && tr < tb) return launch_rows(p, st);
+    if (a.batch <= kFusedMaxBatch && tr < tf && tr < tt && tr < tb) return launch_rows(p, st);
     if (tb < tf && tb < tt) return launch_batch(p, st);
     if (tf < tt) return launch_fused(p, st);
     if (tile_ok) return launch_tile(p, st);

@@ -1,4 +1,4 @@
-// Small batches (2 to 64 tokens) through matrices of few rows: k_batch's arithmetic, one row tile per workgroup and the blocks shared out.
+// Batches through matrices of few rows (up to 256 or 512 workgroups of 32 rows x 64 tokens): k_batch's arithmetic, one row tile per workgroup and the blocks shared out.
 //
 // k_batch's workgroups are 64 or 128 rows high, and a column split needs partial rows that a small image has no room for: 704 x 1024, 15
 // blocks, 32 tokens ran on eleven of 256 compute units, each walking all blocks.  Here a workgroup is 32 rows: eight wavefronts = C column
@@ -28,7 +28,7 @@ constexpr unsigned kRowsWaveLds = kRowsRing * RowsStep::kBytes, kRowsLds = kRows
 constexpr unsigned kUnitSums = 128 * 64 * 4;   // a unit's fp32 sums
 static_assert(kRowsLds <= 160 * 1024 && kRowsWaves / 2 * kUnitSums <= kRowsLds, "half of the wavefronts park their sums in the idle rings");
 
-// GROUPS of 32 tokens; p.n_ks: column chunks at a time (C)
+// GROUPS of 32 tokens to a workgroup; p.n_ks: column chunks at a time (C)
 template <int GROUPS>
 __global__ __launch_bounds__(kRowsWaves * 64, 2) void k_rows(KParams p) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -37,6 +37,7 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void k_rows(KParams p) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hl = lane >> 5, ln = lane & 31;
     const int nch = p.in / kChunkCols, n = p.n_loaded, rt = blockIdx.x;
+    const int tok0 = int(blockIdx.y) * (GROUPS * 32);   // this workgroup's tokens
     const int C = p.n_ks, G = kRowsWaves / C, c = wave % C, g = wave / C;
     const int iters = (nch + C - 1) / C, nb = (n - g + G - 1) / G;   // G <= n
 
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void k_rows(KParams p) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int t = 2 * i + (own >> 5), piece = (own & 31) ^ (t & 15);
-                    load_to_lds(x_rsrc, ring + unsigned(i) * 1024u, unsigned(min(k * 32 + t, p.batch - 1)) * unsigned(p.in) * 2u + unsigned(piece) * 16u,
+                    load_to_lds(x_rsrc, ring + unsigned(i) * 1024u, unsigned(min(tok0 + k * 32 + t, p.batch - 1)) * unsigned(p.in) * 2u + unsigned(piece) * 16u,
                                 unsigned(ch) * (kChunkCols * 2));
                 }
             };
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(kRowsWaves * 64, 2) void k_rows(KParams p) {
                 float sum = 0.0f;
 #pragma unroll
                 for (int w = 0; w < kRowsWaves; ++w) sum += red[(w * 16 + v) * 64 + l];
-                const int tok = k * 32 + t;
+                const int tok = tok0 + k * 32 + t;
                 if (tok < p.batch) {
                     rest = __builtin_fmaf(sum, 0.0f, rest);
                     store_y(p, size_t(tok) * p.out + rt * kTileRows + row, sum);
@@ -211,24 +212,25 @@ hipError_t launch_rows_t(KParams p, int chunks_at_a_time, hipStream_t st) {
         attr_set = true;
     }
     p.n_ks = chunks_at_a_time;
-    hipLaunchKernelGGL((k_rows<GROUPS>), dim3(p.out / kTileRows), dim3(kRowsWaves * 64), kRowsLds, st, p);
+    hipLaunchKernelGGL((k_rows<GROUPS>), dim3(p.out / kTileRows, (p.batch + GROUPS * 32 - 1) / (GROUPS * 32)), dim3(kRowsWaves * 64), kRowsLds, st, p);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// Column chunks at a time, and the estimated duration (microseconds), fitted to 3727 cases (64 x 256 to 16384 x 14336, 1 to 24 blocks, 2 to
-// 64 tokens; each timed with every share; 4.1 % root mean square).  Against k_batch, k_fused and k_tile in those cases: up to 256 row
-// tiles it is the faster one in 57-90 %, and taking it there is worth 13 to 21 % in the mean of all; beyond, where it takes a second round, in 5 %.
+// Column chunks at a time, and the estimated duration (microseconds), fitted to 3727 cases of 2 to 64 tokens (64 x 256 to 16384 x 14336, 1 to
+// 24 blocks; each timed with every share; 4.1 % root mean square) and 1377 of 65 to 1024 (4.5 %).  Where the workgroups fit the chip at once, against
+// k_batch, k_fused and k_tile, it is the faster one in 57-90 % (up to 64 tokens, worth 13 to 21 % in the mean of all by number of
+// workgroups) and 90-100 % (beyond, 34 to 40 %); with a second round of workgroups in 5 and 24 %, worth 1 %.
 static double rows_plan(int out, int in, int batch, int n_loaded, int* chunks_at_a_time) {
-    const int nch = in / kChunkCols, tiles = out / kTileRows, rounds = (tiles + 255) / 256, more = batch > 32 ? 1 : 0;
-    const double fill = tiles < 256 ? tiles / 256.0 : 1.0;
+    const int nch = in / kChunkCols, wgs = out / kTileRows * ((batch + 63) / 64), more = batch > 32 ? 1 : 0, rounds = (wgs + 255) / 256;
+    const double fill = wgs < 256 ? wgs / 256.0 : 1.0;
     double best = 0.0;
     for (int c = kRowsWaves; c >= 1; c /= 2) {
         const int g = kRowsWaves / c;
         if (g > n_loaded) break;
         const double us = 1.52 + 0.53 * more + rounds * (1.54 + (nch + c - 1) / c * ((n_loaded + g - 1) / g * (0.957 + 0.137 * fill) + 2.04 + 0.75 * more +
-                                                                                  (g > 1 ? 1.0 + 0.34 * g : 0.0)));
+                                                                                  (batch > 64 ? 0.4 : 0.0) + (g > 1 ? 1.0 + 0.34 * g : 0.0)));
         if (best == 0.0 || us < best) {
             best = us;
             *chunks_at_a_time = c;
@@ -237,13 +239,16 @@ static double rows_plan(int out, int in, int batch, int n_loaded, int* chunks_at
     return best;
 }
 // For comparison with the other kernels' estimates: 4 % on top, so that an error of either leaves the call where it was (without, 40 of 2585
-// cases are 3 to 15 % slower than with the others)
+// cases are 3 to 15 % slower than with the others), and 20 % with a second round, where the estimates are worth less (2720 x 5888, 6 blocks, 351
+// tokens: 123 us, 69 with k_rows; 7168 x 2048, 5 blocks, 249 tokens: 40, 49)
 double rows_time_us(int out, int in, int batch, int n_loaded) {
     int c;
-    return 1.04 * rows_plan(out, in, batch, n_loaded, &c);
+    const int wgs = out / kTileRows * ((batch + 63) / 64);
+    if (wgs > 512) return 1e30;
+    return (wgs > 256 ? 1.2 : 1.04) * rows_plan(out, in, batch, n_loaded, &c);
 }
 bool rows_fits(const KParams& p) {   // one 32-bit buffer descriptor each over the loaded blocks and the activations
-    return p.batch <= kSmallBatch && size_t(p.n_loaded) * p.block_stride < (size_t(1) << 32) && size_t(p.batch) * p.in * 2 < (size_t(1) << 32);
+    return p.batch <= 1024 && size_t(p.n_loaded) * p.block_stride < (size_t(1) << 32) && size_t(p.batch) * p.in * 2 < (size_t(1) << 32);
 }
 static std::atomic<int> g_forced_chunks{0};   // measurement hook: 0 = the estimate's choice, 16 = never
 void rows_force_chunks(int chunks) { g_forced_chunks = chunks == 1 || chunks == 2 || chunks == 4 || chunks == 8 || chunks == 16 ? chunks : 0; }

@@ -16,14 +16,14 @@ def test_every_output_of_every_share(out, inn, n, chunks):
     import torch
     import paper_2410_23918_amd as B
     st = synth_stack(3, out, inn, n, tag=17)
-    ps = B.PackedStack(st.sign_words(), st.U, st.V, st.s, max_batch=64)
-    x = acts(3, 64, inn, tag=17)
+    ps = B.PackedStack(st.sign_words(), st.U, st.V, st.s, max_batch=200)
+    x = acts(3, 200, inn, tag=17)
     ref = O.forward_dense(st, x, n)
     B.set_option(B.OPT_ROWS_CHUNKS, chunks)
     try:
         for loaded in {1, n}:
             want = ref if loaded == n else O.forward_dense(st, x, loaded)
-            for b in (1, 2, 31, 32, 33, 64):
+            for b in (1, 2, 31, 32, 33, 64, 65, 200):
                 for dt in (torch.float32, torch.float16):
                     y = torch.full((b, out), float("nan"), dtype=dt, device="cuda:0")
                     ps.linear_batched(torch.from_numpy(x[:b]).to("cuda:0"), loaded, y, kernel=B.KERNEL_PANEL)
