@@ -20,6 +20,7 @@ struct bitstack_weight {
     Geometry geo;
     unsigned char* dev;  // caller-owned device buffer
     int resident;        // blocks 0 .. resident-1 are loaded (Section 2.2: blocks come and go in stack order)
+    float rs_max;        // the largest 1/s
 };
 
 static thread_local int g_last_hip = 0;
@@ -69,6 +70,12 @@ static int check_pack_args(int out, int in, int k, int n, int max_batch, const u
     for (int j = 0; j < in; ++j)
         if (!(std::isfinite(s[j]) && s[j] > 0.0f)) return BITSTACK_E_SCALE;
     return BITSTACK_OK;
+}
+
+static float largest_rs(const float* s, int in) {
+    float least = s[0];
+    for (int j = 1; j < in; ++j) least = s[j] < least ? s[j] : least;
+    return 1.0f / least;
 }
 
 // device form of one block: sign tiles, V panels, U rows into blk (block_stride bytes), and the
@@ -171,6 +178,7 @@ int bitstack_pack_blocks(int out, int in, int k, int n, int max_batch, const uin
     w->geo = g;
     w->dev = static_cast<unsigned char*>(device_buf);
     w->resident = n;
+    w->rs_max = largest_rs(s, in);
     *handle = w;
     return BITSTACK_OK;
 }
@@ -223,6 +231,7 @@ int bitstack_create_stack(int out, int in, int k, int n_slots, int max_batch, co
     w->geo = g;
     w->dev = dev;
     w->resident = 0;
+    w->rs_max = largest_rs(s, in);
     *handle = w;
     return BITSTACK_OK;
 }
@@ -320,13 +329,23 @@ static size_t scratch_bytes(const Geometry& g, size_t workspace_bytes) {
     return workspace_bytes >= g.xpack_bytes ? workspace_bytes : g.xpack_bytes;
 }
 
-static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t workspace_bytes) {
+// Up to this 1/s the choice restores the weight wherever that is faster.  Restoring writes W'/s as fp16, and an entry beyond 65504 makes
+// every token NaN, also one whose activation there is zero; the kernels for one token and for batches keep 1/s on the activations, or go
+// back to that when a sum is not finite.  W' is known on the device only, so the line is drawn by s: at 2^12 W' has room up to 16, that is for
+// any weight W'/s that fp16 could hold to begin with, while a channel that calibration left almost silent (s clamped to 1e-5, say) and whose
+// W' the blocks do not follow down to that is beyond it.
+constexpr float kRestoreMaxRs = 4096.0f;
+
+static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t workspace_bytes, float rs_max) {
     if (batch == 1) return BITSTACK_KERNEL_DECODE;
     workspace_bytes = scratch_bytes(g, workspace_bytes);
     const double t_decode = decode_tokens_time_us(g, batch, n_loaded);   // up to four tokens per launch
-    const double t_panel = panel_time_us(g.out, g.in, batch, n_loaded, g.part_slots, g.xpack_bytes != 0);
+    bool tile = false;
+    const double t_panel = panel_time_us(g.out, g.in, batch, n_loaded, g.part_slots, g.xpack_bytes != 0, &tile);
     int kernel = t_decode <= t_panel ? BITSTACK_KERNEL_DECODE : BITSTACK_KERNEL_PANEL;
     const double t_best = t_decode <= t_panel ? t_decode : t_panel;
+    // k_tile writes W'/s as fp16 too: nothing is lost by restoring in its place
+    if (rs_max > kRestoreMaxRs && !(kernel == BITSTACK_KERNEL_PANEL && tile)) return kernel;
     const int slab = slab_rows(g, workspace_bytes);
     // (the dense product addresses x and a slab of the dense weight with 32-bit byte offsets)
     const bool dense_ok = size_t(batch) * g.in * 2 <= 0xffffffffull && size_t(slab) * g.in * 2 <= 0xffffffffull;
@@ -353,7 +372,7 @@ int bitstack_choose_kernel(int out, int in, int n_slots, int max_batch, int batc
     if (!shape_ok(out, in, kRank) || n_slots < 0 || max_batch < 1) return BITSTACK_E_SHAPE;
     if (batch < 1 || batch > max_batch || n_loaded < 0 || n_loaded > n_slots) return BITSTACK_E_RANGE;
     if (n_loaded == 0) return BITSTACK_KERNEL_AUTO;   // nothing to choose: y is cleared
-    return choose_kernel(make_geometry(out, in, n_slots, max_batch), batch, n_loaded, workspace_bytes);
+    return choose_kernel(make_geometry(out, in, n_slots, max_batch), batch, n_loaded, workspace_bytes, 1.0f);
 }
 
 static int linear_impl(const void* x, int batch, const bitstack_weight_t* w, int n_loaded, void* y, int y_dtype,
@@ -377,7 +396,7 @@ static int linear_impl(const void* x, int batch, const bitstack_weight_t* w, int
     if (n_loaded == 0) {
         e = launch_zero(a, st);
     } else {
-        if (kernel == BITSTACK_KERNEL_AUTO) kernel = choose_kernel(g, batch, n_loaded, workspace ? workspace_bytes : 0);
+        if (kernel == BITSTACK_KERNEL_AUTO) kernel = choose_kernel(g, batch, n_loaded, workspace ? workspace_bytes : 0, w->rs_max);
         switch (kernel) {
             case BITSTACK_KERNEL_REFERENCE:
                 e = launch_reference(a, st);

@@ -73,7 +73,7 @@ void rows_force_chunks(int chunks);
 int rows_forced_chunks();
 int batch_forced_tiles();
 double batch_plan_time_us(int out, int in, int batch, int n_loaded, int part_slots);   // what the launch takes, also beyond 64 tokens
-double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok);
+double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok, bool* tile);   // *tile: k_tile is what it takes
 int restore_max_blocks();
 // can the restore kernel take n_loaded blocks of this stride? (block count, and their bytes below 4 GiB)
 bool restore_fits(size_t block_stride, int n_loaded);

@@ -1014,8 +1014,10 @@ static double rows_if_many_steps_us(int out, int in, int batch, int n_loaded, in
 // Beyond 64 tokens the choice between k_batch and k_tile goes by the estimates that its crossover is stated in; this is what the one taken
 // lasts now: k_tile fitted to 4269 cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks; 5.1 % root mean square: activations
 // rearranged, rounds of workgroups over pairs of column chunks, outputs written), k_batch by its plan (4.4 % over 2784).
-static double batch_or_tile_us(int out, int in, int batch, int n_loaded, int part_slots) {
-    if (batch <= 1024 && batch_time_us(out, in, batch, n_loaded, part_slots) < tile_launch_us(out, in, batch, n_loaded))
+static double batch_or_tile_us(int out, int in, int batch, int n_loaded, int part_slots, bool* tile = nullptr) {
+    const bool batched = batch <= 1024 && batch_time_us(out, in, batch, n_loaded, part_slots) < tile_launch_us(out, in, batch, n_loaded);
+    if (tile) *tile = !batched;
+    if (batched)
         return batch_plan_time_us(out, in, batch, n_loaded, part_slots);
     const int wgs = (out + 63) / 64 * ((batch + kTileTokens - 1) / kTileTokens), chunk_pairs = (in / kChunkCols + 1) / 2;
     const double fill = wgs < 256 ? wgs / 256.0 : 1.0, tokens = (batch < kTileTokens ? batch : kTileTokens) / double(kTileTokens);
@@ -1024,12 +1026,17 @@ static double batch_or_tile_us(int out, int in, int batch, int n_loaded, int par
 }
 
 // Duration of what launch_panel takes, for the choice between it and the other paths
-double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok) {
-    const double tt = batch > 32 && tile_ok ? tile_launch_us(out, in, batch, n_loaded) : 1e30;
-    const double tb = batch <= 1024 ? batch_time_us(out, in, batch, n_loaded, part_slots) : 1e30;
-    if (batch <= kFusedMaxBatch)
-        return std::min({fused_time_us(out, in, batch, n_loaded, part_slots), rows_if_many_steps_us(out, in, batch, n_loaded, part_slots), tb, tt});
-    return std::min(rows_time_us(out, in, batch, n_loaded), batch_or_tile_us(out, in, batch, n_loaded, part_slots));
+double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok, bool* tile) {
+    if (batch <= kFusedMaxBatch) {
+        const double tt = batch > 32 && tile_ok ? tile_launch_us(out, in, batch, n_loaded) : 1e30;
+        const double others = std::min({fused_time_us(out, in, batch, n_loaded, part_slots), rows_if_many_steps_us(out, in, batch, n_loaded, part_slots),
+                                        batch_time_us(out, in, batch, n_loaded, part_slots)});
+        *tile = tt <= others;
+        return std::min(others, tt);
+    }
+    const double tr = rows_time_us(out, in, batch, n_loaded), t = batch_or_tile_us(out, in, batch, n_loaded, part_slots, tile);
+    if (tr < t) *tile = false;
+    return std::min(tr, t);
 }
 
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {

@@ -1,0 +1,35 @@
+"""Scales that take W'/s out of fp16's range in a few channels, through the calls that choose their kernel: where a stack of moderate
+scales is restored and multiplied, such a one stays with the kernels that put 1/s on the activations.  Whole numbers, bit for bit."""
+import pytest
+
+from test_gpu_exact import activations, compare, stack
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("out,inn,n,batch,lent", [
+    (4096, 4096, 16, 24, True),
+    (4096, 4096, 16, 32, True),
+    (1024, 4096, 16, 24, False),    # restored through the image's own scratch
+    (1024, 8192, 16, 32, False),
+    (3136, 2560, 12, 193, False),   # beyond 64 tokens: k_batch
+    (1024, 4096, 16, 100, False),   # k_rows
+])
+def test_restored_only_where_the_dense_weight_is_in_range(out, inn, n, batch, lent):
+    import torch
+    import paper_2410_23918_amd as B
+    scratch = torch.empty(B.dense_bytes(out, inn) if lent else 0, dtype=torch.uint8, device="cuda:0")
+    assert B.choose_kernel(out, inn, n, 2048, batch, n, scratch.numel()) == B.KERNEL_MATERIALISE
+    for small in ((), (5, 300, 511, inn - 1)):
+        ps, w = stack(out, inn, n, 2048, small)
+        x = activations(batch, inn, batch, small)
+        image_scratch = ps.buf[ps.buf.numel() // 256 * 256 - 2048 * inn * 2:]   # the image's last 2048 x in fp16 values
+        used = scratch if lent else image_scratch
+        used.fill_(0xff)
+        torch.cuda.synchronize()
+        if lent:
+            compare(ps, w, n, x, lambda y: ps.linear_batched_ws(x, n, scratch, y))
+        else:
+            compare(ps, w, n, x, lambda y: ps.linear_batched(x, n, y))
+        assert bool((used != 0xff).any()) == (not small)   # restored there or not
+        del ps, w
