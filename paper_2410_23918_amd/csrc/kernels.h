@@ -68,7 +68,8 @@ double dense_time_us(int out, int in, int batch);
 double restore_time_us(int rows, int in, int n_loaded);
 // estimated durations of the batch kernels (microseconds); launch_panel takes the cheapest
 double batch_time_us(int out, int in, int batch, int n_loaded, int part_slots);
-double rows_time_us(int out, int in, int batch, int n_loaded);
+bool rows_fits(int out, int in, int batch, int n_loaded);
+double rows_time_us(int out, int in, int batch, int n_loaded);   // out of reach where it does not fit or is not worth it
 void rows_force_chunks(int chunks);
 int rows_forced_chunks();
 int batch_forced_tiles();

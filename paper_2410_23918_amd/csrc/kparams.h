@@ -85,7 +85,6 @@ inline KParams make_params(const LaunchArgs& a) {
 
 // batch kernel for 2 to 1024 tokens, in groups of 64 (batch.hip)
 bool batch_fits(const KParams& p);
-bool rows_fits(const KParams& p);
 hipError_t launch_rows(const KParams& p, hipStream_t st);
 hipError_t launch_batch(const KParams& p, hipStream_t st);
 

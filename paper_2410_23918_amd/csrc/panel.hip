@@ -1049,7 +1049,7 @@ hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     // 146 and 189).  In 8257 cases that were timed with every kernel the one taken is 0.1 % slower than the fastest on average;
     // k_batch is up to 10 % slower than another in its place.
     const int rows_forced = rows_forced_chunks();
-    const double tr = rows_forced != 16 && !batch_forced_tiles() && rows_fits(p) ? rows_forced ? 0.0 : rows_if_many_steps_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
+    const double tr = rows_forced != 16 && !batch_forced_tiles() && rows_fits(p.out, p.in, p.batch, p.n_loaded) ? rows_forced ? 0.0 : rows_if_many_steps_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
     if (a.batch > kFusedMaxBatch && tr < batch_or_tile_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots)) return launch_rows(p, st);
     const bool tile_ok = a.batch > 32 && tile_fits(p);
     const double tf = a.batch <= kFusedMaxBatch && fused_fits(p) ? fused_time_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;

@@ -238,17 +238,21 @@ static double rows_plan(int out, int in, int batch, int n_loaded, int* chunks_at
     }
     return best;
 }
+// What the launch takes, and what the estimate prices: up to 1024 tokens, one 32-bit buffer descriptor each over the loaded blocks and the
+// activations.  (Priced without these conditions, few rows and 1025 to 2048 tokens went to the panel path for k_rows' estimate, where k_tile
+// ran: 544 x 14336, 2 blocks, 1800 tokens 245 us, 99 restored; 60 such calls take 0.52 of the time restored, 0.81 at most.)
+bool rows_fits(int out, int in, int batch, int n_loaded) {
+    return batch <= 1024 && size_t(n_loaded) * make_geometry(out, in, 1, 1).block_stride < (size_t(1) << 32) && size_t(batch) * in * 2 < (size_t(1) << 32);
+}
 // For comparison with the other kernels' estimates: 4 % on top, so that an error of either leaves the call where it was (without, 40 of 2585
 // cases are 3 to 15 % slower than with the others), and 20 % with a second round, where the estimates are worth less (2720 x 5888, 6 blocks, 351
 // tokens: 123 us, 69 with k_rows; 7168 x 2048, 5 blocks, 249 tokens: 40, 49)
 double rows_time_us(int out, int in, int batch, int n_loaded) {
+    if (!rows_fits(out, in, batch, n_loaded)) return 1e30;
     int c;
     const int wgs = out / kTileRows * ((batch + 63) / 64);
     if (wgs > 512) return 1e30;
     return (wgs > 256 ? 1.2 : 1.04) * rows_plan(out, in, batch, n_loaded, &c);
-}
-bool rows_fits(const KParams& p) {   // one 32-bit buffer descriptor each over the loaded blocks and the activations
-    return p.batch <= 1024 && size_t(p.n_loaded) * p.block_stride < (size_t(1) << 32) && size_t(p.batch) * p.in * 2 < (size_t(1) << 32);
 }
 static std::atomic<int> g_forced_chunks{0};   // measurement hook: 0 = the estimate's choice, 16 = never
 void rows_force_chunks(int chunks) { g_forced_chunks = chunks == 1 || chunks == 2 || chunks == 4 || chunks == 8 || chunks == 16 ? chunks : 0; }

@@ -12,6 +12,11 @@ BIG = 1 << 40
     (2528, 5888, 1, 298, 0, False),        # in slabs through the image's own scratch, the second of 480 rows: 33 / 99
     (2688, 13568, 9, 78, 0, False),        # 77 / 211
     (28672, 8192, 16, 2048, 0, True),      # 2100 / 1350
+    # more than 1024 tokens through few rows: k_tile, not k_rows, is what restoring is compared with
+    (544, 14336, 2, 1800, BIG, True),      # 245 / 99
+    (512, 2048, 1, 2048, BIG, True),       # 44 / 18
+    (512, 2048, 1, 2048, 0, True),         # 44 / 18
+    (544, 14336, 2, 1800, 0, True),        # 245 / 98
 ])
 def test_far_from_the_crossover(out, inn, n, tokens, scratch, restore):
     import paper_2410_23918_amd as B
