@@ -821,6 +821,16 @@ hipError_t launch_decode_group(const LaunchArgs* a, int count, hipStream_t st) {
     return e != hipSuccess ? e : run_decode_launch(d, st);
 }
 
+// Small stacks: latency only, of which k_token has less.  The work-split estimate is 1 us too high for calls of 9 to 13 us, and 2
+// where a row has fewer than four column chunks: taken off, the kernel chosen is 0.1 % slower than the other in the mean of
+// 900 single stacks, and in three by more than 2 % (at most 5 %).
+static bool token_is_faster(const LaunchArgs* a, int count, const DecodePlan& pl) {
+    const DecodeTuning& tn = decode_tuning();
+    if (tn.tiles.load() || tn.ks_chunks.load() || tn.bgroups.load() || tn.early.load() >= 0) return false;
+    const double us = token_time_us(a, count);
+    return us > 0.0 && us < pl.us - (a[0].geo.in < kPieceCols ? 2.0 : 1.0);
+}
+
 // Work split and argument block of one launch (host only, nothing is enqueued).
 hipError_t prepare_decode_group(const LaunchArgs* a, int count, DecodeLaunch* d) {
     if (count < 1 || count > kMaxGroup) return hipErrorInvalidValue;
@@ -834,15 +844,9 @@ hipError_t prepare_decode_group(const LaunchArgs* a, int count, DecodeLaunch* d)
     if (!plan_decode(a, count, &pl)) return hipErrorInvalidValue;   // nothing has been launched
     KGroup& grp = d->grp;
     d->token = false;
-    if (!tn.tiles.load() && !tn.ks_chunks.load() && !tn.bgroups.load() && tn.early.load() < 0) {
-        // Small stacks: latency only, of which k_token has less.  The work-split estimate is 1 us too high for calls of 9 to 13 us, and 2
-        // where a row has fewer than four column chunks: taken off, the kernel chosen is 0.1 % slower than the other in the mean of
-        // 900 single stacks, and in three by more than 2 % (at most 5 %).
-        const double us = token_time_us(a, count);
-        if (us > 0.0 && us < pl.us - (a[0].geo.in < kPieceCols ? 2.0 : 1.0)) {
-            prepare_token(a, count, d);
-            return hipSuccess;
-        }
+    if (token_is_faster(a, count, pl)) {
+        prepare_token(a, count, d);
+        return hipSuccess;
     }
     grp.count = count;
     unsigned next = 0;
@@ -1010,6 +1014,23 @@ static double plan_decode_tokens(const Geometry& g, int batch, int n_loaded, int
 
 double decode_tokens_time_us(const Geometry& g, int batch, int n_loaded) {
     return plan_decode_tokens(g, batch, n_loaded, nullptr, nullptr, nullptr, nullptr);
+}
+
+bool decode_tokens_use_token(const Geometry& g, int batch, int n_loaded) {
+    int sizes[kPlanTokens], n = 0, head_size = 1, heads = 0;
+    plan_decode_tokens(g, batch, n_loaded, sizes, &n, &head_size, &heads);
+    bool single = heads > 0 && head_size == 1;
+    for (int i = 0; i < n; ++i) single = single || sizes[i] == 1;
+    if (!single) return false;   // members that share a workspace are not k_token's
+    LaunchArgs a;
+    a.x = a.y = nullptr;
+    a.image = nullptr;
+    a.geo = g;
+    a.batch = 1;
+    a.n_loaded = n_loaded;
+    a.y_f32 = false;
+    DecodePlan pl;
+    return plan_decode(&a, 1, &pl) && token_is_faster(&a, 1, pl);
 }
 
 // A small batch through the decode kernel: one to four tokens per launch, each a member of the

@@ -340,12 +340,19 @@ static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t work
     if (batch == 1) return BITSTACK_KERNEL_DECODE;
     workspace_bytes = scratch_bytes(g, workspace_bytes);
     const double t_decode = decode_tokens_time_us(g, batch, n_loaded);   // up to four tokens per launch
-    bool tile = false;
-    const double t_panel = panel_time_us(g.out, g.in, batch, n_loaded, g.part_slots, g.xpack_bytes != 0, &tile);
-    int kernel = t_decode <= t_panel ? BITSTACK_KERNEL_DECODE : BITSTACK_KERNEL_PANEL;
-    const double t_best = t_decode <= t_panel ? t_decode : t_panel;
+    const PanelEstimate panel = panel_estimate(g.out, g.in, batch, n_loaded, g.part_slots, g.xpack_bytes != 0);
+    int kernel = t_decode <= panel.us ? BITSTACK_KERNEL_DECODE : BITSTACK_KERNEL_PANEL;
+    const double t_best = t_decode <= panel.us ? t_decode : panel.us;
+    const bool wide = rs_max > kRestoreMaxRs;
+    // The kernels for one token hold x/s in fp32; k_rows and the materialising path do not.  Where they are estimated faster than k_batch and
+    // k_fused, they keep the stacks whose x/s may leave fp16's range (s as above), and the cuts in which a token goes through k_token (1.5e-7
+    // of y, 2e-4 with k_rows; 288 x 1280, 23 blocks, 5 tokens: 18.6 us, 28.1 with k_rows -- the estimate of a cut does not know k_token).
+    auto kept = [&](int k) {
+        const bool keep = k != BITSTACK_KERNEL_DECODE && t_decode <= panel.without_rows_us && (wide || decode_tokens_use_token(g, batch, n_loaded));
+        return keep ? int(BITSTACK_KERNEL_DECODE) : k;
+    };
     // k_tile writes W'/s as fp16 too: nothing is lost by restoring in its place
-    if (rs_max > kRestoreMaxRs && !(kernel == BITSTACK_KERNEL_PANEL && tile)) return kernel;
+    if (wide && !(kernel == BITSTACK_KERNEL_PANEL && panel.tile)) return kept(kernel);
     const int slab = slab_rows(g, workspace_bytes);
     // (the dense product addresses x and a slab of the dense weight with 32-bit byte offsets)
     const bool dense_ok = size_t(batch) * g.in * 2 <= 0xffffffffull && size_t(slab) * g.in * 2 <= 0xffffffffull;
@@ -364,7 +371,7 @@ static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t work
         const bool displaces = size_t(slab) * g.in * 2 > (size_t(64) << 20) && batch <= 256;
         if (t_mat * (displaces ? 1.15 : 1.0) < t_best) kernel = BITSTACK_KERNEL_MATERIALISE;
     }
-    return kernel;
+    return kept(kernel);
 }
 
 int bitstack_choose_kernel(int out, int in, int n_slots, int max_batch, int batch, int n_loaded,

@@ -56,6 +56,7 @@ constexpr size_t kStaticPartBytes = size_t(4) << 20;   // partial rows
 constexpr size_t kStaticScratchBytes = kStaticPartBytes + size_t(kCounterSlots) * 4;
 hipError_t launch_decode_static(const LaunchArgs& a, hipStream_t st);
 double decode_tokens_time_us(const Geometry& g, int batch, int n_loaded);
+bool decode_tokens_use_token(const Geometry& g, int batch, int n_loaded);   // is one of the launches k_token's?
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st);
 // materialising path: W' diag(1/s) of the loaded prefix -> a.wdense; then y = x wdense^T
 hipError_t launch_restore(const LaunchArgs& a, hipStream_t st);
@@ -74,7 +75,12 @@ void rows_force_chunks(int chunks);
 int rows_forced_chunks();
 int batch_forced_tiles();
 double batch_plan_time_us(int out, int in, int batch, int n_loaded, int part_slots);   // what the launch takes, also beyond 64 tokens
-double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok, bool* tile);   // *tile: k_tile is what it takes
+struct PanelEstimate {
+    double us;                // what launch_panel takes
+    double without_rows_us;   // if it were not for k_rows
+    bool tile;                // k_tile is what it takes
+};
+PanelEstimate panel_estimate(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok);
 int restore_max_blocks();
 // can the restore kernel take n_loaded blocks of this stride? (block count, and their bytes below 4 GiB)
 bool restore_fits(size_t block_stride, int n_loaded);

@@ -1026,17 +1026,22 @@ static double batch_or_tile_us(int out, int in, int batch, int n_loaded, int par
 }
 
 // Duration of what launch_panel takes, for the choice between it and the other paths
-double panel_time_us(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok, bool* tile) {
+PanelEstimate panel_estimate(int out, int in, int batch, int n_loaded, int part_slots, bool tile_ok) {
+    PanelEstimate e;
+    double rows;
     if (batch <= kFusedMaxBatch) {
         const double tt = batch > 32 && tile_ok ? tile_launch_us(out, in, batch, n_loaded) : 1e30;
-        const double others = std::min({fused_time_us(out, in, batch, n_loaded, part_slots), rows_if_many_steps_us(out, in, batch, n_loaded, part_slots),
-                                        batch_time_us(out, in, batch, n_loaded, part_slots)});
-        *tile = tt <= others;
-        return std::min(others, tt);
+        const double others = std::min(fused_time_us(out, in, batch, n_loaded, part_slots), batch_time_us(out, in, batch, n_loaded, part_slots));
+        e.without_rows_us = std::min(others, tt);
+        e.tile = tt <= others;
+        rows = rows_if_many_steps_us(out, in, batch, n_loaded, part_slots);
+    } else {
+        e.without_rows_us = batch_or_tile_us(out, in, batch, n_loaded, part_slots, &e.tile);
+        rows = rows_time_us(out, in, batch, n_loaded);
     }
-    const double tr = rows_time_us(out, in, batch, n_loaded), t = batch_or_tile_us(out, in, batch, n_loaded, part_slots, tile);
-    if (tr < t) *tile = false;
-    return std::min(tr, t);
+    if (rows < e.without_rows_us) e.tile = false;
+    e.us = std::min(rows, e.without_rows_us);
+    return e;
 }
 
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {

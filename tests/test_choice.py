@@ -22,3 +22,11 @@ def test_far_from_the_crossover(out, inn, n, tokens, scratch, restore):
     import paper_2410_23918_amd as B
     got = B.choose_kernel(out, inn, n, 2048, tokens, n, scratch)
     assert got == (B.KERNEL_MATERIALISE if restore else B.KERNEL_PANEL)
+
+
+@pytest.mark.parametrize("out,inn,n,max_batch,scratch", [(288, 1280, 23, 64, 0), (480, 1280, 24, 2048, 0), (416, 1280, 24, 64, BIG)])
+def test_five_tokens_of_which_one_is_a_launch_of_its_own(out, inn, n, max_batch, scratch):
+    """Estimated faster through k_rows or restored, but that token would be rounded to fp16 on its way (tests/test_gpu_scales.py); 19 us, 28
+    and 29 with k_rows."""
+    import paper_2410_23918_amd as B
+    assert B.choose_kernel(out, inn, n, max_batch, 5, n, scratch) == B.KERNEL_DECODE

@@ -33,3 +33,30 @@ def test_restored_only_where_the_dense_weight_is_in_range(out, inn, n, batch, le
             compare(ps, w, n, x, lambda y: ps.linear_batched(x, n, y))
         assert bool((used != 0xff).any()) == (not small)   # restored there or not
         del ps, w
+
+
+@pytest.mark.parametrize("out,inn,n,batch", [(448, 768, 24, 6), (832, 1024, 10, 2), (672, 1792, 24, 5)])
+def test_activations_over_their_scales_out_of_fp16_range_where_one_token_kernels_serve_the_batch(out, inn, n, batch):
+    """Few tokens, estimated faster through k_rows or restored than through the kernels for one token, which hold x/s in fp32: both x/s
+    and W'/s are beyond fp16 in one channel, y is not beyond fp32."""
+    import torch
+    ps, w = stack(out, inn, n, 2048, (5,))
+    x = torch.randn((batch, inn), device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(1)).half()
+    x[:, 5] = 2.0**-13
+    y = ps.linear_batched(x, n, out_dtype=torch.float32)
+    want = x.double() @ w.t().contiguous()
+    assert ((y.double() - want).abs().amax(dim=1) <= 2e-3 * want.abs().amax(dim=1)).all()   # also false for NaN
+
+
+def test_a_token_of_its_own_keeps_its_precision():
+    """Five tokens through a small stack: four in one launch and one by itself, whose x/s and magnitudes stay in fp32."""
+    import torch
+    import paper_2410_23918_amd as B
+    out, inn, n, batch = 288, 1280, 23, 5
+    assert B.choose_kernel(out, inn, n, 64, batch, n) == B.KERNEL_DECODE
+    ps, w = stack(out, inn, n, 64)
+    x = torch.randn((batch, inn), device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(1)).half()
+    y = ps.linear_batched(x, n, out_dtype=torch.float32).double()
+    want = x.double() @ w.t().contiguous()
+    errors = (y - want).norm(dim=1) / want.norm(dim=1)
+    assert errors.min() < 1e-6 and errors.max() < 1e-3
