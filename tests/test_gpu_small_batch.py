@@ -1,11 +1,14 @@
 """The batch kernel for up to 64 tokens at the edges of its tiling: row counts that end inside a workgroup, chunk counts that
 leave teams without a chunk, both sides of its 16- and 32-token groups, with and without a column split (whose partial
 tiles meet in the workspace).  45 blocks: more than the other small-batch kernel holds, so this one runs; the cases of one
-and two blocks are among those that are seen to take it.  Every element of y in fp32."""
+and two blocks are among those that are seen to take it.  Matrices of few rows go to k_rows instead: every list runs without it (this kernel) and
+as the library chooses.  Every element of y in fp32."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
+
+without_and_with_rows = pytest.mark.parametrize("rows", [16, 0])   # OPT_ROWS_CHUNKS: never, the library's choice
 
 
 @pytest.mark.parametrize("out,inn", [
@@ -14,14 +17,16 @@ pytestmark = pytest.mark.gpu
     (160, 2816),     # 11 chunks, a ragged second row group
 ])
 @pytest.mark.parametrize("batch", [2, 16, 17, 32, 33, 64])
-def test_every_output_of_the_small_batch_kernel(out, inn, batch):
-    check(out, inn, 45, batch)
+@without_and_with_rows
+def test_every_output_of_the_small_batch_kernel(out, inn, batch, rows):
+    check(out, inn, 45, batch, rows=rows)
 
 
 @pytest.mark.parametrize("inn,batch", [(8192, 1), (8192, 2), (8192, 33), (7168, 16), (5120, 17)])
-def test_many_column_ranges(inn, batch):
+@without_and_with_rows
+def test_many_column_ranges(inn, batch, rows):
     """32, 28 and 20 column chunks in eight, seven and five ranges: the last workgroup to arrive adds that many partial tiles."""
-    check(32, inn, 45, batch)
+    check(32, inn, 45, batch, rows=rows)
 
 
 # one block (a step of the ring, then the activations and the next scales at once) and two, in one and two chunk iterations
@@ -30,8 +35,9 @@ FEW_BLOCKS = [(448, 256, 1, 16), (96, 1024, 1, 32), (64, 512, 1, 24), (512, 1024
 
 
 @pytest.mark.parametrize("out,inn,n,batch", FEW_BLOCKS)
-def test_few_blocks(out, inn, n, batch):
-    check(out, inn, n, batch)
+@without_and_with_rows
+def test_few_blocks(out, inn, n, batch, rows):
+    check(out, inn, n, batch, rows=rows)
 
 
 @pytest.mark.parametrize("out,inn,n", [
@@ -39,16 +45,18 @@ def test_few_blocks(out, inn, n, batch):
     (160, 2816, 12),
 ])
 @pytest.mark.parametrize("batch", [65, 128, 129, 1000, 1024, 1025])
-def test_more_than_64_tokens_in_groups(out, inn, n, batch):
+@without_and_with_rows
+def test_more_than_64_tokens_in_groups(out, inn, n, batch, rows):
     """Both sides of the 64-token groups, and of the 1024 tokens up to which they are taken."""
-    check(out, inn, n, batch)
+    check(out, inn, n, batch, rows=rows)
 
 
 @pytest.mark.parametrize("batch", [2, 17, 64, 130])
-def test_weights_over_their_scales_out_of_fp16_range(batch):
+@without_and_with_rows
+def test_weights_over_their_scales_out_of_fp16_range(batch, rows):
     """Four channels scaled down by 2^-30 whose activations are tiny or zero: a weight over its scale is beyond fp16's largest value
     there (W' is of the order of 0.2), the activation over the scale is not."""
-    check(96, 1280, 45, batch, small=(5, 300, 511, 1279))
+    check(96, 1280, 45, batch, small=(5, 300, 511, 1279), rows=rows)
 
 
 @pytest.mark.parametrize("out,inn,n,batch,fused", [
@@ -101,11 +109,12 @@ def test_the_kernel_taken_beyond_64_tokens(out, inn, n, batch, tile):
     assert bool(scratch.any()) == tile
 
 
-def test_an_infinite_activation_stays_with_its_token():
-    check(96, 1280, 45, 20, infinite=7)
+@without_and_with_rows
+def test_an_infinite_activation_stays_with_its_token(rows):
+    check(96, 1280, 45, 20, infinite=7, rows=rows)
 
 
-def check(out, inn, n, batch, small=(), infinite=None):
+def check(out, inn, n, batch, small=(), infinite=None, rows=0):
     import torch
     import paper_2410_23918_amd as B
     g = torch.Generator(device="cuda:0").manual_seed(out + inn + batch)
@@ -134,7 +143,11 @@ def check(out, inn, n, batch, small=(), infinite=None):
     finite = torch.isfinite(x).all(dim=1)
     y = torch.full((batch, out), float("nan"), device="cuda:0")
     for _ in range(2):   # the second call finds the counters as the first left them
-        ps.linear_batched(x, n, y=y, kernel=B.KERNEL_PANEL)
+        B.set_option(B.OPT_ROWS_CHUNKS, rows)
+        try:
+            ps.linear_batched(x, n, y=y, kernel=B.KERNEL_PANEL)
+        finally:
+            B.set_option(B.OPT_ROWS_CHUNKS, 0)
         torch.cuda.synchronize()
         assert not torch.isfinite(y[~finite]).any()
         xa = x[finite].float().abs().double()
