@@ -27,8 +27,9 @@ enum {
                                              3 = 128 x 128, 4 = 128 x 128 for long rows, 5 = 64 x 64 (sums in
                                              the order of 3), 6 = 64 x 64 (of 4) */
     BITSTACK_OPT_BATCH_TILES = 8,         /* row tiles per workgroup of the batch kernel: 2 or 4 (64 / 128 rows) */
-    BITSTACK_OPT_ROWS_CHUNKS = 9          /* the batch kernel of one row tile per workgroup: 1, 2, 4 or 8 = always (up to 64 tokens),
-                                             with so many column chunks at a time; 16 = never */
+    BITSTACK_OPT_ROWS_CHUNKS = 9          /* the batch kernel of one row tile per workgroup: 1, 2, 4 or 8 = always (up to 1024 tokens),
+                                             with so many column chunks at a time where the stack has 8 / value
+                                             blocks or more; 16 = never */
 };
 int bitstack_set_option(int option, int value);
 
