@@ -73,6 +73,25 @@ def test_batches(out, inn, n, batch, tiles):
         B.set_option(B.OPT_BATCH_TILES, 0)
 
 
+@pytest.mark.parametrize("out,inn,n,batch", [
+    (1056, 1024, 3, 31), (64, 2048, 2, 31),              # k_fused, two and four pairs of chunks
+    (1056, 1024, 8, 4), (1056, 2048, 8, 4),              # its columns split two and four ways
+    (64, 4096, 8, 3), (1056, 2048, 6, 31),               # eight ways; 24 steps
+    (32, 256, 45, 65), (96, 512, 32, 128),               # k_panel, one tile of 128 tokens
+    (64, 256, 32, 129), (96, 512, 45, 256),              # two
+])
+def test_batches_without_k_rows(out, inn, n, batch):
+    """Matrices of few rows through the kernels that serve the larger ones, which take seconds to make and to check"""
+    import paper_2410_23918_amd as B
+    ps, w = stack(out, inn, n, max(64, batch))
+    x = activations(batch, inn, batch)
+    B.set_option(B.OPT_ROWS_CHUNKS, 16)
+    try:
+        compare(ps, w, n, x, lambda y: ps.linear_batched(x, n, y=y, kernel=B.KERNEL_PANEL))
+    finally:
+        B.set_option(B.OPT_ROWS_CHUNKS, 0)
+
+
 @pytest.mark.parametrize("tiles", [2, 4])
 @pytest.mark.parametrize("batch", [2, 17, 64, 130])
 def test_scales_out_of_fp16_range(batch, tiles):
