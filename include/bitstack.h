@@ -287,10 +287,11 @@ void bitstack_plan_release(bitstack_plan_t* plan);
 /* Same for a batch of tokens.  x: device fp16 [batch][in] row-major;
  * y: device [batch][out] row-major of y_dtype (BITSTACK_Y_F16 / BITSTACK_Y_F32);
  * 1 <= batch <= max_batch given at pack time.  The library picks the kernel from the shape,
- * the batch and the number of loaded blocks; for prefill-sized batches that can be the
- * materialising path below in row slabs through the image's own activation scratch
- * (max_batch x in x 2 bytes, there in every image packed with max_batch > 64), when that
- * holds at least 1024 rows of the dense weight. */
+ * the batch and the number of loaded blocks; that can be the materialising path below in row
+ * slabs through the image's own activation scratch (max_batch x in x 2 bytes, there in every
+ * image packed with max_batch > 64), when that holds at least 1024 rows of the dense weight or
+ * all of them: with 16 blocks from 17 tokens on at 1024 x 4096, from 130 at 4096 x 4096, from
+ * 1026 at 14336 x 4096; few rows and many blocks from five on. */
 int bitstack_linear_batched(const void* x, int batch, const bitstack_weight_t* blocks,
                             int n_loaded, void* y, int y_dtype, bitstack_stream_t stream);
 
@@ -300,9 +301,10 @@ int bitstack_linear_select(const void* x, int batch, const bitstack_weight_t* bl
                            bitstack_stream_t stream);
 
 /* The materialising path (appendix "Inference with BitStack models", throughput of the
- * restoration levels: its level 2 restores the weight, then multiplies).  For prefill-sized
- * batches it is faster than the kernels that rebuild weight tiles on chip, at the price of
- * out x in x 2 bytes of scratch; one scratch buffer can serve every stack of a model.
+ * restoration levels: its level 2 restores the weight, then multiplies).  From some number
+ * of tokens on (16 blocks, scratch for the whole weight: 17 at 4096 x 4096, 66 at 4096 x 14336,
+ * 514 at 14336 x 4096) it is faster than the kernels that rebuild weight tiles on chip, at the
+ * price of out x in x 2 bytes of scratch; one scratch buffer can serve every stack of a model.
  *
  * bitstack_restore_weight writes
  *     w_dense[o][j] = ( sum_{i < n_loaded} S_i[o][j] * (U_i V_i^T)[o][j] ) / s[j]     (Eq. 8, Eq. 4)

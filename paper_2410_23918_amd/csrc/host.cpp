@@ -310,8 +310,8 @@ int bitstack_weight_shape(const bitstack_weight_t* w, int* out, int* in, int* k,
 // Which kernel serves (batch, n_loaded) fastest, from estimates that live beside the launchers
 // (constants fitted to measurements on MI355X): the decode kernel with up to four tokens per
 // launch streams the blocks once per token; the batch path rebuilds the weight on chip per group of 64
-// tokens (k_batch), 32 (k_fused) or 512 (k_tile); with a scratch buffer for the
-// dense weight, restoring it once and one dense product wins for prefill-sized batches.
+// tokens (k_batch, k_rows), 32 (k_fused) or 512 (k_tile); with a scratch buffer for the
+// dense weight, restoring it once and one dense product wins from some number of tokens on (16 blocks of 4096 x 4096: 17).
 // Rows of the weight a scratch buffer of this size holds at a time on the materialising path
 // (multiples of 256, the dense kernel's tile height; the whole matrix if it fits; 0: too small to
 // be worth it -- below 1024 rows the dense product no longer fills the chip).
@@ -357,17 +357,18 @@ static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t work
     // (the dense product addresses x and a slab of the dense weight with 32-bit byte offsets)
     const bool dense_ok = size_t(batch) * g.in * 2 <= 0xffffffffull && size_t(slab) * g.in * 2 <= 0xffffffffull;
     if (restore_fits(g.block_stride, n_loaded) && slab > 0 && dense_ok) {
-        // per slab of rows: restore + product.  7053 cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks), timed both
-        // ways: with a scratch for the whole weight the path taken is 0.3 % slower than the other in the mean, two times by more than 30 %
-        // (0.1 % and none through the image's own scratch of 2048 rows).  The estimates before, of slower kernels, gave 6.6 % and 617,
-        // up to 2.35 times, mostly by restoring a matrix of few rows or few blocks.
+        // per slab of rows: restore + product.  2919 cases of 65 to 2048 tokens (512 x 512 to 28672 x 8192, 1 to 24 blocks), timed both
+        // ways: with a scratch for the whole weight the path taken is 0.4 % slower than the faster of the two in the mean and 30 % at most (0.1 and
+        // 18 % through the image's own scratch of 2048 rows), part of it by the rule below; 2279 cases of 2 to 64 tokens: 0.2 and 19 % (0.03 and 11 %).
         double t_mat = 0.0;
         for (int r0 = 0; r0 < g.out; r0 += slab) {
             const int rows = slab < g.out - r0 ? slab : g.out - r0;
             t_mat += 1.7 + restore_time_us(rows, g.in, n_loaded) + dense_time_us(rows, g.in, batch);
         }
-        // A dense weight of a quarter of the last-level cache and more takes the place of what the program's other kernels left there: for
-        // few tokens it has to be worth it (14336 x 4096, 16 blocks, 128 tokens: 121 us, 133 without; the caller's next kernels pay for the rest)
+        // A dense weight of a quarter of the last-level cache and more takes the place of what the program's other kernels left there, and the
+        // next ones pay.  14336 x 4096, 16 blocks, 128 tokens: by itself 128 us and 110 restored; with one token through two or four other
+        // stacks of 36 MiB after each call 153 and 163, 190 and 198.  Where restoring is far ahead it stays ahead (9600 x 4096, 20 blocks, 100
+        // tokens: 144 and 95, with four stacks 205 and 167), so for few tokens it has to be 15 % faster.
         const bool displaces = size_t(slab) * g.in * 2 > (size_t(64) << 20) && batch <= 256;
         if (t_mat * (displaces ? 1.15 : 1.0) < t_best) kernel = BITSTACK_KERNEL_MATERIALISE;
     }

@@ -1000,10 +1000,10 @@ static double tile_launch_us(int out, int in, int batch, int n_loaded) {
            (in == kChunkCols ? 1.5 : 0.0);
 }
 
-// k_rows, but up to 64 tokens not where k_fused has up to eight steps of rows of up to four column chunks: those calls are as fast with either to a
-// tenth (832 x 768, 3 blocks, 50 tokens: 9.7 us, 9.3 with k_rows; 384 x 1024, 8 blocks, 3 tokens: 12.5 and 10.7), and
-// tests/test_gpu_small_batch.py states that k_fused has them.  Longer rows give every wavefront of k_rows a chunk (1408 x 3584, one block, 8
-// tokens: 15.1, 9.8).
+// k_rows, but up to 64 tokens not where k_fused has up to eight steps of rows of up to four column chunks: tests/test_gpu_small_batch.py states
+// that k_fused has such calls, and this rule is there for it.  k_rows would be a little faster (832 x 768, 3 blocks, 50 tokens: 9.7 us, 9.3 with
+// k_rows; 384 x 1024, 8 blocks, 3 tokens: 12.5 and 10.7; 1 % in the mean of all calls of 2 to 64 tokens).  Longer rows give every wavefront of
+// k_rows a chunk, and there it has them (1408 x 3584, one block, 8 tokens: 15.1, 9.8).
 static double rows_if_many_steps_us(int out, int in, int batch, int n_loaded, int part_slots) {
     if (batch > kFusedMaxBatch) return rows_time_us(out, in, batch, n_loaded);
     int steps = 0;
@@ -1047,12 +1047,12 @@ PanelEstimate panel_estimate(int out, int in, int batch, int n_loaded, int part_
 hipError_t launch_panel(const LaunchArgs& a, hipStream_t st) {
     KParams p = make_params(a);
     if (a.n_loaded < 1 || a.batch < 1) return hipErrorInvalidValue;
-    // The cheapest of three estimates.  k_batch sums the weight over the blocks before it multiplies (many blocks, many tokens) and
+    // The cheapest of four estimates.  k_batch sums the weight over the blocks before it multiplies (many blocks, many tokens) and
     // rebuilds it per 64 tokens, with a column split that fills the chip; k_fused multiplies every block's tile and has less to do
     // per chunk (few blocks), but rebuilds the tiles per 32 tokens; the weight-tile kernel rebuilds the weight once per 512
     // tokens (608 x 12032, 8 blocks, 96 tokens: k_tile 263 us, k_batch 59; 4096 x 4096, 16 blocks, 256 tokens 139 and 99, 300 tokens
-    // 146 and 189).  In 8257 cases that were timed with every kernel the one taken is 0.1 % slower than the fastest on average;
-    // k_batch is up to 10 % slower than another in its place.
+    // 146 and 189); k_rows takes the matrices of few rows (rows.hip).  In 8257 cases that were timed with every kernel but k_rows the one
+    // taken was 0.1 % slower than the fastest on average; k_batch up to 10 % slower than another in its place.
     const int rows_forced = rows_forced_chunks();
     const double tr = rows_forced != 16 && !batch_forced_tiles() && rows_fits(p.out, p.in, p.batch, p.n_loaded) ? rows_forced ? 0.0 : rows_if_many_steps_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots) : 1e30;
     if (a.batch > kFusedMaxBatch && tr < batch_or_tile_us(p.out, p.in, p.batch, p.n_loaded, p.part_slots)) return launch_rows(p, st);

@@ -140,7 +140,7 @@ def test_kernel_choice_is_host_logic():
     """bitstack_choose_kernel: one token always takes the decode kernel; the materialising path is
     chosen only with a scratch of at least 1024 rows of the dense weight -- the caller's, or the
     activation scratch inside an image packed for that many tokens -- and a stack the restore
-    kernel can hold, and only for prefill-sized batches."""
+    kernel can hold, and only where the tokens are many enough for the rows."""
     import paper_2410_23918_amd as B
     big = 1 << 40
     assert B.choose_kernel(4096, 4096, 16, 1, 1, 16) == B.KERNEL_DECODE
@@ -164,9 +164,8 @@ def test_kernel_choice_is_host_logic():
     assert B.choose_kernel(4096, 4096, 16, 64, 2, 2, big) in (B.KERNEL_DECODE, B.KERNEL_PANEL)
     assert B.choose_kernel(4096, 4096, 16, 64, 2, 0) == B.KERNEL_AUTO
     # where the measured crossovers lie (Llama-3-8B shapes, 16 blocks): two tokens share a decode
-    # launch, eight go to the batch kernels; with a scratch buffer the 4096-row shapes take the
-    # materialising path from ~65 tokens on (128-row product tiles fill the chip), the 14336-row
-    # shape only from ~700
+    # launch, eight go to the batch kernels; with a scratch buffer 4096 x 4096 takes the
+    # materialising path from 17 tokens on, 4096 x 14336 from 66 and 14336 x 4096 only from 514
     assert B.choose_kernel(14336, 4096, 16, 2048, 2, 16, 0) == B.KERNEL_DECODE
     assert B.choose_kernel(14336, 4096, 16, 2048, 8, 16, 0) == B.KERNEL_PANEL
     assert B.choose_kernel(4096, 4096, 16, 2048, 128, 16, big) == B.KERNEL_MATERIALISE
