@@ -363,7 +363,8 @@ __global__ __launch_bounds__(1024) void k_dc_gram(const float* P, int slices, bo
 }
 
 // the Gram matrix from its parts, in a fixed order, into LDS: THREADS threads, the loads of 32 values in flight together.  Buffer
-// loads: past the last part they bring zeros.  LOWER: without the tile above the diagonal (columns 16 on of rows 0-15), by the first
+// loads: past the last part, in the rest of the array of kGramParts, they bring zeros (the bounds take in the scalar offset;
+// tests/test_gpu_decompose_workspace.py fills the array with NaN).  LOWER: without the tile above the diagonal (columns 16 on of rows 0-15), by the first
 // 768 of 1024 threads: what a compute unit can take in (256 KiB from 32 parts) is half of the time.
 template <int THREADS, bool LOWER>
 __device__ __forceinline__ void gram_sum(const double* Gpart, int parts, double (*Gs)[kL + 1]) {
