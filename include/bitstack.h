@@ -334,10 +334,10 @@ int bitstack_restore_max_blocks(void);
  * overwrites the buffer; otherwise the buffer is left alone.  A buffer smaller than the image's
  * own activation scratch is left alone too (the image's is used where the path is taken).
  * Same results contract and errors as bitstack_linear_batched.  A stack with an entry of s below
- * 2^-12 is not restored in place of a kernel that can keep 1/s on the activations: its dense
- * weight may be out of fp16's range there.
+ * 2^-4 (up to 64 tokens) or 2^-12 (beyond) is not restored in place of a kernel that can keep 1/s
+ * on the activations: its dense weight may be out of fp16's range there.
  * bitstack_choose_kernel (host only, no device work) returns the BITSTACK_KERNEL_* value that
- * call would pick for a stack of this shape with s >= 2^-12 (BITSTACK_KERNEL_AUTO for n_loaded =
+ * call would pick for a stack of this shape with s >= 2^-4 (BITSTACK_KERNEL_AUTO for n_loaded =
  * 0, where y is only cleared), or a negative error code for an unsupported shape / out-of-range
  * arguments. */
 int bitstack_linear_batched_ws(const void* x, int batch, const bitstack_weight_t* blocks,

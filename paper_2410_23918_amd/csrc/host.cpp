@@ -331,10 +331,11 @@ static size_t scratch_bytes(const Geometry& g, size_t workspace_bytes) {
 
 // Up to this 1/s the choice restores the weight wherever that is faster.  Restoring writes W'/s as fp16, and an entry beyond 65504 makes
 // every token NaN, also one whose activation there is zero; the kernels for one token and for batches keep 1/s on the activations, or go
-// back to that when a sum is not finite.  W' is known on the device only, so the line is drawn by s: at 2^12 W' has room up to 16, that is for
-// any weight W'/s that fp16 could hold to begin with, while a channel that calibration left almost silent (s clamped to 1e-5, say) and whose
-// W' the blocks do not follow down to that is beyond it.
-constexpr float kRestoreMaxRs = 4096.0f;
+// back to that when a sum is not finite.  W' is known on the device only, so the line is drawn by s.  Up to 64 tokens, where restoring takes 0.79 of
+// the time in the mean, W' has room up to 4094 (s of a standard deviation of 0.5 in the logarithm reach 1/s = 8 in 14336 channels).  Beyond, where it
+// takes down to half (4096 x 4096, 16 blocks, 256 tokens: 49 us, 95), up to 16: room for any weight W'/s that fp16 could hold to begin with, while a channel
+// that calibration left almost silent (s clamped to 1e-5, say) and whose W' the blocks do not follow down to that is on the other side.
+constexpr float kRestoreMaxRsFew = 16.0f, kRestoreMaxRs = 4096.0f;
 
 static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t workspace_bytes, float rs_max) {
     if (batch == 1) return BITSTACK_KERNEL_DECODE;
@@ -343,7 +344,7 @@ static int choose_kernel(const Geometry& g, int batch, int n_loaded, size_t work
     const PanelEstimate panel = panel_estimate(g.out, g.in, batch, n_loaded, g.part_slots, g.xpack_bytes != 0);
     int kernel = t_decode <= panel.us ? BITSTACK_KERNEL_DECODE : BITSTACK_KERNEL_PANEL;
     const double t_best = t_decode <= panel.us ? t_decode : panel.us;
-    const bool wide = rs_max > kRestoreMaxRs;
+    const bool wide = rs_max > (batch <= kSmallBatch ? kRestoreMaxRsFew : kRestoreMaxRs);
     // The kernels for one token hold x/s in fp32; k_rows and the materialising path do not.  Where they are estimated faster than k_batch and
     // k_fused, they keep the stacks whose x/s may leave fp16's range (s as above), and the cuts in which a token goes through k_token (1.5e-7
     // of y, 2e-4 with k_rows; 288 x 1280, 23 blocks, 5 tokens: 18.6 us, 28.1 with k_rows -- the estimate of a cut does not know k_token).

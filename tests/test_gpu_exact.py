@@ -7,13 +7,13 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def stack(out, inn, n, max_batch, small=()):
-    """(packed stack, W' over the scales in fp64): odd magnitudes of at most 31, scales 1 and, in the channels `small`, 2^-30"""
+def stack(out, inn, n, max_batch, small=(), exponent=30):
+    """(packed stack, W' over the scales in fp64): odd magnitudes of at most 31, scales 1 and, in the channels `small`, 2^-exponent"""
     import torch
     import paper_2410_23918_amd as B
     g = torch.Generator(device="cuda:0").manual_seed(out + inn + n)
     s = np.ones(inn, np.float32)
-    s[list(small)] = 2.0**-30
+    s[list(small)] = 2.0**-exponent
     ps = B.PackedStack.empty(out, inn, n, s, max_batch=max_batch)
     bits = torch.arange(32, device="cuda:0", dtype=torch.int32)
     w = torch.zeros((out, inn), device="cuda:0", dtype=torch.float64)
@@ -29,13 +29,13 @@ def stack(out, inn, n, max_batch, small=()):
     return ps, w / torch.from_numpy(s).to("cuda:0").double()
 
 
-def activations(batch, inn, seed, small=()):
+def activations(batch, inn, seed, small=(), exponent=24):
     import torch
     g = torch.Generator(device="cuda:0").manual_seed(seed)
     x = torch.randint(1, 5, (batch, inn), generator=g, device="cuda:0") * (2 * torch.randint(0, 2, (batch, inn), generator=g, device="cuda:0") - 1)
     x = x.half()
     for c in small:
-        x[:, c] *= 2.0**-24
+        x[:, c] *= 2.0**-exponent
     return x
 
 

@@ -20,9 +20,11 @@ def test_restored_only_where_the_dense_weight_is_in_range(out, inn, n, batch, le
     import paper_2410_23918_amd as B
     scratch = torch.empty(B.dense_bytes(out, inn) if lent else 0, dtype=torch.uint8, device="cuda:0")
     assert B.choose_kernel(out, inn, n, 2048, batch, n, scratch.numel()) == B.KERNEL_MATERIALISE
-    for small in ((), (5, 300, 511, inn - 1)):
-        ps, w = stack(out, inn, n, 2048, small)
-        x = activations(batch, inn, batch, small)
+    # scales of 2^-30, and up to 64 tokens (W' between 16 and 4094 is in question beyond) of 2^-11: W' of 32 is out of range over it
+    for small, exponent in (((), 0), ((5, 300, 511, inn - 1), 30), *([((5, 300, 511, inn - 1), 11)] if batch <= 64 else [])):
+        ps, w = stack(out, inn, n, 2048, small, exponent)
+        assert (w.abs().max() > 65504) == bool(small)
+        x = activations(batch, inn, batch, small, min(exponent, 24))
         image_scratch = ps.buf[ps.buf.numel() // 256 * 256 - 2048 * inn * 2:]   # the image's last 2048 x in fp16 values
         used = scratch if lent else image_scratch
         used.fill_(0xff)
